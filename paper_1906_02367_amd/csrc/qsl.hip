@@ -27,9 +27,9 @@
 //   k_pack, k_pack_sent       the packed message (k_pack_sent: QSGD, whose entries of level 0 drop out)
 //   k_dense_norm, k_dense_sum, k_dense_scales, k_dense_encode    an operator that keeps every coordinate, with messages that
 //                carry no indices: two streaming passes
-//   k_aggregate, k_aggregate_entries, k_aggregate_ranges, k_aggregate_dense
+//   k_aggregate, k_aggregate_entries, k_aggregate_cells, k_aggregate_dense
 //                master line of Algorithm 1, atomic-free, messages added in list order: by look-ups in the other
-//                messages (few messages), by coordinate ranges (many), or coordinate by coordinate (every
+//                messages (few entries), by coordinate ranges (many), or coordinate by coordinate (every
 //                message lists every coordinate)
 //
 // A "unit" is one (worker, segment) pair: the operator is applied independently to each unit
@@ -72,6 +72,8 @@ uint32_t bit_width_u64(uint64_t x) { uint32_t w = 0; while (x) { ++w; x >>= 1; }
 // ====================================================================================================
 // host side
 // ====================================================================================================
+constexpr uint32_t AGG_WAVE_ENTRIES = 1024;      // entries of all listed messages from which a cell is given to several waves
+
 struct qsl_ctx {
   qsl_config cfg;
   std::vector<uint64_t> off;
@@ -88,6 +90,7 @@ struct qsl_ctx {
   uint32_t nnz_hint;          // entries a message is expected to hold at most (sizes the aggregation grid)
   uint32_t* agg_dir;          // [64][agg_ndir] directories of the listed messages (only if messages are expected to be long)
   uint32_t agg_ndir;
+  AggCrowd agg[AGG_LEVELS];   // the aggregation's crowded cells (several segments)
   uint32_t n_sampled;         // segments whose guess comes from k_sample
   uint32_t nbig_general;                // how many entries of DevCtx::big_segs are units of the multi-pass kernels (they come first)
   uint32_t nsel_general, ncb_general;   // blocks of the multi-pass kernels without / with (DevCtx::NSEL, NCB) the guessing units' share
@@ -326,6 +329,7 @@ extern "C" qsl_status qsl_create(qsl_ctx** out, const qsl_config* cfg, void* hip
   ctx->cfg.seg_k = ctx->k.data();
   ctx->stream = static_cast<hipStream_t>(hip_stream);
   ctx->Rmax = cfg->max_workers;
+  for (AggCrowd& a : ctx->agg) a = AggCrowd{nullptr, nullptr, 0};
   ctx->last_R = 0; ctx->warm_R = 0; ctx->safe_left = 0;
   ctx->timing = 0; ctx->ev_used = 0;
   ctx->slab = nullptr; ctx->h_status = nullptr; ctx->own_v = nullptr; ctx->order_ev = nullptr; ctx->side = nullptr; ctx->side2 = nullptr; ctx->join2_ev = nullptr; ctx->fork_ev = nullptr; ctx->join_ev = nullptr;
@@ -563,7 +567,38 @@ extern "C" qsl_status qsl_create(qsl_ctx** out, const qsl_config* cfg, void* hip
   const uint64_t o_tmp = carve(4ull * 1024);
   ctx->agg_ndir = static_cast<uint32_t>(((d + (1u << AGG_DIR_SHIFT) - 1) >> AGG_DIR_SHIFT) + 1);
   const bool want_dir = true;                       // (6.4 MB for 25.6 M coordinates)
-  const uint64_t o_dir = carve(4ull * 65 * ctx->agg_ndir);       // 64 directories and the list of crowded ranges
+  const uint64_t o_dir = carve(4ull * 64 * ctx->agg_ndir);       // 64 directories
+  // the cells of 1024 coordinates in which a message is expected to have many entries (segments kept whole, or nearly), in parts
+  std::vector<AggPart> agg_parts[AGG_LEVELS];
+  std::vector<uint32_t> agg_bits[AGG_LEVELS];
+  if (L > 1) {
+    std::vector<float> in_cell(ctx->agg_ndir, 0.0f);
+    for (uint32_t l = 0; l < L; ++l) {
+      const SegInfo& sg = segs[l];
+      const double kl = is_qsgd(cfg->quantizer) ? std::min<double>(sg.k, 1.25 * s * std::sqrt(static_cast<double>(sg.k))) : sg.k;
+      if (kl * AGG_CELL < static_cast<double>(sg.size)) continue;                  // far from crowding anything
+      for (uint64_t a = sg.start; a < sg.start + sg.size;) {
+        const uint64_t b = std::min<uint64_t>(sg.start + sg.size, ((a >> AGG_DIR_SHIFT) + 1) << AGG_DIR_SHIFT);
+        in_cell[a >> AGG_DIR_SHIFT] += static_cast<float>(kl / sg.size * (b - a));
+        a = b;
+      }
+    }
+    for (uint32_t v = 0; v < AGG_LEVELS; ++v) {
+      agg_bits[v].assign((ctx->agg_ndir + 31) / 32, 0u);
+      for (uint32_t t = 0; t + 1 < ctx->agg_ndir; ++t) {
+        uint16_t parts = 0;
+        while (parts < 5 && in_cell[t] > static_cast<float>(AGG_LEVEL[v] << parts)) ++parts;
+        if (!parts) continue;
+        for (uint16_t i = 0; i < (1u << parts); ++i) agg_parts[v].push_back(AggPart{t, i, parts});
+        agg_bits[v][t >> 5] |= 1u << (t & 31);
+      }
+    }
+  }
+  uint64_t o_parts[AGG_LEVELS], o_pbits[AGG_LEVELS];
+  for (uint32_t v = 0; v < AGG_LEVELS; ++v) {
+    o_parts[v] = carve(sizeof(AggPart) * std::max<size_t>(1, agg_parts[v].size()));
+    o_pbits[v] = carve(4ull * std::max<size_t>(1, agg_bits[v].size()));
+  }
   const uint64_t o_ownv = carve((cfg->flags & QSL_FLAG_OWN_V) ? 4ull * R * d : 4);
   const uint64_t dense_nb = dense ? std::min<uint64_t>((d + DTILE - 1) / DTILE, MAX_DENSE_BLOCKS) : 0;
   const uint64_t o_dpart = carve(8ull * R * ACC_SLOTS * dense_nb + 8), o_dtag = carve(4ull * R * dense_nb + 4);
@@ -589,6 +624,13 @@ extern "C" qsl_status qsl_create(qsl_ctx** out, const qsl_config* cfg, void* hip
   upload(o_sstart, seg_start.data(), 4ull * L);
   upload(o_skoff, seg_koff.data(), 4ull * L);
   upload(o_swhole, seg_whole.data(), 4ull * L);
+  for (uint32_t v = 0; v < AGG_LEVELS; ++v) {
+    if (agg_parts[v].empty()) continue;
+    upload(o_parts[v], agg_parts[v].data(), sizeof(AggPart) * agg_parts[v].size());
+    upload(o_pbits[v], agg_bits[v].data(), 4ull * agg_bits[v].size());
+    ctx->agg[v] = AggCrowd{reinterpret_cast<const AggPart*>(base + o_parts[v]), reinterpret_cast<const uint32_t*>(base + o_pbits[v]),
+                           static_cast<uint32_t>(agg_parts[v].size())};
+  }
   ok = ok && hipHostMalloc(reinterpret_cast<void**>(&ctx->h_status), 64, hipHostMallocMapped) == hipSuccess;
   // The events order work on one device (what a kernel wrote is visible device-wide when it ends), so they need no
   // system-scope fence when they complete: with one, every record costs the stream 2-3 us (measured: a round with the
@@ -892,10 +934,22 @@ static qsl_status make_row_list(const uint32_t* worker_list, uint32_t R, RowList
   return QSL_OK;
 }
 
+// Whether k_aggregate_cells takes the listed messages.  Both ways measured on 2 .. 64 messages of 1,600 to 2.6 M entries,
+// d = 70,001 .. 25.6 M: by look-ups about 11 us + 26 us per million entries and group of four other messages, by cells
+// about 12 us + 0.35 us per million coordinates + 12 us per million entries; where `out` is not added to, the look-ups need it
+// cleared first (0.62 us per million coordinates) and the cells write it whole (0.40 more).  Short messages are looked up by
+// k_aggregate, which costs less per look-up: d = 25.6 M, 1,600 entries each, 16 / 32 / 64 messages 13 / 31 / 105 us against
+// 26 / 34 / 46 us by cells.
+static bool aggregate_by_cells(uint32_t nnz_hint, uint32_t ndir, uint32_t R, bool accumulate) {
+  if (nnz_hint < AGG_DIR_MIN) return R >= AGG_CELLS_MIN_R;
+  const double entries = static_cast<double>(nnz_hint) * R, coords = 1024.0 * ndir, groups = (R + 2) / 4;
+  return R > 1 && entries * (26.0 * groups - 12.0) > (accumulate ? 0.35 : 0.13) * coords + 1e6;
+}
+
 // The launches of the master line.  `dir` is room for R directories of `ndir` words, or null (then every message is
-// searched whole); `nnz_hint` sizes the grids.
+// searched whole); `nnz_hint` sizes the grids; `crowd`: the levels' crowded cells of a context with several segments, or null.
 static qsl_status launch_aggregate(const DevCtx& c, hipStream_t st, uint32_t nnz_hint, uint32_t* dir, uint32_t ndir,
-                                   const uint8_t* msg, const RowList& rows, uint32_t R, float scale, int accumulate,
+                                   const AggCrowd* crowd, const uint8_t* msg, const RowList& rows, uint32_t R, float scale, int accumulate,
                                    float* out) {
   if (c.K == c.d && (c.dense || !is_qsgd(c.quantizer))) {   // k = d and nothing dropped: every message lists every coordinate
     const uint32_t blocks = static_cast<uint32_t>(std::min<uint64_t>((c.d / 8 + BLOCK) / BLOCK, 1u << 16));   // two groups of four per thread
@@ -903,23 +957,32 @@ static qsl_status launch_aggregate(const DevCtx& c, hipStream_t st, uint32_t nnz
     QSL_HIP(hipGetLastError());
     return QSL_OK;
   }
+  if (dir && aggregate_by_cells(nnz_hint, ndir, R, accumulate != 0)) {                            // long messages, or many: a block per few cells of 1024 coordinates
+    k_msg_directory<<<dim3(std::min(2048u, (c.K + BLOCK - 1) / BLOCK), R), BLOCK, 0, st>>>(c, msg, rows, dir, ndir);
+    uint32_t level = 0;
+    while (level + 1 < AGG_LEVELS && static_cast<uint64_t>(AGG_LEVEL[level]) * R > AGG_WAVE_ENTRIES) ++level;
+    AggCrowd cr = {nullptr, nullptr, 0};
+    if (crowd && crowd[level].n) cr = crowd[level];
+    int in_order = 1;
+    for (uint32_t q = 0; q < R; ++q) in_order &= rows.row[q] == q;
+    const double per_cell = static_cast<double>(nnz_hint) * R / (ndir - 1);
+    // few cells: fill the chip, as long as a wave still has a few hundred entries (64 messages of 5,000 entries,
+    // d = 70,001: 88 us with a wave per cell, 25 us with 16; d = 3 M, 4 messages of 300,000: 19 us with one, 23 us with two)
+    uint32_t split = 0;
+    while (split < 5 && (static_cast<uint64_t>(ndir - 1) << split) < 2048 && per_cell > (256u << split)) ++split;
+    const uint32_t waves = cr.n + ((ndir - 1) << split);
+    k_aggregate_cells<<<dim3((waves + BLOCK / 64 - 1) / (BLOCK / 64)), BLOCK, 0, st>>>(c, msg, rows, in_order, R, scale, accumulate,
+                                                                                     out, dir, ndir, cr, split);
+    QSL_HIP(hipGetLastError());
+    return QSL_OK;
+  }
   if (!accumulate) {
     const uint32_t blocks = static_cast<uint32_t>(std::min<uint64_t>((c.d + BLOCK * 4 - 1) / (BLOCK * 4), 1u << 16));
     k_fill_zero<<<dim3(blocks), BLOCK, 0, st>>>(out, c.d);
   }
-  const bool by_ranges = R >= AGG_RANGES_MIN_R || (R >= AGG_RANGES_MIN_R_LONG && nnz_hint >= AGG_DIR_MIN);
-  if (dir && by_ranges) {                           // many messages: a wave per 1024 coordinates, work linear in the entries
-    uint32_t* dense_list = dir + 64ull * ndir;      // behind the 64 directories: a counter and up to ndir - 1 ranges
-    k_msg_directory<<<dim3(std::min(2048u, (c.K + BLOCK - 1) / BLOCK), R), BLOCK, 0, st>>>(c, msg, rows, dir, ndir, dense_list);
-    k_aggregate_ranges<<<dim3(ndir - 1), 64, 0, st>>>(c, msg, rows, R, scale, accumulate, out, dir, ndir, dense_list);
-    k_aggregate_dense_ranges<<<dim3(std::min(AGG_DENSE_BLOCKS, ndir - 1)), 1024, 0, st>>>(c, msg, rows, R, scale, accumulate, out, dir,
-                                                                                        ndir, dense_list);
-    QSL_HIP(hipGetLastError());
-    return QSL_OK;
-  }
   if (R == 1 || nnz_hint < AGG_DIR_MIN) dir = nullptr;   // short messages are searched whole
   if (dir) {                                        // long messages: a thread per entry, searches narrowed by the directories
-    k_msg_directory<<<dim3(std::min(2048u, (c.K + BLOCK - 1) / BLOCK), R), BLOCK, 0, st>>>(c, msg, rows, dir, ndir, nullptr);
+    k_msg_directory<<<dim3(std::min(2048u, (c.K + BLOCK - 1) / BLOCK), R), BLOCK, 0, st>>>(c, msg, rows, dir, ndir);
     const uint32_t eb = std::min((c.K + BLOCK - 1) / BLOCK, std::max(4u, (nnz_hint + BLOCK - 1) / BLOCK));
     k_aggregate_entries<<<dim3(eb, R), BLOCK, 0, st>>>(c, msg, rows, R, scale, accumulate, out, dir, ndir);
   } else {                                          // short messages: 8 threads per entry, a block per expected tile of 32
@@ -939,8 +1002,8 @@ extern "C" qsl_status qsl_aggregate(qsl_ctx* ctx, const uint8_t* msg, const uint
   const qsl_status st = make_row_list(worker_list, R, &rows);
   if (st != QSL_OK) return st;
   // the directories were allocated at qsl_create for operators whose messages are long
-  return launch_aggregate(ctx->dc, ctx->stream, ctx->nnz_hint, ctx->agg_dir, ctx->agg_ndir, msg, rows, R, scale,
-                          accumulate, out);
+  return launch_aggregate(ctx->dc, ctx->stream, ctx->nnz_hint, ctx->agg_dir, ctx->agg_ndir, ctx->dc.L > 1 ? ctx->agg : nullptr, msg, rows, R,
+                          scale, accumulate, out);
 }
 
 // ----------------------------------------------------------------------------------------------------
@@ -990,11 +1053,14 @@ extern "C" qsl_status qsl_aggregate_static(const qsl_config* cfg, void* hip_stre
   const WireDims wd = wire_dims(cfg, K64);
   if (wd.capacity / 4 > 0xFFFFFFFFull) return QSL_ERR_UNSUPPORTED;
   const uint32_t ndir = static_cast<uint32_t>(((cfg->d + (1u << AGG_DIR_SHIFT) - 1) >> AGG_DIR_SHIFT) + 1);
-  const bool by_ranges = R >= AGG_RANGES_MIN_R || (R >= AGG_RANGES_MIN_R_LONG && wd.nnz_hint >= AGG_DIR_MIN);
-  const bool want_dir = R > 1 && (wd.nnz_hint >= AGG_DIR_MIN || by_ranges);   // as launch_aggregate uses them
-  // (the kernels for many messages keep a list of up to ndir ranges behind 64 directories)
-  const uint64_t dir_rows = by_ranges ? 65 : R;
-  if (want_dir && STATIC_DIR_OFFSET + 4ull * dir_rows * ndir > QSL_STATIC_SCRATCH_BYTES) return QSL_ERR_UNSUPPORTED;
+  // long messages, or many: a directory per message (the rule of the size is that of 65 rows from 56 messages on, from 24 if long)
+  const bool is_long = wd.nnz_hint >= AGG_DIR_MIN;
+  const bool many = R >= 56 || (R >= 24 && is_long);
+  bool want_dir = R > 1 && (is_long || many);
+  const uint64_t dir_rows = many ? 65 : R;
+  const bool fits = STATIC_DIR_OFFSET + 4ull * dir_rows * ndir <= QSL_STATIC_SCRATCH_BYTES;
+  if (want_dir && !fits) return QSL_ERR_UNSUPPORTED;
+  want_dir = want_dir || (fits && aggregate_by_cells(wd.nnz_hint, ndir, R, accumulate != 0));     // else they are searched whole
   unsigned char* base = nullptr;
   st = static_scratch(&base);
   if (st != QSL_OK) return st;
@@ -1011,7 +1077,7 @@ extern "C" qsl_status qsl_aggregate_static(const qsl_config* cfg, void* hip_stre
   // the call can be captured into a graph); the directories are written in full before they are read
   k_clear_word<<<dim3(1), 64, 0, stream>>>(c.status);
   uint32_t* dir = want_dir ? reinterpret_cast<uint32_t*>(base + STATIC_DIR_OFFSET) : nullptr;
-  return launch_aggregate(c, stream, wd.nnz_hint, dir, ndir, msg, rows, R, scale, accumulate, out);
+  return launch_aggregate(c, stream, wd.nnz_hint, dir, ndir, nullptr, msg, rows, R, scale, accumulate, out);
 }
 
 extern "C" qsl_status qsl_bits_sent(qsl_ctx* ctx, const uint8_t* msg, uint32_t R, uint64_t* bits_host) {

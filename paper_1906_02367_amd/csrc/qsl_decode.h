@@ -1,12 +1,13 @@
 // qsl_decode.h -- Reading messages: the stand-alone error update (k_add_rows, k_subtract_msg) and the master's
-// aggregation (k_fill_zero, k_msg_directory, k_aggregate, k_aggregate_entries, k_aggregate_ranges,
-// k_aggregate_dense_ranges, k_aggregate_dense), k_read_nnz.
+// aggregation (k_fill_zero, k_msg_directory, k_aggregate, k_aggregate_entries, k_aggregate_cells,
+// k_aggregate_dense), k_read_nnz.
 // Part of the single translation unit qsl.hip (included there, in this order: device, layout, select,
 // encode, stream, lean, dense, decode); not a public header.
 #pragma once
 
 #include "qsl_device.h"
 #include "qsl_layout.h"
+#include "qsl_select.h"
 
 namespace {
 
@@ -105,10 +106,7 @@ struct RowList { uint32_t row[64]; };
 constexpr uint32_t AGG_ENTRIES = 32;     // message entries per block; 8 threads look one entry up in parallel
 constexpr uint32_t AGG_DIR_SHIFT = 10;   // a directory entry per 1024 coordinates
 constexpr uint32_t AGG_DIR_MIN = 4096;   // messages expected to be at least this long are searched through their directories
-// k_aggregate_ranges takes over from 24 listed messages on when they are long, from 56 on in any case (measured, 8 workers'
-// messages repeated: 99,400 entries each: 15 / 32 / 64 messages 138 / 442 / 1480 us by look-ups, 170 / 277 / 473 us by
-// ranges; ~1,600 entries each: 14 / 31 / 105 us against 44 / 64 / 93 us)
-constexpr uint32_t AGG_RANGES_MIN_R_LONG = 24, AGG_RANGES_MIN_R = 56;
+constexpr uint32_t AGG_CELLS_MIN_R = 36; // short messages go to k_aggregate_cells from this many on
 
 // Directory of a long message: dir[t] = number of entries whose coordinate lies below t * 1024, for
 // t = 0 .. ndir - 1 (ndir = ceil(d / 1024) + 1, so dir[ndir - 1] = nnz).  Entry j fills the slots between
@@ -116,18 +114,34 @@ constexpr uint32_t AGG_RANGES_MIN_R_LONG = 24, AGG_RANGES_MIN_R = 56;
 // dir[t], dir[t + 1] and a binary search over the few entries of one 1024-block instead of log2(nnz)
 // dependent probes of the whole message.
 __global__ __launch_bounds__(BLOCK) void k_msg_directory(DevCtx c, const uint8_t* msg, RowList rows, uint32_t* dir,
-                                                         uint32_t ndir, uint32_t* dense_list) {
-  const uint32_t q = blockIdx.y;
+                                                         uint32_t ndir) {
+  const uint32_t q = blockIdx.y, lane = lane_id();
   const MsgView v = view_msg(c, msg, rows.row[q]);
   uint32_t* mine = dir + static_cast<uint64_t>(q) * ndir;
-  if (dense_list && q == 0 && blockIdx.x == 0 && threadIdx.x == 0) dense_list[0] = 0;    // the list k_aggregate_ranges fills
   const uint32_t nth = gridDim.x * BLOCK, tid = blockIdx.x * BLOCK + threadIdx.x;
   if (v.nnz == 0) { for (uint32_t t = tid; t < ndir; t += nth) mine[t] = 0; return; }
-  for (uint32_t j = tid; j < v.nnz; j += nth) {
-    const uint32_t cur = min(msg_index(c, v, j) >> AGG_DIR_SHIFT, ndir - 2);           // clamp: a malformed index
-    const uint32_t first = j ? min(msg_index(c, v, j - 1) >> AGG_DIR_SHIFT, ndir - 2) + 1 : 0u;
-    for (uint32_t t = first; t <= cur; ++t) mine[t] = j;                // empty when the predecessor shares the block
-    if (j == v.nnz - 1) for (uint32_t t = cur + 1; t < ndir; ++t) mine[t] = v.nnz;
+  constexpr uint32_t UN = 4;                              // entries per thread and step (one while the grid covers the message), their reads in flight together
+  for (uint64_t j0 = tid; j0 - lane < v.nnz; j0 += static_cast<uint64_t>(nth) * UN) {      // (uniform over the wave)
+    uint32_t cell[UN], prev[UN];
+#pragma unroll
+    for (uint32_t u = 0; u < UN; ++u) {
+      const uint64_t j = j0 + static_cast<uint64_t>(u) * nth;
+      cell[u] = 0; prev[u] = 0;
+      if (j < v.nnz) {
+        cell[u] = min(msg_index(c, v, static_cast<uint32_t>(j)) >> AGG_DIR_SHIFT, ndir - 2);            // clamp: a malformed index
+        if (lane == 0 && j) prev[u] = min(msg_index(c, v, static_cast<uint32_t>(j) - 1) >> AGG_DIR_SHIFT, ndir - 2);
+      }
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < UN; ++u) {
+      const uint64_t j = j0 + static_cast<uint64_t>(u) * nth;
+      const uint32_t below = __shfl_up(cell[u], 1, WAVE);                                  // the entry before stands in the lane before
+      if (j < v.nnz) {
+        const uint32_t first = j == 0 ? 0u : (lane ? below : prev[u]) + 1;
+        for (uint32_t t = first; t <= cell[u]; ++t) mine[t] = static_cast<uint32_t>(j);   // empty when the predecessor shares the block
+        if (j == v.nnz - 1) for (uint32_t t = cell[u] + 1; t < ndir; ++t) mine[t] = v.nnz;
+      }
+    }
   }
 }
 
@@ -309,163 +323,221 @@ __global__ __launch_bounds__(BLOCK) void k_aggregate_entries(DevCtx c, const uin
   }
 }
 
-// Many messages: work linear in the number of entries.  A wave owns 1024 consecutive coordinates (one cell of the
-// directories): lane p knows where listed message p's entries of that range begin and end; the entries of as many
-// messages as the staging list holds are decoded side by side into LDS, then added into an LDS image of the range
-// message after message, in list order -- the entries of one message have distinct coordinates, so the additions of
-// one message do not meet, and the order of the fp32 additions is that of k_aggregate.  No look-ups in other
-// messages: the cost of the kernels above grows with the square of the number of messages (8, 15, 32, 64 messages
-// of 99,400 entries: 55, 138, 442, 1480 us), this one's with their number.  A range that holds more than 4096
-// entries in all (segments kept whole: every message has every coordinate) would keep one wave busy for long, so
-// the waves only list such ranges and a second launch gives each of them a block of 1024 threads.
-constexpr uint32_t AGG_RANGE = 1u << AGG_DIR_SHIFT;      // coordinates per range
-constexpr uint32_t AGG_DENSE_MIN = 4096;                 // entries in a range from which a whole block takes it
-constexpr uint32_t AGG_DENSE_BLOCKS = 512;
+// Long messages, or many: work linear in the number of entries.  A wave owns the 1024 coordinates of a directory cell (or
+// a part of them) and has an image of them in LDS.  Through the directories it finds the listed messages' entries of its range; they are
+// decoded 64 at a time, side by side, whichever message they come from, and added into the image message after message in
+// list order: a message's coordinates are distinct, so the additions of one message do not meet, and a wave's LDS accesses
+// are done in order, so no barrier is needed anywhere.  A place of the image that nothing was added to holds NOBODY.  Then
+// the range of the model is updated, four coordinates at a time.
+// What bounds a wave is the chain of its reads (directory, entries, model: about a microsecond each), so what counts is
+// how many waves are in flight (2048 or 4096 coordinates per wave: slower on every shape tried) and that none is much longer
+// than the others: a cell in which the plan expects many entries (segments kept whole, or nearly) is given to several
+// waves, ahead of the others in the grid (a part's ends by bisection).  Measured, directories included, d = 25.6 M: 8 / 15 /
+// 32 / 64 messages of 99,400 entries in 161 tensors 42 / 46 / 82 / 169 us (by look-ups 53 / 129 / 440 / 1480 us; by ranges
+// added up message after message, a block of 1024 threads per crowded one: 32 / 64 messages 279 / 490 us); 2 / 4 / 8 messages
+// of 2.6 M entries 71 / 93 / 140 us (by look-ups 172 / 336 / 1109 us).
+constexpr uint32_t AGG_CELL = 1u << AGG_DIR_SHIFT;       // coordinates per directory cell
+constexpr uint32_t AGG_SCALES = 192;                     // scales (segments of the range x messages) and ...
+constexpr uint32_t AGG_SEGS = 32;                        // ... segments that a wave has room for in LDS
+constexpr uint32_t AGG_LEVELS = 3;
+constexpr uint32_t AGG_LEVEL[AGG_LEVELS] = {512, 128, 32};       // lists of crowded cells: more entries of one message than this
+constexpr uint32_t NOBODY = 0xFFFFFFFFu;                 // a NaN that no sum of finite values is
 
-template <uint32_t NT>
-__device__ __forceinline__ void range_barrier() {
-  if (NT == WAVE) {                                      // one wave, lanes in lockstep: order the LDS traffic only
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  } else __syncthreads();
+struct AggPart { uint32_t t; uint16_t i, parts; };       // part i of the 2^parts equal parts of cell t
+struct AggCrowd { const AggPart* part; const uint32_t* bits; uint32_t n; };   // the parts of a level's crowded cells; a bit per cell (null: none is crowded)
+
+typedef uint32_t u2u __attribute__((ext_vector_type(2), aligned(4)));
+// `width` (1 .. 32) bits from bit `bit` of a message on, by one 8-byte read that stays inside its cap_words words
+struct FieldRead { u2u w; uint32_t sh; };
+__device__ __forceinline__ FieldRead read_field(const uint32_t* words, uint64_t bit, uint32_t cap_words) {
+  const uint64_t q = min(bit >> 5, static_cast<uint64_t>(cap_words) - 2);
+  FieldRead f;
+  f.w = *reinterpret_cast<const u2u*>(words + q);
+  f.sh = static_cast<uint32_t>(bit - q * 32) & 63u;
+  return f;
+}
+__device__ __forceinline__ uint32_t field_of(const FieldRead& f, uint32_t width) {
+  const uint64_t v = (static_cast<uint64_t>(f.w.y) << 32 | f.w.x) >> f.sh;
+  return width == 32 ? static_cast<uint32_t>(v) : static_cast<uint32_t>(v) & ((1u << width) - 1u);
 }
 
-// One range by NT threads (NT = 64: a wave; else a block).  STAGE: entries the staging list holds (>= 1024, so that one
-// message's share of a range fits).  Returns false, having done nothing, if LIST and the range holds AGG_DENSE_MIN
-// entries or more (uniform over the threads).
-template <uint32_t NT, uint32_t STAGE, bool LIST>
-__device__ bool aggregate_range(const DevCtx& c, const uint8_t* msg, const RowList& rows, uint32_t R, float scale, int accumulate,
-                                float* out, const uint32_t* dir, uint32_t ndir, uint32_t t, float* s_acc, uint8_t* s_has,
-                                uint32_t* s_loc, float* s_val) {
-  const uint32_t lane = lane_id(), tid = threadIdx.x;
-  const uint64_t base = static_cast<uint64_t>(t) << AGG_DIR_SHIFT;
-  // lane p (of every wave): listed message p -- its row, its length, its entries [lo, hi) that fall into this range
-  uint32_t my_row = 0, my_nnz = 0, lo = 0, hi = 0;
-  if (lane < R) {
-    my_row = rows.row[lane];
-    my_nnz = min(reinterpret_cast<const uint32_t*>(msg + static_cast<uint64_t>(my_row) * c.cap_words * 4)[0], c.K);
-    lo = min(dir[static_cast<uint64_t>(lane) * ndir + t], my_nnz);
-    hi = min(dir[static_cast<uint64_t>(lane) * ndir + t + 1], my_nnz);
-    if (hi < lo) hi = lo;
-    if (hi - lo > AGG_RANGE) hi = lo + AGG_RANGE;        // a well-formed message has at most one entry per coordinate
-  }
-  const uint32_t cnt = hi - lo;
-  if (__ballot(cnt != 0) == 0) return true;              // nothing to add here
-  if (LIST && wave_sum(cnt) >= AGG_DENSE_MIN) return false;
-  for (uint32_t i = tid; i < AGG_RANGE; i += NT) s_has[i] = 0;
+// `split`: the cells that are not crowded are given to 2^split waves each (few cells with many entries: a short vector).
+__global__ __launch_bounds__(BLOCK, 8) void k_aggregate_cells(DevCtx c, const uint8_t* msg, RowList rows, int in_order, uint32_t R,
+                                                              float scale, int accumulate, float* out, const uint32_t* dir,
+                                                              uint32_t ndir, AggCrowd crowd, uint32_t split) {
+  __shared__ f4u s_image[BLOCK / 64][AGG_CELL / 4];
+  __shared__ float s_scale[BLOCK / 64][AGG_SCALES];
+  __shared__ uint32_t s_segat[BLOCK / 64][AGG_SEGS];
+  const uint32_t lane = lane_id(), wave = threadIdx.x >> 6;
+  float* image = reinterpret_cast<float*>(s_image[wave]);
+  const uint32_t b = blockIdx.x * (BLOCK / 64) + wave;
+  if (b >= crowd.n + ((ndir - 1) << split)) return;       // (no barrier follows)
+  // ---- the messages: lane p is listed message p
   const bool counts = is_qsgd(c.quantizer) && c.L > 1;
-  const uint64_t hdr = 1 + static_cast<uint64_t>(c.L) + (counts ? c.L : 0);
-  const uint32_t idx_mask = c.w_idx == 32 ? 0xFFFFFFFFu : (1u << c.w_idx) - 1u;
-  // the segments of the range's first and last coordinate: mostly the same one
-  const uint32_t seg_lo = c.L == 1 ? 0u : seg_of_coord(c, static_cast<uint32_t>(base));
-  const uint32_t seg_hi = c.L == 1 ? 0u : seg_of_coord(c, static_cast<uint32_t>(min<uint64_t>(base + AGG_RANGE, c.d) - 1));
-  uint32_t p0 = 0;
-  while (p0 < R) {                                       // uniform over the threads
-    // the batch p0 .. p1 - 1: as many messages as the staging list holds (at least one)
-    uint32_t tot;
-    const uint32_t before = wave_exclusive_scan32(lane >= p0 && lane < R ? cnt : 0u, &tot);
-    const uint64_t over = __ballot(lane > p0 && lane < R && before + cnt > STAGE);
-    const uint32_t p1 = over ? static_cast<uint32_t>(__ffsll(static_cast<unsigned long long>(over)) - 1) : R;
-    const uint32_t n_staged = p1 < R ? __shfl(before, p1, WAVE) : tot;
-    const uint64_t in_batch = __ballot(cnt != 0 && lane >= p0 && lane < p1);
-    // decode the batch side by side, 4 x NT staged entries per step with their loads in flight together: staged entry
-    // f belongs to the last message x of the batch with before_x <= f
-    constexpr uint32_t UN = 4;
-    for (uint32_t f0 = 0; f0 < n_staged; f0 += UN * NT) {
-      uint32_t q_row[UN], q_nnz[UN], q_lo[UN], q_before[UN];
+  const uint32_t hdr = 1 + c.L + (counts ? c.L : 0);
+  uint32_t my_row = lane < R ? lane : 0u;
+  if (!in_order) my_row = rows.row[lane];
+  const uint32_t* my_words = reinterpret_cast<const uint32_t*>(msg + static_cast<uint64_t>(my_row) * c.cap_words * 4);
+  // ---- the coordinates: a cell, or a part of a crowded one
+  uint32_t t0, from, width;
+  const bool crowded = b < crowd.n, is_part = crowded || split != 0;
+  if (crowded) { const AggPart a = crowd.part[b]; t0 = a.t; width = AGG_CELL >> a.parts; from = a.i * width; }
+  else { t0 = (b - crowd.n) >> split; width = AGG_CELL >> split; from = ((b - crowd.n) & ((1u << split) - 1u)) * width; }
+  const uint32_t* my_dir = dir + static_cast<uint64_t>(lane < R ? lane : 0u) * ndir + t0;
+  const uint32_t my_nnz = lane < R ? min(my_words[0], c.K) : 0u;
+  uint32_t lo = lane < R ? min(my_dir[0], my_nnz) : 0u, hi = lane < R ? min(my_dir[1], my_nnz) : 0u;
+  uint32_t seg0 = 0, ns = 1;
+  if (c.L > 1 && !is_part) { seg0 = c.seg_dir[t0]; ns = c.seg_dir[t0 + 1] - seg0 + 1; }
+  if (!crowded && crowd.bits != nullptr && ((crowd.bits[t0 >> 5] >> (t0 & 31u)) & 1u)) return;      // waves of its own look after it
+  const float nobody = __uint_as_float(NOBODY);
+  uint64_t c0 = static_cast<uint64_t>(t0) << AGG_DIR_SHIFT;
+  uint32_t span = AGG_CELL;
+  if (is_part) {
+    // the part's entries among the cell's [lo, hi): both ends by bisection in step, every step reads the quarter points
+    const uint32_t la = lo, lb = max(lo, hi), f1 = from + width;
+    uint32_t l0 = la, h0 = from == 0 ? la : lb, l1 = f1 >= AGG_CELL ? lb : la, h1 = lb;
+    if (lb - la == AGG_CELL) { l0 = h0 = la + from; l1 = h1 = la + f1; }        // every coordinate is there
+    auto at = [&](uint32_t j) { return field_of(read_field(my_words, static_cast<uint64_t>(hdr) * 32 + static_cast<uint64_t>(min(j, my_nnz - 1)) * c.w_idx, c.cap_words), c.w_idx); };
+    while (l0 < h0 || l1 < h1) {
+      uint32_t m0[3], m1[3], x0[3], x1[3];
 #pragma unroll
-      for (uint32_t u = 0; u < UN; ++u) { q_row[u] = 0; q_nnz[u] = 0; q_lo[u] = 0; q_before[u] = 0; }
-      for (uint64_t left = in_batch; left; left &= left - 1) {      // the batch's messages that have entries here, in order
-        const int x = __ffsll(static_cast<unsigned long long>(left)) - 1;     // (uniform: every lane takes part in the shuffles)
-        const uint32_t bx = __shfl(before, x, WAVE);
-        const uint32_t rx = __shfl(my_row, x, WAVE), nx = __shfl(my_nnz, x, WAVE), lx = __shfl(lo, x, WAVE);
-#pragma unroll
-        for (uint32_t u = 0; u < UN; ++u)
-          if (f0 + u * NT + tid >= bx) { q_row[u] = rx; q_nnz[u] = nx; q_lo[u] = lx; q_before[u] = bx; }
+      for (uint32_t q = 0; q < 3; ++q) {
+        m0[q] = l0 + ((h0 - l0) * (q + 1) >> 2); m1[q] = l1 + ((h1 - l1) * (q + 1) >> 2);
+        x0[q] = at(m0[q]); x1[q] = at(m1[q]);
       }
-      uint32_t idx[UN], code[UN];
-      const uint32_t* words[UN];
-#pragma unroll
-      for (uint32_t u = 0; u < UN; ++u) {
-        const uint32_t f = f0 + u * NT + tid;
-        words[u] = reinterpret_cast<const uint32_t*>(msg + static_cast<uint64_t>(q_row[u]) * c.cap_words * 4);
-        idx[u] = 0xFFFFFFFFu; code[u] = 0;
-        if (f < n_staged) {
-          const uint32_t j = q_lo[u] + (f - q_before[u]);
-          idx[u] = get_bits(words[u], hdr * 32 + static_cast<uint64_t>(j) * c.w_idx, c.w_idx) & idx_mask;
-          const uint64_t code_bit0 = (hdr + (static_cast<uint64_t>(q_nnz[u]) * c.w_idx + 31) / 32) * 32;
-          code[u] = get_bits(words[u], code_bit0 + static_cast<uint64_t>(j) * c.w_val, c.w_val);
-        }
+      if (l0 < h0) {
+        if (!(x0[0] < c0 + from)) h0 = m0[0];
+        else if (!(x0[1] < c0 + from)) { l0 = m0[0] + 1; h0 = m0[1]; }
+        else if (!(x0[2] < c0 + from)) { l0 = m0[1] + 1; h0 = m0[2]; }
+        else l0 = m0[2] + 1;
       }
-#pragma unroll
-      for (uint32_t u = 0; u < UN; ++u) {
-        const uint32_t f = f0 + u * NT + tid;
-        if (f < n_staged) {
-          uint32_t loc = 0xFFFFFFFFu;
-          float val = 0.0f;
-          if (idx[u] >= base && idx[u] < base + AGG_RANGE && idx[u] < c.d) {
-            const uint32_t seg = c.L == 1 ? 0u : seg_lo == seg_hi ? seg_lo : seg_of_coord(c, idx[u]);
-            val = value_of_code(c, code[u], __uint_as_float(words[u][1 + seg]));
-            loc = static_cast<uint32_t>(idx[u] - base);
-          } else atomicOr(c.status, 4u);                   // malformed message: the entry is skipped
-          s_loc[f] = loc; s_val[f] = val;
-        }
+      if (l1 < h1) {
+        if (!(x1[0] < c0 + f1)) h1 = m1[0];
+        else if (!(x1[1] < c0 + f1)) { l1 = m1[0] + 1; h1 = m1[1]; }
+        else if (!(x1[2] < c0 + f1)) { l1 = m1[1] + 1; h1 = m1[2]; }
+        else l1 = m1[2] + 1;
       }
     }
-    range_barrier<NT>();
-    // add them message after message
-    for (uint64_t left = in_batch; left; left &= left - 1) {
-      const int x = __ffsll(static_cast<unsigned long long>(left)) - 1;
-      const uint32_t bx = __shfl(before, x, WAVE), cx = __shfl(cnt, x, WAVE);
-      for (uint32_t i = tid; i < cx; i += NT) {
-        const uint32_t loc = s_loc[bx + i];
-        if (loc != 0xFFFFFFFFu) {
-          const float v = s_val[bx + i];
-          s_acc[loc] = s_has[loc] ? s_acc[loc] + v : v;
-          s_has[loc] = 1;
-        }
-      }
-      range_barrier<NT>();
-    }
-    p0 = p1;
+    lo = l0; hi = l1; c0 += from; span = width;
   }
-  for (uint32_t i = tid; i < AGG_RANGE; i += NT) {
-    if (s_has[i]) {
-      const float term = scale * s_acc[i];
-      out[base + i] = accumulate ? out[base + i] + term : term;
+  if (c0 >= c.d) return;
+  const uint32_t cnt = hi > lo ? min(hi - lo, span) : 0u; // a well-formed message has at most one entry per coordinate
+  span = static_cast<uint32_t>(min<uint64_t>(span, c.d - c0));
+  const uint32_t base = static_cast<uint32_t>(c0);
+  uint32_t n;
+  const uint32_t before = wave_exclusive_scan32(cnt, &n);
+  if (n == 0 && accumulate) return;
+  if (c.L > 1 && is_part) { seg0 = seg_of_coord(c, base); ns = seg_of_coord(c, base + span - 1) - seg0 + 1; }
+  // lane p, for the lanes that decode entries of message p: entry f of the item is the message's entry f + my_j
+  const uint32_t my_j = lo - before;
+  const uint32_t my_code = hdr + static_cast<uint32_t>((static_cast<uint64_t>(my_nnz) * c.w_idx + 31) / 32);      // first word of its codes
+  constexpr uint32_t UN = 4;                              // steps of 64 entries whose reads are in flight together
+  FieldRead fi[UN], fc[UN]; uint32_t pp[UN];
+  auto load = [&](uint32_t f0) {
+#pragma unroll
+    for (uint32_t u = 0; u < UN; ++u) {
+      if (f0 + u * WAVE >= n) break;                      // (uniform)
+      const uint32_t f = f0 + u * WAVE + lane;
+      uint32_t a = 0;                                     // the last message whose entries begin at or before f
+      for (uint32_t step = R > 32 ? 32u : R > 16 ? 16u : R > 8 ? 8u : R > 4 ? 4u : R > 2 ? 2u : 1u; step; step >>= 1) {
+        const uint32_t m = a + step;
+        const uint32_t x = __shfl(before, m & 63u, WAVE);
+        if (m < R && x <= f) a = m;
+      }
+      pp[u] = a;
+      const uint32_t j = f + __shfl(my_j, a, WAVE), code0 = __shfl(my_code, a, WAVE), row = __shfl(my_row, a, WAVE);
+      if (f < n) {
+        const uint32_t* words = reinterpret_cast<const uint32_t*>(msg + static_cast<uint64_t>(row) * c.cap_words * 4);
+        fi[u] = read_field(words, static_cast<uint64_t>(hdr) * 32 + static_cast<uint64_t>(j) * c.w_idx, c.cap_words);
+        fc[u] = read_field(words, static_cast<uint64_t>(code0) * 32 + static_cast<uint64_t>(j) * c.w_val, c.cap_words);
+      }
+    }
+  };
+  load(0);
+  // the segments of the range and every message's scales: one segment -- lane p its message's scale; several -- in LDS
+  const bool table = ns <= AGG_SEGS && ns * R <= AGG_SCALES;
+  float my_scale = 0.0f;
+  if (ns == 1) my_scale = lane < R ? __uint_as_float(my_words[1 + seg0]) : 0.0f;
+  else if (table) {
+    if (lane < ns) s_segat[wave][lane] = c.seg_start[seg0 + lane];
+    for (uint32_t i = lane; i - lane < ns * R; i += WAVE) {
+      const uint32_t p = i / ns, g = i - p * ns, row = __shfl(my_row, p & 63u, WAVE);
+      if (p < R) s_scale[wave][i] = reinterpret_cast<const float*>(msg + static_cast<uint64_t>(row) * c.cap_words * 4)[1 + seg0 + g];
     }
   }
-  return true;
-}
-
-// a wave per range; the ranges with too many entries for one wave go to `dense_list` (dense_list[0] counts them)
-__global__ __launch_bounds__(64) void k_aggregate_ranges(DevCtx c, const uint8_t* msg, RowList rows, uint32_t R, float scale,
-                                                         int accumulate, float* out, const uint32_t* dir, uint32_t ndir,
-                                                         uint32_t* dense_list) {
-  __shared__ float s_acc[AGG_RANGE];
-  __shared__ uint8_t s_has[AGG_RANGE];
-  __shared__ uint32_t s_loc[1024];
-  __shared__ float s_val[1024];
-  if (!aggregate_range<64, 1024, true>(c, msg, rows, R, scale, accumulate, out, dir, ndir, blockIdx.x, s_acc, s_has, s_loc, s_val) &&
-      threadIdx.x == 0)
-    dense_list[1 + atomicAdd(&dense_list[0], 1u)] = blockIdx.x;
-}
-
-// a block of 1024 threads per listed range
-__global__ __launch_bounds__(1024) void k_aggregate_dense_ranges(DevCtx c, const uint8_t* msg, RowList rows, uint32_t R,
-                                                                 float scale, int accumulate, float* out, const uint32_t* dir,
-                                                                 uint32_t ndir, const uint32_t* dense_list) {
-  __shared__ float s_acc[AGG_RANGE];
-  __shared__ uint8_t s_has[AGG_RANGE];
-  __shared__ uint32_t s_loc[8192];
-  __shared__ float s_val[8192];
-  const uint32_t n = min(dense_list[0], ndir - 1);
-  for (uint32_t li = blockIdx.x; li < n; li += gridDim.x) {
-    const uint32_t t = dense_list[1 + li];
-    if (t < ndir - 1)
-      aggregate_range<1024, 8192, false>(c, msg, rows, R, scale, accumulate, out, dir, ndir, t, s_acc, s_has, s_loc, s_val);
-    __syncthreads();                                     // the LDS arrays are reused for the block's next range
+  for (uint32_t i = lane; i * 4 < span; i += WAVE) s_image[wave][i] = f4u{nobody, nobody, nobody, nobody};
+  // ---- decode and add
+  for (uint32_t f0 = 0; f0 < n; f0 += UN * WAVE) {
+    if (f0) load(f0);
+#pragma unroll
+    for (uint32_t u = 0; u < UN; ++u) {
+      if (f0 + u * WAVE >= n) break;                      // (uniform)
+      const bool mine = f0 + u * WAVE + lane < n;
+      const uint32_t idx = field_of(fi[u], c.w_idx), loc = idx - base;
+      const bool ok = mine && idx >= base && loc < span;
+      float sc = __shfl(my_scale, pp[u], WAVE);
+      if (ns > 1) {
+        if (table) {
+          uint32_t a = 0, z = ns;
+          while (z - a > 1) { const uint32_t mid = (a + z) >> 1; if (s_segat[wave][mid] <= idx) a = mid; else z = mid; }
+          sc = s_scale[wave][pp[u] * ns + a];
+        } else {
+          const uint32_t row = __shfl(my_row, pp[u], WAVE);
+          if (ok) sc = reinterpret_cast<const float*>(msg + static_cast<uint64_t>(row) * c.cap_words * 4)[1 + seg_of_coord(c, idx)];
+        }
+      }
+      if (mine && !ok) atomicOr(c.status, 4u);            // malformed message: the entry is skipped
+      const float v = value_of_code(c, field_of(fc[u], c.w_val), sc);
+      uint64_t todo = __ballot(ok);
+      while (todo) {                                      // the messages of this step, in order
+        const uint32_t p = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(pp[u]), __ffsll(static_cast<unsigned long long>(todo)) - 1));
+        const bool now = ok && pp[u] == p;
+        if (now) {
+          const float have = image[loc];
+          image[loc] = __float_as_uint(have) == NOBODY ? v : have + v;
+        }
+        todo &= ~__ballot(now);
+        // the next message may hold the same coordinates in other lanes: order the LDS traffic (the lanes run in lockstep)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      }
+    }
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  // ---- the range of the model
+  constexpr uint32_t ON = 4;
+  for (uint32_t i0 = lane * 4; i0 - lane * 4 < span; i0 += ON * WAVE * 4) {
+    f4u a[ON], o[ON];
+    bool any[ON];
+#pragma unroll
+    for (uint32_t u = 0; u < ON; ++u) {
+      const uint32_t i = i0 + u * WAVE * 4;
+      any[u] = false;
+      a[u] = f4u{nobody, nobody, nobody, nobody}; o[u] = f4u{0.f, 0.f, 0.f, 0.f};
+      if (i < span) {
+        a[u] = s_image[wave][i / 4];
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) any[u] = any[u] || __float_as_uint(a[u][j]) != NOBODY;
+        any[u] = any[u] || !accumulate;                   // without `accumulate` the coordinates nobody holds are written too
+        if (any[u] && accumulate) {
+          if (i + 4 <= span) o[u] = *reinterpret_cast<const f4u*>(out + c0 + i);
+          else for (uint32_t j = 0; j < 4; ++j) if (i + j < span) o[u][j] = out[c0 + i + j];
+        }
+      }
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < ON; ++u) {
+      const uint32_t i = i0 + u * WAVE * 4;
+      if (!any[u]) continue;
+#pragma unroll
+      for (uint32_t j = 0; j < 4; ++j)
+        if (__float_as_uint(a[u][j]) != NOBODY) { const float term = scale * a[u][j]; o[u][j] = accumulate ? o[u][j] + term : term; }
+      if (i + 4 <= span) *reinterpret_cast<f4u*>(out + c0 + i) = o[u];
+      else for (uint32_t j = 0; j < 4; ++j) if (i + j < span) out[c0 + i + j] = o[u][j];
+    }
   }
 }
 

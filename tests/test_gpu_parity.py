@@ -717,3 +717,45 @@ def test_aggregate_long_messages_shared_coordinates(P, case):
     want = _aggregate_by_definition(decoded, list(range(8)), 1.0, x0, False, wl.d)
     assert np.array_equal(out.cpu().numpy().view(np.uint32), want.view(np.uint32))
     assert q.device_status() == B.OK
+
+
+# k_aggregate_cells at the edges of its dispatch: more segments in a cell than a wave's table holds, a vector of a few cells
+# in many parts, a last cell of one coordinate, a message per lane, lists out of order
+@pytest.mark.parametrize("case", ["tiny_segments", "few_cells", "one_coordinate_in_the_last_cell", "kept_whole_and_sparse"])
+def test_aggregate_by_cells_edges(P, case):
+    from paper_1906_02367_amd import binding as B
+    rng = np.random.default_rng(len(case))
+    if case == "tiny_segments":            # 34 segments in every cell, 40 messages: scales read one by one
+        off = list(range(0, 3_001, 30)) + [3_001]
+        wl = custom(3_001, off, [min(7, b - a) for a, b in zip(off, off[1:])], 3, W.TOPK, W.QSGD, R=8)
+        lists = [list(range(40)), [int(x) for x in rng.permutation(64)[:63]]]
+    elif case == "few_cells":              # 69 cells with up to 4,600 entries: 16 waves per cell
+        wl = custom(70_001, [0, 70_001], [5_000], 1, W.TOPK, W.SIGN_L1, R=8)
+        lists = [list(range(64)), [9, 2, 40, 3], [int(x) for x in rng.permutation(64)[:31]]]
+    elif case == "one_coordinate_in_the_last_cell":
+        wl = custom(20_481, [0, 20_481], [6_000], 1, W.RANDK, W.FP32, R=8)
+        lists = [list(range(17)), [63, 1], list(range(33))]
+    else:
+        off = [0, 900, 2_948, 200_000, 200_064, 260_000]
+        wl = custom(260_000, off, [900, 2_048, 3_000, 64, 900], 1, W.TOPK, W.SIGN_L2, R=8)
+        lists = [list(range(64)), [5, 3, 60, 2, 1, 8, 7], list(range(12))]
+    q = B.from_workload(wl)
+    op = P.oracle_for(wl)
+    msg = q.new_msg(64)
+    common = rng.standard_normal(wl.d).astype(f32)
+    for b in range(8):
+        own = rng.standard_normal((8, wl.d)).astype(f32)
+        delta = torch.from_numpy(((common[None, :] + f32(b % 3) * own) * np.exp(rng.standard_normal(wl.d))).astype(f32)).to(q.device)
+        m = torch.zeros(8, wl.d, device=q.device)
+        q.compress(m, delta, m, 8 * b, b, msg[8 * b: 8 * b + 8])
+    torch.cuda.synchronize()
+    decoded = [op.decode(x) for x in msg.cpu().numpy()]
+    x0 = rng.standard_normal(wl.d).astype(f32)
+    for lst in lists:
+        for accumulate in (True, False):
+            out = torch.from_numpy(x0).to(q.device)
+            q.aggregate(msg, out, -1.0 / 64, worker_list=lst, accumulate=accumulate)
+            torch.cuda.synchronize()
+            want = _aggregate_by_definition(decoded, lst, -1.0 / 64, x0, accumulate, wl.d)
+            assert np.array_equal(out.cpu().numpy().view(np.uint32), want.view(np.uint32)), (case, len(lst), accumulate)
+    assert q.device_status() == B.OK
