@@ -74,6 +74,8 @@ uint32_t bit_width_u64(uint64_t x) { uint32_t w = 0; while (x) { ++w; x >>= 1; }
 // ====================================================================================================
 constexpr uint32_t AGG_WAVE_ENTRIES = 1024;      // entries of all listed messages from which a cell is given to several waves
 
+constexpr uint32_t PACK_BLOCKS = 4096;           // blocks of k_pack at most, for all workers
+
 struct qsl_ctx {
   qsl_config cfg;
   std::vector<uint64_t> off;
@@ -867,12 +869,8 @@ static qsl_status launch_compress(qsl_ctx* ctx, const float* m, const float* del
     if (c.QB > MAX_QB_INLINE) k_surv_scan<<<dim3(R), 1024, 0, st>>>(c);
     k_pack_sent<<<dim3(c.QB, R), BLOCK, 0, st>>>(c, msg, msg_bits, nzero);
   } else {                                         // every selected coordinate is sent: the final arrays are written already
-    // a thread per message word -- two words per thread once the blocks would no longer all be resident at once (2048
-    // blocks of 256 threads): a kernel of many short threads is bound by the rate at which its waves start (161 tensors,
-    // 99,400 entries, 8 workers: 13.0 us with one word per thread, 10.2 us with two, 11.2 with four, 14.3 with eight; with
-    // a quarter of the entries one word per thread is the faster by 1.5 us)
-    uint32_t pack_blocks = (c.cap_words + BLOCK - 1) / BLOCK;
-    if (static_cast<uint64_t>(pack_blocks) * R > 2048) pack_blocks = (pack_blocks + 1) / 2;
+    // a wave per 64 entries, several of them a grid's width apart once the chip is full
+    const uint32_t pack_blocks = std::max(1u, std::min((c.K + 64 * (BLOCK / 64) - 1) / (64 * (BLOCK / 64)), std::max(1u, PACK_BLOCKS / R)));
     k_pack<<<dim3(pack_blocks, R), BLOCK, 0, st>>>(c, msg, msg_bits, nzero);
   }
   QSL_HIP(hipGetLastError());
