@@ -62,6 +62,7 @@
 #include "qsl_encode.h"
 #include "qsl_stream.h"
 #include "qsl_lean.h"
+#include "qsl_window.h"
 #include "qsl_dense.h"
 #include "qsl_decode.h"
 
@@ -83,6 +84,7 @@ struct qsl_ctx {
   std::vector<SegInfo> segs;
   hipStream_t stream;
   DevCtx dc;
+  WinCtx wc;                  // a dense k on the whole vector (DevCtx::win)
   StreamSeg one;
   void* slab;                 // one allocation holding every scratch array
   uint32_t Rmax;
@@ -281,6 +283,49 @@ static double plan_segment(const qsl_config* cfg, SegInfo& sg) {
   return cand;
 }
 
+// Whether the only segment of an operator, which plan_segment gives to the multi-pass kernels, goes the way of the window
+// (qsl_window.h); fills the fields of the plan that this needs.  The window is two quantiles of a sample: runs of 16
+// coordinates, a 32nd of the vector but at least 32,768 and at most 2^20 of them -- more, up to half of it, while the
+// window's coordinates would not fit the slots well -- with a margin of 6.5 sigma of a sample of an eighth of that size on
+// either side: runs share their surroundings' scale.  Too small a window costs a call with the multi-pass kernels, a large
+// one slots: at d = 25.6 M, k = d / 10 it holds 1.4 % of the vector.  From 3 M coordinates on: the window takes twelve
+// launches, six of them idle, against eight (k = d / 10, one worker: 1.5 M coordinates 71 us both ways, 3 M 76 against 86;
+// k = 3 %, eight workers: 1 M 100 against 88, 3 M 165 against 213).
+constexpr uint64_t WINDOW_MIN = 3ull << 20;
+static bool plan_window(const qsl_config* cfg, SegInfo& sg) {
+  if (cfg->num_segments != 1 || sg.mode != PATH_GENERAL || sg.size < WINDOW_MIN || sg.k == sg.size ||
+      (cfg->flags & (QSL_FLAG_NO_FAST_PATH | QSL_FLAG_NO_SMALL_PATH))) return false;
+  const double n = static_cast<double>(sg.size), p = sg.k / n;
+  double need = 0;                                 // places that a chunk's slot should have: the expected coordinates and 4 sigma
+  if (cfg->sparsifier == QSL_TOPK) {
+    for (double target = std::min(1048576.0, std::max(32768.0, n / 32)); target <= n / 2; target *= 2) {
+      sg.n_runs = static_cast<uint32_t>(std::ceil(target / WRUN));
+      sg.samp_stride = static_cast<uint32_t>(sg.size / sg.n_runs);
+      const double ns = sg.n_runs * static_cast<double>(WRUN), mu = ns * p;
+      const double margin = 6.5 * std::sqrt(8.0 * ns * p * (1 - p)) + 16;
+      sg.r_tau = static_cast<uint32_t>(std::max(0.0, std::floor(mu - margin)));
+      sg.r_s = static_cast<uint32_t>(std::min(ns, std::ceil(mu + margin)));
+      sg.nsamp = std::min(64u, std::max(1u, (sg.n_runs + 511) / 512));    // a block keeps 512 runs in flight
+      const double pc = (2 * margin / ns + 0.008) * CHUNK;                // + the bins at both ends, 1/64 of a binade each
+      need = pc + 4 * std::sqrt(pc);
+      if (need <= 47) break;
+    }
+  } else {
+    const double q = 7.0 * std::sqrt(p * (1 - p) / n);
+    const double lo = std::floor(4294967296.0 * std::max(0.0, 1 - p - q)), hi = std::min(4294967295.0, std::ceil(4294967296.0 * (1 - p + q)));
+    sg.T_static = static_cast<uint32_t>(lo); sg.r_s = static_cast<uint32_t>(hi);
+    const double pc = (hi - lo) / 4294967296.0 * CHUNK;
+    need = pc + 4 * std::sqrt(pc);
+  }
+  if (need > 63) return false;
+  sg.lpc = need <= 15 ? 8 : need <= 31 ? 16 : 32;
+  sg.ovf_cap = static_cast<uint32_t>(std::min<uint64_t>(sg.size, std::max<uint64_t>(8192, sg.size / 8)));
+  const uint64_t rows = (static_cast<uint64_t>(sg.nwt) * sg.lpc + 63) / 64;
+  // a thousand-thread block per compute unit at most, about three slot rows per wave (as for the guessing units)
+  sg.nsel = static_cast<uint32_t>(std::max<uint64_t>(1, std::min<uint64_t>({MAX_SELECT_BLOCKS, 256 / std::min(256u, cfg->max_workers), (rows + 47) / 48})));
+  return true;
+}
+
 extern "C" qsl_status qsl_plan_paths(const qsl_config* cfg, uint32_t* path_out) {
   uint64_t K = 0;
   if (!path_out) return QSL_ERR_INVALID_ARG;
@@ -353,6 +398,7 @@ extern "C" qsl_status qsl_create(qsl_ctx** out, const qsl_config* cfg, void* hip
   std::vector<uint32_t> fast, smalls;
   uint64_t slot_elems = 0, ovf_entries = 0, d0_entries = 0, nwt64 = 0, nwc = 0;
   uint32_t koff = 0, n_in_stream = 0;
+  bool window = false;
   ctx->n_sampled = 0;
   for (uint32_t l = 0; l < L; ++l) {
     SegInfo& sg = segs[l];
@@ -417,6 +463,7 @@ extern "C" qsl_status qsl_create(qsl_ctx** out, const qsl_config* cfg, void* hip
       // at most 256 compaction blocks per unit, each a contiguous range of groups: every block ends with up to 20
       // atomics on the unit's digit counters, and thousands of blocks on the same few lines serialise there
       sg.ncb = std::min<uint32_t>(256, (sg.nwt + GGROUP - 1) / GGROUP);
+      if (plan_window(cfg, sg)) { window = true; slot_elems = static_cast<uint64_t>(sg.nwt) * sg.lpc * 2; ovf_entries = sg.ovf_cap; }
     }
   }
   // blocks of a fast unit in the selection kernels: ~3 slot rows per wave, and no more than one block
@@ -517,6 +564,7 @@ extern "C" qsl_status qsl_create(qsl_ctx** out, const qsl_config* cfg, void* hip
   const uint64_t o_hist = carve(4ull * 3 * HBINS * U), o_ctr = carve(4ull * CTR_LINES * PAD * U);
   const uint64_t o_acc = carve(8ull * ACC_SLOTS * U), o_status = carve(8);
   const uint64_t o_blk = carve(4ull * QB * R * 2);    // the two arrays of per-block counters of transmitted entries
+  const uint64_t o_wsam = carve(window ? 4ull * WCOPIES * WBINS * R : 4), o_whist = carve(window ? 4ull * HBINS * R : 4);
   const uint64_t zero_bytes = bytes;
   const uint64_t o_segs = carve(sizeof(SegInfo) * L), o_wts = carve(sizeof(WtInfo) * std::max<size_t>(1, wts.size()));
   const uint64_t o_sels = carve(sizeof(SelInfo) * NSEL), o_cbs = carve(sizeof(CbInfo) * NCB);
@@ -560,6 +608,9 @@ extern "C" qsl_status qsl_create(qsl_ctx** out, const qsl_config* cfg, void* hip
   const uint64_t o_d0k = carve(4ull * std::max<uint64_t>(1, d0_entries) * R);
   const uint64_t o_wc = carve(4ull * NWC * R), o_ws = carve(4ull * NWC * R), o_cbc = carve(8ull * NCB * R);
   const uint64_t o_tlist = carve(16ull * LISTCAP * std::max<size_t>(1, fast.size()) * R);
+  const uint64_t o_wstate = carve(sizeof(WinState) * R);
+  const uint64_t o_wpart = carve(window ? 8ull * acc_slots(cfg->quantizer) * ((NWT + 3) / 4) * R : 8);
+  const uint64_t o_wlist = carve(window ? 16ull * WLIST * R : 16), o_woff = carve(window ? 4ull * NWT * R : 4);
   const bool dense = (cfg->flags & QSL_FLAG_DENSE_FORMAT) != 0;
   const uint64_t KA = dense ? 1 : K;                 // the index-free format needs no per-entry arrays
   const uint64_t o_si = carve(4ull * KA * R), o_sv = carve(4ull * KA * R), o_sc = carve(4ull * KA * R);
@@ -674,6 +725,18 @@ extern "C" qsl_status qsl_create(qsl_ctx** out, const qsl_config* cfg, void* hip
   c.wave_cnt = reinterpret_cast<uint32_t*>(base + o_wc); c.wave_sel = reinterpret_cast<uint32_t*>(base + o_ws);
   c.cb_cnt = reinterpret_cast<uint2*>(base + o_cbc);
   c.tlist = reinterpret_cast<uint4*>(base + o_tlist);
+  c.win = window ? 1u : 0u;
+  WinCtx& wc = ctx->wc;
+  wc.state = reinterpret_cast<WinState*>(base + o_wstate);
+  wc.sample = reinterpret_cast<uint32_t*>(base + o_wsam); wc.hist = reinterpret_cast<uint32_t*>(base + o_whist);
+  wc.part = reinterpret_cast<uint64_t*>(base + o_wpart); wc.list = reinterpret_cast<uint4*>(base + o_wlist);
+  wc.off = reinterpret_cast<uint32_t*>(base + o_woff);
+  if (window) {                                     // Rand_k: the window is fixed
+    WinState ws = {segs[0].T_static, segs[0].r_s, 0, 0, 0};
+    while (((ws.hi - 1 - ws.lo) >> ws.sh) >= HBINS) ++ws.sh;
+    const std::vector<WinState> all(R, ws);
+    if (hipMemcpy(wc.state, all.data(), sizeof(WinState) * R, hipMemcpyHostToDevice) != hipSuccess) { free_ctx(ctx); return QSL_ERR_DEVICE; }
+  }
   ctx->h_status[8] = 0;
   {
     void* dflag = nullptr;                          // the device's address of a word of the pinned host block
@@ -779,6 +842,10 @@ static qsl_status launch_compress(qsl_ctx* ctx, const float* m, const float* del
     k_sample<<<dim3(ctx->nsamp_blocks * R), BIG, 0, st>>>(c, m, delta, xm, R);
     k_sample_scan<<<dim3(c.nfast, R), BIG, 0, st>>>(c);
   }
+  if (SPARS == QSL_TOPK && c.win) {                // the window: every call's own sample
+    k_win_sample<<<dim3(ctx->segs[0].nsamp * R), BIG, 0, st>>>(c, ctx->wc, ctx->segs[0], m, delta, xm, R);
+    k_win_scan<<<dim3(R), BIG, 0, st>>>(ctx->wc, ctx->segs[0]);
+  }
   ctx->warm_R = std::max(ctx->warm_R, R);
   const bool timed = ctx->timing != 0;
   if (timed) {
@@ -790,7 +857,11 @@ static qsl_status launch_compress(qsl_ctx* ctx, const float* m, const float* del
   const uint32_t nblk = (c.NWT + 3) / 4;
   // QSGD: k_pack_sent adds the fields of the transmitted entries to messages that the streaming pass has cleared
   uint32_t* msg_zero = is_qsgd(c.quantizer) ? reinterpret_cast<uint32_t*>(msg) : nullptr;
-  if (xm == nullptr) {
+  if (c.win) {                                     // a dense k on the whole vector: qsl_window.h
+    const dim3 sgrid(nblk, R), dgrid(static_cast<uint32_t>(static_cast<uint64_t>((nblk + 7) / 8) * 8 * R));
+    if (xm == nullptr) k_win_stream<SPARS, false><<<sgrid, BLOCK, 0, st>>>(c, ctx->wc, ctx->one, m, delta, xm, m_out, worker0, round, R, msg_zero);
+    else k_win_stream<SPARS, true><<<dgrid, BLOCK, 0, st>>>(c, ctx->wc, ctx->one, m, delta, xm, m_out, worker0, round, R, msg_zero);
+  } else if (xm == nullptr) {
     const dim3 sgrid(nblk, R);
     if (c.L == 1) k_stream<SPARS, true, false><<<sgrid, BLOCK, 0, st>>>(c, ctx->one, m, delta, xm, m_out, worker0, round, R, msg_zero, sel_idx, sel_level);
     else k_stream<SPARS, false, false><<<sgrid, BLOCK, 0, st>>>(c, ctx->one, m, delta, xm, m_out, worker0, round, R, msg_zero, sel_idx, sel_level);
@@ -847,6 +918,13 @@ static qsl_status launch_compress(qsl_ctx* ctx, const float* m, const float* del
     k_lean_hist<SPARS><<<dim3(c.NSELF * R), BIG, 0, st>>>(c, ctx->segs[0], R);
     k_lean_mark<SPARS><<<dim3(c.NSELF * R), BIG, 0, st>>>(c, ctx->segs[0], R);
   }
+  if (c.win) {
+    const SegInfo& sg = ctx->segs[0];
+    k_win_hist<SPARS><<<dim3(sg.nsel * R), BIG, 0, st>>>(c, ctx->wc, sg, R);
+    k_win_mark<SPARS><<<dim3(sg.nsel * R), BIG, 0, st>>>(c, ctx->wc, sg, R);
+    k_win_mid<SPARS><<<dim3(sg.nsel * R), BIG, 0, st>>>(c, ctx->wc, sg, R);
+    k_win_apply<SPARS><<<dim3(nblk, R), BLOCK, 0, st>>>(c, ctx->wc, sg, m_out, worker0, round, sel_idx, sel_level);
+  }
   // the multi-pass kernels: a launch per digit and two for the compaction, for the units planned that way -- and for
   // the guessing units too while failed guesses are expected
   const uint32_t nsel = safe ? c.NSEL : ctx->nsel_general, ncb = safe ? c.NCB : ctx->ncb_general;
@@ -857,7 +935,7 @@ static qsl_status launch_compress(qsl_ctx* ctx, const float* m, const float* del
     k_tile_count<SPARS><<<dim3(ncb * R), BLOCK, 0, st>>>(c, ctx->segs[0], m_out, worker0, round, R);
     k_tile_write<SPARS><<<dim3(ncb * R), BLOCK, 0, st>>>(c, ctx->segs[0], m_out, worker0, round, R);
   }
-  if (ctx->n_other || safe) k_quantize<<<dim3(c.QB, R), BLOCK, 0, st>>>(c, m_out, worker0, round, sel_idx, sel_level, safe ? 1 : 0);
+  if (ctx->n_other || safe) k_quantize<<<dim3(c.win ? std::min(c.QB, 256u) : c.QB, R), BLOCK, 0, st>>>(c, m_out, worker0, round, sel_idx, sel_level, safe ? 1 : 0);
   // the guessing units' exact threshold, ordered output and codes; one more block per guessing unit for failures
   if (c.NSELF)
     k_lean_emit<SPARS><<<dim3((c.NSELF + c.nfast) * R), BIG, 0, st>>>(c, ctx->segs[0], R, c.NSELF * R, m_out, worker0, round,

@@ -118,12 +118,11 @@ __device__ __forceinline__ UnitScale unit_scale(const DevCtx& c, float sc, uint3
 }
 
 // One selected coordinate (slot `slot` of the worker-major [R][K] arrays; coordinate idx, value bits): its code
-// (QSGD: Definition 1, example 1; Sign: Definition 2), the arrays the message is packed from, the error update
-// m <- v - g on a transmitted coordinate (Algorithm 1, second worker line), the optional debug outputs.
+// (QSGD: Definition 1, example 1; Sign: Definition 2), the arrays the message is packed from, the optional debug outputs;
+// *g_out: the value that its message entry stands for.
 // Returns whether the coordinate is transmitted.  rk1: the random stream of the QSGD rounding.
-__device__ __forceinline__ bool encode_entry(const DevCtx& c, uint32_t w, uint64_t slot, uint32_t idx, uint32_t bits,
-                                             UnitScale us, const RandKey& rk1, float* m_out, uint32_t* dbg_idx,
-                                             uint16_t* dbg_level) {
+__device__ __forceinline__ bool encode_entry_at(const DevCtx& c, uint64_t slot, uint32_t idx, uint32_t bits, UnitScale us,
+                                                const RandKey& rk1, uint32_t* dbg_idx, uint16_t* dbg_level, float* g_out) {
   const float v = __uint_as_float(bits);
   const bool neg = v < 0.0f;
   uint32_t level;
@@ -147,18 +146,27 @@ __device__ __forceinline__ bool encode_entry(const DevCtx& c, uint32_t w, uint64
     level = 1;
     g = neg ? -us.scale : us.scale;
   }
-  const bool sent = level != 0;
   if (is_qsgd(c.quantizer)) { c.sel_idx[slot] = idx; c.sel_code[slot] = level | (neg ? 0x80000000u : 0u); }   // k_pack_sent reads both
   else {                                                 // every selected coordinate is sent: nothing to compact
     c.surv_idx[slot] = idx;
     c.surv_code[slot] = c.quantizer == QSL_FP32 ? bits : (neg ? 1u : 0u);
   }
-  if (sent) {
-    if (idx < c.d) m_out[static_cast<uint64_t>(w) * c.d + idx] = v - g;
-    else atomicOr(c.status, 2u);                       // cannot happen: a selected slot was never written
-  }
   if (dbg_idx) dbg_idx[slot] = idx;
   if (dbg_level) dbg_level[slot] = static_cast<uint16_t>(level);
+  *g_out = g;
+  return level != 0;
+}
+
+// ... and the error update m <- v - g on a transmitted coordinate (Algorithm 1, second worker line)
+__device__ __forceinline__ bool encode_entry(const DevCtx& c, uint32_t w, uint64_t slot, uint32_t idx, uint32_t bits,
+                                             UnitScale us, const RandKey& rk1, float* m_out, uint32_t* dbg_idx,
+                                             uint16_t* dbg_level) {
+  float g;
+  const bool sent = encode_entry_at(c, slot, idx, bits, us, rk1, dbg_idx, dbg_level, &g);
+  if (sent) {
+    if (idx < c.d) m_out[static_cast<uint64_t>(w) * c.d + idx] = __uint_as_float(bits) - g;
+    else atomicOr(c.status, 2u);                       // cannot happen: a selected slot was never written
+  }
   return sent;
 }
 
@@ -213,24 +221,27 @@ __device__ void block_encode_tail(const DevCtx& c, const SegInfo& sg, uint32_t w
   }
 }
 
-// The units that k_lean_emit has already encoded are skipped here: a guessing unit, unless its guess failed and
-// the multi-pass kernels of this call took it over (`safe`).
+// The units that are encoded already are skipped here: a guessing unit, unless its guess failed and the multi-pass kernels
+// of this call took it over (`safe`), and one whose window held.
 __global__ __launch_bounds__(BLOCK) void k_quantize(DevCtx c, float* m_out, uint32_t worker0, uint64_t round,
                                                     uint32_t* dbg_idx, uint16_t* dbg_level, int safe) {
   __shared__ uint32_t s_w[BLOCK / 64];
   __shared__ float s_scale[BLOCK];
   __shared__ uint32_t s_mine[BLOCK];
   const uint32_t w = blockIdx.y;
-  const uint32_t j = blockIdx.x * BLOCK + threadIdx.x;
+  if (c.win && settled(c, c.units[w])) return;             // (uniform)
+  // a block of 256 slots per block, or several a grid's width apart (the launch that only stands by for a window is short)
+  for (uint32_t blk = blockIdx.x; blk < c.QB; blk += gridDim.x) {
+  const uint32_t j = blk * BLOCK + threadIdx.x;
   // the scales of the units this block's slots belong to (at most one unit per slot)
-  const uint32_t j_first = blockIdx.x * BLOCK, j_last = min(j_first + BLOCK, c.K) - 1;
+  const uint32_t j_first = blk * BLOCK, j_last = min(j_first + BLOCK, c.K) - 1;
   const uint32_t seg_first = c.L == 1 ? 0u : seg_of_slot(c, j_first);
   const uint32_t seg_last = c.L == 1 ? 0u : seg_of_slot(c, j_last);
   for (uint32_t i = threadIdx.x >> 6; i <= seg_last - seg_first; i += BLOCK / 64) {     // a wave per unit
     const uint32_t seg = seg_first + i;
     const uint64_t u = static_cast<uint64_t>(w) * c.L + seg;
     const UnitState us = c.units[u];
-    const bool mine = us.path != PATH_SMALL && !(us.path == PATH_FAST && !(safe && us.fell_back));
+    const bool mine = us.path != PATH_SMALL && !(us.path == PATH_FAST && !(safe && us.fell_back)) && !settled(c, us);
     float sc = 0.0f;
     if (mine) sc = finalize_scale(c.norm_acc + u * ACC_SLOTS, c.quantizer, c.segs[seg].k);
     if (lane_id() == 0) {
@@ -253,7 +264,7 @@ __global__ __launch_bounds__(BLOCK) void k_quantize(DevCtx c, float* m_out, uint
       if (sent && is_qsgd(c.quantizer) && c.L > 1) atomicAdd(&c.units[u].nnz, 1u);
     }
   }
-  if (!is_qsgd(c.quantizer)) return;                       // survivors are counted only where some may drop out
+  if (!is_qsgd(c.quantizer)) { __syncthreads(); continue; }      // survivors are counted only where some may drop out
   const uint32_t wc = __popcll(__ballot(sent));
   if (lane_id() == 0) s_w[threadIdx.x >> 6] = wc;
   __syncthreads();
@@ -261,7 +272,9 @@ __global__ __launch_bounds__(BLOCK) void k_quantize(DevCtx c, float* m_out, uint
   // a block of 256 slots may also hold entries that another kernel encodes: the counts are added (they start at zero)
   if (threadIdx.x == 0) {
     const uint32_t n = s_w[0] + s_w[1] + s_w[2] + s_w[3];
-    if (n) atomicAdd(&cnt[blockIdx.x], n);
+    if (n) atomicAdd(&cnt[blk], n);
+  }
+  __syncthreads();                                         // the arrays are used again
   }
 }
 

@@ -25,6 +25,7 @@ constexpr uint32_t CTR_OVF = NSUB;         // counter NSUB: cursor of the unit's
 constexpr uint32_t CTR_FAIL = NSUB + 1;    // counter NSUB + 1: set when the overflow pool ran out
 constexpr uint32_t CTR_LIST = NSUB + 2;    // counter NSUB + 2: entries in the unit's list of threshold-bin candidates
 constexpr uint32_t CTR_LINES = NSUB + 3;
+constexpr uint32_t WLIST = 1024;           // entries of the window path's list of threshold-bin candidates
 constexpr uint32_t LISTCAP = 256;          // entries of that list; a threshold bin that holds more sends the unit to the block-wide selection
 
 enum : uint32_t { PATH_FAST = 0, PATH_GENERAL = 1, PATH_FALLBACK = 2, PATH_SMALL = 3, PATH_FULL = 4 };
@@ -86,7 +87,7 @@ struct UnitState {
   uint32_t tau, need, n_gt; // threshold key, how many equal to it are kept, how many above (k_tile_count)
   uint32_t nnz;         // transmitted coordinates (zeroed by k_select<0>, counted by k_quantize)
   uint32_t scale_bits;  // fp32 scale that the message carries (k_quantize, k_lean_emit, ...)
-  uint32_t scale_code;  // index-free format only: the scale the codes are computed with (k_dense_scales)
+  uint32_t scale_code;  // the scale the codes are computed with (index-free format: k_dense_scales; window path: k_win_mid)
 };
 
 struct DevCtx {
@@ -126,6 +127,7 @@ struct DevCtx {
   uint32_t dense;       // 1: every coordinate is kept and the messages have the index-free format
   uint32_t L, K, NWT, NSEL, NCB, NWC, QB, NSELF, nfast, nblock, Rmax, nbig, s, w_idx, w_lev, w_val, sparsifier, quantizer, cap_words;
   uint32_t none;        // entries of one_segs
+  uint32_t win;         // 1: the only segment goes the way of the window (a dense k on a large vector), the multi-pass kernels standing by
 };
 
 __device__ __forceinline__ uint32_t key_of_value(uint32_t vbits) { return (vbits & 0x7FFFFFFFu) << 1; }
@@ -150,8 +152,10 @@ __host__ __device__ __forceinline__ uint32_t norm_power(uint32_t q) {
 __host__ __device__ __forceinline__ uint32_t acc_slots(uint32_t q) { return norm_power(q) <= 2u ? 20u : ACC_SLOTS; }
 __host__ __device__ __forceinline__ uint32_t acc_stride(uint32_t q) { return acc_slots(q) + 1u; }
 
-__device__ __forceinline__ uint32_t eff_path(const UnitState& us) {
-  return us.path == PATH_FAST && us.fell_back ? static_cast<uint32_t>(PATH_FALLBACK) : us.path;
+// Whether the unit is none of the multi-pass kernels' business: its guess, or its window, held.
+__device__ __forceinline__ bool settled(const DevCtx& c, const UnitState& us) {
+  if (us.path == PATH_FAST) return !us.fell_back;
+  return c.win != 0 && !us.fell_back && !us.crowded;
 }
 
 // Find, scanning the first NBINS bins of a histogram from the top, the bin in which the running count

@@ -16,6 +16,7 @@ namespace {
 // ------------------------------------------------------------------------------------------------
 struct SlotRow {
   uint32_t count;        // candidates of this lane's chunk (0 if the chunk does not exist)
+  uint32_t above;        // window path: the chunk's coordinates above the window, at the lane that holds its header (else 0)
   uint32_t ovf_at;       // where they are in the overflow pool, if count > cap
   uint32_t n;            // candidates this lane is responsible for: 0..2 of its own elements, or all
                          // `count` entries in the overflow pool if it holds the header of such a chunk
@@ -43,6 +44,7 @@ __device__ __forceinline__ RawRow load_slot_row(const uint2* slots, const uint32
   return r;
 }
 
+template <bool WINDOW = false>
 __device__ __forceinline__ SlotRow parse_slot_row(const RawRow& raw, uint32_t lpc) {
   SlotRow r;
   const uint32_t lane = lane_id();
@@ -52,6 +54,8 @@ __device__ __forceinline__ SlotRow parse_slot_row(const RawRow& raw, uint32_t lp
   const uint32_t leader = lane & ~(lpc - 1);
   r.count = __shfl(q.x, leader, WAVE);
   r.ovf_at = __shfl(q.y, leader, WAVE);
+  r.above = 0;
+  if (WINDOW) { r.above = sub == 0 ? r.count >> 16 : 0u; r.count &= 0xFFFFu; }
   const uint32_t cap = lpc * 2 - 1;
   const bool inl = r.count <= cap;
   const uint32_t e0 = sub * 2;                    // element numbers of this lane; element e holds candidate e - 1
@@ -106,13 +110,13 @@ __global__ __launch_bounds__(BIG) void k_select(DevCtx c, SegInfo one, const flo
   const uint64_t u = static_cast<uint64_t>(w) * c.L + si.seg;
   UnitState* usp = &c.units[u];
   const UnitState us = *usp;
-  if (us.path == PATH_FAST && !us.fell_back) return;         // its guess held: k_lean_* select it
+  if (settled(c, us)) return;                                // its guess (its window) held: k_lean_* (k_win_*) select it
   uint32_t* hist = c.hist + u * 3 * HBINS;
   for (uint32_t i = threadIdx.x; i < HBINS; i += BIG) lh[i] = 0;
   __syncthreads();
   uint32_t prefix = 0, k_rem = sg.k;
   if (LEVEL == 0) {
-    if (us.path != PATH_FAST && threadIdx.x == 0 && si.j == 0) { usp->cand = 0; usp->fell_back = 0; usp->nnz = 0; }
+    if (us.path != PATH_FAST && !c.win && threadIdx.x == 0 && si.j == 0) { usp->cand = 0; usp->fell_back = 0; usp->nnz = 0; }
   } else {
     uint32_t above;
     if (LEVEL == 1) {
@@ -467,7 +471,7 @@ __global__ __launch_bounds__(BLOCK) void k_tile_count(DevCtx c, SegInfo one, con
   const SegInfo sg = c.L == 1 ? one : c.segs[cb.seg];
   const uint64_t u = static_cast<uint64_t>(w) * c.L + cb.seg;
   const UnitState us = c.units[u];
-  if (us.path == PATH_FAST && !us.fell_back) return;         // its guess held: k_lean_* select it
+  if (settled(c, us)) return;                                // its guess (its window) held: k_lean_* (k_win_*) select it
   const Thresh th = last_digit(c, u, us, scratch, result);
   if (threadIdx.x == 0 && cb.b == 0) { c.units[u].tau = th.tau; c.units[u].need = th.need; c.units[u].n_gt = sg.k - th.need; }
   const RandKey rk = make_rand_key(c.seed, worker0 + w, round, 0);
@@ -492,7 +496,7 @@ __global__ __launch_bounds__(BLOCK) void k_tile_write(DevCtx c, SegInfo one, con
   const SegInfo sg = c.L == 1 ? one : c.segs[cb.seg];
   const uint64_t u = static_cast<uint64_t>(w) * c.L + cb.seg;
   const UnitState us = c.units[u];
-  if (us.path == PATH_FAST && !us.fell_back) return;         // its guess held: k_lean_* select it
+  if (settled(c, us)) return;                                // its guess (its window) held: k_lean_* (k_win_*) select it
   Thresh th; th.tau = us.tau; th.need = us.need;
   const RandKey rk = make_rand_key(c.seed, worker0 + w, round, 0);
   const uint32_t wave = threadIdx.x >> 6, lane = lane_id();

@@ -759,3 +759,57 @@ def test_aggregate_by_cells_edges(P, case):
             want = _aggregate_by_definition(decoded, lst, -1.0 / 64, x0, accumulate, wl.d)
             assert np.array_equal(out.cpu().numpy().view(np.uint32), want.view(np.uint32)), (case, len(lst), accumulate)
     assert q.device_status() == B.OK
+
+
+# a dense k on a large vector (the way of the window): inputs on which the window holds, and ones -- ties, zeros, one
+# magnitude, scales in stretches -- on which the multi-pass kernels have to take over; against those kernels (NO_FAST_PATH),
+# which the tests above compare with the oracle, and against the oracle itself
+@pytest.mark.parametrize("kind,expect_held", [("normal", True), ("heavy", True), ("stretches", None), ("sorted", None), ("zeros", False),
+                                              ("ties", False), ("constant", False)])
+def test_window_of_a_dense_k(P, kind, expect_held):
+    from paper_1906_02367_amd import binding as B
+    rng = np.random.default_rng(len(kind))
+    shapes = [(3_145_729, 50_001, W.TOPK, W.QSGD, 15), (3_145_728, 2_900_000, W.TOPK, W.SIGN_L1, 1), (3_200_003, 400_000, W.RANDK, W.FP32, 1),
+              (3_145_731, 314_573, W.TOPK, W.QSGD_SCALED, 3), (3_145_733, 1_000_000, W.TOPK, W.SIGN_L4, 1)]
+    for n, (d, k, sp, qz, s) in enumerate(shapes):
+        R = 2 if n < 2 else 1
+        wl = custom(d, [0, d], [k], s, sp, qz, R=R)
+        qa, qb = B.from_workload(wl), B.from_workload(wl, flags=B.FLAG_NO_FAST_PATH)
+        ma = torch.zeros(R, d, device=qa.device)
+        mb = torch.zeros(R, d, device=qa.device)
+        for t in range(2):
+            v = rng.standard_normal((R, d), dtype=f32)
+            if kind == "heavy":
+                v *= np.exp(2 * rng.standard_normal(d)).astype(f32)
+            elif kind == "stretches":
+                v *= np.repeat(np.exp(3 * rng.standard_normal(d // 700 + 1)), 700)[:d].astype(f32)
+            elif kind == "sorted":
+                v = np.sort(np.abs(v), axis=1)
+            elif kind == "zeros":
+                v[rng.random((R, d), dtype=f32) < 0.99] = 0
+            elif kind == "ties":
+                v = np.round(v * 4) / f32(4)
+            elif kind == "constant":
+                v[:] = 0.5
+            delta = torch.from_numpy(v).to(qa.device)
+            outs = []
+            for q, m in ((qa, ma), (qb, mb)):
+                msg, bits = q.new_msg(R).fill_(0xCD), torch.zeros(R, dtype=torch.int64, device=q.device)
+                idx, lev = torch.zeros(R, k, dtype=torch.int32, device=q.device), torch.zeros(R, k, dtype=torch.int16, device=q.device)
+                if t == 0:
+                    q.compress(m, delta, m, 3, t, msg, bits, idx, lev)
+                else:                                             # Delta formed on the fly: x = 0, xhat = -Delta
+                    q.compress_diff(m, torch.zeros(d, device=q.device), -delta, m, 3, t, msg, bits, idx, lev)
+                outs.append((m.view(torch.int32), msg, bits, idx, lev))
+            torch.cuda.synchronize()
+            assert qa.device_status() == B.OK and qb.device_status() == B.OK
+            for a, b in zip(*outs):
+                assert torch.equal(a, b), (kind, d, k, t)
+            if t == 0:
+                op = P.oracle_for(wl)
+                o = op.compress(np.zeros(d, f32), v[0], 3, 0)
+                assert np.array_equal(outs[0][1][0].cpu().numpy(), o["msg"]) and np.array_equal(P.bits(ma[0].cpu().numpy()), P.bits(o["m_out"]))
+                if expect_held is not None and sp == W.TOPK:      # candidates of the window: none are reported without one
+                    units = qa.debug_units()
+                    assert np.all(units[:, 0] == 1)
+                    assert not expect_held or np.all((units[:, 1] > 0) & (units[:, 1] < d // 8)), units
