@@ -809,11 +809,16 @@ static qsl_status launch_dense(qsl_ctx* ctx, const float* m, const float* delta,
   if (xm == nullptr) k_dense_norm<false><<<grid, BLOCK, 0, st>>>(c, m, delta, xm, m_out);
   else k_dense_norm<true><<<grid, BLOCK, 0, st>>>(c, m, delta, xm, m_out);
   if (timed) { QSL_HIP(hipEventRecord(ctx->ev[ctx->ev_used + 1], st)); ctx->ev_used += 2; }
-  if (c.quantizer != QSL_FP32) k_dense_sum<<<dim3((grid.x + SUM_ROWS - 1) / SUM_ROWS, R), SUM_BLOCK, 0, st>>>(c, grid.x);
-  const uint32_t U = R * c.L;
-  k_dense_scales<<<dim3((U + BLOCK / 64 - 1) / (BLOCK / 64)), BLOCK, 0, st>>>(c, U);
-  const dim3 egrid(static_cast<uint32_t>(std::min<uint64_t>(ntiles, MAX_ENCODE_BLOCKS)), R);
-  k_dense_encode<<<egrid, BLOCK, 0, st>>>(c, m_out, worker0, round, msg, msg_bits, sel_idx, sel_level);
+  if (c.L == 1 && grid.x <= SUM_ONE) k_dense_sum_scale<<<dim3(R), SUM_BLOCK, 0, st>>>(c, grid.x);
+  else {
+    if (c.quantizer != QSL_FP32) k_dense_sum<<<dim3((grid.x + SUM_ROWS - 1) / SUM_ROWS, R), SUM_BLOCK, 0, st>>>(c, grid.x);
+    const uint32_t U = R * c.L;
+    k_dense_scales<<<dim3((U + BLOCK / 64 - 1) / (BLOCK / 64)), BLOCK, 0, st>>>(c, U);
+  }
+  const dim3 egrid(static_cast<uint32_t>(ntiles), R);      // a wave per 1024 coordinates
+  if (is_qsgd(c.quantizer)) k_dense_encode<DENSE_QSGD><<<egrid, BLOCK, 0, st>>>(c, m_out, worker0, round, msg, msg_bits, sel_idx, sel_level);
+  else if (c.quantizer == QSL_FP32) k_dense_encode<DENSE_FP32><<<egrid, BLOCK, 0, st>>>(c, m_out, worker0, round, msg, msg_bits, sel_idx, sel_level);
+  else k_dense_encode<DENSE_SIGN><<<egrid, BLOCK, 0, st>>>(c, m_out, worker0, round, msg, msg_bits, sel_idx, sel_level);
   QSL_HIP(hipGetLastError());
   return QSL_OK;
 }
@@ -1028,8 +1033,16 @@ static qsl_status launch_aggregate(const DevCtx& c, hipStream_t st, uint32_t nnz
                                    const AggCrowd* crowd, const uint8_t* msg, const RowList& rows, uint32_t R, float scale, int accumulate,
                                    float* out) {
   if (c.K == c.d && (c.dense || !is_qsgd(c.quantizer))) {   // k = d and nothing dropped: every message lists every coordinate
-    const uint32_t blocks = static_cast<uint32_t>(std::min<uint64_t>((c.d / 8 + BLOCK) / BLOCK, 1u << 16));   // two groups of four per thread
-    k_aggregate_dense<<<dim3(blocks), BLOCK, 0, st>>>(c, msg, rows, R, scale, accumulate, out);
+    const uint64_t chunks = (c.d + CHUNK - 1) / CHUNK;
+    const dim3 grid(static_cast<uint32_t>((chunks + BLOCK / 64 - 1) / (BLOCK / 64)));      // a wave per 1024 coordinates
+    const bool sign = !is_qsgd(c.quantizer) && c.quantizer != QSL_FP32;
+    if (c.L == 1 && sign) k_aggregate_dense_one<AGG_SIGN><<<grid, BLOCK, 0, st>>>(c, msg, rows, R, scale, accumulate, out);
+    else if (c.L == 1 && c.w_val <= 8 && R << c.w_val <= AGG_TABLE_MAX)
+      k_aggregate_dense_one<AGG_TABLE><<<grid, BLOCK, 0, st>>>(c, msg, rows, R, scale, accumulate, out);
+    else {
+      const uint32_t blocks = static_cast<uint32_t>(std::min<uint64_t>((c.d / 8 + BLOCK) / BLOCK, 1u << 16));   // two groups of four per thread
+      k_aggregate_dense<<<dim3(blocks), BLOCK, 0, st>>>(c, msg, rows, R, scale, accumulate, out);
+    }
     QSL_HIP(hipGetLastError());
     return QSL_OK;
   }

@@ -8,6 +8,7 @@
 #include "qsl_device.h"
 #include "qsl_layout.h"
 #include "qsl_select.h"
+#include "qsl_encode.h"
 
 namespace {
 
@@ -620,6 +621,98 @@ __global__ __launch_bounds__(BLOCK) void k_aggregate_dense(DevCtx c, const uint8
     }
     aggregate_dense_quad(c, msg, rows, R, scale, accumulate, out, code_bit0, ja, na, oa);
     if (nb) aggregate_dense_quad(c, msg, rows, R, scale, accumulate, out, code_bit0, jb, nb, ob);
+  }
+}
+
+// The same for one segment and narrow codes.
+// A wave per 1024 coordinates, four times four per lane; what `out` holds of them and the codes of several messages are read
+// before anything waits.  What a code stands for is looked up: one-bit codes choose between two values that the whole wave
+// shares, codes of up to eight bits index a table in LDS that the block makes first (all messages' values of all codes), if
+// it has room for that; everything else is computed value by value, by k_aggregate_dense.  Measured: 2 x 25.6 M coordinates
+// 46 us with one-bit codes, 47 us with five-bit ones (k_aggregate_dense: 69 and 71 us), 13 x 17.2 M four-bit codes 58 us;
+// held to 6 waves per SIMD 51, 52 and 58 us, to 8: 51, 63 and 74 us.
+enum { AGG_SIGN, AGG_TABLE };
+constexpr uint32_t AGG_TABLE_MAX = 2048;
+template <int MODE>
+__global__ __launch_bounds__(BLOCK) void k_aggregate_dense_one(DevCtx c, const uint8_t* __restrict__ msg, RowList rows, uint32_t R,
+                                                               float scale, int accumulate, float* __restrict__ out) {
+  __shared__ float s_value[MODE == AGG_TABLE ? AGG_TABLE_MAX : 1];
+  const uint32_t lane = lane_id(), wv = c.w_val;
+  const uint64_t chunk = static_cast<uint64_t>(blockIdx.x) * (BLOCK / 64) + (threadIdx.x >> 6), base = chunk * CHUNK;
+  const uint32_t valid = base < c.d ? static_cast<uint32_t>(min(static_cast<uint64_t>(CHUNK), c.d - base)) : 0u;
+  const uint64_t code_bit0 = (2 + (c.d * c.w_idx + 31) / 32) * 32 + base * wv;      // of the chunk, in a message that holds all d entries
+  auto words_of = [&](uint32_t p) { return reinterpret_cast<const uint32_t*>(msg + static_cast<uint64_t>(rows.row[p]) * c.cap_words * 4); };
+  f4u o[4], acc[4];
+#pragma unroll
+  for (uint32_t t = 0; t < 4; ++t) {
+    const uint32_t e = t * 256 + lane * 4;
+    o[t] = acc[t] = f4u{0.f, 0.f, 0.f, 0.f};
+    if (accumulate) {
+      if (valid == CHUNK) o[t] = *reinterpret_cast<const f4u*>(out + base + e);
+      else {
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) if (e + j < valid) o[t][j] = out[base + e + j];
+      }
+    }
+  }
+  if (MODE == AGG_TABLE) {
+    for (uint32_t i = threadIdx.x; i < R << wv; i += BLOCK) s_value[i] = value_of_code(c, i & ((1u << wv) - 1u), __uint_as_float(words_of(i >> wv)[1]));
+    __syncthreads();
+  }
+  if (valid == 0) return;
+  bool first = true;
+  constexpr uint32_t UN = 2;                           // messages whose codes are read together
+  for (uint32_t p0 = 0; p0 < R; p0 += UN) {
+    uint32_t four[UN][4], nnz[UN];                     // the lane's four codes of each group, at most 32 bits
+    float sc[UN];
+#pragma unroll
+    for (uint32_t u = 0; u < UN; ++u) {
+      if (p0 + u >= R) break;
+      const uint32_t* words = words_of(p0 + u);
+      nnz[u] = words[0]; sc[u] = __uint_as_float(words[1]);
+#pragma unroll
+      for (uint32_t t = 0; t < 4; ++t) {
+        const uint32_t e = t * 256 + lane * 4;
+        if (MODE == AGG_SIGN) four[u][t] = e < valid ? words[(code_bit0 >> 5) + (e >> 5)] >> (e & 31u) : 0u;      // (a chunk's bits begin with a word)
+        else { const FieldRead f = read_field(words, code_bit0 + e * wv, c.cap_words); four[u][t] = static_cast<uint32_t>((static_cast<uint64_t>(f.w.y) << 32 | f.w.x) >> f.sh); }
+      }
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < UN; ++u) {
+      if (p0 + u >= R) break;
+      if (nnz[u] != c.d) {
+        if (nnz[u] != 0 && chunk == 0 && lane == 0) atomicOr(c.status, 4u);
+        continue;
+      }
+      const float* value = s_value + (MODE == AGG_TABLE ? (p0 + u) << wv : 0u);
+      const uint32_t mask = (1u << wv) - 1u;
+#pragma unroll
+      for (uint32_t t = 0; t < 4; ++t) {
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) {
+          float val;
+          if (MODE == AGG_SIGN) val = (four[u][t] >> j) & 1u ? -sc[u] : sc[u];
+          else val = value[(four[u][t] >> (j * wv)) & mask];
+          acc[t][j] = first ? val : acc[t][j] + val;
+        }
+      }
+      first = false;
+    }
+  }
+  if (first && accumulate) return;                       // no message had anything to add
+#pragma unroll
+  for (uint32_t t = 0; t < 4; ++t) {
+    const uint32_t e = t * 256 + lane * 4;
+#pragma unroll
+    for (uint32_t j = 0; j < 4; ++j) {
+      const float term = scale * acc[t][j];
+      o[t][j] = first ? 0.0f : accumulate ? o[t][j] + term : term;
+    }
+    if (valid == CHUNK) *reinterpret_cast<f4u*>(out + base + e) = o[t];
+    else {
+#pragma unroll
+      for (uint32_t j = 0; j < 4; ++j) if (e + j < valid) out[base + e + j] = o[t][j];
+    }
   }
 }
 

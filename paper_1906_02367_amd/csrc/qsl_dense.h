@@ -25,7 +25,6 @@ constexpr uint32_t DTILE = 4096;             // coordinates per tile: 256 thread
 // rows up; only what a block meets beyond its first unit (few blocks, if any) goes to the counters directly.
 constexpr uint32_t MAX_DENSE_BLOCKS = 16384;
 constexpr uint32_t NO_UNIT = 0xFFFFFFFFu;
-constexpr uint32_t MAX_ENCODE_BLOCKS = 8192; // ... and of the second, which has no such ending
 
 // digits of |v| (or v^2) straight into a unit's counters in memory (for the few tiles that span several segments)
 __device__ __forceinline__ void add_digits_global(uint64_t* acc, uint32_t bits, uint32_t power) {
@@ -206,6 +205,33 @@ __global__ __launch_bounds__(SUM_BLOCK) void k_dense_sum(DevCtx c, uint32_t nb) 
   }
 }
 
+// One segment and at most SUM_ONE rows per worker: sums and scale by one block per worker, in one launch instead of two
+// (4 x 100,003 coordinates, QSGD: 25.2 -> 23.0 us per call).
+constexpr uint32_t SUM_ONE = 1024;
+__global__ __launch_bounds__(SUM_BLOCK) void k_dense_sum_scale(DevCtx c, uint32_t nb) {
+  __shared__ uint64_t acc[ACC_SLOTS];
+  const uint32_t w = blockIdx.x, lane = lane_id(), wave = threadIdx.x >> 6;
+  const uint32_t ns = c.quantizer == QSL_FP32 ? 0u : acc_slots(c.quantizer);
+  for (uint32_t s = wave; s < ns; s += SUM_BLOCK / 64) {
+    const uint64_t* row = c.dense_part + (static_cast<uint64_t>(w) * ACC_SLOTS + s) * nb;
+    uint64_t x = 0;
+#pragma unroll
+    for (uint32_t g = 0; g < SUM_ONE / 64; ++g) if (g * 64 + lane < nb) x += row[g * 64 + lane];
+    x = wave_sum64(x);
+    if (lane == 0) acc[s] = x;
+  }
+  __syncthreads();
+  if (wave != 0) return;
+  const uint32_t k = static_cast<uint32_t>(c.d);
+  const UnitScale us = unit_scale(c, ns ? finalize_scale(acc, c.quantizer, k) : 0.0f, k);
+  if (lane == 0) {
+    UnitState* u = &c.units[w];
+    u->scale_code = __float_as_uint(us.scale);
+    u->scale_bits = __float_as_uint(us.sent);
+    u->cand = 0; u->fell_back = 0; u->tau = 0; u->need = 0; u->n_gt = k; u->nnz = k;
+  }
+}
+
 // one wave per unit: the scale the codes are computed with and the scale the message carries; the digit counters
 // are returned to zero for the next call
 __global__ __launch_bounds__(BLOCK) void k_dense_scales(DevCtx c, uint32_t U) {
@@ -223,123 +249,158 @@ __global__ __launch_bounds__(BLOCK) void k_dense_scales(DevCtx c, uint32_t U) {
   }
 }
 
-__global__ __launch_bounds__(BLOCK) void k_dense_encode(DevCtx c, float* m_out, uint32_t worker0, uint64_t round, uint8_t* msg,
-                                                        uint64_t* msg_bits, uint32_t* dbg_idx, uint16_t* dbg_level) {
-  __shared__ uint32_t s_bits[(DTILE / 32) * 32];        // the tile's part of the code stream: 128 words per bit of code width
-  const uint32_t w = blockIdx.y;
+// The second pass, a wave per 1024 coordinates as in the streaming pass: v is read once more, m' = v - g and the packed codes
+// written.  The coordinates of a wave fill whole words of the code stream: sign bits are put together by shuffles, wider
+// codes in an LDS line of the wave.  Workers and chunks go from the last to the first: what the first pass wrote last
+// may still be in the last-level cache.  2 x 25.6 M coordinates: sign 75 us with 6 waves per SIMD (3: 88, 4: 76, 8: 78; blocks
+// of 4096 coordinates with barriers around a shared bit buffer: 94), no quantiser 3; QSGD 92 us with 8 (4: 125, 6: 103; IEEE divisions in
+// blocks of 4096: 127), where the vector ALU is the bound: Philox and two quotients per coordinate.
+enum { DENSE_SIGN, DENSE_QSGD, DENSE_FP32 };
+template <int KIND>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(KIND == DENSE_QSGD ? 8 : KIND == DENSE_SIGN ? 6 : 3, KIND == DENSE_QSGD ? 8 : KIND == DENSE_SIGN ? 6 : 3)))
+void k_dense_encode(DevCtx c, float* m_out, uint32_t worker0, uint64_t round, uint8_t* msg, uint64_t* msg_bits, uint32_t* dbg_idx,
+                    uint16_t* dbg_level) {
+  __shared__ uint32_t s_bits[KIND == DENSE_QSGD ? BLOCK / 64 : 1][KIND == DENSE_QSGD ? 32 * 17 : 1];      // at most 17 bits per code
+  const uint32_t w = gridDim.y - 1 - blockIdx.y, wave = threadIdx.x >> 6, lane = lane_id();
   const uint32_t wv = c.w_val;
   uint32_t* words = reinterpret_cast<uint32_t*>(msg + static_cast<uint64_t>(w) * c.cap_words * 4);
   const uint64_t hdr = 1 + static_cast<uint64_t>(c.L);
   const uint64_t code_words = (c.d * wv + 31) / 32;
-  if (blockIdx.x == 0) {                               // header: the length word, the scales; the payload bit count
+  if (blockIdx.x == 0) {                               // header: the length word, the scales; the payload bit count; padding
     for (uint64_t i = threadIdx.x; i < hdr; i += BLOCK)
       words[i] = i == 0 ? static_cast<uint32_t>(c.d) : c.units[static_cast<uint64_t>(w) * c.L + (i - 1)].scale_bits;
+    for (uint64_t i = hdr + code_words + threadIdx.x; i < c.cap_words; i += BLOCK) words[i] = 0;
     if (threadIdx.x == 0 && msg_bits) msg_bits[w] = hdr * 32 + c.d * wv;
   }
-  if (blockIdx.x == gridDim.x - 1)                     // zero padding up to the capacity
-    for (uint64_t i = hdr + code_words + threadIdx.x; i < c.cap_words; i += BLOCK) words[i] = 0;
-  const uint64_t row = static_cast<uint64_t>(w) * c.d;
-  const RandKey rk1 = make_rand_key(c.seed, worker0 + w, round, 1);
-  uint64_t t_lo, t_hi;
-  dense_range(c.d, blockIdx.x, gridDim.x, &t_lo, &t_hi);
-  uint32_t cur = 0xFFFFFFFFu;
-  float cur_scale = 0.f, cur_sent = 0.f;
-  for (uint64_t tile = t_lo; tile < t_hi; ++tile) {
-    const uint64_t base = tile * DTILE;
-    const uint64_t last = min(base + DTILE, c.d) - 1;
-    const uint32_t seg_first = c.L == 1 ? 0u : seg_of_coord(c, static_cast<uint32_t>(base));
-    const uint32_t seg_last = c.L == 1 ? 0u : seg_of_coord(c, static_cast<uint32_t>(last));
-    const bool one_seg = seg_first == seg_last;
-    if (one_seg && seg_first != cur) {
-      cur = seg_first;
-      const UnitState& us = c.units[static_cast<uint64_t>(w) * c.L + cur];
-      cur_scale = __uint_as_float(us.scale_code); cur_sent = __uint_as_float(us.scale_bits);
-    }
-    for (uint32_t i = threadIdx.x; i < (DTILE / 32) * wv; i += BLOCK) s_bits[i] = 0;
-    __syncthreads();
+  const uint64_t nchunk = (c.d + CHUNK - 1) / CHUNK, at = static_cast<uint64_t>(blockIdx.x) * (BLOCK / 64) + wave;
+  if (at >= nchunk) return;                            // (no barrier follows)
+  const uint64_t chunk = nchunk - 1 - at, base = chunk * CHUNK;
+  const uint32_t valid = static_cast<uint32_t>(min(static_cast<uint64_t>(CHUNK), c.d - base));
+  const uint32_t seg = c.L == 1 ? 0u : seg_of_coord(c, static_cast<uint32_t>(base));
+  const bool one_seg = c.L == 1 || seg == seg_of_coord(c, static_cast<uint32_t>(base + valid - 1));
+  const UnitState& us = c.units[static_cast<uint64_t>(w) * c.L + seg];
+  const float scale = __uint_as_float(us.scale_code), sent = __uint_as_float(us.scale_bits);      // of the whole chunk, if it is one segment
+  float* vp = m_out + static_cast<uint64_t>(w) * c.d + base;
+  f4u v[4];
 #pragma unroll
-    for (uint32_t q = 0; q < 4; ++q) {
-      const uint32_t le = q * 1024 + threadIdx.x * 4;           // inside the tile
-      const uint64_t e = base + le;
-      if (e >= c.d) continue;
-      f4u x = {0.f, 0.f, 0.f, 0.f};
-      const bool whole = e + 4 <= c.d;
-      if (whole) x = __builtin_nontemporal_load(reinterpret_cast<const f4u*>(m_out + row + e));
+  for (uint32_t t = 0; t < 4; ++t) {
+    const uint32_t e = t * 256 + lane * 4;
+    v[t] = f4u{0.f, 0.f, 0.f, 0.f};
+    if (valid == CHUNK) v[t] = __builtin_nontemporal_load(reinterpret_cast<const f4u*>(vp + e));
+    else {
+#pragma unroll
+      for (uint32_t j = 0; j < 4; ++j) if (e + j < valid) v[t][j] = vp[e + j];
+    }
+  }
+  const float s = static_cast<float>(c.s);
+  const RandKey rk1 = make_rand_key(c.seed, worker0 + w, round, 1);
+  SharedDivisor by_norm = {}, by_s = {};
+  bool quick = false;                                  // divisions by the chunk's norm and by s may take the short way
+  if (KIND == DENSE_QSGD) {
+    by_norm = shared_divisor(scale); by_s = shared_divisor(s);
+    quick = one_seg && by_norm.ok && sent >= 0x1p-40f && sent <= 0x1p60f;
+    for (uint32_t i = lane; i < 32 * wv; i += WAVE) s_bits[wave][i] = 0;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");      // the line is private to the wave
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+  uint32_t sign_word = 0;                              // KIND == DENSE_SIGN: lane l = 8 g + t (t < 4) holds word t * 8 + g of the chunk
+#pragma unroll
+  for (uint32_t t = 0; t < 4; ++t) {
+    const uint32_t e = t * 256 + lane * 4;
+    Words4 rw = {{0u, 0u, 0u, 0u}};
+    if (KIND == DENSE_QSGD) rw = rand_words4(rk1, static_cast<uint32_t>(base) + e);             // a multiple of 4: one block
+    f4u res = v[t];
+    uint32_t code[4], level[4] = {1u, 1u, 1u, 1u};
+    bool plain = true;                                 // no coordinate of the wave's that the short division is not made for
+    if (KIND == DENSE_QSGD) {
+      bool odd = !quick;
+#pragma unroll
+      for (uint32_t j = 0; j < 4; ++j) { const float x = fabsf(v[t][j]); odd = odd || (x < by_norm.lo && x > 0.0f) || x > 0x1p100f; }
+      plain = __ballot(odd) == 0;
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < 4; ++j) {
+      const float x = v[t][j];
+      const bool neg = x < 0.0f;
+      float sc = scale, se = sent;
+      if (!one_seg && e + j < valid) {
+        const UnitState& u = c.units[static_cast<uint64_t>(w) * c.L + seg_of_coord(c, static_cast<uint32_t>(base) + e + j)];
+        sc = __uint_as_float(u.scale_code); se = __uint_as_float(u.scale_bits);
+      }
+      if (KIND == DENSE_QSGD) {                        // Definition 1, example 1: the same single IEEE operations as encode_entry
+        float lf = 0.0f;
+        if (sc > 0.0f) {
+          const float a = plain ? shared_div(fabsf(x), by_norm) : fabsf(x) / sc;
+          float tt = a * s;
+          if (tt > s) tt = s;
+          const float fl = floorf(tt);
+          const float frac = tt - fl;
+          const float r01 = static_cast<float>(rw.w[j] >> 8) * 0x1p-24f;
+          lf = fl + (r01 < frac ? 1.0f : 0.0f);
+        }
+        level[j] = static_cast<uint32_t>(lf);
+        const float prod = se * lf;
+        const float mag = plain ? shared_div(prod, by_s) : prod / s;
+        const float g = neg ? -mag : mag;
+        if (level[j] != 0) res[j] = x - g;             // Algorithm 1, second worker line
+        code[j] = level[j] | (static_cast<uint32_t>(neg) << c.w_lev);
+      } else if (KIND == DENSE_FP32) {
+        res[j] = x - x;
+        code[j] = __float_as_uint(x);
+      } else {                                         // Definition 2
+        res[j] = x - (neg ? -sc : sc);
+        code[j] = neg;
+      }
+      if (e + j < valid) {
+        const uint64_t slot = static_cast<uint64_t>(w) * c.K + base + e + j;
+        if (dbg_idx) dbg_idx[slot] = static_cast<uint32_t>(base) + e + j;
+        if (dbg_level) dbg_level[slot] = static_cast<uint16_t>(level[j]);
+      } else code[j] = 0;
+    }
+    if (valid == CHUNK) __builtin_nontemporal_store(res, reinterpret_cast<f4u*>(vp + e));
+    else {
+#pragma unroll
+      for (uint32_t j = 0; j < 4; ++j) if (e + j < valid) vp[e + j] = res[j];
+    }
+    if (KIND == DENSE_FP32) {
+      if (valid == CHUNK) __builtin_nontemporal_store(u4u{code[0], code[1], code[2], code[3]}, reinterpret_cast<u4u*>(words + hdr + base + e));
       else {
 #pragma unroll
-        for (uint32_t j = 0; j < 4; ++j) if (e + j < c.d) x[j] = m_out[row + e + j];
+        for (uint32_t j = 0; j < 4; ++j) if (e + j < valid) words[hdr + base + e + j] = code[j];
       }
-      Words4 rw = {{0u, 0u, 0u, 0u}};
-      if (is_qsgd(c.quantizer)) rw = rand_words4(rk1, static_cast<uint32_t>(e));     // e is a multiple of 4: one block
-      f4u res = x;
-      uint32_t code[4];
+    } else if (KIND == DENSE_SIGN) {
+      uint32_t x = (code[0] | code[1] << 1 | code[2] << 2 | code[3] << 3) << (lane & 7u) * 4;
+#pragma unroll
+      for (int o = 1; o < 8; o <<= 1) x |= __shfl_xor(x, o, WAVE);
+      if ((lane & 7u) == t) sign_word = x;
+    } else if (wv <= 16) {
+      const uint64_t val = static_cast<uint64_t>(code[0]) | (static_cast<uint64_t>(code[1]) << wv) |
+                           (static_cast<uint64_t>(code[2]) << (2 * wv)) | (static_cast<uint64_t>(code[3]) << (3 * wv));
+      const uint32_t o = e * wv, word = o >> 5, sh = o & 31u;
+      const uint64_t lo = val << sh;
+      if (static_cast<uint32_t>(lo)) atomicOr(&s_bits[wave][word], static_cast<uint32_t>(lo));
+      if (lo >> 32) atomicOr(&s_bits[wave][word + 1], static_cast<uint32_t>(lo >> 32));
+      if (sh && (val >> (64 - sh))) atomicOr(&s_bits[wave][word + 2], static_cast<uint32_t>(val >> (64 - sh)));
+    } else {
 #pragma unroll
       for (uint32_t j = 0; j < 4; ++j) {
-        float scale = cur_scale, sent_scale = cur_sent;
-        if (!one_seg && e + j < c.d) {
-          const UnitState& us = c.units[static_cast<uint64_t>(w) * c.L + seg_of_coord(c, static_cast<uint32_t>(e + j))];
-          scale = __uint_as_float(us.scale_code); sent_scale = __uint_as_float(us.scale_bits);
-        }
-        const float v = x[j];
-        const bool neg = v < 0.0f;
-        uint32_t level = 1;
-        float g;
-        if (is_qsgd(c.quantizer)) {                      // Definition 1, example 1: the same single IEEE operations as encode_entry
-          level = 0;
-          if (scale > 0.0f) {
-            const float a = fabsf(v) / scale;
-            float t = a * static_cast<float>(c.s);
-            if (t > static_cast<float>(c.s)) t = static_cast<float>(c.s);
-            const float fl = floorf(t);
-            const float frac = t - fl;
-            const float r01 = static_cast<float>(rw.w[j] >> 8) * 0x1p-24f;
-            level = static_cast<uint32_t>(fl) + (r01 < frac ? 1u : 0u);
-          }
-          g = qsgd_value(sent_scale, level, c.s, neg);
-          code[j] = level | (static_cast<uint32_t>(neg) << c.w_lev);
-        } else if (c.quantizer == QSL_FP32) {
-          g = v; code[j] = __float_as_uint(v);
-        } else {                                         // Definition 2
-          g = neg ? -scale : scale; code[j] = neg;
-        }
-        if (level != 0) res[j] = v - g;                  // Algorithm 1, second worker line
-        if (e + j < c.d) {
-          if (dbg_idx) dbg_idx[static_cast<uint64_t>(w) * c.K + e + j] = static_cast<uint32_t>(e + j);
-          if (dbg_level) dbg_level[static_cast<uint64_t>(w) * c.K + e + j] = static_cast<uint16_t>(level);
-        } else code[j] = 0;
-      }
-      if (whole) __builtin_nontemporal_store(res, reinterpret_cast<f4u*>(m_out + row + e));
-      else {
-#pragma unroll
-        for (uint32_t j = 0; j < 4; ++j) if (e + j < c.d) m_out[row + e + j] = res[j];
-      }
-      // the four codes into the tile's bit buffer
-      if (wv == 32) {
-#pragma unroll
-        for (uint32_t j = 0; j < 4; ++j) s_bits[le + j] = code[j];
-      } else if (wv <= 16) {
-        const uint64_t val = static_cast<uint64_t>(code[0]) | (static_cast<uint64_t>(code[1]) << wv) |
-                             (static_cast<uint64_t>(code[2]) << (2 * wv)) | (static_cast<uint64_t>(code[3]) << (3 * wv));
-        const uint32_t o = le * wv, word = o >> 5, sh = o & 31u;
-        const uint64_t lo = val << sh;
-        if (static_cast<uint32_t>(lo)) atomicOr(&s_bits[word], static_cast<uint32_t>(lo));
-        if (lo >> 32) atomicOr(&s_bits[word + 1], static_cast<uint32_t>(lo >> 32));
-        if (sh && (val >> (64 - sh))) atomicOr(&s_bits[word + 2], static_cast<uint32_t>(val >> (64 - sh)));
-      } else {
-#pragma unroll
-        for (uint32_t j = 0; j < 4; ++j) {
-          const uint32_t o = (le + j) * wv, word = o >> 5, sh = o & 31u;
-          const uint64_t lo = static_cast<uint64_t>(code[j]) << sh;
-          if (static_cast<uint32_t>(lo)) atomicOr(&s_bits[word], static_cast<uint32_t>(lo));
-          if (lo >> 32) atomicOr(&s_bits[word + 1], static_cast<uint32_t>(lo >> 32));
-        }
+        const uint32_t o = (e + j) * wv, word = o >> 5, sh = o & 31u;
+        const uint64_t lo = static_cast<uint64_t>(code[j]) << sh;
+        if (static_cast<uint32_t>(lo)) atomicOr(&s_bits[wave][word], static_cast<uint32_t>(lo));
+        if (lo >> 32) atomicOr(&s_bits[wave][word + 1], static_cast<uint32_t>(lo >> 32));
       }
     }
-    __syncthreads();
-    const uint64_t w0 = tile * (DTILE / 32) * wv;        // the tile's first word of the code stream
-    for (uint32_t i = threadIdx.x; i < (DTILE / 32) * wv; i += BLOCK)
-      if (w0 + i < code_words) words[hdr + w0 + i] = s_bits[i];
-    __syncthreads();
+  }
+  const uint64_t w0 = chunk * (CHUNK / 32) * wv;       // the chunk's first word of the code stream
+  if (KIND == DENSE_SIGN) {
+    const uint64_t q = w0 + (lane & 7u) * 8 + (lane >> 3);
+    if ((lane & 7u) < 4 && q < code_words) words[hdr + q] = sign_word;
+  } else if (KIND == DENSE_QSGD) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    for (uint32_t i = lane; i < 32 * wv; i += WAVE) if (w0 + i < code_words) words[hdr + w0 + i] = s_bits[wave][i];
   }
 }
 

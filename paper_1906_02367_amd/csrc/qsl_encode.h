@@ -98,6 +98,24 @@ __device__ __forceinline__ uint32_t seg_of_coord(const DevCtx& c, uint32_t i) {
   return lo;
 }
 
+// x / b for a b that many x share, as IEEE division rounds it: with y = 1 / b correctly rounded, q = x y is off by at most two
+// units in the last place, and a correction q <- q + (x - q b) y with a fused remainder leaves the correctly rounded
+// quotient once q is within one (Markstein, IBM J. Res. Dev. 34, 1990): two corrections.  Exact while neither quotient nor
+// remainder leaves the normal range, which `lo` and `ok` see to; 5 instructions where the division is 11 or 12.
+struct SharedDivisor { float b, y, lo; bool ok; };       // x = 0 or lo <= x <= 2^100
+__device__ __forceinline__ SharedDivisor shared_divisor(float b) {
+  SharedDivisor d;
+  d.b = b; d.ok = b >= 0x1p-40f && b <= 0x1p60f;
+  d.y = 1.0f / b;
+  d.lo = b * 0x1p-60f;                                   // (at least 2^-100: the remainder's last bit lies above 2^-149)
+  return d;
+}
+__device__ __forceinline__ float shared_div(float x, const SharedDivisor& d) {
+  float q = x * d.y;
+  q = __builtin_fmaf(__builtin_fmaf(-q, d.b, x), d.y, q);
+  return __builtin_fmaf(__builtin_fmaf(-q, d.b, x), d.y, q);
+}
+
 __device__ __forceinline__ float qsgd_value(float N, uint32_t level, uint32_t s, bool neg) {
   const float prod = N * static_cast<float>(level);
   const float mag = prod / static_cast<float>(s);

@@ -813,3 +813,33 @@ def test_window_of_a_dense_k(P, kind, expect_held):
                     units = qa.debug_units()
                     assert np.all(units[:, 0] == 1)
                     assert not expect_held or np.all((units[:, 1] > 0) & (units[:, 1] < d // 8)), units
+
+
+# index-free messages where the second pass and the master line change their way: norms outside the range of the short
+# division, coordinates far below the norm, codes of 1, 8, 9 and 17 bits, the last chunk of one coordinate, the largest
+# vector whose sums one block adds up (1024 rows of 4096 coordinates) and the one after it, tables that just fit or do not
+@pytest.mark.parametrize("d,quantizer,s,factor", [
+    (5_003, W.QSGD, 15, 1e-30), (5_003, W.QSGD, 15, 1e25), (5_003, W.QSGD_SCALED, 3, "mixed"), (1_025, W.QSGD, 127, 1.0), (1_024, W.QSGD, 128, 1.0),
+    (1_023, W.QSGD, 32768, "mixed"), (2_049, W.QSGD, 1, 1e-13), (4_097, W.SIGN_L1, 1, 1.0), (3_001, W.FP32, 1, "mixed"), (4_194_304, W.QSGD, 4, 1.0),
+    (4_194_305, W.QSGD, 4, 1.0), (4_194_305, W.SIGN_L2, 1, 1.0)])
+def test_index_free_edges(P, d, quantizer, s, factor):
+    from paper_1906_02367_amd import binding as B
+    rng = np.random.default_rng(d + s)
+    R = 2 if d > 100_000 else 34
+    wl = custom(d, [0, d], [d], s, W.TOPK, quantizer, R=R)
+    v = rng.standard_normal((1, R, d)).astype(f32)
+    if factor == "mixed":                                # the norm comes from a few; the others lie up to 10^30 below it, some are zero
+        v *= (10.0 ** rng.uniform(-30, 0, size=(1, R, d))).astype(f32)
+        v[0, :, ::7] = 0
+    else:
+        v = (v * f32(factor)).astype(f32)
+    run, op, m_host, _ = P.run_parity(wl, 1, deltas=v, dense=True, expect_path=4, worker0=7)
+    decoded = [op.decode(x) for x in run.msg.cpu().numpy()]
+    x0 = (rng.standard_normal(d) * np.abs(v).max()).astype(f32)
+    for lst, accumulate in [(list(range(R)), True), ([1], False), ([1, 0] + list(range(2, min(R, 9))), True)]:
+        out = torch.from_numpy(x0).to(run.q.device)
+        run.q.aggregate(run.msg, out, -0.25, worker_list=lst, accumulate=accumulate)
+        torch.cuda.synchronize()
+        want = _aggregate_by_definition(decoded, lst, -0.25, x0, accumulate, d)
+        assert np.array_equal(out.cpu().numpy().view(np.uint32), want.view(np.uint32)), (d, quantizer, s, lst)
+    assert run.q.device_status() == B.OK
