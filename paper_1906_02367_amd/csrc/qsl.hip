@@ -101,6 +101,8 @@ struct qsl_ctx {
   uint32_t n_other;           // segments that k_quantize encodes (not the guessing ones)
   uint32_t warm_R;            // workers whose guessing units carry a guess from an earlier call
   uint32_t safe_left;         // calls still to be made with the multi-pass kernels standing by for failed guesses
+  uint32_t recent_left;       // calls for which the last failed guess still counts as recent
+  uint32_t cold_left, strikes; // calls still to be made with sampled guesses, and failures reported during them
   uint32_t* blk_cnt2[2];      // the two arrays of per-block counters of transmitted entries, used in turn
   uint64_t calls;             // compress calls made
   uint32_t nsamp_blocks;      // blocks of the sampling kernel (per worker)
@@ -377,7 +379,7 @@ extern "C" qsl_status qsl_create(qsl_ctx** out, const qsl_config* cfg, void* hip
   ctx->stream = static_cast<hipStream_t>(hip_stream);
   ctx->Rmax = cfg->max_workers;
   for (AggCrowd& a : ctx->agg) a = AggCrowd{nullptr, nullptr, 0};
-  ctx->last_R = 0; ctx->warm_R = 0; ctx->safe_left = 0;
+  ctx->last_R = 0; ctx->warm_R = 0; ctx->safe_left = 0; ctx->cold_left = 0; ctx->strikes = 0; ctx->recent_left = 0;
   ctx->timing = 0; ctx->ev_used = 0;
   ctx->slab = nullptr; ctx->h_status = nullptr; ctx->own_v = nullptr; ctx->order_ev = nullptr; ctx->side = nullptr; ctx->side2 = nullptr; ctx->join2_ev = nullptr; ctx->fork_ev = nullptr; ctx->join_ev = nullptr;
 
@@ -836,13 +838,23 @@ static qsl_status launch_compress(qsl_ctx* ctx, const float* m, const float* del
     return QSL_ERR_UNSUPPORTED;                    // ... and so does the streaming kernel when it reads x_t
   c.blk_cnt = ctx->blk_cnt2[ctx->calls & 1]; c.blk_cnt_next = ctx->blk_cnt2[(ctx->calls & 1) ^ 1];
   ++ctx->calls;
-  // A kernel that had to resolve a failed guess with one block (slow for a large unit) leaves a word in pinned host
-  // memory; the next calls then keep the multi-pass kernels standing by for the units whose guess fails.  The word
-  // may be seen a few calls late: only speed depends on it, never the result.
-  if (ctx->h_status[8] != 0) { ctx->h_status[8] = 0; ctx->safe_left = 16; }
+  // A failed guess leaves a word in pinned host memory; it may be seen a few calls late, and only speed depends on it,
+  // never the result.  1, made good by many blocks: when it happens again within 16 calls, the next 32 take their guesses
+  // from samples, as a context's first call does (15 workers of 5.4 M coordinates whose thresholds jump from call to call:
+  // 490 us a call that way, 1000 with failed guesses made good; 260 undisturbed).  2, made good by
+  // one block walking through a large unit, or guesses that keep failing all the same: the multi-pass kernels stand by for
+  // the units whose guess fails.
+  const uint32_t flag = ctx->h_status[8];
+  if (flag != 0) {
+    ctx->h_status[8] = 0;
+    if (flag == 2 || (ctx->cold_left > 0 && ++ctx->strikes > 3)) ctx->safe_left = 16;
+    if (ctx->cold_left == 0 && ctx->recent_left > 0) { ctx->cold_left = 32; ctx->strikes = 0; }
+    ctx->recent_left = 16;
+  } else if (ctx->recent_left > 0) --ctx->recent_left;
   const bool safe = ctx->safe_left > 0;
   if (safe) --ctx->safe_left;
-  const bool cold = ctx->warm_R < R || (ctx->cfg.flags & QSL_FLAG_NO_WARM_START) != 0;
+  const bool cold = ctx->warm_R < R || ctx->cold_left > 0 || (ctx->cfg.flags & QSL_FLAG_NO_WARM_START) != 0;
+  if (ctx->cold_left > 0) --ctx->cold_left;
   if (SPARS == QSL_TOPK && ctx->n_sampled > 0 && cold) {
     k_sample<<<dim3(ctx->nsamp_blocks * R), BIG, 0, st>>>(c, m, delta, xm, R);
     k_sample_scan<<<dim3(c.nfast, R), BIG, 0, st>>>(c);
@@ -920,8 +932,8 @@ static qsl_status launch_compress(qsl_ctx* ctx, const float* m, const float* del
   // guessing units of a single block: the whole way from the slots to the encoded entries in one launch
   if (c.none && !swapped && !one_aside) k_lean_one<SPARS><<<dim3(c.none * R), BIG, 0, st>>>(c, ctx->segs[0], R, m_out, worker0, round, sel_idx, sel_level, safe ? 1 : 0);
   if (c.NSELF) {                                   // guessing units: candidates' histogram, threshold bin and dense list
-    k_lean_hist<SPARS><<<dim3(c.NSELF * R), BIG, 0, st>>>(c, ctx->segs[0], R);
-    k_lean_mark<SPARS><<<dim3(c.NSELF * R), BIG, 0, st>>>(c, ctx->segs[0], R);
+    k_lean_hist<SPARS><<<dim3(c.NSELF * R), BIG, 0, st>>>(c, ctx->segs[0], R, m_out, safe ? 1 : 0);
+    k_lean_mark<SPARS><<<dim3(c.NSELF * R), BIG, 0, st>>>(c, ctx->segs[0], R, m_out, safe ? 1 : 0);
   }
   if (c.win) {
     const SegInfo& sg = ctx->segs[0];
@@ -940,7 +952,8 @@ static qsl_status launch_compress(qsl_ctx* ctx, const float* m, const float* del
     k_tile_count<SPARS><<<dim3(ncb * R), BLOCK, 0, st>>>(c, ctx->segs[0], m_out, worker0, round, R);
     k_tile_write<SPARS><<<dim3(ncb * R), BLOCK, 0, st>>>(c, ctx->segs[0], m_out, worker0, round, R);
   }
-  if (ctx->n_other || safe) k_quantize<<<dim3(c.win ? std::min(c.QB, 256u) : c.QB, R), BLOCK, 0, st>>>(c, m_out, worker0, round, sel_idx, sel_level, safe ? 1 : 0);
+  if (c.win) k_quantize<true><<<dim3(std::min(c.QB, 256u), R), BLOCK, 0, st>>>(c, m_out, worker0, round, sel_idx, sel_level, 0);
+  else if (ctx->n_other || safe) k_quantize<false><<<dim3(c.QB, R), BLOCK, 0, st>>>(c, m_out, worker0, round, sel_idx, sel_level, safe ? 1 : 0);
   // the guessing units' exact threshold, ordered output and codes; one more block per guessing unit for failures
   if (c.NSELF)
     k_lean_emit<SPARS><<<dim3((c.NSELF + c.nfast) * R), BIG, 0, st>>>(c, ctx->segs[0], R, c.NSELF * R, m_out, worker0, round,
@@ -1027,6 +1040,13 @@ static bool aggregate_by_cells(uint32_t nnz_hint, uint32_t ndir, uint32_t R, boo
   return R > 1 && entries * (26.0 * groups - 12.0) > (accumulate ? 0.35 : 0.13) * coords + 1e6;
 }
 
+static void launch_directory(const DevCtx& c, hipStream_t st, const uint8_t* msg, const RowList& rows, uint32_t R, uint32_t* dir,
+                             uint32_t ndir) {
+  const uint32_t blocks = (c.K + BLOCK - 1) / BLOCK;
+  if (blocks <= 2048) k_msg_directory<1><<<dim3(blocks, R), BLOCK, 0, st>>>(c, msg, rows, dir, ndir);
+  else k_msg_directory<4><<<dim3(2048, R), BLOCK, 0, st>>>(c, msg, rows, dir, ndir);
+}
+
 // The launches of the master line.  `dir` is room for R directories of `ndir` words, or null (then every message is
 // searched whole); `nnz_hint` sizes the grids; `crowd`: the levels' crowded cells of a context with several segments, or null.
 static qsl_status launch_aggregate(const DevCtx& c, hipStream_t st, uint32_t nnz_hint, uint32_t* dir, uint32_t ndir,
@@ -1047,7 +1067,7 @@ static qsl_status launch_aggregate(const DevCtx& c, hipStream_t st, uint32_t nnz
     return QSL_OK;
   }
   if (dir && aggregate_by_cells(nnz_hint, ndir, R, accumulate != 0)) {                            // long messages, or many: a block per few cells of 1024 coordinates
-    k_msg_directory<<<dim3(std::min(2048u, (c.K + BLOCK - 1) / BLOCK), R), BLOCK, 0, st>>>(c, msg, rows, dir, ndir);
+    launch_directory(c, st, msg, rows, R, dir, ndir);
     uint32_t level = 0;
     while (level + 1 < AGG_LEVELS && static_cast<uint64_t>(AGG_LEVEL[level]) * R > AGG_WAVE_ENTRIES) ++level;
     AggCrowd cr = {nullptr, nullptr, 0};
@@ -1071,7 +1091,7 @@ static qsl_status launch_aggregate(const DevCtx& c, hipStream_t st, uint32_t nnz
   }
   if (R == 1 || nnz_hint < AGG_DIR_MIN) dir = nullptr;   // short messages are searched whole
   if (dir) {                                        // long messages: a thread per entry, searches narrowed by the directories
-    k_msg_directory<<<dim3(std::min(2048u, (c.K + BLOCK - 1) / BLOCK), R), BLOCK, 0, st>>>(c, msg, rows, dir, ndir);
+    launch_directory(c, st, msg, rows, R, dir, ndir);
     const uint32_t eb = std::min((c.K + BLOCK - 1) / BLOCK, std::max(4u, (nnz_hint + BLOCK - 1) / BLOCK));
     k_aggregate_entries<<<dim3(eb, R), BLOCK, 0, st>>>(c, msg, rows, R, scale, accumulate, out, dir, ndir);
   } else {                                          // short messages: 8 threads per entry, a block per expected tile of 32

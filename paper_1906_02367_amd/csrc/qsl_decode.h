@@ -114,6 +114,8 @@ constexpr uint32_t AGG_CELLS_MIN_R = 36; // short messages go to k_aggregate_cel
 // its predecessor's 1024-block and its own; the last entry also fills the rest.  A lookup then needs
 // dir[t], dir[t + 1] and a binary search over the few entries of one 1024-block instead of log2(nnz)
 // dependent probes of the whole message.
+// UN: entries per thread and step, their reads in flight together (1 while the grid covers the messages).
+template <uint32_t UN>
 __global__ __launch_bounds__(BLOCK) void k_msg_directory(DevCtx c, const uint8_t* msg, RowList rows, uint32_t* dir,
                                                          uint32_t ndir) {
   const uint32_t q = blockIdx.y, lane = lane_id();
@@ -121,7 +123,6 @@ __global__ __launch_bounds__(BLOCK) void k_msg_directory(DevCtx c, const uint8_t
   uint32_t* mine = dir + static_cast<uint64_t>(q) * ndir;
   const uint32_t nth = gridDim.x * BLOCK, tid = blockIdx.x * BLOCK + threadIdx.x;
   if (v.nnz == 0) { for (uint32_t t = tid; t < ndir; t += nth) mine[t] = 0; return; }
-  constexpr uint32_t UN = 4;                              // entries per thread and step (one while the grid covers the message), their reads in flight together
   for (uint64_t j0 = tid; j0 - lane < v.nnz; j0 += static_cast<uint64_t>(nth) * UN) {      // (uniform over the wave)
     uint32_t cell[UN], prev[UN];
 #pragma unroll

@@ -241,15 +241,17 @@ __device__ void block_encode_tail(const DevCtx& c, const SegInfo& sg, uint32_t w
 
 // The units that are encoded already are skipped here: a guessing unit, unless its guess failed and the multi-pass kernels
 // of this call took it over (`safe`), and one whose window held.
+// WINDOW: the launch that only stands by for a window is short; its blocks take several 256 slots, a grid's width apart.
+template <bool WINDOW>
 __global__ __launch_bounds__(BLOCK) void k_quantize(DevCtx c, float* m_out, uint32_t worker0, uint64_t round,
                                                     uint32_t* dbg_idx, uint16_t* dbg_level, int safe) {
   __shared__ uint32_t s_w[BLOCK / 64];
   __shared__ float s_scale[BLOCK];
   __shared__ uint32_t s_mine[BLOCK];
   const uint32_t w = blockIdx.y;
-  if (c.win && settled(c, c.units[w])) return;             // (uniform)
-  // a block of 256 slots per block, or several a grid's width apart (the launch that only stands by for a window is short)
-  for (uint32_t blk = blockIdx.x; blk < c.QB; blk += gridDim.x) {
+  if (WINDOW && settled(c, c.units[w])) return;            // (uniform)
+  uint32_t blk = blockIdx.x;                               // < c.QB: the grid is no wider
+  do {
   const uint32_t j = blk * BLOCK + threadIdx.x;
   // the scales of the units this block's slots belong to (at most one unit per slot)
   const uint32_t j_first = blk * BLOCK, j_last = min(j_first + BLOCK, c.K) - 1;
@@ -259,7 +261,7 @@ __global__ __launch_bounds__(BLOCK) void k_quantize(DevCtx c, float* m_out, uint
     const uint32_t seg = seg_first + i;
     const uint64_t u = static_cast<uint64_t>(w) * c.L + seg;
     const UnitState us = c.units[u];
-    const bool mine = us.path != PATH_SMALL && !(us.path == PATH_FAST && !(safe && us.fell_back)) && !settled(c, us);
+    const bool mine = us.path != PATH_SMALL && !(us.path == PATH_FAST && !(safe && us.fell_back));
     float sc = 0.0f;
     if (mine) sc = finalize_scale(c.norm_acc + u * ACC_SLOTS, c.quantizer, c.segs[seg].k);
     if (lane_id() == 0) {
@@ -282,7 +284,7 @@ __global__ __launch_bounds__(BLOCK) void k_quantize(DevCtx c, float* m_out, uint
       if (sent && is_qsgd(c.quantizer) && c.L > 1) atomicAdd(&c.units[u].nnz, 1u);
     }
   }
-  if (!is_qsgd(c.quantizer)) { __syncthreads(); continue; }      // survivors are counted only where some may drop out
+  if (!is_qsgd(c.quantizer)) { if (WINDOW) __syncthreads(); continue; }      // survivors are counted only where some may drop out
   const uint32_t wc = __popcll(__ballot(sent));
   if (lane_id() == 0) s_w[threadIdx.x >> 6] = wc;
   __syncthreads();
@@ -292,8 +294,8 @@ __global__ __launch_bounds__(BLOCK) void k_quantize(DevCtx c, float* m_out, uint
     const uint32_t n = s_w[0] + s_w[1] + s_w[2] + s_w[3];
     if (n) atomicAdd(&cnt[blk], n);
   }
-  __syncthreads();                                         // the arrays are used again
-  }
+  if (WINDOW) __syncthreads();                             // the arrays are used again
+  } while (WINDOW && (blk += gridDim.x) < c.QB);
 }
 
 // only for very large K: exclusive prefix (and total) of the per-block survivor counts, one block per worker

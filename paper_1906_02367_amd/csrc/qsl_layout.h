@@ -110,7 +110,7 @@ struct DevCtx {
   uint32_t* wave_cnt;   // [R][NWC]: candidates met by each wave of k_lean_hist
   uint32_t* wave_sel;   // [R][NWC]: of these, how many lie in the bins above the threshold's (k_lean_mark)
   uint4* tlist;         // [R][nfast][LISTCAP]: the candidates in the threshold's bin: (place in the dense list, value bits, key, -)
-  uint32_t* host_flag;  // pinned host memory: set when a failed guess had to be resolved by one block reading the whole unit
+  uint32_t* host_flag;  // pinned host memory: 1 when a guess failed, 2 when it had to be made good by one block reading a large unit whole
   uint2* cb_cnt;        // [R][NCB]: (#key > tau, #key == tau) of each compaction block
   uint32_t* hist;       // [U][3][HBINS], one histogram per radix digit; all zero between calls
   uint32_t* ctr;        // [U][CTR_LINES][PAD]; word 0 of each line is a counter; all zero between calls

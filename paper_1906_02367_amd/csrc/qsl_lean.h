@@ -51,7 +51,7 @@ __device__ __forceinline__ void lean_unit(const DevCtx& c, const SegInfo& one, u
   lu.wsel = c.wave_sel + static_cast<uint64_t>(lu.w) * c.NWC + sg.wc_base;
   lu.nrows = static_cast<uint32_t>((static_cast<uint64_t>(sg.nwt) * sg.lpc + 63) >> 6);   // < 2^20
   const uint32_t nwaves = sg.nsel * (BIG / 64);
-  lu.gw = si.j * (BIG / 64) + (threadIdx.x >> 6);
+  lu.gw = si.j * (BIG / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // the same for the wave: scalar registers
   lu.rpw = (lu.nrows + nwaves - 1) / nwaves;     // every wave a contiguous range of slot rows
   lu.r_lo = static_cast<uint64_t>(lu.gw) * lu.rpw;
   lu.r_hi = lu.r_lo + lu.rpw < lu.nrows ? lu.r_lo + lu.rpw : lu.nrows;
@@ -73,10 +73,45 @@ __device__ __forceinline__ uint32_t waves_before(const uint32_t* cnt, uint32_t g
 }
 
 // ------------------------------------------------------------------------------------------------
+// A failed guess of a unit with several blocks is made good in the same three launches: all of them histogram the unit's
+// v (k_lean_hist), take the bin of the k-th largest key from that and collect what lies in it and above, every wave in
+// a part of the dense list of its own (k_lean_mark); one block selects from those (k_lean_emit).  Two passes over v by all
+// blocks instead of five by one: a call with a failed guess of one of 15 units of 5.4 M coordinates 9.4 -> 1.0 ms.  Only
+// if a wave's part overflows (the values cluster, or tie) does one block walk through v by itself, as before.
+// ------------------------------------------------------------------------------------------------
+// f(first coordinate of the lane's four inside the unit, their value bits, how many of them lie inside the unit): the wave's
+// share of the unit's chunks, in order; all lanes of the wave make the same calls
+// (N: groups of 256 coordinates in flight)
+template <uint32_t N, typename F>
+__device__ __forceinline__ void lean_walk_v(const LeanUnit& lu, const float* vp, F&& f) {
+  const uint32_t nw = lu.sg.nsel * (BIG / 64), lane = lane_id();
+  const uint32_t c_lo = static_cast<uint32_t>(static_cast<uint64_t>(lu.sg.nwt) * lu.gw / nw), c_hi = static_cast<uint32_t>(static_cast<uint64_t>(lu.sg.nwt) * (lu.gw + 1) / nw);
+#pragma unroll 1
+  for (uint64_t base = static_cast<uint64_t>(c_lo) * CHUNK; base < static_cast<uint64_t>(c_hi) * CHUNK; base += N * 256) {
+    f4u x[N];
+#pragma unroll
+    for (uint32_t t = 0; t < N; ++t) {
+      const uint64_t e = base + t * 256 + lane * 4;
+      x[t] = f4u{0.f, 0.f, 0.f, 0.f};
+      if (e + 4 <= lu.sg.size) x[t] = *reinterpret_cast<const f4u*>(vp + e);
+      else {
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) if (e + j < lu.sg.size) x[t][j] = vp[e + j];
+      }
+    }
+#pragma unroll
+    for (uint32_t t = 0; t < N; ++t) {
+      const uint64_t e = base + t * 256 + lane * 4;
+      f(e, x[t], e < lu.sg.size ? static_cast<uint32_t>(min<uint64_t>(4, lu.sg.size - e)) : 0u);
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------------------
 // first launch: the candidates' histogram
 // ------------------------------------------------------------------------------------------------
 template <int SPARS>
-__global__ __launch_bounds__(BIG) void k_lean_hist(DevCtx c, SegInfo one, uint32_t R) {
+__global__ __launch_bounds__(BIG) void k_lean_hist(DevCtx c, SegInfo one, uint32_t R, const float* v, int safe) {
   __shared__ uint32_t lh[HBINS];
   __shared__ uint32_t s_ctr[CTR_LINES];
   LeanUnit lu;
@@ -104,17 +139,17 @@ __global__ __launch_bounds__(BIG) void k_lean_hist(DevCtx c, SegInfo one, uint32
       usp->sh_next = sh;
     }
   }
-  if (failed) return;
+  const uint64_t r_hi = failed ? lu.r_lo : lu.r_hi;  // (uniform) a discarded guess's candidates are not read
   const uint32_t lane = lane_id();
   uint32_t seen = 0;
-  for (uint64_t row0 = lu.r_lo; row0 < lu.r_hi; row0 += ROWS_IN_FLIGHT) {
+  for (uint64_t row0 = lu.r_lo; row0 < r_hi; row0 += ROWS_IN_FLIGHT) {
     if (row0 != lu.r_lo) {
 #pragma unroll
-      for (int b = 0; b < ROWS_IN_FLIGHT; ++b) rr[b] = load_slot_row(lu.slots, lu.slot_key, sg.lpc, sg.nwt, row0 + b, lu.r_hi);
+      for (int b = 0; b < ROWS_IN_FLIGHT; ++b) rr[b] = load_slot_row(lu.slots, lu.slot_key, sg.lpc, sg.nwt, row0 + b, r_hi);
     }
 #pragma unroll
     for (int b = 0; b < ROWS_IN_FLIGHT; ++b) {
-      if (row0 + b >= lu.r_hi) break;                              // uniform over the wave
+      if (row0 + b >= r_hi) break;                              // uniform over the wave
       const SlotRow r = parse_slot_row(rr[b], sg.lpc);
       seen += r.n;
       if (!r.spill) {
@@ -132,8 +167,20 @@ __global__ __launch_bounds__(BIG) void k_lean_hist(DevCtx c, SegInfo one, uint32
       }
     }
   }
-  seen = wave_sum(seen);
-  if (lane == 0) lu.wcnt[lu.gw] = seen;
+  if (failed) {
+    if (SPARS != QSL_TOPK || safe) return;       // safe mode: the multi-pass kernels take the unit
+    // a coordinate per lane, and only after the rows: ahead of them the kernel of an undisturbed call is slower (15 units of
+    // 10^6, k = 10^4: 5.9 us; here 5.75, without the walk 5.6)
+    const float* vp = v + static_cast<uint64_t>(lu.w) * c.d + sg.start;
+    const uint32_t nw = sg.nsel * (BIG / 64);
+    const uint64_t hi = min<uint64_t>(sg.size, (static_cast<uint64_t>(sg.nwt) * (lu.gw + 1) / nw) * CHUNK);
+#pragma unroll 1
+    for (uint64_t e = (static_cast<uint64_t>(sg.nwt) * lu.gw / nw) * CHUNK + lane; e < hi; e += WAVE)
+      atomicAdd(&lh[key_of_value(__float_as_uint(vp[e])) >> 20], 1u);
+  } else {
+    seen = wave_sum(seen);
+    if (lane == 0) lu.wcnt[lu.gw] = seen;
+  }
   __syncthreads();
   flush_hist(lh, c.hist + lu.u * 3 * HBINS);
 }
@@ -142,7 +189,7 @@ __global__ __launch_bounds__(BIG) void k_lean_hist(DevCtx c, SegInfo one, uint32
 // second launch: threshold bin, dense list, what is certainly selected, the short list
 // ------------------------------------------------------------------------------------------------
 template <int SPARS>
-__global__ __launch_bounds__(BIG) void k_lean_mark(DevCtx c, SegInfo one, uint32_t R) {
+__global__ __launch_bounds__(BIG) void k_lean_mark(DevCtx c, SegInfo one, uint32_t R, const float* v, int safe) {
   __shared__ uint64_t acc[LEAN_ROWS * (ACC_SLOTS + 1)];
   __shared__ uint64_t scratch[17];
   __shared__ uint32_t result[6];
@@ -151,7 +198,35 @@ __global__ __launch_bounds__(BIG) void k_lean_mark(DevCtx c, SegInfo one, uint32
   const SegInfo& sg = lu.sg;
   UnitState* usp = &c.units[lu.u];
   const UnitState us = *usp;
-  if (us.fell_back) return;
+  if (us.fell_back) {                               // (uniform)
+    if (SPARS != QSL_TOPK || safe) return;
+    find2_from_top<BIG>(c.hist + lu.u * 3 * HBINS, sg.k, sg.r_warm, scratch, result, false);
+    const uint32_t lowest = result[0] << 20;        // the bin of the k-th largest key: everything from its lower edge on
+    if (threadIdx.x == 0 && lu.j == 0) {            // the next guess, as after a fresh sample
+      uint32_t s = 11;
+      while (s < 20 && (1u << (s - 11)) < result[0] + 1 - result[2]) ++s;
+      usp->T_next = result[2] << 20; usp->sh_next = s;
+    }
+    const uint32_t cap = sg.d0_cap / (sg.nsel * (BIG / 64));
+    uint2* part = lu.d0 + static_cast<uint64_t>(lu.gw) * cap;
+    uint32_t n = 0;
+    lean_walk_v<4>(lu, v + static_cast<uint64_t>(lu.w) * c.d + sg.start, [&](uint64_t e, const f4u& x, uint32_t nv) {
+      uint32_t below = 0, tot = 0, nib = 0;
+#pragma unroll
+      for (uint32_t j = 0; j < 4; ++j) {
+        const bool in = j < nv && key_of_value(__float_as_uint(x[j])) >= lowest;
+        const uint64_t bal = __ballot(in);
+        nib |= (in ? 1u : 0u) << j; below += popc_below(bal); tot += static_cast<uint32_t>(__popcll(bal));
+      }
+      uint32_t at = n + below;
+#pragma unroll
+      for (uint32_t j = 0; j < 4; ++j)
+        if ((nib >> j) & 1u) { if (at < cap) part[at] = make_uint2(static_cast<uint32_t>(sg.start + e + j), __float_as_uint(x[j])); ++at; }
+      n += tot;
+    });
+    if (lane_id() == 0) lu.wcnt[lu.gw] = n;         // more than `cap`: k_lean_emit sees that the list is not whole
+    return;
+  }
   const uint32_t T = us.T, sh = us.sh;
   // the loads that depend on nothing are issued first: this wave's first slot rows, the earlier waves' counts
   RawRow rr[ROWS_IN_FLIGHT];
@@ -390,34 +465,41 @@ __global__ __launch_bounds__(BIG) void k_block_units(DevCtx c, uint32_t R, float
 // keys come from v itself) or whose threshold bin was too crowded for the short list (from the dense list).  Slow
 // for a large unit read from v, and rare: the host switches to the multi-pass kernels when it has happened.
 // ------------------------------------------------------------------------------------------------
-template <int SPARS, bool FROM_V>
+enum { FROM_LIST, FROM_V, FROM_PARTS };             // FROM_PARTS: `n` places in parts of `cap`, the first part_n[p] of part p filled
+template <int SPARS, int FROM>
 __device__ void block_select_encode(const DevCtx& c, const SegInfo& sg, uint32_t w, uint64_t u, const float* vp,
-                                    const uint2* d0, const uint32_t* d0k, uint64_t n, uint32_t worker0, uint64_t round,
+                                    const uint2* d0, const uint32_t* d0k, uint64_t n, uint32_t cap, const uint32_t* part_n,
+                                    uint32_t worker0, uint64_t round,
                                     float* m_out, uint32_t* dbg_idx, uint16_t* dbg_level, uint32_t* lh, uint64_t* acc,
                                     uint64_t* scratch, uint32_t* result, float* s_scale, uint32_t* s_count) {
   const RandKey rk = make_rand_key(c.seed, worker0 + w, round, 0);
   const uint32_t wave = threadIdx.x >> 6, lane = lane_id();
   auto load = [&](uint64_t i, uint32_t* idx, uint32_t* bits, uint32_t* key) {
-    if (FROM_V) {
+    if (FROM == FROM_V) {
       *idx = static_cast<uint32_t>(sg.start + i);
       *bits = __float_as_uint(vp[i]);
       *key = SPARS == QSL_TOPK ? key_of_value(*bits) : rand_word(rk, *idx);
     } else {
+      if (FROM == FROM_PARTS) {
+        const uint32_t p = static_cast<uint32_t>(i) / cap;
+        if (static_cast<uint32_t>(i) - p * cap >= part_n[p]) return false;
+      }
       const uint2 e = d0[i];
       *idx = e.x; *bits = e.y;
       *key = SPARS == QSL_TOPK ? key_of_value(e.y) : d0k[i];
     }
+    return true;
   };
   for (uint32_t i = threadIdx.x; i < HBINS; i += BIG) lh[i] = 0;
   for (uint32_t i = threadIdx.x; i < LEAN_ROWS * acc_stride(c.quantizer); i += BIG) acc[i] = 0;
   __syncthreads();
   uint32_t prefix = 0, k_rem = sg.k, above, idx, bits, key;
-  for (uint64_t i = threadIdx.x; i < n; i += BIG) { load(i, &idx, &bits, &key); atomicAdd(&lh[key >> 20], 1u); }
+  for (uint64_t i = threadIdx.x; i < n; i += BIG) if (load(i, &idx, &bits, &key)) atomicAdd(&lh[key >> 20], 1u);
   __syncthreads();
   uint32_t bin_w = 0;
-  if (FROM_V && SPARS == QSL_TOPK) bin_w = find_from_top<BIG>(lh, sg.r_warm, &above, scratch, result, false);
+  if (FROM == FROM_V && SPARS == QSL_TOPK) bin_w = find_from_top<BIG>(lh, sg.r_warm, &above, scratch, result, false);
   uint32_t bin = find_from_top<BIG>(lh, k_rem, &above, scratch, result, true);
-  if (FROM_V && SPARS == QSL_TOPK && threadIdx.x == 0) {
+  if (FROM == FROM_V && SPARS == QSL_TOPK && threadIdx.x == 0) {
     // the guess had failed: the next one comes from this histogram of the whole unit, as after a fresh sample
     uint32_t sh = 11;
     while (sh < 20 && (1u << (sh - 11)) < bin + 1 - bin_w) ++sh;
@@ -425,15 +507,13 @@ __device__ void block_select_encode(const DevCtx& c, const SegInfo& sg, uint32_t
   }
   prefix = bin << 20; k_rem -= above;
   for (uint64_t i = threadIdx.x; i < n; i += BIG) {
-    load(i, &idx, &bits, &key);
-    if ((key >> 20) == (prefix >> 20)) atomicAdd(&lh[(key >> 8) & 0xFFFu], 1u);
+    if (load(i, &idx, &bits, &key) && (key >> 20) == (prefix >> 20)) atomicAdd(&lh[(key >> 8) & 0xFFFu], 1u);
   }
   __syncthreads();
   bin = find_from_top<BIG>(lh, k_rem, &above, scratch, result, true);
   prefix |= bin << 8; k_rem -= above;
   for (uint64_t i = threadIdx.x; i < n; i += BIG) {
-    load(i, &idx, &bits, &key);
-    if ((key >> 8) == (prefix >> 8)) atomicAdd(&lh[key & 0xFFu], 1u);
+    if (load(i, &idx, &bits, &key) && (key >> 8) == (prefix >> 8)) atomicAdd(&lh[key & 0xFFu], 1u);
   }
   __syncthreads();
   bin = find_from_top<BIG, 1024>(lh, k_rem, &above, scratch, result, true);      // bins 256 .. 1023 are empty
@@ -450,10 +530,7 @@ __device__ void block_select_encode(const DevCtx& c, const SegInfo& sg, uint32_t
     for (uint32_t q = 0; q < 4; ++q) {
       const uint64_t i = base + threadIdx.x * 4ull + q;
       ix[q] = 0; bt[q] = 0;
-      if (i < n) {
-        load(i, &ix[q], &bt[q], &key);
-        gm |= (key > tau ? 1u : 0u) << q; qm |= (key == tau ? 1u : 0u) << q;
-      }
+      if (i < n && load(i, &ix[q], &bt[q], &key)) { gm |= (key > tau ? 1u : 0u) << q; qm |= (key == tau ? 1u : 0u) << q; }
     }
     uint64_t total;
     const uint64_t ex = block_exclusive_scan64((static_cast<uint64_t>(__popc(qm)) << 32) | __popc(gm), scratch, &total);
@@ -496,13 +573,33 @@ __global__ __launch_bounds__(BIG) void k_lean_emit(DevCtx c, SegInfo one, uint32
     const UnitState us = c.units[u];
     if (us.fell_back) {
       if (safe) return;                                           // the multi-pass kernels of this call took the unit
-      if (threadIdx.x == 0) *c.host_flag = 1u;                    // the host will ask for them on its next calls
-      block_select_encode<SPARS, true>(c, sg, w, u, m_out + static_cast<uint64_t>(w) * c.d + sg.start, nullptr, nullptr,
-                                       sg.size, worker0, round, m_out, dbg_idx, dbg_level, lh, acc, scratch, result, &s_scale,
+      if (SPARS == QSL_TOPK) {                                    // what the waves of k_lean_mark collected, if all of it found room
+        const uint32_t nw = sg.nsel * (BIG / 64), cap = sg.d0_cap / nw;
+        static_assert(sizeof s_list >= 4 * MAX_SELECT_BLOCKS * (BIG / 64) && MAX_SELECT_BLOCKS * (BIG / 64) <= BIG, "a count per wave, a thread per count");
+        uint32_t* part_n = reinterpret_cast<uint32_t*>(s_list);
+        if (threadIdx.x == 0) s_need = 0;
+        __syncthreads();
+        if (threadIdx.x < nw) {
+          const uint32_t x = (c.wave_cnt + static_cast<uint64_t>(w) * c.NWC + sg.wc_base)[threadIdx.x];
+          part_n[threadIdx.x] = x;
+          if (x > cap) s_need = 1;
+        }
+        __syncthreads();
+        if (s_need == 0) {                                        // (uniform)
+          if (threadIdx.x == 0) *c.host_flag = 1u;                // the next calls' guesses come from samples
+          block_select_encode<SPARS, FROM_PARTS>(c, sg, w, u, nullptr, c.d0 + static_cast<uint64_t>(w) * c.d0_stride + sg.d0_off, nullptr,
+                                                 static_cast<uint64_t>(nw) * cap, cap, part_n, worker0, round, m_out, dbg_idx, dbg_level,
+                                                 lh, acc, scratch, result, &s_scale, &s_count);
+          return;
+        }
+      }
+      if (threadIdx.x == 0) *c.host_flag = 2u;                    // the host will ask for the multi-pass kernels on its next calls
+      block_select_encode<SPARS, FROM_V>(c, sg, w, u, m_out + static_cast<uint64_t>(w) * c.d + sg.start, nullptr, nullptr,
+                                       sg.size, 0, nullptr, worker0, round, m_out, dbg_idx, dbg_level, lh, acc, scratch, result, &s_scale,
                                        &s_count);
     } else if (us.crowded) {
-      block_select_encode<SPARS, false>(c, sg, w, u, nullptr, c.d0 + static_cast<uint64_t>(w) * c.d0_stride + sg.d0_off,
-                                        c.d0_key + static_cast<uint64_t>(w) * c.d0_stride + sg.d0_off, us.cand, worker0,
+      block_select_encode<SPARS, FROM_LIST>(c, sg, w, u, nullptr, c.d0 + static_cast<uint64_t>(w) * c.d0_stride + sg.d0_off,
+                                        c.d0_key + static_cast<uint64_t>(w) * c.d0_stride + sg.d0_off, us.cand, 0, nullptr, worker0,
                                         round, m_out, dbg_idx, dbg_level, lh, acc, scratch, result, &s_scale, &s_count);
     }
     return;
@@ -679,7 +776,7 @@ __global__ __launch_bounds__(BIG) void k_lean_one(DevCtx c, SegInfo one, uint32_
     if (safe) return;                                 // the multi-pass kernels of this call take the unit
     if (threadIdx.x == 0) *c.host_flag = 1u;
     __syncthreads();
-    block_select_encode<SPARS, true>(c, sg, w, u, m_out + static_cast<uint64_t>(w) * c.d + sg.start, nullptr, nullptr, sg.size,
+    block_select_encode<SPARS, FROM_V>(c, sg, w, u, m_out + static_cast<uint64_t>(w) * c.d + sg.start, nullptr, nullptr, sg.size, 0, nullptr,
                                      worker0, round, m_out, dbg_idx, dbg_level, lh, acc, scratch, result, &s_scale, &s_count);
     return;
   }
@@ -792,7 +889,7 @@ __global__ __launch_bounds__(BIG) void k_lean_one(DevCtx c, SegInfo one, uint32_
   __threadfence_block();                             // the dense list is read back below, by other waves too
   __syncthreads();
   if (crowded) {                                     // more ties in the threshold's bin than the short list holds
-    block_select_encode<SPARS, false>(c, sg, w, u, nullptr, d0, d0k, cand, worker0, round, m_out, dbg_idx, dbg_level, lh, acc,
+    block_select_encode<SPARS, FROM_LIST>(c, sg, w, u, nullptr, d0, d0k, cand, 0, nullptr, worker0, round, m_out, dbg_idx, dbg_level, lh, acc,
                                       scratch, result, &s_scale, &s_count);
     return;
   }

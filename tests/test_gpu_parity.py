@@ -510,6 +510,21 @@ def test_guess_from_the_previous_call_survives_a_change_of_the_inputs(P):
             assert all(sset == [0] for sset in seen), seen        # a fresh sample never fails on these inputs
 
 
+# a failed guess made good by all blocks of a unit: values spread over many bins (the waves' parts hold them), and values of
+# nearly one magnitude (one bin holds them all, the parts overflow and one block walks through v)
+@pytest.mark.parametrize("d,k", [(300_007, 300), (1_000_003, 1000), (2_000_001, 20_000)])
+@pytest.mark.parametrize("cluster", [False, True])
+def test_failed_guess_made_good_by_many_blocks(P, d, k, cluster):
+    rng = np.random.default_rng(d + cluster)
+    R = 2
+    deltas = [rng.standard_normal((R, d)).astype(f32) for _ in range(2)]
+    x = 1e6 * (1.0 + 0.1 * rng.random((R, d))) * np.sign(rng.standard_normal((R, d))) if cluster else 1e4 * rng.standard_normal((R, d))
+    deltas.append(x.astype(f32))
+    wl = custom(d, [0, d], [k], 16, W.TOPK, W.QSGD, R)
+    run, op, m_host, paths = P.run_parity(wl, 3, deltas=deltas)
+    assert (paths[2] == 2).all(), paths[2]
+
+
 def test_ties_at_the_threshold_beyond_the_short_list(P):
     """Thousands of equal magnitudes exactly at the threshold: the threshold's histogram bin holds more candidates
     than the short list takes, so one block selects the unit from its dense candidate list (ties to the lower
