@@ -1,6 +1,6 @@
 // qsl_decode.h -- Reading messages: the stand-alone error update (k_add_rows, k_subtract_msg) and the master's
 // aggregation (k_fill_zero, k_msg_directory, k_aggregate, k_aggregate_entries, k_aggregate_cells,
-// k_aggregate_dense), k_read_nnz.
+// k_aggregate_dense, k_aggregate_dense_one), k_read_nnz.
 // Part of the single translation unit qsl.hip (included there, in this order: device, layout, select,
 // encode, stream, lean, dense, decode); not a public header.
 #pragma once
