@@ -130,7 +130,9 @@ __global__ __launch_bounds__(BLOCK) void k_msg_directory(DevCtx c, const uint8_t
       const uint64_t j = j0 + static_cast<uint64_t>(u) * nth;
       cell[u] = 0; prev[u] = 0;
       if (j < v.nnz) {
-        cell[u] = min(msg_index(c, v, static_cast<uint32_t>(j)) >> AGG_DIR_SHIFT, ndir - 2);            // clamp: a malformed index
+        const uint32_t idx = msg_index(c, v, static_cast<uint32_t>(j));
+        if (idx >= c.d) atomicOr(c.status, 4u);            // malformed message: here every index is seen, whoever decodes the entry
+        cell[u] = min(idx >> AGG_DIR_SHIFT, ndir - 2);
         if (lane == 0 && j) prev[u] = min(msg_index(c, v, static_cast<uint32_t>(j) - 1) >> AGG_DIR_SHIFT, ndir - 2);
       }
     }
@@ -424,6 +426,7 @@ __global__ __launch_bounds__(BLOCK, 8) void k_aggregate_cells(DevCtx c, const ui
   }
   if (c0 >= c.d) return;
   const uint32_t cnt = hi > lo ? min(hi - lo, span) : 0u; // a well-formed message has at most one entry per coordinate
+  if (hi > lo && hi - lo > span) atomicOr(c.status, 4u);  // malformed: what is beyond that is skipped
   span = static_cast<uint32_t>(min<uint64_t>(span, c.d - c0));
   const uint32_t base = static_cast<uint32_t>(c0);
   uint32_t n;

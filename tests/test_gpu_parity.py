@@ -858,3 +858,56 @@ def test_index_free_edges(P, d, quantizer, s, factor):
         want = _aggregate_by_definition(decoded, lst, -0.25, x0, accumulate, d)
         assert np.array_equal(out.cpu().numpy().view(np.uint32), want.view(np.uint32)), (d, quantizer, s, lst)
     assert run.q.device_status() == B.OK
+
+
+# a message with an index >= d: reported by the status word (once), the entry skipped, everything else added up
+# as ever -- whichever kernel meets it: one wave per cell, a cell in parts (where the entry lies behind d, in a part that has
+# no coordinates), a last cell that the plan calls crowded, short messages, look-ups
+@pytest.mark.parametrize("case", ["cells", "parts", "crowded_last_cell", "short", "lookups", "qsgd_segments"])
+def test_aggregate_reports_malformed_indices(P, case):
+    from paper_1906_02367_amd import binding as B
+    rng = np.random.default_rng(len(case))
+    d, off, k, s, qz, R = {"cells": (300_001, [0, 300_001], [5_000], 1, W.SIGN_L1, 8),
+                           "parts": (70_001, [0, 70_001], [5_000], 1, W.SIGN_L1, 64),          # 16 parts of 64; 369 coordinates in the last cell
+                           "crowded_last_cell": (260_100, [0, 259_700, 260_100], [6_000, 400], 1, W.SIGN_L2, 24),
+                           "short": (50_001, [0, 50_001], [500], 1, W.FP32, 40),
+                           "lookups": (9_000_001, [0, 9_000_001], [5_000], 1, W.SIGN_L1, 2),
+                           "qsgd_segments": (300_001, [0, 900, 300_001], [900, 9_000], 15, W.QSGD, 12)}[case]
+    wl = custom(d, off, k, s, W.TOPK, qz, R=R)
+    q = B.from_workload(wl)
+    op = P.oracle_for(wl)
+    msg = q.new_msg(R)
+    delta = torch.from_numpy(rng.standard_normal((R, d)).astype(f32)).to(q.device)
+    m = torch.zeros(R, d, device=q.device)
+    q.compress(m, delta, m, 0, 0, msg)
+    torch.cuda.synchronize()
+    good = msg.cpu().numpy()
+    decoded = [op.decode(x) for x in good]
+    w_idx, L = (d - 1).bit_length(), len(k)
+    bit0 = 32 * (1 + L + (L if qz == W.QSGD and L > 1 else 0))
+    x0 = rng.standard_normal(d).astype(f32)
+
+    def patched(r, j, value):
+        bad = good.copy()
+        bits = np.unpackbits(bad[r], bitorder="little")
+        at = bit0 + j * w_idx
+        bits[at: at + w_idx] = (value >> np.arange(w_idx)) & 1
+        bad[r] = np.packbits(bits, bitorder="little")
+        return torch.from_numpy(bad).to(q.device)
+
+    for r in (0, R - 1):
+        n = int(good[r].view(np.uint32)[0])
+        for value in (d, (1 << w_idx) - 1):              # the message's last entry: its order stays right
+            out = torch.from_numpy(x0).to(q.device)
+            q.aggregate(patched(r, n - 1, value), out, -0.5, accumulate=True)
+            assert q.device_status() == B.ERR_DEVICE and q.device_status() == B.OK, (case, r, value)
+            rest = [(i[:-1], v[:-1]) if p == r else (i, v) for p, (i, v) in enumerate(decoded)]
+            want = _aggregate_by_definition(rest, list(range(R)), -0.5, x0, True, d)
+            assert np.array_equal(out.cpu().numpy().view(np.uint32), want.view(np.uint32)), (case, r, value)
+        out = torch.from_numpy(x0).to(q.device)          # in the middle: what else happens to that message is open
+        q.aggregate(patched(r, n // 2, d), out, -0.5, accumulate=True)
+        assert q.device_status() == B.ERR_DEVICE and q.device_status() == B.OK, (case, r, "middle")
+    out = torch.from_numpy(x0).to(q.device)
+    q.aggregate(msg, out, -0.5, accumulate=True)
+    assert q.device_status() == B.OK
+    assert np.array_equal(out.cpu().numpy().view(np.uint32), _aggregate_by_definition(decoded, list(range(R)), -0.5, x0, True, d).view(np.uint32))
