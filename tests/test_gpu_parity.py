@@ -911,3 +911,42 @@ def test_aggregate_reports_malformed_indices(P, case):
     q.aggregate(msg, out, -0.5, accumulate=True)
     assert q.device_status() == B.OK
     assert np.array_equal(out.cpu().numpy().view(np.uint32), _aggregate_by_definition(decoded, list(range(R)), -0.5, x0, True, d).view(np.uint32))
+
+
+# NaNs of every kind in a message reach the model, through each way of the master line: none of them stands for "no entry"
+@pytest.mark.parametrize("R,d,k", [(8, 300_001, 5_000), (64, 70_001, 5_000), (40, 50_001, 500), (2, 50_001, 500)])
+@pytest.mark.parametrize("quantizer", [W.FP32, W.SIGN_L1])
+def test_aggregate_keeps_nans(P, R, d, k, quantizer):
+    from paper_1906_02367_amd import binding as B
+    rng = np.random.default_rng(R)
+    wl = custom(d, [0, d], [k], 1, W.TOPK, quantizer, R=R)
+    q = B.from_workload(wl)
+    op = P.oracle_for(wl)
+    msg = q.new_msg(R)
+    base = rng.standard_normal(d).astype(f32)
+    base[100:104] = 50.0                                  # four coordinates that every message holds
+    v = (base[None, :] + rng.standard_normal((R, d))).astype(f32)
+    m = torch.zeros(R, d, device=q.device)
+    q.compress(m, torch.from_numpy(v).to(q.device), m, 0, 0, msg)
+    torch.cuda.synchronize()
+    good = msg.cpu().numpy()
+    decoded = [op.decode(x) for x in good]
+    bad = good.copy()
+    if quantizer == W.FP32:                               # the codes are the values
+        n_idx = (k * (d - 1).bit_length() + 31) // 32
+        for r, coord, code in ((0, 100, 0xFFFFFFFF), (R - 1, 101, 0xFFFFFFFF), (R // 2, 102, 0xFFBFFFFF), (0, 103, 0x7FC00000), (R - 1, 103, 0xFFFFFFFF)):
+            bad[r].view(np.uint32)[2 + n_idx + int(np.searchsorted(decoded[r][0], coord))] = code
+        nan_at = np.arange(100, 104)
+    else:                                                 # the scale: its negative is the NaN with all bits set
+        bad[R - 1].view(np.uint32)[1] = 0x7FFFFFFF
+        nan_at = decoded[R - 1][0].astype(np.int64)
+    x0 = rng.standard_normal(d).astype(f32)
+    for accumulate in (True, False):
+        out = torch.from_numpy(x0).to(q.device)
+        q.aggregate(torch.from_numpy(bad).to(q.device), out, -1.0 / R, accumulate=accumulate)
+        torch.cuda.synchronize()
+        want = _aggregate_by_definition(decoded, list(range(R)), -1.0 / R, x0, accumulate, d)
+        got = out.cpu().numpy()
+        assert np.all(np.isnan(got[nan_at]))
+        got[nan_at] = want[nan_at] = 0
+        assert np.array_equal(got.view(np.uint32), want.view(np.uint32))
