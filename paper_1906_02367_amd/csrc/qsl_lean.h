@@ -139,17 +139,29 @@ __global__ __launch_bounds__(BIG) void k_lean_hist(DevCtx c, SegInfo one, uint32
       usp->sh_next = sh;
     }
   }
-  const uint64_t r_hi = failed ? lu.r_lo : lu.r_hi;  // (uniform) a discarded guess's candidates are not read
   const uint32_t lane = lane_id();
+  if (__builtin_expect(failed, 0)) {                 // (uniform) a discarded guess's candidates are not read
+    if (SPARS != QSL_TOPK || safe) return;           // safe mode: the multi-pass kernels take the unit
+    // (a coordinate per lane: with more in flight, or without the hint above, an undisturbed call is slower by 0.2 us)
+    const float* vp = v + static_cast<uint64_t>(lu.w) * c.d + sg.start;
+    const uint32_t nw = sg.nsel * (BIG / 64);
+    const uint64_t hi = min<uint64_t>(sg.size, (static_cast<uint64_t>(sg.nwt) * (lu.gw + 1) / nw) * CHUNK);
+#pragma unroll 1
+    for (uint64_t e = (static_cast<uint64_t>(sg.nwt) * lu.gw / nw) * CHUNK + lane; e < hi; e += WAVE)
+      atomicAdd(&lh[key_of_value(__float_as_uint(vp[e])) >> 20], 1u);
+    __syncthreads();
+    flush_hist(lh, c.hist + lu.u * 3 * HBINS);
+    return;
+  }
   uint32_t seen = 0;
-  for (uint64_t row0 = lu.r_lo; row0 < r_hi; row0 += ROWS_IN_FLIGHT) {
+  for (uint64_t row0 = lu.r_lo; row0 < lu.r_hi; row0 += ROWS_IN_FLIGHT) {
     if (row0 != lu.r_lo) {
 #pragma unroll
-      for (int b = 0; b < ROWS_IN_FLIGHT; ++b) rr[b] = load_slot_row(lu.slots, lu.slot_key, sg.lpc, sg.nwt, row0 + b, r_hi);
+      for (int b = 0; b < ROWS_IN_FLIGHT; ++b) rr[b] = load_slot_row(lu.slots, lu.slot_key, sg.lpc, sg.nwt, row0 + b, lu.r_hi);
     }
 #pragma unroll
     for (int b = 0; b < ROWS_IN_FLIGHT; ++b) {
-      if (row0 + b >= r_hi) break;                              // uniform over the wave
+      if (row0 + b >= lu.r_hi) break;                              // uniform over the wave
       const SlotRow r = parse_slot_row(rr[b], sg.lpc);
       seen += r.n;
       if (!r.spill) {
@@ -167,20 +179,8 @@ __global__ __launch_bounds__(BIG) void k_lean_hist(DevCtx c, SegInfo one, uint32
       }
     }
   }
-  if (failed) {
-    if (SPARS != QSL_TOPK || safe) return;       // safe mode: the multi-pass kernels take the unit
-    // a coordinate per lane, and only after the rows: ahead of them the kernel of an undisturbed call is slower (15 units of
-    // 10^6, k = 10^4: 5.9 us; here 5.75, without the walk 5.6)
-    const float* vp = v + static_cast<uint64_t>(lu.w) * c.d + sg.start;
-    const uint32_t nw = sg.nsel * (BIG / 64);
-    const uint64_t hi = min<uint64_t>(sg.size, (static_cast<uint64_t>(sg.nwt) * (lu.gw + 1) / nw) * CHUNK);
-#pragma unroll 1
-    for (uint64_t e = (static_cast<uint64_t>(sg.nwt) * lu.gw / nw) * CHUNK + lane; e < hi; e += WAVE)
-      atomicAdd(&lh[key_of_value(__float_as_uint(vp[e])) >> 20], 1u);
-  } else {
-    seen = wave_sum(seen);
-    if (lane == 0) lu.wcnt[lu.gw] = seen;
-  }
+  seen = wave_sum(seen);
+  if (lane == 0) lu.wcnt[lu.gw] = seen;
   __syncthreads();
   flush_hist(lh, c.hist + lu.u * 3 * HBINS);
 }
@@ -257,6 +257,7 @@ __global__ __launch_bounds__(BIG) void k_lean_mark(DevCtx c, SegInfo one, uint32
   }
   const uint32_t wave = threadIdx.x >> 6, lane = lane_id();
   const uint32_t power = norm_power(c.quantizer);
+  const bool need_norm = c.quantizer != QSL_FP32;            // (uniform)
   uint64_t* mine = acc + ((wave & 7u) * 8 + (lane & 7u)) * acc_stride(c.quantizer);
   uint32_t* cursor = c.ctr + (lu.u * CTR_LINES + CTR_LIST) * PAD;
   uint4* list = c.tlist + (static_cast<uint64_t>(lu.w) * c.nfast + sg.fidx) * LISTCAP;
@@ -269,7 +270,7 @@ __global__ __launch_bounds__(BIG) void k_lean_mark(DevCtx c, SegInfo one, uint32
       lu.d0[p] = make_uint2(idx, bits);
       if (SPARS == QSL_RANDK) lu.d0k[p] = key;
       const uint32_t b = lean_bin(key, T, sh);
-      if (b > taubin) { ++n_above; add_digits(mine, bits, power); }
+      if (b > taubin) { ++n_above; if (need_norm) add_digits(mine, bits, power); }
       else inside = b == taubin && !crowded;
     }
     const uint64_t ib = __ballot(inside);
@@ -314,6 +315,7 @@ __global__ __launch_bounds__(BIG) void k_lean_mark(DevCtx c, SegInfo one, uint32
   }
   n_above = wave_sum(n_above);
   if (lane == 0) lu.wsel[lu.gw] = n_above;
+  if (!need_norm) return;
   __syncthreads();
   uint64_t* ga = c.norm_acc + lu.u * ACC_SLOTS;
   for (uint32_t s = wave; s < acc_slots(c.quantizer); s += BIG / 64) {
@@ -616,6 +618,7 @@ __global__ __launch_bounds__(BIG) void k_lean_emit(DevCtx c, SegInfo one, uint32
   const uint32_t k_rem = sg.k - us.above;                         // how many of the threshold bin's candidates are selected (>= 1)
   const uint32_t wave = threadIdx.x >> 6, lane = lane_id();
   const uint32_t power = norm_power(c.quantizer);
+  const bool need_norm = c.quantizer != QSL_FP32;                 // (uniform)
   // The loads that depend on nothing are issued together: the list's length and entries (a thread per entry of the
   // whole array; what lies beyond the length is stale and ignored), the digits of the norm, the counts of the waves.
   static_assert(LISTCAP <= BIG, "a thread per list entry");
@@ -646,7 +649,7 @@ __global__ __launch_bounds__(BIG) void k_lean_emit(DevCtx c, SegInfo one, uint32
     sel = rank < k_rem;
     s_sel[threadIdx.x] = sel;
     if (rank == k_rem - 1) s_tau = me.z;                          // the k-th largest key of the unit
-    if (sel) add_digits(acc, me.y, power);                      // the rest of the norm (LDS atomics on one row)
+    if (sel && need_norm) add_digits(acc, me.y, power);                      // the rest of the norm (LDS atomics on one row)
   }
   __syncthreads();
   if (sel && me.z == s_tau) atomicAdd(&s_need, 1u);
@@ -654,7 +657,7 @@ __global__ __launch_bounds__(BIG) void k_lean_emit(DevCtx c, SegInfo one, uint32
   if (threadIdx.x < acc_slots(c.quantizer)) acc[threadIdx.x] += my_digit;
   __syncthreads();
   if (wave == 0) {
-    const float sc = finalize_scale(acc, c.quantizer, sg.k);
+    const float sc = need_norm ? finalize_scale(acc, c.quantizer, sg.k) : 0.0f;
     if (lane == 0) s_scale = sc;
   }
   __syncthreads();
