@@ -56,6 +56,7 @@
 #include <vector>
 
 #include "qsl.h"
+#include "qsl_policy.h"
 #include "qsl_device.h"
 #include "qsl_layout.h"
 #include "qsl_select.h"
@@ -100,9 +101,7 @@ struct qsl_ctx {
   uint32_t nsel_general, ncb_general;   // blocks of the multi-pass kernels without / with (DevCtx::NSEL, NCB) the guessing units' share
   uint32_t n_other;           // segments that k_quantize encodes (not the guessing ones)
   uint32_t warm_R;            // workers whose guessing units carry a guess from an earlier call
-  uint32_t safe_left;         // calls still to be made with the multi-pass kernels standing by for failed guesses
-  uint32_t recent_left;       // calls for which the last failed guess still counts as recent
-  uint32_t cold_left, strikes; // calls still to be made with sampled guesses, and failures reported during them
+  GuessPolicy guesses;        // what is made of failed guesses
   uint32_t* blk_cnt2[2];      // the two arrays of per-block counters of transmitted entries, used in turn
   uint64_t calls;             // compress calls made
   uint32_t nsamp_blocks;      // blocks of the sampling kernel (per worker)
@@ -379,7 +378,7 @@ extern "C" qsl_status qsl_create(qsl_ctx** out, const qsl_config* cfg, void* hip
   ctx->stream = static_cast<hipStream_t>(hip_stream);
   ctx->Rmax = cfg->max_workers;
   for (AggCrowd& a : ctx->agg) a = AggCrowd{nullptr, nullptr, 0};
-  ctx->last_R = 0; ctx->warm_R = 0; ctx->safe_left = 0; ctx->cold_left = 0; ctx->strikes = 0; ctx->recent_left = 0;
+  ctx->last_R = 0; ctx->warm_R = 0;
   ctx->timing = 0; ctx->ev_used = 0;
   ctx->slab = nullptr; ctx->h_status = nullptr; ctx->own_v = nullptr; ctx->order_ev = nullptr; ctx->side = nullptr; ctx->side2 = nullptr; ctx->join2_ev = nullptr; ctx->fork_ev = nullptr; ctx->join_ev = nullptr;
 
@@ -739,9 +738,9 @@ extern "C" qsl_status qsl_create(qsl_ctx** out, const qsl_config* cfg, void* hip
     const std::vector<WinState> all(R, ws);
     if (hipMemcpy(wc.state, all.data(), sizeof(WinState) * R, hipMemcpyHostToDevice) != hipSuccess) { free_ctx(ctx); return QSL_ERR_DEVICE; }
   }
-  ctx->h_status[8] = 0;
+  for (uint32_t i = 0; i < N_FLAGS; ++i) ctx->h_status[8 + i] = 0;
   {
-    void* dflag = nullptr;                          // the device's address of a word of the pinned host block
+    void* dflag = nullptr;                          // the device's address of words of the pinned host block
     if (hipHostGetDevicePointer(&dflag, ctx->h_status + 8, 0) != hipSuccess || !dflag) { free_ctx(ctx); return QSL_ERR_DEVICE; }
     c.host_flag = static_cast<uint32_t*>(dflag);
   }
@@ -838,23 +837,11 @@ static qsl_status launch_compress(qsl_ctx* ctx, const float* m, const float* del
     return QSL_ERR_UNSUPPORTED;                    // ... and so does the streaming kernel when it reads x_t
   c.blk_cnt = ctx->blk_cnt2[ctx->calls & 1]; c.blk_cnt_next = ctx->blk_cnt2[(ctx->calls & 1) ^ 1];
   ++ctx->calls;
-  // A failed guess leaves a word in pinned host memory; it may be seen a few calls late, and only speed depends on it,
-  // never the result.  1, made good by many blocks: when it happens again within 16 calls, the next 32 take their guesses
-  // from samples, as a context's first call does (15 workers of 5.4 M coordinates whose thresholds jump from call to call:
-  // 490 us a call that way, 1000 with failed guesses made good; 260 undisturbed).  2, made good by
-  // one block walking through a large unit, or guesses that keep failing all the same: the multi-pass kernels stand by for
-  // the units whose guess fails.
-  const uint32_t flag = ctx->h_status[8];
-  if (flag != 0) {
-    ctx->h_status[8] = 0;
-    if (flag == 2 || (ctx->cold_left > 0 && ++ctx->strikes > 3)) ctx->safe_left = 16;
-    if (ctx->cold_left == 0 && ctx->recent_left > 0) { ctx->cold_left = 32; ctx->strikes = 0; }
-    ctx->recent_left = 16;
-  } else if (ctx->recent_left > 0) --ctx->recent_left;
-  const bool safe = ctx->safe_left > 0;
-  if (safe) --ctx->safe_left;
-  const bool cold = ctx->warm_R < R || ctx->cold_left > 0 || (ctx->cfg.flags & QSL_FLAG_NO_WARM_START) != 0;
-  if (ctx->cold_left > 0) --ctx->cold_left;
+  bool flag[N_FLAGS];                              // left by kernels of earlier calls
+  for (uint32_t i = 0; i < N_FLAGS; ++i) { flag[i] = ctx->h_status[8 + i] != 0; if (flag[i]) ctx->h_status[8 + i] = 0; }
+  const GuessPolicy::Call policy = ctx->guesses.next(flag[FLAG_MILD], flag[FLAG_CRAWL], flag[FLAG_HOPELESS],
+                                                     ctx->warm_R < R || (ctx->cfg.flags & QSL_FLAG_NO_WARM_START) != 0);
+  const bool safe = policy.safe, cold = policy.cold;
   if (SPARS == QSL_TOPK && ctx->n_sampled > 0 && cold) {
     k_sample<<<dim3(ctx->nsamp_blocks * R), BIG, 0, st>>>(c, m, delta, xm, R);
     k_sample_scan<<<dim3(c.nfast, R), BIG, 0, st>>>(c);

@@ -28,6 +28,12 @@ constexpr uint32_t CTR_LINES = NSUB + 3;
 constexpr uint32_t WLIST = 1024;           // entries of the window path's list of threshold-bin candidates
 constexpr uint32_t LISTCAP = 256;          // entries of that list; a threshold bin that holds more sends the unit to the block-wide selection
 
+// What the kernels report to the host (qsl_policy.h): a failed guess made good by many blocks, or by one block on a small unit; one
+// made good by one block that walked through a large one (more than CRAWL_MIN coordinates: 150 us and up); the same, on values
+// of which a sampled guess would have let too many through as well.
+enum : uint32_t { FLAG_MILD = 0, FLAG_CRAWL = 1, FLAG_HOPELESS = 2, N_FLAGS };
+constexpr uint32_t CRAWL_MIN = 1u << 17;
+
 enum : uint32_t { PATH_FAST = 0, PATH_GENERAL = 1, PATH_FALLBACK = 2, PATH_SMALL = 3, PATH_FULL = 4 };
 constexpr uint32_t MAX_FULL_BLOCKS = 512;  // blocks per unit of k_full (each ends with up to 20 atomics on the unit's digit counters)
 constexpr uint32_t SMALL_CHUNKS = 4;       // a unit of at most 4 chunks (4096 coordinates) is always selected by one block
@@ -110,7 +116,7 @@ struct DevCtx {
   uint32_t* wave_cnt;   // [R][NWC]: candidates met by each wave of k_lean_hist
   uint32_t* wave_sel;   // [R][NWC]: of these, how many lie in the bins above the threshold's (k_lean_mark)
   uint4* tlist;         // [R][nfast][LISTCAP]: the candidates in the threshold's bin: (place in the dense list, value bits, key, -)
-  uint32_t* host_flag;  // pinned host memory: 1 when a guess failed, 2 when it had to be made good by one block reading a large unit whole
+  uint32_t* host_flag;  // pinned host memory: the words FLAG_*, set by kernels (plain stores), cleared by the host
   uint2* cb_cnt;        // [R][NCB]: (#key > tau, #key == tau) of each compaction block
   uint32_t* hist;       // [U][3][HBINS], one histogram per radix digit; all zero between calls
   uint32_t* ctr;        // [U][CTR_LINES][PAD]; word 0 of each line is a counter; all zero between calls

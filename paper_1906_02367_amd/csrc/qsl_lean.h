@@ -465,7 +465,7 @@ __global__ __launch_bounds__(BIG) void k_block_units(DevCtx c, uint32_t R, float
 // exact selection of one unit by one block of 1024 threads, by radix digits (12 + 12 + 8 bits) and an ordered pass,
 // followed by the norm and the encoding of the k selected coordinates: for a unit whose guess failed (FROM_V: the
 // keys come from v itself) or whose threshold bin was too crowded for the short list (from the dense list).  Slow
-// for a large unit read from v, and rare: the host switches to the multi-pass kernels when it has happened.
+// for a large unit read from v, and rare: the host sees to it that it does not happen again at once (qsl_policy.h).
 // ------------------------------------------------------------------------------------------------
 enum { FROM_LIST, FROM_V, FROM_PARTS };             // FROM_PARTS: `n` places in parts of `cap`, the first part_n[p] of part p filled
 template <int SPARS, int FROM>
@@ -499,7 +499,12 @@ __device__ void block_select_encode(const DevCtx& c, const SegInfo& sg, uint32_t
   for (uint64_t i = threadIdx.x; i < n; i += BIG) if (load(i, &idx, &bits, &key)) atomicAdd(&lh[key >> 20], 1u);
   __syncthreads();
   uint32_t bin_w = 0;
-  if (FROM == FROM_V && SPARS == QSL_TOPK) bin_w = find_from_top<BIG>(lh, sg.r_warm, &above, scratch, result, false);
+  uint32_t let_through = 0xFFFFFFFFu;               // candidates of a guess at rank r_warm, as a sample would give it
+  if (FROM == FROM_V && SPARS == QSL_TOPK) {
+    bin_w = find_from_top<BIG>(lh, sg.r_warm, &above, scratch, result, false);
+    let_through = above + lh[bin_w];
+  }
+  if (FROM == FROM_V && threadIdx.x == 0) c.host_flag[sg.size <= CRAWL_MIN ? FLAG_MILD : let_through > sg.ovf_cap ? FLAG_HOPELESS : FLAG_CRAWL] = 1u;
   uint32_t bin = find_from_top<BIG>(lh, k_rem, &above, scratch, result, true);
   if (FROM == FROM_V && SPARS == QSL_TOPK && threadIdx.x == 0) {
     // the guess had failed: the next one comes from this histogram of the whole unit, as after a fresh sample
@@ -588,14 +593,13 @@ __global__ __launch_bounds__(BIG) void k_lean_emit(DevCtx c, SegInfo one, uint32
         }
         __syncthreads();
         if (s_need == 0) {                                        // (uniform)
-          if (threadIdx.x == 0) *c.host_flag = 1u;                // the next calls' guesses come from samples
+          if (threadIdx.x == 0) c.host_flag[FLAG_MILD] = 1u;
           block_select_encode<SPARS, FROM_PARTS>(c, sg, w, u, nullptr, c.d0 + static_cast<uint64_t>(w) * c.d0_stride + sg.d0_off, nullptr,
                                                  static_cast<uint64_t>(nw) * cap, cap, part_n, worker0, round, m_out, dbg_idx, dbg_level,
                                                  lh, acc, scratch, result, &s_scale, &s_count);
           return;
         }
       }
-      if (threadIdx.x == 0) *c.host_flag = 2u;                    // the host will ask for the multi-pass kernels on its next calls
       block_select_encode<SPARS, FROM_V>(c, sg, w, u, m_out + static_cast<uint64_t>(w) * c.d + sg.start, nullptr, nullptr,
                                        sg.size, 0, nullptr, worker0, round, m_out, dbg_idx, dbg_level, lh, acc, scratch, result, &s_scale,
                                        &s_count);
@@ -777,7 +781,6 @@ __global__ __launch_bounds__(BIG) void k_lean_one(DevCtx c, SegInfo one, uint32_
   }
   if (failed) {
     if (safe) return;                                 // the multi-pass kernels of this call take the unit
-    if (threadIdx.x == 0) *c.host_flag = 1u;
     __syncthreads();
     block_select_encode<SPARS, FROM_V>(c, sg, w, u, m_out + static_cast<uint64_t>(w) * c.d + sg.start, nullptr, nullptr, sg.size, 0, nullptr,
                                      worker0, round, m_out, dbg_idx, dbg_level, lh, acc, scratch, result, &s_scale, &s_count);

@@ -1,0 +1,48 @@
+// qsl_policy.h -- What the host makes of the failures that the kernels report through pinned words.  Plain C++, no HIP.  A
+// report may be seen a few calls late; only speed depends on it, never the result.
+#pragma once
+
+#include <algorithm>
+#include <cstdint>
+
+namespace {
+
+// Guessing units (Top_k takes its guesses from the previous call, or from a sample; Rand_k's are fixed).  Three kinds of failure:
+//   mild      made good by many blocks, or by one block on a small unit.  When it happens again within 16 calls, the next 32 take
+//             their guesses from samples, as a context's first call does (15 workers of 5.4 M coordinates whose thresholds jump
+//             from call to call: 490 us a call that way, 1000 with failed guesses made good; 260 undisturbed).  If guesses keep
+//             failing all the same, the multi-pass kernels stand by for the units whose guess fails.
+//   crawl     one block walked through a large unit, for milliseconds: the next four calls take samples at once, so that a
+//             second jump costs no second walk.
+//   hopeless  the same, and no sample would have helped (too few non-zero values, ties): the multi-pass kernels stand by for 16
+//             calls, and again at the next such failure.
+struct GuessPolicy {
+  uint32_t safe_left = 0;      // calls still to be made with the multi-pass kernels standing by
+  uint32_t cold_left = 0;      // calls still to be made with sampled guesses
+  uint32_t recent_left = 0;    // calls for which the last failure still counts as recent
+  uint32_t strikes = 0;        // mild failures reported while guesses were sampled
+  bool last_cold = false;      // the previous call sampled
+
+  struct Call { bool safe, cold; };
+  // `must`: the call samples in any case (its context's first one, or a flag)
+  Call next(bool mild, bool crawl, bool hopeless, bool must) {
+    if (mild || crawl || hopeless) {
+      if (hopeless || (crawl && last_cold)) safe_left = 16;
+      else {
+        if (cold_left > 0 && ++strikes > 3) safe_left = 16;
+        if (cold_left == 0 && recent_left > 0) { cold_left = 32; strikes = 0; }
+        else if (cold_left == 0 && crawl) { cold_left = 4; strikes = 0; }
+      }
+      recent_left = 16;
+    } else if (recent_left > 0) --recent_left;
+    Call c;
+    c.safe = safe_left > 0;
+    if (c.safe) --safe_left;
+    c.cold = must || cold_left > 0;
+    if (cold_left > 0) --cold_left;
+    last_cold = c.cold;
+    return c;
+  }
+};
+
+}  // namespace

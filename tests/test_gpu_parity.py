@@ -950,3 +950,46 @@ def test_aggregate_keeps_nans(P, R, d, k, quantizer):
         assert np.all(np.isnan(got[nan_at]))
         got[nan_at] = want[nan_at] = 0
         assert np.array_equal(got.view(np.uint32), want.view(np.uint32))
+
+
+# guessing units of a single block (segments x workers >= 256 blocks), small ones and ones that the host is to hear about as
+# walked through by one block: thresholds that jump down and up, too few non-zero values, ties; two jumps in a row
+def test_failed_guesses_of_single_block_units(P):
+    from paper_1906_02367_amd import binding as B
+    rng = np.random.default_rng(31)
+    sizes = [140_001, 20_003] * 8
+    off = np.concatenate([[0], np.cumsum(sizes)]).tolist()
+    R = 16
+    wl = custom(off[-1], off, [max(1, n // 400) for n in sizes], 1, W.TOPK, W.SIGN_L1, R=R)
+    assert set(B.plan_paths(wl.d, wl.seg_offset, wl.seg_k, wl.s, wl.sparsifier, wl.quantizer).tolist()) == {0}
+    qa, qb = B.from_workload(wl), B.from_workload(wl, flags=B.FLAG_NO_FAST_PATH)
+    op = P.oracle_for(wl)
+    ma, mb = torch.zeros(R, wl.d, device=qa.device), torch.zeros(R, wl.d, device=qa.device)
+    failed = []
+    for t, kind in enumerate(["plain", "plain", "down", "up", "plain", "zeros", "zeros", "zeros", "plain", "ties", "plain"]):
+        v = rng.standard_normal((R, wl.d), dtype=f32)
+        if kind == "down":
+            v *= f32(0.01)
+        elif kind == "up":
+            v *= f32(100)
+        elif kind == "zeros":
+            v[rng.random((R, wl.d), dtype=f32) < 0.999] = 0
+        elif kind == "ties":
+            v = np.round(v)
+        delta = torch.from_numpy(v).to(qa.device)
+        if t % 3 == 2 or kind == "zeros":                       # the error memory starts anew, so that thresholds do jump
+            ma.zero_(); mb.zero_()
+        m_before = ma[3].cpu().numpy()
+        outs = []
+        for q, m in ((qa, ma), (qb, mb)):
+            msg = q.new_msg(R).fill_(0xCD)
+            q.compress(m, delta, m, 0, t, msg)
+            outs.append((m.view(torch.int32), msg))
+        torch.cuda.synchronize()
+        assert qa.device_status() == B.OK and qb.device_status() == B.OK
+        for a, b in zip(*outs):
+            assert torch.equal(a, b), (t, kind)
+        o = op.compress(m_before, v[3], 3, t)
+        assert np.array_equal(outs[0][1][3].cpu().numpy(), o["msg"]) and np.array_equal(P.bits(ma[3].cpu().numpy()), P.bits(o["m_out"]))
+        failed.append(int((qa.debug_units()[:, 0] == 2).sum()))
+    assert failed[0] == 0 and failed[2] > 0 and max(failed[5:8]) > 0, failed

@@ -277,3 +277,60 @@ def test_host_generators_are_deterministic_and_shaped():
 def test_bench_refuses_more_than_one_gpu():
     res = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True)
     assert res.returncode != 0 and "ONE GPU" in res.stderr
+
+
+# qsl_policy.h, the host's answer to reported failures, on sequences of calls whose guesses fail: the report of a call is seen
+# `delay` calls later.  A "crawl" (one block walks through a large unit) takes milliseconds, so what counts is how many there are.
+POLICY_MAIN = r"""
+#include <cstdio>
+#include <cstdlib>
+#include <deque>
+#include <string>
+#include "qsl_policy.h"
+// argv: sequence, calls, delay; prints crawls, calls with the multi-pass kernels standing by, calls with samples
+int main(int, char** a) {
+  const std::string kind = a[1];
+  const int n = atoi(a[2]), delay = atoi(a[3]);
+  GuessPolicy p;
+  std::deque<int> seen(delay, 0);
+  int crawls = 0, safes = 0, colds = 0;
+  for (int i = 0; i < n; ++i) {
+    const int report = seen.empty() ? 0 : seen.front();
+    if (!seen.empty()) seen.pop_front();
+    const GuessPolicy::Call c = p.next(report == 1, report == 2, report == 3, i == 0);
+    bool fails = false;
+    if (kind == "hopeless" || kind == "to_hopeless") fails = kind == "hopeless" || i >= 20;      // a sampled guess fails like any other
+    else if (kind == "twice") fails = !c.cold && (i == 20 || i == 21);
+    else if (kind == "once" || kind == "mild") fails = !c.cold && i == 20;
+    else if (kind == "always") fails = !c.cold && i > 0;                   // thresholds jump from call to call
+    const bool crawl = fails && !c.safe;
+    crawls += crawl; safes += c.safe; colds += c.cold;
+    seen.push_back(!crawl ? 0 : kind == "mild" ? 1 : kind.find("hopeless") != std::string::npos ? 3 : 2);
+  }
+  printf("%d %d %d\n", crawls, safes, colds);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def policy(tmp_path_factory):
+    tmp = tmp_path_factory.mktemp("policy")
+    (tmp / "main.cpp").write_text(POLICY_MAIN)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-I" + os.path.join(ROOT, "paper_1906_02367_amd", "csrc"), "-o", str(tmp / "p"),
+                    str(tmp / "main.cpp")], check=True)
+    return lambda *args: [int(x) for x in subprocess.run([str(tmp / "p")] + [str(x) for x in args], check=True, capture_output=True,
+                                                          text=True).stdout.split()]
+
+
+def test_failed_guesses_are_not_walked_again_and_again(policy):
+    # the report seen at the next call
+    assert policy("once", 100, 1) == [1, 0, 1 + 4]                # one walk, samples for four calls
+    assert policy("mild", 100, 1) == [1, 0, 1]                    # a cheap failure changes nothing by itself
+    assert policy("twice", 100, 1)[0] == 1                        # a second jump at once costs no second walk
+    assert policy("always", 400, 1)[0] <= 2 + 2 * 400 // 37       # 4 and 32 calls with samples, a walk after each
+    for kind in ("hopeless", "to_hopeless"):                      # no sample helps: 16 calls of 17 stand by, from the first report on
+        crawls, safes, _ = policy(kind, 420, 1)
+        assert crawls <= 1 + 420 // 17 and safes >= 16 * (400 // 17)
+    # ... and four calls later
+    assert policy("once", 100, 4)[0] == 1
+    assert policy("hopeless", 400, 4)[0] <= 4 * (1 + 400 // 20)
