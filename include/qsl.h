@@ -111,8 +111,8 @@ enum {
 };
 
 /* Which way each segment of an operator will take through the selection -- the `path` that qsl_debug_units
- * reports, before any failed guess: 0 = single-pass with a guessed threshold, 1 = multi-pass, 3 = one block,
- * 4 = no selection (k = size).  The decision depends on (size, k, sparsifier, flags) only; qsl_create makes it
+ * reports, before any failed guess: 0 = single-pass with a guessed threshold, 1 = multi-pass (on a large vector mostly by
+ * a window of rank keys, see qsl_debug_units), 3 = one block, 4 = no selection (k = size).  The decision depends on (size, k, sparsifier, flags) only; qsl_create makes it
  * with the same code.  Needs no context and no GPU.
  *   cfg host; path_out host, uint32 [num_segments] */
 qsl_status qsl_plan_paths(const qsl_config *cfg, uint32_t *path_out);
@@ -217,8 +217,10 @@ qsl_status qsl_device_status(qsl_ctx *ctx);
 /* Per-unit diagnostics of the last compress call (unit = worker-major (worker, segment)); synchronises.
  * out_host receives, per unit, 8 uint32: {path, candidates, threshold key, n_greater, n_equal_taken,
  * guess key, scale bits, transmitted}; path: 0 = single-pass fast path, 1 = multi-pass path by
- * configuration, 2 = multi-pass path after a failed guess, 3 = one-block selection of a small segment,
- * 4 = no selection (k equals the size of the segment: every coordinate is kept).  */
+ * configuration (a dense k on a large vector: with candidates > 0 the window of rank keys that holds the threshold was
+ * enough, with 0 the multi-pass kernels went over all of it), 2 = multi-pass path after a failed guess or a window that did
+ * not hold, 3 = one-block selection of a small segment, 4 = no selection (k equals the size of the segment: every
+ * coordinate is kept).  */
 qsl_status qsl_debug_units(qsl_ctx *ctx, uint32_t *out_host, uint32_t max_units, uint32_t *n_units);
 
 /* Kernel timing for the benchmark: when enabled, compress calls bracket the streaming kernel with

@@ -102,6 +102,8 @@ struct qsl_ctx {
   uint32_t n_other;           // segments that k_quantize encodes (not the guessing ones)
   uint32_t warm_R;            // workers whose guessing units carry a guess from an earlier call
   GuessPolicy guesses;        // what is made of failed guesses
+  WindowPolicy windows;       // ... and of windows that did not hold
+  bool last_win;              // the last compress call tried the window
   uint32_t* blk_cnt2[2];      // the two arrays of per-block counters of transmitted entries, used in turn
   uint64_t calls;             // compress calls made
   uint32_t nsamp_blocks;      // blocks of the sampling kernel (per worker)
@@ -289,10 +291,13 @@ static double plan_segment(const qsl_config* cfg, SegInfo& sg) {
 // coordinates, a 32nd of the vector but at least 32,768 and at most 2^20 of them -- more, up to half of it, while the
 // window's coordinates would not fit the slots well -- with a margin of 6.5 sigma of a sample of an eighth of that size on
 // either side: runs share their surroundings' scale.  Too small a window costs a call with the multi-pass kernels, a large
-// one slots: at d = 25.6 M, k = d / 10 it holds 1.4 % of the vector.  From 3 M coordinates on: the window takes twelve
-// launches, six of them idle, against eight (k = d / 10, one worker: 1.5 M coordinates 71 us both ways, 3 M 76 against 86;
-// k = 3 %, eight workers: 1 M 100 against 88, 3 M 165 against 213).
+// one slots: at d = 25.6 M, k = d / 10 it holds 1.4 % of the vector.  From 3 M coordinates on: the window takes fourteen
+// launches (Rand_k: twelve), six of them idle, against eight (k = d / 10, one worker: 1.5 M coordinates 71 us both ways, 3 M 76
+// against 86; k = 3 %, eight workers: 1 M 100 against 88, 3 M 165 against 213).
 constexpr uint64_t WINDOW_MIN = 3ull << 20;
+// ... in a call with R workers: QSGD, whose entries k_win_apply has to count, pays from 4 M on with one worker or two (k = d / 10,
+// two workers: 3.2 M coordinates 103 us by the window, 99 by the multi-pass kernels; 4.3 M 113 against 133).
+static bool window_pays(const SegInfo& sg, bool qsgd, uint32_t R) { return !qsgd || R > 2 || sg.size >= 1ull << 22; }
 static bool plan_window(const qsl_config* cfg, SegInfo& sg) {
   if (cfg->num_segments != 1 || sg.mode != PATH_GENERAL || sg.size < WINDOW_MIN || sg.k == sg.size ||
       (cfg->flags & (QSL_FLAG_NO_FAST_PATH | QSL_FLAG_NO_SMALL_PATH))) return false;
@@ -314,17 +319,21 @@ static bool plan_window(const qsl_config* cfg, SegInfo& sg) {
   } else {
     const double q = 7.0 * std::sqrt(p * (1 - p) / n);
     const double lo = std::floor(4294967296.0 * std::max(0.0, 1 - p - q)), hi = std::min(4294967295.0, std::ceil(4294967296.0 * (1 - p + q)));
-    sg.T_static = static_cast<uint32_t>(lo); sg.r_s = static_cast<uint32_t>(hi);
+    sg.T_static = static_cast<uint32_t>(lo); sg.r_s = static_cast<uint32_t>(hi);       // (k_init takes T_static for guessing units only)
     const double pc = (hi - lo) / 4294967296.0 * CHUNK;
     need = pc + 4 * std::sqrt(pc);
   }
   if (need > 63) return false;
   sg.lpc = need <= 15 ? 8 : need <= 31 ? 16 : 32;
   sg.ovf_cap = static_cast<uint32_t>(std::min<uint64_t>(sg.size, std::max<uint64_t>(8192, sg.size / 8)));
-  const uint64_t rows = (static_cast<uint64_t>(sg.nwt) * sg.lpc + 63) / 64;
-  // a thousand-thread block per compute unit at most, about three slot rows per wave (as for the guessing units)
-  sg.nsel = static_cast<uint32_t>(std::max<uint64_t>(1, std::min<uint64_t>({MAX_SELECT_BLOCKS, 256 / std::min(256u, cfg->max_workers), (rows + 47) / 48})));
   return true;
+}
+
+// Blocks per unit of the window's kernels in a call with R workers: a thousand-thread block per compute unit at most, about
+// three slot rows per wave (as for the guessing units).
+static uint32_t window_blocks(const SegInfo& sg, uint32_t R) {
+  const uint64_t rows = (static_cast<uint64_t>(sg.nwt) * sg.lpc + 63) / 64;
+  return static_cast<uint32_t>(std::max<uint64_t>(1, std::min<uint64_t>({MAX_SELECT_BLOCKS, 256 / std::min(256u, R), (rows + 47) / 48})));
 }
 
 extern "C" qsl_status qsl_plan_paths(const qsl_config* cfg, uint32_t* path_out) {
@@ -378,7 +387,7 @@ extern "C" qsl_status qsl_create(qsl_ctx** out, const qsl_config* cfg, void* hip
   ctx->stream = static_cast<hipStream_t>(hip_stream);
   ctx->Rmax = cfg->max_workers;
   for (AggCrowd& a : ctx->agg) a = AggCrowd{nullptr, nullptr, 0};
-  ctx->last_R = 0; ctx->warm_R = 0;
+  ctx->last_R = 0; ctx->last_win = false; ctx->warm_R = 0;
   ctx->timing = 0; ctx->ev_used = 0;
   ctx->slab = nullptr; ctx->h_status = nullptr; ctx->own_v = nullptr; ctx->order_ev = nullptr; ctx->side = nullptr; ctx->side2 = nullptr; ctx->join2_ev = nullptr; ctx->fork_ev = nullptr; ctx->join_ev = nullptr;
 
@@ -506,7 +515,7 @@ extern "C" qsl_status qsl_create(qsl_ctx** out, const qsl_config* cfg, void* hip
       (guessing ? sels_f : sels).push_back(si);
       if (guessing && (sg.nsel > 1 || !one_kernel)) fsels.push_back(si);      // (else the unit goes to k_lean_one)
     }
-    sg.wc_base = static_cast<uint32_t>(nwc); nwc += sg.nsel * (BIG / 64);
+    sg.wc_base = static_cast<uint32_t>(nwc); nwc += (window ? MAX_SELECT_BLOCKS : sg.nsel) * (BIG / 64);      // (the window's blocks: see window_blocks)
     sg.cb_base = cb_slots; cb_slots += sg.ncb;
     for (uint32_t b = 0; b < sg.ncb; ++b) { CbInfo ci; ci.seg = l; ci.b = b; ci.pad0 = ci.pad1 = 0; (guessing ? cbs_f : cbs).push_back(ci); }
   }
@@ -829,7 +838,7 @@ static qsl_status launch_compress(qsl_ctx* ctx, const float* m, const float* del
                                   uint32_t worker0,
                                   uint32_t R, uint64_t round, uint8_t* msg, uint64_t* msg_bits, uint32_t* sel_idx,
                                   uint16_t* sel_level) {
-  DevCtx& c = ctx->dc;
+  DevCtx c = ctx->dc;                              // of this call
   hipStream_t st = ctx->stream;
   if (static_cast<uint64_t>(std::max(std::max(c.NSEL, c.NCB), std::max(std::max(ctx->nsamp_blocks, c.nblock), c.NSELF + c.nfast + c.none))) * R > 0x7FFFFFFFull)
     return QSL_ERR_UNSUPPORTED;                    // the list kernels use one-dimensional grids of (list entries x workers)
@@ -842,6 +851,8 @@ static qsl_status launch_compress(qsl_ctx* ctx, const float* m, const float* del
   const GuessPolicy::Call policy = ctx->guesses.next(flag[FLAG_MILD], flag[FLAG_CRAWL], flag[FLAG_HOPELESS],
                                                      ctx->warm_R < R || (ctx->cfg.flags & QSL_FLAG_NO_WARM_START) != 0);
   const bool safe = policy.safe, cold = policy.cold;
+  if (c.win && (!window_pays(ctx->segs[0], is_qsgd(c.quantizer), R) || !ctx->windows.next(flag[FLAG_WINDOW]))) c.win = 0;
+  ctx->last_win = c.win != 0;
   if (SPARS == QSL_TOPK && ctx->n_sampled > 0 && cold) {
     k_sample<<<dim3(ctx->nsamp_blocks * R), BIG, 0, st>>>(c, m, delta, xm, R);
     k_sample_scan<<<dim3(c.nfast, R), BIG, 0, st>>>(c);
@@ -923,7 +934,8 @@ static qsl_status launch_compress(qsl_ctx* ctx, const float* m, const float* del
     k_lean_mark<SPARS><<<dim3(c.NSELF * R), BIG, 0, st>>>(c, ctx->segs[0], R, m_out, safe ? 1 : 0);
   }
   if (c.win) {
-    const SegInfo& sg = ctx->segs[0];
+    SegInfo sg = ctx->segs[0];
+    sg.nsel = window_blocks(sg, R);
     k_win_hist<SPARS><<<dim3(sg.nsel * R), BIG, 0, st>>>(c, ctx->wc, sg, R);
     k_win_mark<SPARS><<<dim3(sg.nsel * R), BIG, 0, st>>>(c, ctx->wc, sg, R);
     k_win_mid<SPARS><<<dim3(sg.nsel * R), BIG, 0, st>>>(c, ctx->wc, sg, R);
@@ -931,15 +943,18 @@ static qsl_status launch_compress(qsl_ctx* ctx, const float* m, const float* del
   }
   // the multi-pass kernels: a launch per digit and two for the compaction, for the units planned that way -- and for
   // the guessing units too while failed guesses are expected
-  const uint32_t nsel = safe ? c.NSEL : ctx->nsel_general, ncb = safe ? c.NCB : ctx->ncb_general;
+  SegInfo sel_one = ctx->segs[0];
+  uint32_t nsel = safe ? c.NSEL : ctx->nsel_general;
+  const uint32_t ncb = safe ? c.NCB : ctx->ncb_general;
+  if (c.win) nsel = sel_one.nsel = std::max(1u, std::min(sel_one.nsel, 256 / std::min(256u, R)));      // mostly they find nothing to do
   if (nsel) {
-    k_select<0, SPARS><<<dim3(nsel * R), BIG, 0, st>>>(c, ctx->segs[0], m_out, worker0, round, R);
-    k_select<1, SPARS><<<dim3(nsel * R), BIG, 0, st>>>(c, ctx->segs[0], m_out, worker0, round, R);
-    k_select<2, SPARS><<<dim3(nsel * R), BIG, 0, st>>>(c, ctx->segs[0], m_out, worker0, round, R);
+    k_select<0, SPARS><<<dim3(nsel * R), BIG, 0, st>>>(c, sel_one, m_out, worker0, round, R);
+    k_select<1, SPARS><<<dim3(nsel * R), BIG, 0, st>>>(c, sel_one, m_out, worker0, round, R);
+    k_select<2, SPARS><<<dim3(nsel * R), BIG, 0, st>>>(c, sel_one, m_out, worker0, round, R);
     k_tile_count<SPARS><<<dim3(ncb * R), BLOCK, 0, st>>>(c, ctx->segs[0], m_out, worker0, round, R);
     k_tile_write<SPARS><<<dim3(ncb * R), BLOCK, 0, st>>>(c, ctx->segs[0], m_out, worker0, round, R);
   }
-  if (c.win) k_quantize<true><<<dim3(std::min(c.QB, 256u), R), BLOCK, 0, st>>>(c, m_out, worker0, round, sel_idx, sel_level, 0);
+  if (c.win) k_quantize<true><<<dim3(std::min(c.QB, std::max(256u, 1024 / R)), R), BLOCK, 0, st>>>(c, m_out, worker0, round, sel_idx, sel_level, 0);
   else if (ctx->n_other || safe) k_quantize<false><<<dim3(c.QB, R), BLOCK, 0, st>>>(c, m_out, worker0, round, sel_idx, sel_level, safe ? 1 : 0);
   // the guessing units' exact threshold, ordered output and codes; one more block per guessing unit for failures
   if (c.NSELF)
@@ -1208,7 +1223,8 @@ extern "C" qsl_status qsl_debug_units(qsl_ctx* ctx, uint32_t* out_host, uint32_t
   QSL_HIP(hipStreamSynchronize(ctx->stream));
   for (uint32_t u = 0; u < U; ++u) {
     uint32_t* o = out_host + 8ull * u;
-    o[0] = us[u].path == PATH_FAST && us[u].fell_back ? static_cast<uint32_t>(PATH_FALLBACK) : us[u].path;
+    const bool failed = us[u].path == PATH_FAST ? us[u].fell_back != 0 : ctx->last_win && (us[u].fell_back || us[u].crowded);
+    o[0] = failed ? static_cast<uint32_t>(PATH_FALLBACK) : us[u].path;
     o[1] = us[u].cand; o[2] = us[u].tau; o[3] = us[u].n_gt; o[4] = us[u].need; o[5] = us[u].path == PATH_FAST ? us[u].T_used : us[u].T;
     o[6] = us[u].scale_bits; o[7] = us[u].nnz;
   }

@@ -31,7 +31,8 @@ constexpr uint32_t LISTCAP = 256;          // entries of that list; a threshold 
 // What the kernels report to the host (qsl_policy.h): a failed guess made good by many blocks, or by one block on a small unit; one
 // made good by one block that walked through a large one (more than CRAWL_MIN coordinates: 150 us and up); the same, on values
 // of which a sampled guess would have let too many through as well.
-enum : uint32_t { FLAG_MILD = 0, FLAG_CRAWL = 1, FLAG_HOPELESS = 2, N_FLAGS };
+// FLAG_WINDOW: a window that did not hold.
+enum : uint32_t { FLAG_MILD = 0, FLAG_CRAWL = 1, FLAG_HOPELESS = 2, FLAG_WINDOW = 3, N_FLAGS };
 constexpr uint32_t CRAWL_MIN = 1u << 17;
 
 enum : uint32_t { PATH_FAST = 0, PATH_GENERAL = 1, PATH_FALLBACK = 2, PATH_SMALL = 3, PATH_FULL = 4 };
@@ -133,7 +134,7 @@ struct DevCtx {
   uint32_t dense;       // 1: every coordinate is kept and the messages have the index-free format
   uint32_t L, K, NWT, NSEL, NCB, NWC, QB, NSELF, nfast, nblock, Rmax, nbig, s, w_idx, w_lev, w_val, sparsifier, quantizer, cap_words;
   uint32_t none;        // entries of one_segs
-  uint32_t win;         // 1: the only segment goes the way of the window (a dense k on a large vector), the multi-pass kernels standing by
+  uint32_t win;         // 1: in this call the only segment goes the way of the window (a dense k on a large vector), the multi-pass kernels standing by
 };
 
 __device__ __forceinline__ uint32_t key_of_value(uint32_t vbits) { return (vbits & 0x7FFFFFFFu) << 1; }

@@ -45,4 +45,17 @@ struct GuessPolicy {
   }
 };
 
+// The window of a dense k (qsl_window.h).  While it fails -- the threshold among ties or zeros -- its kernels are left out and the
+// multi-pass kernels take every unit at once: for 2, 8, 32 and then 128 calls after a failure, then it is tried again.  16 calls
+// without a report, and the next failure starts at 2 again.
+struct WindowPolicy {
+  uint32_t skip_left = 0, backoff = 0, held = 0;
+  bool next(bool failed) {     // whether this call tries the window
+    if (failed) { backoff = std::min(128u, std::max(2u, 4 * backoff)); skip_left = backoff; held = 0; }
+    if (skip_left > 0) { --skip_left; return false; }
+    if (backoff > 0 && ++held > 16) backoff = 0;
+    return true;
+  }
+};
+
 }  // namespace

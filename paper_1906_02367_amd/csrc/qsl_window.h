@@ -11,7 +11,8 @@
 //                 worker line) written chunk by chunk
 // v is read twice in all (20 bytes per coordinate with the streaming pass), where the multi-pass kernels read it six times
 // and update it by scattered words.  If the window did not hold the threshold, held too much (ties, zeros) or its bin holds
-// more than the list takes, the unit is left to the multi-pass kernels, whose launches stand by (they end at once otherwise).
+// more than the list takes, the unit is left to the multi-pass kernels, whose launches stand by (they end at once otherwise);
+// the host hears of it and leaves the window out of the next calls (WindowPolicy in qsl_policy.h).
 // Part of the single translation unit qsl.hip (included after qsl_lean.h); not a public header.
 #pragma once
 
@@ -79,7 +80,7 @@ __global__ __launch_bounds__(BIG) void k_win_sample(DevCtx c, WinCtx wc, SegInfo
 // the window from the sample's ranks r_tau (above the threshold) and r_s (below it); the histogram back to zero
 __global__ __launch_bounds__(BIG) void k_win_scan(WinCtx wc, SegInfo sg) {
   __shared__ uint64_t scratch[17];
-  __shared__ uint32_t s_bin[2];
+  __shared__ uint32_t s_bin[2], s_cum[2];
   constexpr uint32_t PER = WBINS / BIG;
   const uint32_t w = blockIdx.x, t = threadIdx.x;
   uint32_t* gh = wc.sample + static_cast<uint64_t>(w) * WCOPIES * WBINS;
@@ -96,7 +97,7 @@ __global__ __launch_bounds__(BIG) void k_win_scan(WinCtx wc, SegInfo sg) {
     }
     sum += h[i] + h[i + 1] + h[i + 2] + h[i + 3];
   }
-  if (t == 0) { s_bin[0] = 0; s_bin[1] = 0; }
+  if (t == 0) { s_bin[0] = 0; s_bin[1] = 0; s_cum[0] = 0; s_cum[1] = 0xFFFFFFFFu; }
   uint64_t total;
   const uint64_t before = block_exclusive_scan64(sum, scratch, &total);
 #pragma unroll
@@ -106,7 +107,8 @@ __global__ __launch_bounds__(BIG) void k_win_scan(WinCtx wc, SegInfo sg) {
       uint64_t cum = before;
 #pragma unroll
       for (uint32_t i = PER; i-- > 0;) {
-        if (cum + h[i] >= target) { s_bin[which] = low + i; break; }
+        // s_cum: the sample's coordinates above the window, and those above its lower end
+        if (cum + h[i] >= target) { s_bin[which] = low + i; s_cum[which] = static_cast<uint32_t>(which ? cum + h[i] : cum); break; }
         cum += h[i];
       }
     }
@@ -123,9 +125,13 @@ __global__ __launch_bounds__(BIG) void k_win_scan(WinCtx wc, SegInfo sg) {
     WinState* ws = &wc.state[w];
     const uint32_t lo = s_bin[1] << WSHIFT;
     const uint32_t hi = sg.r_tau == 0 || s_bin[0] == WBINS - 1 ? 0xFFFFFFFFu : (s_bin[0] + 1) << WSHIFT;
+    // An eighth of the sample or more inside: ties, or more places than there are non-zero coordinates.  No pool would take
+    // what such a window holds; it is closed, so that the streaming pass lists nothing (k_win_hist sees that it failed).
+    const uint32_t inside = static_cast<uint32_t>(min<uint64_t>(s_cum[1], total)) - s_cum[0];
+    const bool closed = static_cast<uint64_t>(inside) * 8 >= total;
     uint32_t sh = 0;
     while (((hi - 1 - lo) >> sh) >= HBINS) ++sh;
-    ws->lo = lo; ws->hi = hi; ws->sh = sh;
+    ws->lo = closed ? 0xFFFFFFFFu : lo; ws->hi = closed ? 0xFFFFFFFFu : hi; ws->sh = sh;
   }
 }
 
@@ -331,7 +337,10 @@ __global__ __launch_bounds__(BIG) void k_win_hist(DevCtx c, WinCtx wc, SegInfo o
   for (uint32_t i = 0; i < NSUB; ++i) sum += s_ctr[i];
   const uint32_t cand = static_cast<uint32_t>(sum), above = static_cast<uint32_t>(sum >> 32);
   const bool failed = s_ctr[CTR_FAIL] != 0 || above >= sg.k || static_cast<uint64_t>(above) + cand < sg.k;
-  if (threadIdx.x == 0 && lu.j == 0) { usp->cand = cand; wc.state[lu.w].above = above; usp->fell_back = failed; usp->nnz = 0; }
+  if (threadIdx.x == 0 && lu.j == 0) {
+    usp->cand = cand; wc.state[lu.w].above = above; usp->fell_back = failed; usp->crowded = 0; usp->nnz = 0;
+    if (failed) c.host_flag[FLAG_WINDOW] = 1u;
+  }
   if (failed) return;
   const uint32_t lane = lane_id();
   for (uint64_t row0 = lu.r_lo; row0 < lu.r_hi; row0 += ROWS_IN_FLIGHT) {
@@ -376,8 +385,15 @@ __global__ __launch_bounds__(BIG) void k_win_mark(DevCtx c, WinCtx wc, SegInfo o
   const uint32_t target = sg.k - wc.state[lu.w].above;                 // >= 1
   find2_from_top<BIG>(wc.hist + lu.u * HBINS, target, target, scratch, result, false);
   const uint32_t taubin = result[0], above = result[1];
-  const bool crowded = result[4] > WLIST;
-  if (threadIdx.x == 0 && lu.j == 0) { usp->taubin = taubin; usp->above = above; usp->crowded = crowded; }
+  // Four times what a bin holds on average is as much as smooth values put into one; a longer list (ties) is worth ranking where
+  // the multi-pass kernels would have much to read, for large vectors and for many workers, whose lists are ranked side by side
+  // (3.2 M values on a grid of 0.001, 660 of them at the threshold: one worker 137 us by the list, 88 by the multi-pass kernels;
+  // 64 workers 1110 and 1900).
+  const bool crowded = result[4] > max(256u, static_cast<uint32_t>(min<uint64_t>(WLIST, (static_cast<uint64_t>(us.cand) * R) >> 10)));
+  if (threadIdx.x == 0 && lu.j == 0) {
+    usp->taubin = taubin; usp->above = above; usp->crowded = crowded;
+    if (crowded) c.host_flag[FLAG_WINDOW] = 1u;
+  }
   if (crowded) return;                                       // (uniform) the multi-pass kernels take the unit
   const uint32_t wave = threadIdx.x >> 6, lane = lane_id();
   const uint32_t power = norm_power(c.quantizer);

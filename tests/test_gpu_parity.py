@@ -778,21 +778,24 @@ def test_aggregate_by_cells_edges(P, case):
 
 # a dense k on a large vector (the way of the window): inputs on which the window holds, and ones -- ties, zeros, one
 # magnitude, scales in stretches -- on which the multi-pass kernels have to take over; against those kernels (NO_FAST_PATH),
-# which the tests above compare with the oracle, and against the oracle itself
+# which the tests above compare with the oracle, and against the oracle itself.  What the kernels report shows which way a call
+# went: 1 with candidates, the window held; 2, it was tried and failed; 1 without, it was left out (the two calls after a failure)
 @pytest.mark.parametrize("kind,expect_held", [("normal", True), ("heavy", True), ("stretches", None), ("sorted", None), ("zeros", False),
                                               ("ties", False), ("constant", False)])
 def test_window_of_a_dense_k(P, kind, expect_held):
     from paper_1906_02367_amd import binding as B
     rng = np.random.default_rng(len(kind))
-    shapes = [(3_145_729, 50_001, W.TOPK, W.QSGD, 15), (3_145_728, 2_900_000, W.TOPK, W.SIGN_L1, 1), (3_200_003, 400_000, W.RANDK, W.FP32, 1),
-              (3_145_731, 314_573, W.TOPK, W.QSGD_SCALED, 3), (3_145_733, 1_000_000, W.TOPK, W.SIGN_L4, 1)]
-    for n, (d, k, sp, qz, s) in enumerate(shapes):
-        R = 2 if n < 2 else 1
+    # (the second to last: QSGD with two workers, below the size from which the window pays there -- it is left out)
+    shapes = [(3_145_729, 50_001, W.TOPK, W.QSGD, 15, 3), (3_145_728, 2_900_000, W.TOPK, W.SIGN_L1, 1, 2), (3_200_003, 400_000, W.RANDK, W.FP32, 1, 1),
+              (4_194_307, 314_573, W.TOPK, W.QSGD_SCALED, 3, 1), (4_194_303, 314_573, W.TOPK, W.QSGD, 3, 2), (3_145_733, 1_000_000, W.TOPK, W.SIGN_L4, 1, 1)]
+    for d, k, sp, qz, s, R in shapes:
+        left_out = qz == W.QSGD and R == 2
         wl = custom(d, [0, d], [k], s, sp, qz, R=R)
         qa, qb = B.from_workload(wl), B.from_workload(wl, flags=B.FLAG_NO_FAST_PATH)
         ma = torch.zeros(R, d, device=qa.device)
         mb = torch.zeros(R, d, device=qa.device)
-        for t in range(2):
+        for t in range(4):
+            ma.zero_(); mb.zero_()
             v = rng.standard_normal((R, d), dtype=f32)
             if kind == "heavy":
                 v *= np.exp(2 * rng.standard_normal(d)).astype(f32)
@@ -811,7 +814,7 @@ def test_window_of_a_dense_k(P, kind, expect_held):
             for q, m in ((qa, ma), (qb, mb)):
                 msg, bits = q.new_msg(R).fill_(0xCD), torch.zeros(R, dtype=torch.int64, device=q.device)
                 idx, lev = torch.zeros(R, k, dtype=torch.int32, device=q.device), torch.zeros(R, k, dtype=torch.int16, device=q.device)
-                if t == 0:
+                if t < 2:
                     q.compress(m, delta, m, 3, t, msg, bits, idx, lev)
                 else:                                             # Delta formed on the fly: x = 0, xhat = -Delta
                     q.compress_diff(m, torch.zeros(d, device=q.device), -delta, m, 3, t, msg, bits, idx, lev)
@@ -824,10 +827,16 @@ def test_window_of_a_dense_k(P, kind, expect_held):
                 op = P.oracle_for(wl)
                 o = op.compress(np.zeros(d, f32), v[0], 3, 0)
                 assert np.array_equal(outs[0][1][0].cpu().numpy(), o["msg"]) and np.array_equal(P.bits(ma[0].cpu().numpy()), P.bits(o["m_out"]))
-                if expect_held is not None and sp == W.TOPK:      # candidates of the window: none are reported without one
-                    units = qa.debug_units()
-                    assert np.all(units[:, 0] == 1)
-                    assert not expect_held or np.all((units[:, 1] > 0) & (units[:, 1] < d // 8)), units
+            units = qa.debug_units()
+            if left_out:
+                assert np.all((units[:, 0] == 1) & (units[:, 1] == 0)), (kind, d, k, t, units)
+            elif expect_held or sp == W.RANDK:                    # (the keys of Rand_k do not depend on the values)
+                assert np.all((units[:, 0] == 1) & (units[:, 1] > 0) & (units[:, 1] < d // 8)), (kind, d, k, t, units)
+            elif expect_held is False:
+                assert np.all(units[:, 0] == (2 if t in (0, 3) else 1)), (kind, d, k, t, units)
+                # closed by the sample, or left out: nothing was listed; ties: listed, and too many in the threshold's bin
+                assert np.all((units[:, 1] > 0) == (kind == "ties" and t in (0, 3))), (kind, d, k, t, units)
+            assert np.all(qb.debug_units()[:, 0] == 1)
 
 
 # index-free messages where the second pass and the master line change their way: norms outside the range of the short

@@ -291,6 +291,20 @@ POLICY_MAIN = r"""
 int main(int, char** a) {
   const std::string kind = a[1];
   const int n = atoi(a[2]), delay = atoi(a[3]);
+  if (kind.find("window") == 0) {                  // prints calls that tried the window, and those of the last 100
+    WindowPolicy w;
+    std::deque<int> late(delay, 0);
+    int tried = 0, last = 0;
+    for (int i = 0; i < n; ++i) {
+      const int report = late.front();
+      late.pop_front();
+      const bool t = w.next(report != 0);
+      tried += t; last += t && i >= n - 100;
+      late.push_back(t && (kind == "window_never" || (kind == "window_once" && i == 20) || (kind == "window_recovers" && i < 300)));
+    }
+    printf("%d %d\n", tried, last);
+    return 0;
+  }
   GuessPolicy p;
   std::deque<int> seen(delay, 0);
   int crawls = 0, safes = 0, colds = 0;
@@ -334,3 +348,12 @@ def test_failed_guesses_are_not_walked_again_and_again(policy):
     # ... and four calls later
     assert policy("once", 100, 4)[0] == 1
     assert policy("hopeless", 400, 4)[0] <= 4 * (1 + 400 // 20)
+
+
+def test_a_failing_window_is_left_out(policy):
+    for delay in (1, 3):
+        assert policy("window_once", 200, delay) == [200 - 2, 100]               # one failure costs two calls without
+        tried, last = policy("window_never", 1000, delay)                        # 2, 8, 32, 128, 128, ... calls without between two tries
+        assert tried <= delay * (4 + 1000 // 128) and last <= delay
+        tried, last = policy("window_recovers", 1000, delay)                     # tried again within 128 calls, and then always
+        assert last == 100 and tried >= 1000 - 300 - 128
