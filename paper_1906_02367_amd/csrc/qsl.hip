@@ -367,7 +367,8 @@ static void free_ctx(qsl_ctx* ctx) {
   delete ctx;
 }
 
-extern "C" qsl_status qsl_create(qsl_ctx** out, const qsl_config* cfg, void* hip_stream) {
+// `windows`: a dense k may be planned by way of the window.  *no_room: the window's scratch is what there was no memory for.
+static qsl_status create_ctx(qsl_ctx** out, const qsl_config* cfg, void* hip_stream, bool windows, bool* no_room) {
   uint64_t K64 = 0;
   if (!out) return QSL_ERR_INVALID_ARG;
   const qsl_status cfg_status = check_config(cfg, &K64);
@@ -473,7 +474,7 @@ extern "C" qsl_status qsl_create(qsl_ctx** out, const qsl_config* cfg, void* hip
       // at most 256 compaction blocks per unit, each a contiguous range of groups: every block ends with up to 20
       // atomics on the unit's digit counters, and thousands of blocks on the same few lines serialise there
       sg.ncb = std::min<uint32_t>(256, (sg.nwt + GGROUP - 1) / GGROUP);
-      if (plan_window(cfg, sg)) { window = true; slot_elems = static_cast<uint64_t>(sg.nwt) * sg.lpc * 2; ovf_entries = sg.ovf_cap; }
+      if (windows && plan_window(cfg, sg)) { window = true; slot_elems = static_cast<uint64_t>(sg.nwt) * sg.lpc * 2; ovf_entries = sg.ovf_cap; }
     }
   }
   // blocks of a fast unit in the selection kernels: ~3 slot rows per wave, and no more than one block
@@ -665,7 +666,12 @@ extern "C" qsl_status qsl_create(qsl_ctx** out, const qsl_config* cfg, void* hip
   const uint64_t o_ownv = carve((cfg->flags & QSL_FLAG_OWN_V) ? 4ull * R * d : 4);
   const uint64_t dense_nb = dense ? std::min<uint64_t>((d + DTILE - 1) / DTILE, MAX_DENSE_BLOCKS) : 0;
   const uint64_t o_dpart = carve(8ull * R * ACC_SLOTS * dense_nb + 8), o_dtag = carve(4ull * R * dense_nb + 4);
-  if (hipMalloc(&ctx->slab, bytes) != hipSuccess) { ctx->slab = nullptr; free_ctx(ctx); return QSL_ERR_DEVICE; }
+  if (hipMalloc(&ctx->slab, bytes) != hipSuccess) {
+    (void)hipGetLastError();                        // (the next call is not to find this error)
+    ctx->slab = nullptr; free_ctx(ctx);
+    *no_room = window;
+    return QSL_ERR_DEVICE;
+  }
   char* base = static_cast<char*>(ctx->slab);
   bool ok = hipMemset(base, 0, zero_bytes) == hipSuccess;
   auto upload = [&](uint64_t o, const void* src, size_t n) {
@@ -777,6 +783,12 @@ extern "C" qsl_status qsl_create(qsl_ctx** out, const qsl_config* cfg, void* hip
   if (hipStreamSynchronize(ctx->stream) != hipSuccess) { free_ctx(ctx); return QSL_ERR_DEVICE; }
   *out = ctx;
   return QSL_OK;
+}
+
+extern "C" qsl_status qsl_create(qsl_ctx** out, const qsl_config* cfg, void* hip_stream) {
+  bool no_room = false;
+  const qsl_status st = create_ctx(out, cfg, hip_stream, true, &no_room);
+  return no_room ? create_ctx(out, cfg, hip_stream, false, &no_room) : st;      // speed is what a window is for: without it, if it must be
 }
 
 extern "C" qsl_status qsl_destroy(qsl_ctx* ctx) {

@@ -134,3 +134,58 @@ def test_same_bytes_whatever_the_launch_shape(P, cfg, d):
         assert torch.equal(msg6, msg9) and torch.equal(msg6, msg1), f"round {t}: messages differ"
         assert torch.equal(m6.view(torch.int32), m9.view(torch.int32)), f"round {t}: memory differs (9-worker context)"
         assert torch.equal(m6.view(torch.int32), m1.view(torch.int32)), f"round {t}: memory differs (one worker per call)"
+
+
+def test_context_without_room_for_a_window(P):
+    """A dense k whose plain scratch fits the memory that is left, but not with the window's on top: the context is created and
+    selects by the multi-pass kernels."""
+    from paper_1906_02367_amd import binding as B
+    d, k = 120_000_000, 12_000_000
+    dev = torch.device("cuda")
+    m, delta = torch.zeros(1, d, device=dev), torch.randn(1, d, device=dev)
+    make = lambda flags=0: B.Qsl(d, [0, d], [k], 1, B.TOPK, B.SIGN_L1, 1, 1, flags=flags, device=dev)
+    def run(q):
+        msg = q.new_msg(1)
+        m.zero_()
+        q.compress(m, delta, m, 0, 0, msg)
+        torch.cuda.synchronize()
+        assert q.device_status() == B.OK
+        return msg, q.debug_units()[0]
+    torch.cuda.empty_cache()
+    free0 = torch.cuda.mem_get_info()[0]
+    q = make(B.FLAG_NO_FAST_PATH)
+    plain = free0 - torch.cuda.mem_get_info()[0]
+    want, unit = run(q)
+    assert unit[0] == 1 and unit[1] == 0
+    q.close()
+    q = make()
+    extra = free0 - torch.cuda.mem_get_info()[0] - plain
+    got, unit = run(q)
+    assert unit[0] == 1 and unit[1] > 0 and torch.equal(got, want) and extra > (128 << 20)
+    q.close()
+    del got
+    torch.cuda.empty_cache()
+    # everything that is left, in pieces, since more than what is reported may be had; then room for the context halfway between
+    piece = 16 << 20
+    hog = [torch.empty(max(piece, torch.cuda.mem_get_info()[0] - plain - extra), dtype=torch.uint8, device=dev)]
+    try:
+        while len(hog) < 400:
+            hog.append(torch.empty(piece, dtype=torch.uint8, device=dev))
+        pytest.skip("the memory has no end that a test could find")
+    except torch.OutOfMemoryError:
+        pass
+    try:
+        del hog[len(hog) - (plain + extra // 2 + want.numel()) // piece:]
+        torch.cuda.empty_cache()
+        msg = torch.empty_like(want)
+        q = make()
+        m.zero_()
+        q.compress(m, delta, m, 0, 0, msg)
+        torch.cuda.synchronize()
+        assert q.device_status() == B.OK
+        unit = q.debug_units()[0]
+        assert unit[0] == 1 and unit[1] == 0 and torch.equal(msg, want)
+        q.close()
+    finally:
+        hog.clear()
+        torch.cuda.empty_cache()
