@@ -302,7 +302,7 @@ static bool plan_window(const qsl_config* cfg, SegInfo& sg) {
   if (cfg->num_segments != 1 || sg.mode != PATH_GENERAL || sg.size < WINDOW_MIN || sg.k == sg.size ||
       (cfg->flags & (QSL_FLAG_NO_FAST_PATH | QSL_FLAG_NO_SMALL_PATH))) return false;
   const double n = static_cast<double>(sg.size), p = sg.k / n;
-  double need = 0;                                 // places that a chunk's slot should have: the expected coordinates and 4 sigma
+  double need = 0, share = 0;                      // places that a chunk's slot should have (the expected coordinates and 4 sigma); share of the vector inside
   if (cfg->sparsifier == QSL_TOPK) {
     for (double target = std::min(1048576.0, std::max(32768.0, n / 32)); target <= n / 2; target *= 2) {
       sg.n_runs = static_cast<uint32_t>(std::ceil(target / WRUN));
@@ -312,7 +312,8 @@ static bool plan_window(const qsl_config* cfg, SegInfo& sg) {
       sg.r_tau = static_cast<uint32_t>(std::max(0.0, std::floor(mu - margin)));
       sg.r_s = static_cast<uint32_t>(std::min(ns, std::ceil(mu + margin)));
       sg.nsamp = std::min(64u, std::max(1u, (sg.n_runs + 511) / 512));    // a block keeps 512 runs in flight
-      const double pc = (2 * margin / ns + 0.008) * CHUNK;                // + the bins at both ends, 1/64 of a binade each
+      share = 2 * margin / ns + 0.008;                                    // + the bins at both ends, 1/64 of a binade each
+      const double pc = share * CHUNK;
       need = pc + 4 * std::sqrt(pc);
       if (need <= 47) break;
     }
@@ -320,10 +321,15 @@ static bool plan_window(const qsl_config* cfg, SegInfo& sg) {
     const double q = 7.0 * std::sqrt(p * (1 - p) / n);
     const double lo = std::floor(4294967296.0 * std::max(0.0, 1 - p - q)), hi = std::min(4294967295.0, std::ceil(4294967296.0 * (1 - p + q)));
     sg.T_static = static_cast<uint32_t>(lo); sg.r_s = static_cast<uint32_t>(hi);       // (k_init takes T_static for guessing units only)
-    const double pc = (hi - lo) / 4294967296.0 * CHUNK;
+    share = (hi - lo) / 4294967296.0;
+    const double pc = share * CHUNK;
     need = pc + 4 * std::sqrt(pc);
   }
   if (need > 63) return false;
+  // A bin of the window (4096 in all) has to fit the short list.  The bins at both ends are cut in the middle on average, so half of
+  // what is allowed for them above counts here (normal values, k = d / 10, as the sample falls: 268 M coordinates 850 to 1,050 to
+  // a bin, 400 M 1,270, where every call would pay for a window that fails: 5.9 ms against 5.5).
+  if ((share - 0.004) * n / HBINS > WLIST) return false;
   sg.lpc = need <= 15 ? 8 : need <= 31 ? 16 : 32;
   sg.ovf_cap = static_cast<uint32_t>(std::min<uint64_t>(sg.size, std::max<uint64_t>(8192, sg.size / 8)));
   return true;

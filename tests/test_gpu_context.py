@@ -189,3 +189,25 @@ def test_context_without_room_for_a_window(P):
     finally:
         hog.clear()
         torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("d,k,held", [(200_000_000, 20_000_000, True), (400_000_000, 40_000_000, False)])
+def test_window_only_where_its_bins_fit_the_list(P, d, k, held):
+    """The largest vectors: a window that would hold too many coordinates per bin is not planned at all."""
+    from paper_1906_02367_amd import binding as B
+    dev = torch.device("cuda")
+    g = torch.Generator(device=dev); g.manual_seed(5)
+    m, delta, out = torch.zeros(1, d, device=dev), torch.randn(1, d, generator=g, device=dev), []
+    for flags in (0, B.FLAG_NO_FAST_PATH):
+        q = B.Qsl(d, [0, d], [k], 1, B.TOPK, B.SIGN_L1, 1, 1, flags=flags, device=dev)
+        msg, m_out = q.new_msg(1), torch.empty_like(m)
+        q.compress(m, delta, m_out, 0, 0, msg)
+        torch.cuda.synchronize()
+        assert q.device_status() == B.OK
+        unit = q.debug_units()[0]
+        assert unit[0] == 1 and (unit[1] > 0) == (held and flags == 0), unit
+        out.append((msg, m_out.view(torch.int32)))
+        q.close()
+    assert all(torch.equal(a, b) for a, b in zip(*out))
+    del m, delta, out, msg, m_out
+    torch.cuda.empty_cache()
