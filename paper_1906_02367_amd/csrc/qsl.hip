@@ -76,6 +76,8 @@ uint32_t bit_width_u64(uint64_t x) { uint32_t w = 0; while (x) { ++w; x >>= 1; }
 // ====================================================================================================
 constexpr uint32_t AGG_WAVE_ENTRIES = 1024;      // entries of all listed messages from which a cell is given to several waves
 
+constexpr uint32_t AGG_PILE_BLOCKS = 512;        // blocks of k_aggregate_cells for the cells in which entries pile up
+
 constexpr uint32_t PACK_BLOCKS = 4096;           // blocks of k_pack at most, for all workers
 
 struct qsl_ctx {
@@ -96,6 +98,8 @@ struct qsl_ctx {
   uint32_t* agg_dir;          // [64][agg_ndir] directories of the listed messages (only if messages are expected to be long)
   uint32_t agg_ndir;
   AggCrowd agg[AGG_LEVELS];   // the aggregation's crowded cells (several segments)
+  AggPile pile;               // room for the list of the cells in which a call's entries pile up
+  PilePolicy piles;           // ... and whether a call makes one
   uint32_t n_sampled;         // segments whose guess comes from k_sample
   uint32_t nbig_general;                // how many entries of DevCtx::big_segs are units of the multi-pass kernels (they come first)
   uint32_t nsel_general, ncb_general;   // blocks of the multi-pass kernels without / with (DevCtx::NSEL, NCB) the guessing units' share
@@ -581,6 +585,8 @@ static qsl_status create_ctx(qsl_ctx** out, const qsl_config* cfg, void* hip_str
   const uint64_t o_hist = carve(4ull * 3 * HBINS * U), o_ctr = carve(4ull * CTR_LINES * PAD * U);
   const uint64_t o_acc = carve(8ull * ACC_SLOTS * U), o_status = carve(8);
   const uint64_t o_blk = carve(4ull * QB * R * 2);    // the two arrays of per-block counters of transmitted entries
+  ctx->agg_ndir = static_cast<uint32_t>(((d + (1u << AGG_DIR_SHIFT) - 1) >> AGG_DIR_SHIFT) + 1);
+  const uint64_t o_pile = carve(4ull * (2 + (ctx->agg_ndir + 31) / 32));
   const uint64_t o_wsam = carve(window ? 4ull * WCOPIES * WBINS * R : 4), o_whist = carve(window ? 4ull * HBINS * R : 4);
   const uint64_t zero_bytes = bytes;
   const uint64_t o_segs = carve(sizeof(SegInfo) * L), o_wts = carve(sizeof(WtInfo) * std::max<size_t>(1, wts.size()));
@@ -635,7 +641,7 @@ static qsl_status create_ctx(qsl_ctx** out, const qsl_config* cfg, void* hip_str
   const uint64_t KV = is_qsgd(cfg->quantizer) ? 1 : KA;     // the final arrays of the quantisers that send every selected coordinate
   const uint64_t o_vi = carve(4ull * KV * R), o_vc = carve(4ull * KV * R);
   const uint64_t o_tmp = carve(4ull * 1024);
-  ctx->agg_ndir = static_cast<uint32_t>(((d + (1u << AGG_DIR_SHIFT) - 1) >> AGG_DIR_SHIFT) + 1);
+  const uint64_t o_plist = carve(4ull * ctx->agg_ndir);
   const bool want_dir = true;                       // (6.4 MB for 25.6 M coordinates)
   const uint64_t o_dir = carve(4ull * 64 * ctx->agg_ndir);       // 64 directories
   // the cells of 1024 coordinates in which a message is expected to have many entries (segments kept whole, or nearly), in parts
@@ -759,7 +765,7 @@ static qsl_status create_ctx(qsl_ctx** out, const qsl_config* cfg, void* hip_str
     const std::vector<WinState> all(R, ws);
     if (hipMemcpy(wc.state, all.data(), sizeof(WinState) * R, hipMemcpyHostToDevice) != hipSuccess) { free_ctx(ctx); return QSL_ERR_DEVICE; }
   }
-  for (uint32_t i = 0; i < N_FLAGS; ++i) ctx->h_status[8 + i] = 0;
+  for (uint32_t i = 0; i <= FLAG_PILE; ++i) ctx->h_status[8 + i] = 0;
   {
     void* dflag = nullptr;                          // the device's address of words of the pinned host block
     if (hipHostGetDevicePointer(&dflag, ctx->h_status + 8, 0) != hipSuccess || !dflag) { free_ctx(ctx); return QSL_ERR_DEVICE; }
@@ -778,6 +784,7 @@ static qsl_status create_ctx(qsl_ctx** out, const qsl_config* cfg, void* hip_str
   c.dense_part = reinterpret_cast<uint64_t*>(base + o_dpart); c.dense_tag = reinterpret_cast<uint32_t*>(base + o_dtag);
   ctx->d_nnz_tmp = reinterpret_cast<uint32_t*>(base + o_tmp);
   ctx->agg_dir = want_dir ? reinterpret_cast<uint32_t*>(base + o_dir) : nullptr;
+  { uint32_t* p = reinterpret_cast<uint32_t*>(base + o_pile); ctx->pile = AggPile{p, p + 2, reinterpret_cast<uint32_t*>(base + o_plist), nullptr, c.host_flag + FLAG_PILE}; }
   ctx->own_v = (cfg->flags & QSL_FLAG_OWN_V) ? reinterpret_cast<float*>(base + o_ownv) : nullptr;
   c.d = d; c.seed = cfg->seed; c.L = L; c.K = K; c.NWT = NWT; c.NSEL = NSEL; c.NCB = NCB; c.NWC = NWC; c.QB = QB;
   c.NSELF = NSELF; c.nfast = static_cast<uint32_t>(fast.size()); c.s = s; c.w_idx = w_idx; c.w_lev = w_lev; c.w_val = w_val;
@@ -1061,16 +1068,16 @@ static bool aggregate_by_cells(uint32_t nnz_hint, uint32_t ndir, uint32_t R, boo
 }
 
 static void launch_directory(const DevCtx& c, hipStream_t st, const uint8_t* msg, const RowList& rows, uint32_t R, uint32_t* dir,
-                             uint32_t ndir) {
+                             uint32_t ndir, const AggPile& pile) {
   const uint32_t blocks = (c.K + BLOCK - 1) / BLOCK;
-  if (blocks <= 2048) k_msg_directory<1><<<dim3(blocks, R), BLOCK, 0, st>>>(c, msg, rows, dir, ndir);
-  else k_msg_directory<4><<<dim3(2048, R), BLOCK, 0, st>>>(c, msg, rows, dir, ndir);
+  if (blocks <= 2048) k_msg_directory<1><<<dim3(blocks, R), BLOCK, 0, st>>>(c, msg, rows, dir, ndir, pile);
+  else k_msg_directory<4><<<dim3(2048, R), BLOCK, 0, st>>>(c, msg, rows, dir, ndir, pile);
 }
 
 // The launches of the master line.  `dir` is room for R directories of `ndir` words, or null (then every message is
 // searched whole); `nnz_hint` sizes the grids; `crowd`: the levels' crowded cells of a context with several segments, or null.
 static qsl_status launch_aggregate(const DevCtx& c, hipStream_t st, uint32_t nnz_hint, uint32_t* dir, uint32_t ndir,
-                                   const AggCrowd* crowd, const uint8_t* msg, const RowList& rows, uint32_t R, float scale, int accumulate,
+                                   const AggCrowd* crowd, const AggPile* room, const uint8_t* msg, const RowList& rows, uint32_t R, float scale, int accumulate,
                                    float* out) {
   if (c.K == c.d && (c.dense || !is_qsgd(c.quantizer))) {   // k = d and nothing dropped: every message lists every coordinate
     const uint64_t chunks = (c.d + CHUNK - 1) / CHUNK;
@@ -1087,11 +1094,15 @@ static qsl_status launch_aggregate(const DevCtx& c, hipStream_t st, uint32_t nnz
     return QSL_OK;
   }
   if (dir && aggregate_by_cells(nnz_hint, ndir, R, accumulate != 0)) {                            // long messages, or many: a block per few cells of 1024 coordinates
-    launch_directory(c, st, msg, rows, R, dir, ndir);
     uint32_t level = 0;
     while (level + 1 < AGG_LEVELS && static_cast<uint64_t>(AGG_LEVEL[level]) * R > AGG_WAVE_ENTRIES) ++level;
     AggCrowd cr = {nullptr, nullptr, 0};
     if (crowd && crowd[level].n) cr = crowd[level];
+    // Cells in which entries pile up are listed (if the caller has room for that) while a message has fewer than 32 in a cell on
+    // average: above that no cell has more than 32 times its share, and all of them are long.
+    AggPile pile = {nullptr, nullptr, nullptr, nullptr, nullptr};
+    if (room && nnz_hint / (ndir - 1) < 32) { pile = *room; pile.planned = cr.bits; }
+    launch_directory(c, st, msg, rows, R, dir, ndir, pile);
     int in_order = 1;
     for (uint32_t q = 0; q < R; ++q) in_order &= rows.row[q] == q;
     const double per_cell = static_cast<double>(nnz_hint) * R / (ndir - 1);
@@ -1100,8 +1111,10 @@ static qsl_status launch_aggregate(const DevCtx& c, hipStream_t st, uint32_t nnz
     uint32_t split = 0;
     while (split < 5 && (static_cast<uint64_t>(ndir - 1) << split) < 2048 && per_cell > (256u << split)) ++split;
     const uint32_t waves = cr.n + ((ndir - 1) << split);
-    k_aggregate_cells<<<dim3((waves + BLOCK / 64 - 1) / (BLOCK / 64)), BLOCK, 0, st>>>(c, msg, rows, in_order, R, scale, accumulate,
-                                                                                     out, dir, ndir, cr, split);
+    k_aggregate_cells<false><<<dim3((waves + BLOCK / 64 - 1) / (BLOCK / 64)), BLOCK, 0, st>>>(c, msg, rows, in_order, R, scale, accumulate,
+                                                                                            out, dir, ndir, cr, split, pile);
+    if (pile.list)
+      k_aggregate_cells<true><<<dim3(AGG_PILE_BLOCKS), BLOCK, 0, st>>>(c, msg, rows, in_order, R, scale, accumulate, out, dir, ndir, cr, split, pile);
     QSL_HIP(hipGetLastError());
     return QSL_OK;
   }
@@ -1111,7 +1124,7 @@ static qsl_status launch_aggregate(const DevCtx& c, hipStream_t st, uint32_t nnz
   }
   if (R == 1 || nnz_hint < AGG_DIR_MIN) dir = nullptr;   // short messages are searched whole
   if (dir) {                                        // long messages: a thread per entry, searches narrowed by the directories
-    launch_directory(c, st, msg, rows, R, dir, ndir);
+    launch_directory(c, st, msg, rows, R, dir, ndir, AggPile{nullptr, nullptr, nullptr, nullptr, nullptr});
     const uint32_t eb = std::min((c.K + BLOCK - 1) / BLOCK, std::max(4u, (nnz_hint + BLOCK - 1) / BLOCK));
     k_aggregate_entries<<<dim3(eb, R), BLOCK, 0, st>>>(c, msg, rows, R, scale, accumulate, out, dir, ndir);
   } else {                                          // short messages: 8 threads per entry, a block per expected tile of 32
@@ -1131,8 +1144,12 @@ extern "C" qsl_status qsl_aggregate(qsl_ctx* ctx, const uint8_t* msg, const uint
   const qsl_status st = make_row_list(worker_list, R, &rows);
   if (st != QSL_OK) return st;
   // the directories were allocated at qsl_create for operators whose messages are long
-  return launch_aggregate(ctx->dc, ctx->stream, ctx->nnz_hint, ctx->agg_dir, ctx->agg_ndir, ctx->dc.L > 1 ? ctx->agg : nullptr, msg, rows, R,
-                          scale, accumulate, out);
+  AggPile pile = ctx->pile;
+  const bool met = ctx->h_status[8 + FLAG_PILE] != 0;            // left by kernels of earlier calls
+  if (met) ctx->h_status[8 + FLAG_PILE] = 0;
+  if (!ctx->piles.next(met)) pile.list = nullptr;
+  return launch_aggregate(ctx->dc, ctx->stream, ctx->nnz_hint, ctx->agg_dir, ctx->agg_ndir, ctx->dc.L > 1 ? ctx->agg : nullptr, &pile, msg, rows,
+                          R, scale, accumulate, out);
 }
 
 // ----------------------------------------------------------------------------------------------------
@@ -1142,12 +1159,14 @@ static __device__ __align__(256) unsigned char scratch[QSL_STATIC_SCRATCH_BYTES]
 
 namespace {
 constexpr int MAX_STATIC_DEVICES = 64;
-constexpr uint64_t STATIC_DIR_OFFSET = 256;       // bytes [0, 256): the status word; then the directories
+constexpr uint64_t STATIC_DIR_OFFSET = 256;       // bytes [0, 256): the status word, AggPile's two counters; then the directories
 void* g_scratch_ptr[MAX_STATIC_DEVICES];          // where `scratch` lies on each GPU (every GPU holds its own copy)
 std::mutex g_scratch_mutex;
 
-__global__ void k_clear_word(uint32_t* p) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) *p = 0;
+// the status word, the counters and the bits of AggPile
+__global__ __launch_bounds__(BLOCK) void k_clear_static(uint32_t* head, uint32_t* bits, uint32_t n_bits) {
+  if (threadIdx.x < 4) head[threadIdx.x] = 0;
+  for (uint32_t i = threadIdx.x; i < n_bits; i += BLOCK) bits[i] = 0;
 }
 
 // the device address of `scratch` on the current GPU; in host code the array's name is not that address
@@ -1204,9 +1223,14 @@ extern "C" qsl_status qsl_aggregate_static(const qsl_config* cfg, void* hip_stre
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   // the array keeps what the last call left: the status word starts at zero (a kernel, not a memset node, so that
   // the call can be captured into a graph); the directories are written in full before they are read
-  k_clear_word<<<dim3(1), 64, 0, stream>>>(c.status);
   uint32_t* dir = want_dir ? reinterpret_cast<uint32_t*>(base + STATIC_DIR_OFFSET) : nullptr;
-  return launch_aggregate(c, stream, wd.nnz_hint, dir, ndir, nullptr, msg, rows, R, scale, accumulate, out);
+  // the list of piled-up cells behind the directories, if it finds room there
+  const uint32_t n_bits = (ndir + 31) / 32;
+  const bool room = want_dir && STATIC_DIR_OFFSET + 4ull * (static_cast<uint64_t>(R) * ndir + n_bits + ndir) <= QSL_STATIC_SCRATCH_BYTES;
+  uint32_t* behind = dir + static_cast<uint64_t>(R) * ndir;
+  const AggPile pile = {c.status + 2, behind, behind + n_bits, nullptr, nullptr};
+  k_clear_static<<<dim3(1), BLOCK, 0, stream>>>(c.status, room ? behind : nullptr, room ? n_bits : 0u);
+  return launch_aggregate(c, stream, wd.nnz_hint, dir, ndir, nullptr, room ? &pile : nullptr, msg, rows, R, scale, accumulate, out);
 }
 
 extern "C" qsl_status qsl_bits_sent(qsl_ctx* ctx, const uint8_t* msg, uint32_t R, uint64_t* bits_host) {

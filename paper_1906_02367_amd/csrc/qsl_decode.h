@@ -109,15 +109,25 @@ constexpr uint32_t AGG_DIR_SHIFT = 10;   // a directory entry per 1024 coordinat
 constexpr uint32_t AGG_DIR_MIN = 4096;   // messages expected to be at least this long are searched through their directories
 constexpr uint32_t AGG_CELLS_MIN_R = 36; // short messages go to k_aggregate_cells from this many on
 
+// Cells in which the listed messages' entries pile up, found while the directories are made (k_aggregate_cells gives them to many
+// waves).  count[0], count[1] and bits are zero between calls.  list == nullptr: they are not listed.
+struct AggPile {
+  uint32_t* count; uint32_t* bits; uint32_t* list;
+  const uint32_t* planned;   // a bit per cell that the plan already gives to several waves (or null)
+  uint32_t* flag;            // pinned host memory: set when a cell is piled up (or null)
+};
+
 // Directory of a long message: dir[t] = number of entries whose coordinate lies below t * 1024, for
 // t = 0 .. ndir - 1 (ndir = ceil(d / 1024) + 1, so dir[ndir - 1] = nnz).  Entry j fills the slots between
 // its predecessor's 1024-block and its own; the last entry also fills the rest.  A lookup then needs
 // dir[t], dir[t + 1] and a binary search over the few entries of one 1024-block instead of log2(nnz)
 // dependent probes of the whole message.
 // UN: entries per thread and step, their reads in flight together (1 while the grid covers the messages).
+// `pile`: the cells in which a message has 64 entries side by side in one wave's hands are listed, once each (the first such wave
+// of a message looks whether the cell's bit is set already).
 template <uint32_t UN>
 __global__ __launch_bounds__(BLOCK) void k_msg_directory(DevCtx c, const uint8_t* msg, RowList rows, uint32_t* dir,
-                                                         uint32_t ndir) {
+                                                         uint32_t ndir, AggPile pile) {
   const uint32_t q = blockIdx.y, lane = lane_id();
   const MsgView v = view_msg(c, msg, rows.row[q]);
   uint32_t* mine = dir + static_cast<uint64_t>(q) * ndir;
@@ -125,17 +135,19 @@ __global__ __launch_bounds__(BLOCK) void k_msg_directory(DevCtx c, const uint8_t
   if (v.nnz == 0) { for (uint32_t t = tid; t < ndir; t += nth) mine[t] = 0; return; }
   for (uint64_t j0 = tid; j0 - lane < v.nnz; j0 += static_cast<uint64_t>(nth) * UN) {      // (uniform over the wave)
     uint32_t cell[UN], prev[UN];
+    bool bad = false;
 #pragma unroll
     for (uint32_t u = 0; u < UN; ++u) {
       const uint64_t j = j0 + static_cast<uint64_t>(u) * nth;
       cell[u] = 0; prev[u] = 0;
       if (j < v.nnz) {
         const uint32_t idx = msg_index(c, v, static_cast<uint32_t>(j));
-        if (idx >= c.d) atomicOr(c.status, 4u);            // malformed message: here every index is seen, whoever decodes the entry
+        bad = bad || idx >= c.d;                           // malformed message: here every index is seen, whoever decodes the entry
         cell[u] = min(idx >> AGG_DIR_SHIFT, ndir - 2);
         if (lane == 0 && j) prev[u] = min(msg_index(c, v, static_cast<uint32_t>(j) - 1) >> AGG_DIR_SHIFT, ndir - 2);
       }
     }
+    if (bad) atomicOr(c.status, 4u);
 #pragma unroll
     for (uint32_t u = 0; u < UN; ++u) {
       const uint64_t j = j0 + static_cast<uint64_t>(u) * nth;
@@ -144,6 +156,19 @@ __global__ __launch_bounds__(BLOCK) void k_msg_directory(DevCtx c, const uint8_t
         const uint32_t first = j == 0 ? 0u : (lane ? below : prev[u]) + 1;
         for (uint32_t t = first; t <= cell[u]; ++t) mine[t] = static_cast<uint32_t>(j);   // empty when the predecessor shares the block
         if (j == v.nnz - 1) for (uint32_t t = cell[u] + 1; t < ndir; ++t) mine[t] = v.nnz;
+      }
+      if (pile.list != nullptr) {
+        const uint32_t t0 = __builtin_amdgcn_readfirstlane(cell[u]);
+        if (j - lane + 63 < v.nnz && t0 == static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(cell[u]), 63)) && lane == 0 &&
+            (j < 64 || (msg_index(c, v, static_cast<uint32_t>(j) - 64) >> AGG_DIR_SHIFT) != t0)) {
+          uint32_t* word = pile.bits + (t0 >> 5);
+          const uint32_t bit = 1u << (t0 & 31u);
+          const bool planned = pile.planned != nullptr && (pile.planned[t0 >> 5] & bit);
+          if (!planned && !(__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit) && !(atomicOr(word, bit) & bit)) {
+            const uint32_t at = atomicAdd(&pile.count[0], 1u);
+            if (at < ndir) pile.list[at] = t0;               // (a cell once: there is room)
+          }
+        }
       }
     }
   }
@@ -366,16 +391,42 @@ __device__ __forceinline__ uint32_t field_of(const FieldRead& f, uint32_t width)
 }
 
 // `split`: the cells that are not crowded are given to 2^split waves each (few cells with many entries: a short vector).
-__global__ __launch_bounds__(BLOCK, 8) void k_aggregate_cells(DevCtx c, const uint8_t* msg, RowList rows, int in_order, uint32_t R,
-                                                              float scale, int accumulate, float* out, const uint32_t* dir,
-                                                              uint32_t ndir, AggCrowd crowd, uint32_t split) {
+// `pile`: cells that no plan could foresee, in a vector whose large coordinates stand side by side (AGG_PILE entries or more, a
+// whole 64 of them from one message).  With a list of them the launch with PILE set gives each to 16 or 32 waves, and
+// their own waves leave them alone; without one they are worked through as they are and the host hears of it.
+// 10^6 coordinates, 10,000 entries among the first 12,000, 8 / 16 / 32 / 64 messages: 102 / 184 / 203 / 227 us without a list, 49 / 52 / 61 / 84
+// with one.
+constexpr uint32_t AGG_PILE = 2048;
+// (uniform) whether the cell whose entries of message `lane` are [lo, hi) is such a one
+__device__ __forceinline__ bool piled_up(uint32_t lo, uint32_t hi, uint32_t split) {
+  const bool whole = hi > lo && ((lo + 63u) & ~63u) + 64 <= hi;
+  return __ballot(whole) != 0 && wave_sum(hi > lo ? min(hi - lo, AGG_CELL) : 0u) >= AGG_PILE << split;
+}
+
+// PILE: the listed cells, AGG_PILE_BLOCKS blocks.  Else a wave per item of the grid, which it returns from as soon as it can.
+template <bool PILE>
+__global__ __launch_bounds__(BLOCK, PILE ? 4 : 8) void k_aggregate_cells(DevCtx c, const uint8_t* msg, RowList rows, int in_order, uint32_t R,
+                                                                         float scale, int accumulate, float* out, const uint32_t* dir,
+                                                                         uint32_t ndir, AggCrowd crowd, uint32_t split, AggPile pile) {
   __shared__ f4u s_image[BLOCK / 64][AGG_CELL / 4];
   __shared__ float s_scale[BLOCK / 64][AGG_SCALES];
   __shared__ uint32_t s_segat[BLOCK / 64][AGG_SEGS];
+  __shared__ uint32_t s_last;
   const uint32_t lane = lane_id(), wave = threadIdx.x >> 6;
   float* image = reinterpret_cast<float*>(s_image[wave]);
-  const uint32_t b = blockIdx.x * (BLOCK / 64) + wave;
-  if (b >= crowd.n + ((ndir - 1) << split)) return;       // (no barrier follows)
+  uint32_t n_items, parts = 0;
+  if (PILE) {
+    const uint32_t n = min(pile.count[0], ndir);
+    if (n == 0) return;                                   // (uniform over the grid)
+    parts = n <= 64 ? 5u : 4u;                            // (few of them: 40 messages, 3 cells of 27,000 entries 48 us in 16 parts, 38 in 32; 300 cells 844 and 858)
+    n_items = n << parts;
+  } else n_items = crowd.n + ((ndir - 1) << split);       // (no barrier follows)
+  for (uint32_t b = blockIdx.x * (BLOCK / 64) + wave; b < n_items; b += gridDim.x * (BLOCK / 64)) {
+  if (PILE) {                                             // the LDS of the item before is used again
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
   // ---- the messages: lane p is listed message p
   const bool counts = is_qsgd(c.quantizer) && c.L > 1;
   const uint32_t hdr = 1 + c.L + (counts ? c.L : 0);
@@ -384,15 +435,23 @@ __global__ __launch_bounds__(BLOCK, 8) void k_aggregate_cells(DevCtx c, const ui
   const uint32_t* my_words = reinterpret_cast<const uint32_t*>(msg + static_cast<uint64_t>(my_row) * c.cap_words * 4);
   // ---- the coordinates: a cell, or a part of a crowded one
   uint32_t t0, from, width;
-  const bool crowded = b < crowd.n, is_part = crowded || split != 0;
-  if (crowded) { const AggPart a = crowd.part[b]; t0 = a.t; width = AGG_CELL >> a.parts; from = a.i * width; }
+  const bool crowded = !PILE && b < crowd.n, is_part = PILE || crowded || split != 0;
+  if (PILE) { t0 = pile.list[b >> parts]; width = AGG_CELL >> parts; from = (b & ((1u << parts) - 1u)) * width; }
+  else if (crowded) { const AggPart a = crowd.part[b]; t0 = a.t; width = AGG_CELL >> a.parts; from = a.i * width; }
   else { t0 = (b - crowd.n) >> split; width = AGG_CELL >> split; from = ((b - crowd.n) & ((1u << split) - 1u)) * width; }
   const uint32_t* my_dir = dir + static_cast<uint64_t>(lane < R ? lane : 0u) * ndir + t0;
   const uint32_t my_nnz = lane < R ? min(my_words[0], c.K) : 0u;
   uint32_t lo = lane < R ? min(my_dir[0], my_nnz) : 0u, hi = lane < R ? min(my_dir[1], my_nnz) : 0u;
   uint32_t seg0 = 0, ns = 1;
   if (c.L > 1 && !is_part) { seg0 = c.seg_dir[t0]; ns = c.seg_dir[t0 + 1] - seg0 + 1; }
-  if (!crowded && crowd.bits != nullptr && ((crowd.bits[t0 >> 5] >> (t0 & 31u)) & 1u)) return;      // waves of its own look after it
+  if (!crowded && crowd.bits != nullptr && ((crowd.bits[t0 >> 5] >> (t0 & 31u)) & 1u)) { if (PILE) continue; return; }      // waves of its own look after it
+  if (PILE) {
+    if (!piled_up(lo, hi, split)) continue;
+    if (lane == 0 && from == 0 && pile.flag != nullptr) *pile.flag = 1u;
+  } else if (split != 0 && !crowded && piled_up(lo, hi, split)) {
+    if (pile.list != nullptr) return;
+    if (lane == 0 && pile.flag != nullptr) *pile.flag = 1u;
+  }
   const float nobody = __uint_as_float(NOBODY);
   uint64_t c0 = static_cast<uint64_t>(t0) << AGG_DIR_SHIFT;
   uint32_t span = AGG_CELL;
@@ -424,14 +483,18 @@ __global__ __launch_bounds__(BLOCK, 8) void k_aggregate_cells(DevCtx c, const ui
     }
     lo = l0; hi = l1; c0 += from; span = width;
   }
-  if (c0 >= c.d) return;
+  if (c0 >= c.d) { if (PILE) continue; return; }
   const uint32_t cnt = hi > lo ? min(hi - lo, span) : 0u; // a well-formed message has at most one entry per coordinate
   if (hi > lo && hi - lo > span) atomicOr(c.status, 4u);  // malformed: what is beyond that is skipped
   span = static_cast<uint32_t>(min<uint64_t>(span, c.d - c0));
   const uint32_t base = static_cast<uint32_t>(c0);
   uint32_t n;
   const uint32_t before = wave_exclusive_scan32(cnt, &n);
-  if (n == 0 && accumulate) return;
+  if (n == 0 && accumulate) { if (PILE) continue; return; }
+  if (!is_part && n >= AGG_PILE && piled_up(lo, hi, 0)) {     // (a cell in parts has been looked at as a whole above)
+    if (pile.list != nullptr) return;
+    if (lane == 0 && pile.flag != nullptr) *pile.flag = 1u;
+  }
   if (c.L > 1 && is_part) { seg0 = seg_of_coord(c, base); ns = seg_of_coord(c, base + span - 1) - seg0 + 1; }
   // lane p, for the lanes that decode entries of message p: entry f of the item is the message's entry f + my_j
   const uint32_t my_j = lo - before;
@@ -544,6 +607,15 @@ __global__ __launch_bounds__(BLOCK, 8) void k_aggregate_cells(DevCtx c, const ui
       else for (uint32_t j = 0; j < 4; ++j) if (i + j < span) out[c0 + i + j] = o[u][j];
     }
   }
+  if (!PILE) return;
+  }
+  if (!PILE) return;                                      // (a wave beyond the last item)
+  __syncthreads();                                        // the last block to be done clears the list for the next call
+  if (threadIdx.x == 0) s_last = atomicAdd(&pile.count[1], 1u) + 1 == gridDim.x;
+  __syncthreads();
+  if (s_last == 0) return;
+  for (uint32_t i = threadIdx.x; i < n_items >> parts; i += BLOCK) pile.bits[pile.list[i] >> 5] = 0;
+  if (threadIdx.x == 0) { pile.count[0] = 0; pile.count[1] = 0; }
 }
 
 // The master line when every message holds every coordinate (an operator with k = d whose quantiser drops

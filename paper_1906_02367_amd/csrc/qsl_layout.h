@@ -31,8 +31,8 @@ constexpr uint32_t LISTCAP = 256;          // entries of that list; a threshold 
 // What the kernels report to the host (qsl_policy.h): a failed guess made good by many blocks, or by one block on a small unit; one
 // made good by one block that walked through a large one (more than CRAWL_MIN coordinates: 150 us and up); the same, on values
 // of which a sampled guess would have let too many through as well.
-// FLAG_WINDOW: a window that did not hold.
-enum : uint32_t { FLAG_MILD = 0, FLAG_CRAWL = 1, FLAG_HOPELESS = 2, FLAG_WINDOW = 3, N_FLAGS };
+// FLAG_WINDOW: a window that did not hold.  FLAG_PILE: entries piled up in a cell of the master line.
+enum : uint32_t { FLAG_MILD = 0, FLAG_CRAWL = 1, FLAG_HOPELESS = 2, FLAG_WINDOW = 3, N_FLAGS = 4, FLAG_PILE = N_FLAGS };      // (N_FLAGS: those that qsl_compress reads)
 constexpr uint32_t CRAWL_MIN = 1u << 17;
 
 enum : uint32_t { PATH_FAST = 0, PATH_GENERAL = 1, PATH_FALLBACK = 2, PATH_SMALL = 3, PATH_FULL = 4 };

@@ -58,4 +58,16 @@ struct WindowPolicy {
   }
 };
 
+// The master line: cells in which the messages' entries pile up (qsl_decode.h).  Once they are met, the next 64 calls list them and
+// give them to many waves in a launch of its own, as do the calls after those while there still are any.
+struct PilePolicy {
+  uint32_t left = 0;
+  bool next(bool met) {        // whether this call lists them
+    if (met) left = 64;
+    if (left == 0) return false;
+    --left;
+    return true;
+  }
+};
+
 }  // namespace

@@ -1002,3 +1002,53 @@ def test_failed_guesses_of_single_block_units(P):
         assert np.array_equal(outs[0][1][3].cpu().numpy(), o["msg"]) and np.array_equal(P.bits(ma[3].cpu().numpy()), P.bits(o["m_out"]))
         failed.append(int((qa.debug_units()[:, 0] == 2).sum()))
     assert failed[0] == 0 and failed[2] > 0 and max(failed[5:8]) > 0, failed
+
+
+# entries that pile up in a few cells which no plan foresees: worked through as they are by the first call, listed and given to many
+# waves by the calls after it (and by the call without a context), beside calls with entries all over the vector; cells at the
+# start, across a segment's end, in a last cell of few coordinates; cells that the plan calls crowded beside them
+@pytest.mark.parametrize("case", ["start", "last_cell", "few_messages", "segments", "short", "fp32", "split"])
+def test_aggregate_piled_up_cells(P, case):
+    from paper_1906_02367_amd import binding as B
+    rng = np.random.default_rng(len(case))
+    d, off, k, s, sp, qz, spot, lists = {
+        "start": (1_000_003, [0, 1_000_003], [10_000], 1, W.TOPK, W.SIGN_L1, (0, 11_000), [range(64), range(40), [63, 5, 9, 8, 7, 1, 0, 33, 21, 40]]),
+        "last_cell": (300_033, [0, 300_033], [4_500], 1, W.TOPK, W.SIGN_L2, (295_000, 300_033), [range(64), range(16)]),
+        "few_messages": (2_000_001, [0, 2_000_001], [60_000], 1_000, W.TOPK, W.QSGD, (700_000, 762_000), [range(3), [5, 4, 3, 2, 1, 0, 7, 6]]),
+        "segments": (600_000, [0, 900, 2_000, 250_500, 600_000], [900, 1_100, 4_000, 6_000], 1, W.TOPK, W.SIGN_L1, (248_000, 254_000), [range(64), range(24)]),
+        "short": (200_000, [0, 200_000], [2_000], 1, W.TOPK, W.SIGN_L1, (1_000, 4_000), [range(40), range(64)]),
+        "fp32": (1_000_003, [0, 1_000_003], [10_000], 1, W.TOPK, W.FP32, (500_000, 511_000), [range(33)]),
+        "split": (70_001, [0, 70_001], [2_000], 1, W.TOPK, W.SIGN_L1, (20_000, 22_100), [range(64)])}[case]
+    wl = custom(d, off, k, s, sp, qz, R=8)
+    q = B.from_workload(wl)
+    op = P.oracle_for(wl)
+    both = []
+    for piled in (True, False):
+        msg = q.new_msg(64)
+        for b in range(8):
+            v = rng.standard_normal((8, d)).astype(f32)
+            if piled:
+                v[:, spot[0]:spot[1]] *= f32(100)
+            m = torch.zeros(8, d, device=q.device)
+            q.compress(m, torch.from_numpy(v).to(q.device), m, 8 * b, b, msg[8 * b: 8 * b + 8])
+        torch.cuda.synchronize()
+        both.append((msg, [op.decode(x) for x in msg.cpu().numpy()]))
+    in_spot = np.bincount((both[0][1][0][0] >> 10).astype(np.int64)).max()
+    assert in_spot >= 128                                     # two whole waves of entries of one message in a cell
+    x0 = rng.standard_normal(d).astype(f32)
+    for call in range(6):                                     # piled up, again, all over, piled up ...
+        msg, decoded = both[1 if call in (2, 4) else 0]
+        for lst in lists:
+            lst = [int(x) for x in lst]
+            accumulate = call % 2 == 0
+            want = _aggregate_by_definition(decoded, lst, -1.0 / 64, x0, accumulate, d)
+            out = torch.from_numpy(x0).to(q.device)
+            q.aggregate(msg, out, -1.0 / 64, worker_list=lst, accumulate=accumulate)
+            torch.cuda.synchronize()
+            assert np.array_equal(out.cpu().numpy().view(np.uint32), want.view(np.uint32)), (case, call, len(lst))
+            if len(off) == 2 and call < 3:
+                out = torch.from_numpy(x0).to(q.device)
+                B.aggregate_static(d, k[0], s, sp, qz, msg, out, -1.0 / 64, worker_list=lst, accumulate=accumulate)
+                torch.cuda.synchronize()
+                assert np.array_equal(out.cpu().numpy().view(np.uint32), want.view(np.uint32)), (case, call, len(lst), "static")
+    assert q.device_status() == B.OK

@@ -305,6 +305,18 @@ int main(int, char** a) {
     printf("%d %d\n", tried, last);
     return 0;
   }
+  if (kind == "pile") {                            // entries pile up in the calls 10 .. 119: calls that list the cells, of those and of all
+    PilePolicy w;
+    int listed = 0, in_time = 0;
+    bool met = false;
+    for (int i = 0; i < n; ++i) {
+      const bool l = w.next(met), piled = i >= 10 && i < 120;
+      met = piled;
+      listed += l; in_time += l && piled;
+    }
+    printf("%d %d\n", in_time, listed);
+    return 0;
+  }
   GuessPolicy p;
   std::deque<int> seen(delay, 0);
   int crawls = 0, safes = 0, colds = 0;
@@ -357,3 +369,7 @@ def test_a_failing_window_is_left_out(policy):
         assert tried <= delay * (4 + 1000 // 128) and last <= delay
         tried, last = policy("window_recovers", 1000, delay)                     # tried again within 128 calls, and then always
         assert last == 100 and tried >= 1000 - 300 - 128
+
+
+def test_piled_up_cells_are_listed_while_there_are_any(policy):
+    assert policy("pile", 400, 1) == [109, 109 + 64]              # from the second call with them on, and 64 calls beyond the last
