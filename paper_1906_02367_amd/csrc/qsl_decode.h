@@ -370,7 +370,7 @@ constexpr uint32_t AGG_SCALES = 192;                     // scales (segments of 
 constexpr uint32_t AGG_SEGS = 32;                        // ... segments that a wave has room for in LDS
 constexpr uint32_t AGG_LEVELS = 3;
 constexpr uint32_t AGG_LEVEL[AGG_LEVELS] = {512, 128, 32};       // lists of crowded cells: more entries of one message than this
-constexpr uint32_t NOBODY = 0xFFFFFFFFu;                 // a NaN; a sum that has just these bits is kept as the NaN beside it
+constexpr uint32_t NOBODY = 0xFFFFFFFFu;                 // a NaN that no value and no sum is (a sum keeps the payload of its NaN)
 
 struct AggPart { uint32_t t; uint16_t i, parts; };       // part i of the 2^parts equal parts of cell t
 struct AggCrowd { const AggPart* part; const uint32_t* bits; uint32_t n; };   // the parts of a level's crowded cells; a bit per cell (null: none is crowded)
@@ -555,14 +555,15 @@ __global__ __launch_bounds__(BLOCK, PILE ? 4 : 8) void k_aggregate_cells(DevCtx 
         }
       }
       if (mine && !ok) atomicOr(c.status, 4u);            // malformed message: the entry is skipped
-      const float v = value_of_code(c, field_of(fc[u], c.w_val), sc);
+      float v = value_of_code(c, field_of(fc[u], c.w_val), sc);
+      if ((__float_as_uint(v) | 0x400000u) == NOBODY) v = __uint_as_float(NOBODY - 1u);      // that NaN, quiet or not: the one beside it
       uint64_t todo = __ballot(ok);
       while (todo) {                                      // the messages of this step, in order
         const uint32_t p = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(pp[u]), __ffsll(static_cast<unsigned long long>(todo)) - 1));
         const bool now = ok && pp[u] == p;
         if (now) {
-          const float have = image[loc], sum = __float_as_uint(have) == NOBODY ? v : have + v;
-          image[loc] = __float_as_uint(sum) == NOBODY ? __uint_as_float(NOBODY - 1u) : sum;
+          const float have = image[loc];
+          image[loc] = __float_as_uint(have) == NOBODY ? v : have + v;
         }
         todo &= ~__ballot(now);
         // the next message may hold the same coordinates in other lanes: order the LDS traffic (the lanes run in lockstep)
