@@ -1,5 +1,6 @@
 // qsl.hip -- host side and C ABI of the compression hot path of Qsparse-local-SGD for gfx950; the kernels
-// are in the headers included below (qsl_stream.h, qsl_lean.h, qsl_select.h, qsl_encode.h, qsl_dense.h, qsl_decode.h).
+// are in the headers included below (qsl_stream.h, qsl_lean.h, qsl_window.h, qsl_select.h, qsl_encode.h, qsl_dense.h,
+// qsl_decode.h), what the host makes of the failures that they report in qsl_policy.h.
 //
 // One synchronisation step of Algorithm 1 (arXiv:1906.02367) for a batch of R workers:
 //   k_stream     v = m + Delta (worker line 1), written over the error memory in ONE pass over HBM;
@@ -24,10 +25,13 @@
 //                exact radix selection (12 + 12 + 8 bits) over the whole vector, ordered compaction and
 //                encoding: dense k on a large unit, and the units whose guess failed while the host expects
 //                failures (always exact; only the speed depends on the guess)
+//   k_win_sample, k_win_scan, k_win_stream, k_win_hist, k_win_mark, k_win_mid, k_win_apply
+//                dense k on a single large segment, instead of those: a window of rank keys around the threshold,
+//                two passes over v; the kernels above stand by for a window that does not hold
 //   k_pack, k_pack_sent       the packed message (k_pack_sent: QSGD, whose entries of level 0 drop out)
-//   k_dense_norm, k_dense_sum, k_dense_scales, k_dense_encode    an operator that keeps every coordinate, with messages that
-//                carry no indices: two streaming passes
-//   k_aggregate, k_aggregate_entries, k_aggregate_cells, k_aggregate_dense
+//   k_dense_norm, k_dense_sum, k_dense_scales, k_dense_sum_scale, k_dense_encode    an operator that keeps every coordinate, with
+//                messages that carry no indices: two streaming passes
+//   k_msg_directory, k_aggregate, k_aggregate_entries, k_aggregate_cells, k_aggregate_dense, k_aggregate_dense_one
 //                master line of Algorithm 1, atomic-free, messages added in list order: by look-ups in the other
 //                messages (few entries), by coordinate ranges (many), or coordinate by coordinate (every
 //                message lists every coordinate)
@@ -1093,7 +1097,7 @@ static qsl_status launch_aggregate(const DevCtx& c, hipStream_t st, uint32_t nnz
     QSL_HIP(hipGetLastError());
     return QSL_OK;
   }
-  if (dir && aggregate_by_cells(nnz_hint, ndir, R, accumulate != 0)) {                            // long messages, or many: a block per few cells of 1024 coordinates
+  if (dir && aggregate_by_cells(nnz_hint, ndir, R, accumulate != 0)) {                            // long messages, or many: a wave per cell of 1024 coordinates
     uint32_t level = 0;
     while (level + 1 < AGG_LEVELS && static_cast<uint64_t>(AGG_LEVEL[level]) * R > AGG_WAVE_ENTRIES) ++level;
     AggCrowd cr = {nullptr, nullptr, 0};

@@ -2,7 +2,7 @@
 // aggregation (k_fill_zero, k_msg_directory, k_aggregate, k_aggregate_entries, k_aggregate_cells,
 // k_aggregate_dense, k_aggregate_dense_one), k_read_nnz.
 // Part of the single translation unit qsl.hip (included there, in this order: device, layout, select,
-// encode, stream, lean, dense, decode); not a public header.
+// encode, stream, lean, window, dense, decode); not a public header.
 #pragma once
 
 #include "qsl_device.h"
@@ -647,8 +647,8 @@ __device__ __forceinline__ void aggregate_dense_quad(const DevCtx& c, const uint
       continue;
     }
     // the codes of the four coordinates are consecutive in the stream: up to 8 bits each come in one read
-    // (77 -> 62 us for two messages of 25.6 M one-bit codes; issuing the reads of several messages together, or a
-    // wave per 1024 coordinates as in the streaming pass, were both slower again: 72-77 us)
+    // (77 -> 62 us for two messages of 25.6 M one-bit codes; with the value computed per code, as here, a wave per 1024
+    // coordinates and the reads of several messages together were slower, 72 - 77 us: k_aggregate_dense_one looks it up)
     const bool packed = c.w_val <= 8;                      // uniform
     const uint32_t four = packed ? get_bits(words, code_bit0 + j0 * c.w_val, nj * c.w_val) : 0u;
     const float scale0 = __uint_as_float(words[1 + seg[0]]);

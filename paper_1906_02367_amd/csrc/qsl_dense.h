@@ -4,9 +4,10 @@
 //   k_dense_norm    v = m + Delta (Algorithm 1, first worker line) written over the error memory, 12 bytes per
 //                   coordinate, with the exact digits of every segment's norm added up on the way
 //   k_dense_sum     the digit sums that the blocks of k_dense_norm stored, into their units' counters
-//   k_dense_scales  one wave per unit: digits -> fp32 scale (||v||_2 for QSGD, ||v||_1 / k or ||v||_2 / k for Sign)
+//   k_dense_scales  one wave per unit: digits -> fp32 scale (||v||_2 for QSGD, ||v||_1 / k or ||v||_2 / k for Sign); with one segment
+//                   and few rows of sums both steps are one launch, k_dense_sum_scale
 //   k_dense_encode  reads v, writes m' = v - g (second worker line) and the packed codes, 8 bytes per coordinate:
-//                   a block owns 4096 consecutive coordinates and with them whole 32-bit words of the code stream
+//                   a wave owns 1024 consecutive coordinates and with them whole 32-bit words of the code stream
 // Part of the single translation unit qsl.hip (included after qsl_encode.h); not a public header.
 #pragma once
 

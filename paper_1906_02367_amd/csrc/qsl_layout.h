@@ -85,9 +85,9 @@ struct UnitState {
   uint32_t sh;          // the candidates' histogram has bins of 2^sh keys above T (same sources as T)
   uint32_t T_next, sh_next;   // guess and bin width for the next call, from this call's candidates (k_lean_mark)
   uint32_t T_used;      // the guess the last call worked with (k_pack; diagnostics)
-  uint32_t cand;        // candidates collected (k_lean_hist)
-  uint32_t fell_back;   // 1: the guess failed -- too few candidates or no room for them (k_lean_hist)
-  uint32_t crowded;     // 1: the threshold's bin holds more than LISTCAP candidates (k_lean_mark)
+  uint32_t cand;        // candidates collected (k_lean_hist, k_win_hist)
+  uint32_t fell_back;   // 1: the guess (the window) failed -- too few candidates or no room for them (k_lean_hist, k_win_hist)
+  uint32_t crowded;     // 1: the threshold's bin holds more candidates than the short list takes (k_lean_mark, k_win_mark)
   uint32_t taubin, above;     // bin of the k-th largest candidate, candidates in the bins above it (k_lean_mark)
   uint32_t prefix1, k_rem1; // radix selection state after the first digit (found by k_select<1> from the first histogram) ...
   uint32_t prefix2, k_rem2; // ... and after the second (k_select<2>); the third is found by k_tile_count
