@@ -975,7 +975,9 @@ static qsl_status launch_compress(qsl_ctx* ctx, const float* m, const float* del
   SegInfo sel_one = ctx->segs[0];
   uint32_t nsel = safe ? c.NSEL : ctx->nsel_general;
   const uint32_t ncb = safe ? c.NCB : ctx->ncb_general;
-  if (c.win) nsel = sel_one.nsel = std::max(1u, std::min(sel_one.nsel, 256 / std::min(256u, R)));      // mostly they find nothing to do
+  // behind a window they mostly find nothing to do: few blocks (64 instead of 17, and 1024 of k_quantize: 78.5 us instead of 75.7
+  // for 3.2 M coordinates, k = d / 10, one worker)
+  if (c.win) nsel = sel_one.nsel = window_blocks(sel_one, R);
   if (nsel) {
     k_select<0, SPARS><<<dim3(nsel * R), BIG, 0, st>>>(c, sel_one, m_out, worker0, round, R);
     k_select<1, SPARS><<<dim3(nsel * R), BIG, 0, st>>>(c, sel_one, m_out, worker0, round, R);
@@ -983,7 +985,7 @@ static qsl_status launch_compress(qsl_ctx* ctx, const float* m, const float* del
     k_tile_count<SPARS><<<dim3(ncb * R), BLOCK, 0, st>>>(c, ctx->segs[0], m_out, worker0, round, R);
     k_tile_write<SPARS><<<dim3(ncb * R), BLOCK, 0, st>>>(c, ctx->segs[0], m_out, worker0, round, R);
   }
-  if (c.win) k_quantize<true><<<dim3(std::min(c.QB, std::max(256u, 1024 / R)), R), BLOCK, 0, st>>>(c, m_out, worker0, round, sel_idx, sel_level, 0);
+  if (c.win) k_quantize<true><<<dim3(std::min(c.QB, 256u), R), BLOCK, 0, st>>>(c, m_out, worker0, round, sel_idx, sel_level, 0);
   else if (ctx->n_other || safe) k_quantize<false><<<dim3(c.QB, R), BLOCK, 0, st>>>(c, m_out, worker0, round, sel_idx, sel_level, safe ? 1 : 0);
   // the guessing units' exact threshold, ordered output and codes; one more block per guessing unit for failures
   if (c.NSELF)
