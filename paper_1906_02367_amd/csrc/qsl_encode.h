@@ -12,7 +12,7 @@
 namespace {
 
 // digits -> one correctly rounded double -> the fp32 scale of the unit.  Called by all 64 lanes of a
-// wave with the same arguments; lane i holds digit counter i, everything else is shuffles and ballots
+// wave with the same arguments; lane i holds digit counter i, everything else is lane moves and ballots
 // (a per-thread digit array would live in scratch memory and cost microseconds).
 // The cube root by a fixed sequence of IEEE double operations (Lemma 3 with m = 3 fixes the norm, not how its root is
 // rounded): 2^floor(E / 3) times 1, 2^(1/3) or 2^(2/3) for the binary exponent E of x, then eight Newton steps
@@ -38,7 +38,7 @@ __device__ float finalize_scale(const uint64_t* acc, uint32_t quantizer, uint32_
   const uint32_t lane = lane_id();
   const uint64_t a = lane < acc_slots(quantizer) ? acc[lane] : 0;
   // 32-bit digits: low half of the own counter plus the high half of the one below, then ripple the carries
-  auto from_below = [&](uint32_t x) { const uint32_t y = __shfl_up(x, 1, WAVE); return lane ? y : 0u; };
+  auto from_below = [&](uint32_t x) { return dpp_or_zero<DPP_WAVE_SHR1, 0xF>(x); };
   uint64_t t = (a & 0xFFFFFFFFull) + from_below(static_cast<uint32_t>(a >> 32));
   for (uint32_t it = 0; it < WAVE; ++it) {                            // ends after a few rounds; bounded anyway
     const uint32_t carry = static_cast<uint32_t>(t >> 32);
@@ -50,20 +50,20 @@ __device__ float finalize_scale(const uint64_t* acc, uint32_t quantizer, uint32_
   double S = 0.0;
   if (nz != 0) {
     const int tw = 63 - __clzll(static_cast<long long>(nz));
-    const int top = tw * 32 + 31 - __clz(static_cast<int>(__shfl(dig, tw, WAVE)));
+    const int top = tw * 32 + 31 - __clz(static_cast<int>(lane_value(dig, tw)));
     const int low = top - 52;                       // position of the last kept bit
     uint64_t mant; int e2;
     if (low <= 0) {
-      mant = (static_cast<uint64_t>(__shfl(dig, 1, WAVE)) << 32) | __shfl(dig, 0, WAVE); e2 = 0;   // the whole value, exact
+      mant = (static_cast<uint64_t>(lane_value(dig, 1)) << 32) | lane_value(dig, 0); e2 = 0;   // the whole value, exact
     } else {
       const int wq = low >> 5, r = low & 31;
-      const uint64_t lo64 = (static_cast<uint64_t>(__shfl(dig, wq + 1, WAVE)) << 32) | __shfl(dig, wq, WAVE);
-      const uint64_t hi32 = __shfl(dig, wq + 2, WAVE);                // lanes above the top digit hold 0
+      const uint64_t lo64 = (static_cast<uint64_t>(lane_value(dig, wq + 1)) << 32) | lane_value(dig, wq);
+      const uint64_t hi32 = lane_value(dig, wq + 2);                // lanes above the top digit hold 0
       uint64_t win = lo64 >> r;
       if (r) win |= hi32 << (64 - r);
       mant = win & ((1ull << 53) - 1);
       const int g = low - 1, gq = g >> 5, gb = g & 31;
-      const uint32_t dg = __shfl(dig, gq, WAVE);
+      const uint32_t dg = lane_value(dig, gq);
       const uint32_t guard = (dg >> gb) & 1u;
       const bool sticky = (dg & ((1u << gb) - 1u)) != 0 || __ballot(dig != 0 && lane < static_cast<uint32_t>(gq)) != 0;
       if (guard && (sticky || (mant & 1u))) mant += 1;

@@ -278,7 +278,7 @@ __global__ __launch_bounds__(BIG) void k_lean_mark(DevCtx c, SegInfo one, uint32
       const int first = __ffsll(static_cast<unsigned long long>(ib)) - 1;
       uint32_t base = 0;
       if (static_cast<int>(lane) == first) base = atomicAdd(cursor, static_cast<uint32_t>(__popcll(ib)));
-      base = __shfl(base, first, WAVE);
+      base = lane_value(base, first);
       const uint32_t q = base + popc_below(ib);
       if (inside && q < LISTCAP) list[q] = make_uint4(p, bits, key, idx);
     }
@@ -855,7 +855,7 @@ __global__ __launch_bounds__(BIG) void k_lean_one(DevCtx c, SegInfo one, uint32_
       const int first = __ffsll(static_cast<unsigned long long>(ib)) - 1;
       uint32_t base = 0;
       if (static_cast<int>(lane) == first) base = atomicAdd(&s_nlist, static_cast<uint32_t>(__popcll(ib)));
-      base = __shfl(base, first, WAVE);
+      base = lane_value(base, first);
       const uint32_t q = base + popc_below(ib);
       if (inside && q < LISTCAP) s_list[q] = make_uint4(p, bits, key, idx);
     }

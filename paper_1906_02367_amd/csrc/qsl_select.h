@@ -69,17 +69,6 @@ __device__ __forceinline__ SlotRow parse_slot_row(const RawRow& raw, uint32_t lp
 
 constexpr int ROWS_IN_FLIGHT = 8;                 // slot rows a wave of the guessing units' kernels loads at a time
 
-__device__ __forceinline__ uint32_t wave_exclusive_scan32(uint32_t x, uint32_t* total) {
-  uint32_t inc = x;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t y = __shfl_up(inc, o, WAVE);
-    if (lane_id() >= static_cast<uint32_t>(o)) inc += y;
-  }
-  *total = __shfl(inc, 63, WAVE);
-  return inc - x;
-}
-
 // ------------------------------------------------------------------------------------------------
 // radix selection, one kernel per digit
 // ------------------------------------------------------------------------------------------------

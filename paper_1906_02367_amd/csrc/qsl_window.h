@@ -423,7 +423,7 @@ __global__ __launch_bounds__(BIG) void k_win_mark(DevCtx c, WinCtx wc, SegInfo o
       const int first = __ffsll(static_cast<unsigned long long>(ib)) - 1;
       uint32_t base = 0;
       if (static_cast<int>(lane) == first) base = atomicAdd(cursor, static_cast<uint32_t>(__popcll(ib)));
-      base = __shfl(base, first, WAVE);
+      base = lane_value(base, first);
       const uint32_t q = base + popc_below(ib);
       if (inside && q < WLIST) list[q] = make_uint4(idx, bits, key, 0u);
     }
