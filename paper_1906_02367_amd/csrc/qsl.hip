@@ -29,7 +29,7 @@
 //                dense k on a single large segment, instead of those: a window of rank keys around the threshold,
 //                two passes over v; the kernels above stand by for a window that does not hold
 //   k_pack, k_pack_sent       the packed message (k_pack_sent: QSGD, whose entries of level 0 drop out)
-//   k_dense_norm, k_dense_sum, k_dense_scales, k_dense_sum_scale, k_dense_encode    an operator that keeps every coordinate, with
+//   k_dense_norm_one, k_dense_scale_one (several segments: k_dense_norm, k_dense_sum, k_dense_scales), k_dense_encode    an operator that keeps every coordinate, with
 //                messages that carry no indices: two streaming passes
 //   k_msg_directory, k_aggregate, k_aggregate_entries, k_aggregate_cells, k_aggregate_dense, k_aggregate_dense_one
 //                master line of Algorithm 1, atomic-free, messages added in list order: by look-ups in the other
@@ -367,6 +367,9 @@ extern "C" qsl_status qsl_plan_paths(const qsl_config* cfg, uint32_t* path_out) 
   return QSL_OK;
 }
 
+// One segment whose sum is one of magnitudes or squares (or that wants none): k_dense_norm_one takes the first pass.
+static bool dense_one(uint32_t L, uint32_t quantizer) { return L == 1 && norm_power(quantizer) <= 2; }
+
 // releases everything a (possibly half-built) context holds
 static void free_ctx(qsl_ctx* ctx) {
   if (ctx->side) { (void)hipStreamSynchronize(ctx->side); (void)hipStreamDestroy(ctx->side); }
@@ -592,6 +595,8 @@ static qsl_status create_ctx(qsl_ctx** out, const qsl_config* cfg, void* hip_str
   ctx->agg_ndir = static_cast<uint32_t>(((d + (1u << AGG_DIR_SHIFT) - 1) >> AGG_DIR_SHIFT) + 1);
   const uint64_t o_pile = carve(4ull * (2 + (ctx->agg_ndir + 31) / 32));
   const uint64_t o_wsam = carve(window ? 4ull * WCOPIES * WBINS * R : 4), o_whist = carve(window ? 4ull * HBINS * R : 4);
+  const bool one_pass = (cfg->flags & QSL_FLAG_DENSE_FORMAT) && dense_one(L, cfg->quantizer);     // k_dense_norm_one's counters
+  const uint64_t o_dcopies = carve(one_pass ? 8ull * 20 * DENSE_PITCH * DENSE_COPIES * R : 8);
   const uint64_t zero_bytes = bytes;
   const uint64_t o_segs = carve(sizeof(SegInfo) * L), o_wts = carve(sizeof(WtInfo) * std::max<size_t>(1, wts.size()));
   const uint64_t o_sels = carve(sizeof(SelInfo) * NSEL), o_cbs = carve(sizeof(CbInfo) * NCB);
@@ -680,8 +685,10 @@ static qsl_status create_ctx(qsl_ctx** out, const qsl_config* cfg, void* hip_str
     o_pbits[v] = carve(4ull * std::max<size_t>(1, agg_bits[v].size()));
   }
   const uint64_t o_ownv = carve((cfg->flags & QSL_FLAG_OWN_V) ? 4ull * R * d : 4);
-  const uint64_t dense_nb = dense ? std::min<uint64_t>((d + DTILE - 1) / DTILE, MAX_DENSE_BLOCKS) : 0;
-  const uint64_t o_dpart = carve(8ull * R * ACC_SLOTS * dense_nb + 8), o_dtag = carve(4ull * R * dense_nb + 4);
+  const uint64_t dense_nb = dense && !one_pass ? std::min<uint64_t>((d + DTILE - 1) / DTILE, MAX_DENSE_BLOCKS) : 0;
+  const uint64_t o_dtag = carve(4ull * R * dense_nb + 4);
+  const uint64_t o_dpart_rows = carve(one_pass ? 8 : 8ull * R * ACC_SLOTS * dense_nb + 8);
+  const uint64_t o_dpart = one_pass ? o_dcopies : o_dpart_rows;
   if (hipMalloc(&ctx->slab, bytes) != hipSuccess) {
     (void)hipGetLastError();                        // (the next call is not to find this error)
     ctx->slab = nullptr; free_ctx(ctx);
@@ -845,10 +852,23 @@ static qsl_status launch_dense(qsl_ctx* ctx, const float* m, const float* delta,
     }
     QSL_HIP(hipEventRecord(ctx->ev[ctx->ev_used], st));
   }
-  if (xm == nullptr) k_dense_norm<false><<<grid, BLOCK, 0, st>>>(c, m, delta, xm, m_out);
-  else k_dense_norm<true><<<grid, BLOCK, 0, st>>>(c, m, delta, xm, m_out);
+  const bool one = dense_one(c.L, c.quantizer);
+  const dim3 ngrid(static_cast<uint32_t>(ntiles), R);      // a wave per 1024 coordinates
+  const uint32_t power = c.quantizer == QSL_FP32 ? 0u : norm_power(c.quantizer);
+  if (!one) {
+    if (xm == nullptr) k_dense_norm<false><<<grid, BLOCK, 0, st>>>(c, m, delta, xm, m_out);
+    else k_dense_norm<true><<<grid, BLOCK, 0, st>>>(c, m, delta, xm, m_out);
+  } else if (xm == nullptr) {
+    if (power == 0) k_dense_norm_one<0, false><<<ngrid, BLOCK, 0, st>>>(c, m, delta, xm, m_out);
+    else if (power == 1) k_dense_norm_one<1, false><<<ngrid, BLOCK, 0, st>>>(c, m, delta, xm, m_out);
+    else k_dense_norm_one<2, false><<<ngrid, BLOCK, 0, st>>>(c, m, delta, xm, m_out);
+  } else {
+    if (power == 0) k_dense_norm_one<0, true><<<ngrid, BLOCK, 0, st>>>(c, m, delta, xm, m_out);
+    else if (power == 1) k_dense_norm_one<1, true><<<ngrid, BLOCK, 0, st>>>(c, m, delta, xm, m_out);
+    else k_dense_norm_one<2, true><<<ngrid, BLOCK, 0, st>>>(c, m, delta, xm, m_out);
+  }
   if (timed) { QSL_HIP(hipEventRecord(ctx->ev[ctx->ev_used + 1], st)); ctx->ev_used += 2; }
-  if (c.L == 1 && grid.x <= SUM_ONE) k_dense_sum_scale<<<dim3(R), SUM_BLOCK, 0, st>>>(c, grid.x);
+  if (one) k_dense_scale_one<<<dim3(R), SUM_BLOCK, 0, st>>>(c);
   else {
     if (c.quantizer != QSL_FP32) k_dense_sum<<<dim3((grid.x + SUM_ROWS - 1) / SUM_ROWS, R), SUM_BLOCK, 0, st>>>(c, grid.x);
     const uint32_t U = R * c.L;

@@ -4,8 +4,8 @@
 //   k_dense_norm    v = m + Delta (Algorithm 1, first worker line) written over the error memory, 12 bytes per
 //                   coordinate, with the exact digits of every segment's norm added up on the way
 //   k_dense_sum     the digit sums that the blocks of k_dense_norm stored, into their units' counters
-//   k_dense_scales  one wave per unit: digits -> fp32 scale (||v||_2 for QSGD, ||v||_1 / k or ||v||_2 / k for Sign); with one segment
-//                   and few rows of sums both steps are one launch, k_dense_sum_scale
+//   k_dense_scales  one wave per unit: digits -> fp32 scale (||v||_2 for QSGD, ||v||_1 / k or ||v||_2 / k for Sign)
+//   k_dense_norm_one, k_dense_scale_one   in place of those for one segment: a wave's sum formed in registers
 //   k_dense_encode  reads v, writes m' = v - g (second worker line) and the packed codes, 8 bytes per coordinate:
 //                   a wave owns 1024 consecutive coordinates and with them whole 32-bit words of the code stream
 // Part of the single translation unit qsl.hip (included after qsl_encode.h); not a public header.
@@ -206,18 +206,122 @@ __global__ __launch_bounds__(SUM_BLOCK) void k_dense_sum(DevCtx c, uint32_t nb) 
   }
 }
 
-// One segment and at most SUM_ONE rows per worker: sums and scale by one block per worker, in one launch instead of two
-// (4 x 100,003 coordinates, QSGD: 25.2 -> 23.0 us per call).
-constexpr uint32_t SUM_ONE = 1024;
-__global__ __launch_bounds__(SUM_BLOCK) void k_dense_sum_scale(DevCtx c, uint32_t nb) {
-  __shared__ uint64_t acc[ACC_SLOTS];
-  const uint32_t w = blockIdx.x, lane = lane_id(), wave = threadIdx.x >> 6;
-  const uint32_t ns = c.quantizer == QSL_FP32 ? 0u : acc_slots(c.quantizer);
-  for (uint32_t s = wave; s < ns; s += SUM_BLOCK / 64) {
-    const uint64_t* row = c.dense_part + (static_cast<uint64_t>(w) * ACC_SLOTS + s) * nb;
-    uint64_t x = 0;
+// The same first pass for one segment, by the streaming pass's recipe: a wave per 1024 coordinates, no LDS and no barrier.  The
+// exact sum of a wave's magnitudes (or squares) is formed in registers: every lane adds its 16 as integers counted from
+// the lowest exponent of a window of 30 (squares: 32) octaves that ends at the wave's largest, DPP adds the lanes, and five
+// lanes add the total's 32-bit digits to one of DENSE_COPIES rows of counters, each counter in a cache line of its own.
+// Bits: 24 + 29 + 4 (16 values) + 6 (lanes) = 63; squares 48 + 62 + 4 + 6 = 120 of 128.  Magnitudes below the window, if there
+// are any, have a window of their own after it.  2 x 25.6 M coordinates, by LDS digits, barriers and rows per block (k_dense_norm, for
+// several segments and for cubes and fourth powers) / this way: magnitudes 108 / 97 us, squares 118 / 99; the sums after it, two
+// launches of 4.7 us / one of 5.  3 to 6 waves per SIMD: 98, 97, 98, 98 us.
+constexpr uint32_t DENSE_COPIES = 64, DENSE_PITCH = 16;      // rows; 64-bit words from counter to counter
+
+template <uint32_t POWER>
+__device__ __forceinline__ void add_wave_digits(uint64_t* row, const f4u (&v)[4]) {
+  const uint32_t lane = lane_id();
+  uint32_t ab[16], top = 0;
 #pragma unroll
-    for (uint32_t g = 0; g < SUM_ONE / 64; ++g) if (g * 64 + lane < nb) x += row[g * 64 + lane];
+  for (uint32_t i = 0; i < 16; ++i) { ab[i] = __float_as_uint(v[i >> 2][i & 3]) & 0x7FFFFFFFu; top = max(top, ab[i]); }
+  top = wave_max(top);
+  while (top != 0) {                                         // (uniform) a window; at most 9 of them
+    const bool last = top < 2u << 23;                        // exponents 0 and 1: the bits are the mantissa, the unit is the same
+    const uint32_t e0 = last ? 1u : max(2u, (top >> 23) - min(top >> 23, POWER == 1 ? 29u : 31u)), low = last ? 1u : e0 << 23;
+    uint64_t lo = 0, hi = 0;                                 // the lane's sum is hi * 2^64 + lo
+    uint32_t rest = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < 16; ++i) {
+      const bool in = ab[i] >= low;
+      const uint32_t M = in ? (last ? ab[i] : (ab[i] & 0x7FFFFFu) | 0x800000u) : 0u, e = last ? 0u : (ab[i] >> 23) - e0;
+      ab[i] = in ? 0u : ab[i];
+      rest = max(rest, ab[i]);
+      if (POWER == 1) lo += static_cast<uint64_t>(M) << (e & 63u);
+      else {
+        const uint64_t sq = static_cast<uint64_t>(M) * M;
+        const uint32_t sh = 2u * e & 63u;
+        const uint64_t x = sq << sh;
+        lo += x;
+        hi += (sq >> 1 >> (63u - sh)) + (lo < x ? 1u : 0u);
+      }
+    }
+    if (POWER == 1) lo = wave_sum64(lo);
+    else {                                                   // limbs none of which overflows
+      const uint64_t s0 = wave_sum64(lo & 0xFFFFFFFFu), s1 = wave_sum64(lo >> 32), s2 = wave_sum64(hi);
+      lo = s0 + (s1 << 32);
+      hi = s2 + (s1 >> 32) + (lo < s0 ? 1u : 0u);
+    }
+    const uint32_t p = POWER * (e0 - 1u), q = p >> 5, r = p & 31u;      // bit 0 of the sum is bit p of the digits
+    const uint64_t a0 = lo << r, a1 = (hi << r) | (lo >> 1 >> (63u - r));
+    const uint32_t digit = lane == 0 ? static_cast<uint32_t>(a0) : lane == 1 ? static_cast<uint32_t>(a0 >> 32) : lane == 2 ? static_cast<uint32_t>(a1)
+                         : lane == 3 ? static_cast<uint32_t>(a1 >> 32) : static_cast<uint32_t>(hi >> 1 >> (63u - r));
+    if (lane < 5 && digit) atomicAdd(reinterpret_cast<unsigned long long*>(row + (q + lane) * DENSE_PITCH), static_cast<unsigned long long>(digit));
+    top = wave_max(rest);
+  }
+}
+
+template <uint32_t POWER, bool DIFF>      // POWER 0: no norm wanted
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_dense_norm_one(
+    DevCtx c, const float* m, const float* delta, const float* xm, float* m_out) {
+  const uint32_t w = blockIdx.y, lane = lane_id();
+  const uint64_t chunk = static_cast<uint64_t>(blockIdx.x) * (BLOCK / 64) + (threadIdx.x >> 6), base = chunk * CHUNK;
+  if (base >= c.d) return;
+  const uint32_t valid = static_cast<uint32_t>(min(static_cast<uint64_t>(CHUNK), c.d - base));
+  const uint64_t row = static_cast<uint64_t>(w) * c.d + base;
+  const float* mp = m + row;
+  const float* dp = delta + row;
+  const float* xp = DIFF ? xm + base : nullptr;
+  float* op = m_out + row;
+  f4u v[4];
+  if (valid == CHUNK) {
+    f4u a[4], b[4], x[4];
+#pragma unroll
+    for (uint32_t t = 0; t < 4; ++t) {
+      const uint32_t e = t * 256 + lane * 4;
+      a[t] = __builtin_nontemporal_load(reinterpret_cast<const f4u*>(mp + e));
+      b[t] = __builtin_nontemporal_load(reinterpret_cast<const f4u*>(dp + e));
+      if (DIFF) x[t] = *reinterpret_cast<const f4u*>(xp + e);
+    }
+#pragma unroll
+    for (uint32_t t = 0; t < 4; ++t) {
+      if (DIFF) b[t] = x[t] - b[t];
+      v[t] = a[t] + b[t];
+      __builtin_nontemporal_store(v[t], reinterpret_cast<f4u*>(op + t * 256 + lane * 4));
+    }
+  } else {
+#pragma unroll
+    for (uint32_t t = 0; t < 4; ++t) {
+#pragma unroll
+      for (uint32_t j = 0; j < 4; ++j) {
+        const uint32_t e = t * 256 + lane * 4 + j;
+        float x = 0.0f;
+        if (e < valid) {
+          const float dl = DIFF ? xp[e] - dp[e] : dp[e];
+          x = mp[e] + dl; op[e] = x;
+        }
+        v[t][j] = x;
+      }
+    }
+  }
+  bool nonfinite = false;
+#pragma unroll
+  for (uint32_t t = 0; t < 4; ++t) {
+#pragma unroll
+    for (uint32_t j = 0; j < 4; ++j) nonfinite |= (__float_as_uint(v[t][j]) & 0x7FFFFFFFu) >= 0x7F800000u;
+  }
+  if (__ballot(nonfinite) != 0 && lane == 0) atomicOr(c.status, 1u);
+  if (POWER != 0)
+    add_wave_digits<POWER>(c.dense_part + (static_cast<uint64_t>(w) * DENSE_COPIES + (static_cast<uint32_t>(chunk) & (DENSE_COPIES - 1))) * (20 * DENSE_PITCH), v);
+}
+
+// ... and its rows added up, one block per worker: the scales; the rows back to zero.
+__global__ __launch_bounds__(SUM_BLOCK) void k_dense_scale_one(DevCtx c) {
+  __shared__ uint64_t acc[20];
+  static_assert(DENSE_COPIES == 64, "a row per lane");
+  const uint32_t w = blockIdx.x, lane = lane_id(), wave = threadIdx.x >> 6;
+  const uint32_t ns = c.quantizer == QSL_FP32 ? 0u : 20u;
+  for (uint32_t s = wave; s < ns; s += SUM_BLOCK / 64) {
+    uint64_t* p = c.dense_part + ((static_cast<uint64_t>(w) * DENSE_COPIES + lane) * 20 + s) * DENSE_PITCH;
+    uint64_t x = *p;
+    if (x) *p = 0;
     x = wave_sum64(x);
     if (lane == 0) acc[s] = x;
   }

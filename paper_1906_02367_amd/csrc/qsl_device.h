@@ -70,6 +70,16 @@ __device__ __forceinline__ uint32_t wave_exclusive_scan32(uint32_t x, uint32_t* 
   return inc - x;
 }
 
+__device__ __forceinline__ uint32_t wave_max(uint32_t x) {
+  x = max(x, dpp_or_zero<DPP_ROW_SHR + 1, 0xF>(x));
+  x = max(x, dpp_or_zero<DPP_ROW_SHR + 2, 0xF>(x));
+  x = max(x, dpp_or_zero<DPP_ROW_SHR + 4, 0xF>(x));
+  x = max(x, dpp_or_zero<DPP_ROW_SHR + 8, 0xF>(x));
+  x = max(x, dpp_or_zero<DPP_BCAST15, 0xA>(x));
+  x = max(x, dpp_or_zero<DPP_BCAST31, 0xC>(x));
+  return lane_value(x, 63);
+}
+
 // Exclusive prefix sum over a block of up to 1024 threads (blockDim.x a multiple of 64).
 // `scratch` holds at least 17 uint64.  Returns the exclusive prefix of x; *total = block sum.  Every wave adds up the waves'
 // sums for itself.

@@ -869,6 +869,27 @@ def test_index_free_edges(P, d, quantizer, s, factor):
     assert run.q.device_status() == B.OK
 
 
+# index-free messages of one segment: the norm of values from the smallest subnormal to 1e36, side by side in one wave (several windows
+# of exponents), alone in a chunk, and only subnormal ones; chunks of zeros; a last chunk of one coordinate.  Bit for bit (exact sums).
+@pytest.mark.parametrize("quantizer,s", [(W.SIGN_L1, 1), (W.SIGN_L2, 1), (W.QSGD, 15)])
+@pytest.mark.parametrize("d,kind", [(6_145, "all"), (6_145, "subnormal"), (1_024, "zeros"), (66_561, "windows"), (1, "all")])
+def test_index_free_norms_over_the_whole_range(P, quantizer, s, d, kind):
+    rng = np.random.default_rng(d + s)
+    v = rng.standard_normal((2, 2, d)).astype(f32)
+    if kind == "all":
+        v = np.ldexp(v, rng.integers(-148, 119, v.shape)).astype(f32)
+    elif kind == "subnormal":
+        v = (v * f32(1e-40)).astype(f32)
+        v[:, :, 1_024:2_048] = 0
+    elif kind == "zeros":
+        v[:] = 0
+    else:                                                # chunk c: magnitudes around 2^(4 c - 140), a few others 2^30 and 2^64 below them
+        e = np.repeat(np.arange(66) * 4 - 140, 1_024)[:d]
+        e = np.concatenate([e, np.full(d - e.size, 0)])
+        v = np.ldexp(v, np.maximum(e - rng.choice([0, 0, 0, 29, 30, 31, 32, 64], v.shape), -149)).astype(f32)
+    P.run_parity(custom(d, [0, d], [d], s, W.TOPK, quantizer, R=2), 2, deltas=v, dense=True, expect_path=4)
+
+
 # a message with an index >= d: reported by the status word (once), the entry skipped, everything else added up
 # as ever -- whichever kernel meets it: one wave per cell, a cell in parts (where the entry lies behind d, in a part that has
 # no coordinates), a last cell that the plan calls crowded, short messages, look-ups
