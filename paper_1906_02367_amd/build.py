@@ -9,7 +9,7 @@ ROOT = os.path.dirname(_HERE)
 LIB_PATH = os.path.join(_HERE, "libqsl.so")
 SOURCES = [os.path.join(_HERE, "csrc", "qsl.hip")]
 HEADERS = [os.path.join(_HERE, "csrc", h) for h in ("qsl_policy.h", "qsl_device.h", "qsl_layout.h", "qsl_stream.h", "qsl_select.h",
-                                                    "qsl_encode.h", "qsl_lean.h", "qsl_window.h", "qsl_dense.h",
+                                                    "qsl_encode.h", "qsl_lean.h", "qsl_whole.h", "qsl_window.h", "qsl_dense.h",
                                                     "qsl_decode.h")] + [os.path.join(ROOT, "include", "qsl.h")]
 
 HIPCC_FLAGS = [

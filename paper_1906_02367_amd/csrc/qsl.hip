@@ -17,6 +17,7 @@
 //                Top_k / Rand_k, ties to the lower coordinate), the exact ||v_S||_2^2 or ||v_S||_1 (proof of
 //                Lemma 1; Lemma 3, m = 1), QSGD levels (Definition 1, example 1) or signs (Definition 2), and
 //                the error update m <- v - g on the transmitted coordinates (Algorithm 1, worker line 2)
+//   k_whole      a short vector that is one segment: all of this and the message, one block per worker, one launch
 //   k_lean_one   the same three steps in one launch for a guessing unit that needs only one block
 //   k_block_units  a unit too dense for guessing, of at most 40,960 coordinates: all of the above by one block,
 //                on a second stream beside the guessing units' kernels
@@ -67,6 +68,7 @@
 #include "qsl_encode.h"
 #include "qsl_stream.h"
 #include "qsl_lean.h"
+#include "qsl_whole.h"
 #include "qsl_window.h"
 #include "qsl_dense.h"
 #include "qsl_decode.h"
@@ -96,6 +98,7 @@ struct qsl_ctx {
   void* slab;                 // one allocation holding every scratch array
   uint32_t Rmax;
   uint32_t last_R;
+  bool whole;                 // a short vector: every call is one launch (k_whole)
   uint32_t nsmall;            // segments selected by one block each (k_small)
   uint32_t nfull_blocks;      // blocks of k_full (per worker): segments with k = size
   uint32_t nnz_hint;          // entries a message is expected to hold at most (sizes the aggregation grid)
@@ -765,6 +768,9 @@ static qsl_status create_ctx(qsl_ctx** out, const qsl_config* cfg, void* hip_str
   c.cb_cnt = reinterpret_cast<uint2*>(base + o_cbc);
   c.tlist = reinterpret_cast<uint4*>(base + o_tlist);
   c.win = window ? 1u : 0u;
+  // (longer vectors would spill registers; a longer list of selected entries would not fit LDS beside the histogram)
+  ctx->whole = L == 1 && d <= WHOLE_MAX && K <= WHOLE_K && !(cfg->flags & (QSL_FLAG_NO_FAST_PATH | QSL_FLAG_NO_SMALL_PATH | QSL_FLAG_DENSE_FORMAT)) &&
+               segs[0].mode != PATH_FULL;
   WinCtx& wc = ctx->wc;
   wc.state = reinterpret_cast<WinState*>(base + o_wstate);
   wc.sample = reinterpret_cast<uint32_t*>(base + o_wsam); wc.hist = reinterpret_cast<uint32_t*>(base + o_whist);
@@ -1026,6 +1032,33 @@ static qsl_status launch_compress(qsl_ctx* ctx, const float* m, const float* del
   return QSL_OK;
 }
 
+// A short vector that is one segment: everything in one launch (qsl_whole.h).
+template <int SPARS>
+static void launch_whole_as(qsl_ctx* ctx, const float* m, const float* delta, const float* xm, float* m_out, uint32_t worker0, uint32_t R,
+                            uint64_t round, uint8_t* msg, uint64_t* msg_bits, uint32_t* sel_idx, uint16_t* sel_level) {
+  const DevCtx& c = ctx->dc;
+  const SegInfo& sg = ctx->segs[0];
+  hipStream_t st = ctx->stream;
+  if (c.d <= 4096) k_whole<SPARS, 1><<<dim3(R), BIG, 0, st>>>(c, sg, m, delta, xm, m_out, worker0, round, msg, msg_bits, sel_idx, sel_level);
+  else if (c.d <= 8192) k_whole<SPARS, 2><<<dim3(R), BIG, 0, st>>>(c, sg, m, delta, xm, m_out, worker0, round, msg, msg_bits, sel_idx, sel_level);
+  else k_whole<SPARS, 4><<<dim3(R), BIG, 0, st>>>(c, sg, m, delta, xm, m_out, worker0, round, msg, msg_bits, sel_idx, sel_level);
+}
+static qsl_status launch_whole(qsl_ctx* ctx, const float* m, const float* delta, const float* xm, float* m_out, uint32_t worker0, uint32_t R,
+                               uint64_t round, uint8_t* msg, uint64_t* msg_bits, uint32_t* sel_idx, uint16_t* sel_level) {
+  const bool timed = ctx->timing != 0;
+  if (timed) {
+    if (ctx->ev_used + 2 > ctx->ev.size()) {
+      for (int i = 0; i < 2; ++i) { hipEvent_t e; QSL_HIP(hipEventCreateWithFlags(&e, hipEventDisableSystemFence)); ctx->ev.push_back(e); }
+    }
+    QSL_HIP(hipEventRecord(ctx->ev[ctx->ev_used], ctx->stream));
+  }
+  if (ctx->cfg.sparsifier == QSL_TOPK) launch_whole_as<QSL_TOPK>(ctx, m, delta, xm, m_out, worker0, R, round, msg, msg_bits, sel_idx, sel_level);
+  else launch_whole_as<QSL_RANDK>(ctx, m, delta, xm, m_out, worker0, R, round, msg, msg_bits, sel_idx, sel_level);
+  if (timed) { QSL_HIP(hipEventRecord(ctx->ev[ctx->ev_used + 1], ctx->stream)); ctx->ev_used += 2; }
+  QSL_HIP(hipGetLastError());
+  return QSL_OK;
+}
+
 static qsl_status compress_checked(qsl_ctx* ctx, const float* m, const float* delta, const float* xm, float* m_out,
                                    uint32_t worker0, uint32_t R, uint64_t round, uint8_t* msg, uint64_t* msg_bits,
                                    uint32_t* sel_idx, uint16_t* sel_level) {
@@ -1038,6 +1071,7 @@ static qsl_status compress_checked(qsl_ctx* ctx, const float* m, const float* de
   if ((reinterpret_cast<uintptr_t>(msg) | reinterpret_cast<uintptr_t>(msg_bits)) & 7) return QSL_ERR_INVALID_ARG;
   if (reinterpret_cast<uintptr_t>(sel_level) & 1) return QSL_ERR_INVALID_ARG;
   ctx->last_R = R;
+  if (ctx->whole) return launch_whole(ctx, m, delta, xm, m_out, worker0, R, round, msg, msg_bits, sel_idx, sel_level);
   if (ctx->dc.dense) return launch_dense(ctx, m, delta, xm, m_out, worker0, R, round, msg, msg_bits, sel_idx, sel_level);
   if (ctx->cfg.sparsifier == QSL_TOPK)
     return launch_compress<QSL_TOPK>(ctx, m, delta, xm, m_out, worker0, R, round, msg, msg_bits, sel_idx, sel_level);
@@ -1100,6 +1134,14 @@ static void launch_directory(const DevCtx& c, hipStream_t st, const uint8_t* msg
   else k_msg_directory<4><<<dim3(2048, R), BLOCK, 0, st>>>(c, msg, rows, dir, ndir, pile);
 }
 
+// Whether k_aggregate_small takes the listed messages.  Every block reads all of their entries, so they have to be few; where `out`
+// is added to it saves no launch and pays only against the look-ups of many messages (GPU and call, us, by clearing and look-ups /
+// this way: 8 x 1,000 entries, d = 50,000: 12.2 / 10.8; 8 x 4,000, d = 4,200: 11.4 / 19.2; 35 x 100, d = 130,000, added: 16.1 / 8.9;
+// 8 x 1,000, d = 260,000, added: 8.7 / 8.9).
+static bool aggregate_small(uint64_t d, uint32_t nnz_hint, uint32_t R, bool accumulate) {
+  return d <= 1u << 18 && static_cast<uint64_t>(nnz_hint) * R <= 1u << 13 && (!accumulate || R >= 24);
+}
+
 // The launches of the master line.  `dir` is room for R directories of `ndir` words, or null (then every message is
 // searched whole); `nnz_hint` sizes the grids; `crowd`: the levels' crowded cells of a context with several segments, or null.
 static qsl_status launch_aggregate(const DevCtx& c, hipStream_t st, uint32_t nnz_hint, uint32_t* dir, uint32_t ndir,
@@ -1141,6 +1183,13 @@ static qsl_status launch_aggregate(const DevCtx& c, hipStream_t st, uint32_t nnz
                                                                                             out, dir, ndir, cr, split, pile);
     if (pile.list)
       k_aggregate_cells<true><<<dim3(AGG_PILE_BLOCKS), BLOCK, 0, st>>>(c, msg, rows, in_order, R, scale, accumulate, out, dir, ndir, cr, split, pile);
+    QSL_HIP(hipGetLastError());
+    return QSL_OK;
+  }
+  if (aggregate_small(c.d, nnz_hint, R, accumulate != 0)) {
+    uint32_t span = SMALL_AGG_THREADS;                     // the fewest coordinates that give every thread of a block one
+    const uint32_t lds = 4 * (R + 2) * span;
+    k_aggregate_small<<<dim3(static_cast<uint32_t>((c.d + span - 1) / span)), SMALL_AGG_THREADS, lds, st>>>(c, msg, rows, R, scale, accumulate, out, span);
     QSL_HIP(hipGetLastError());
     return QSL_OK;
   }

@@ -103,6 +103,21 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3, 3))) v
   }
 }
 
+typedef uint32_t u2u __attribute__((ext_vector_type(2), aligned(4)));
+// `width` (1 .. 32) bits from bit `bit` of a message on, by one 8-byte read that stays inside its cap_words words
+struct FieldRead { u2u w; uint32_t sh; };
+__device__ __forceinline__ FieldRead read_field(const uint32_t* words, uint64_t bit, uint32_t cap_words) {
+  const uint64_t q = min(bit >> 5, static_cast<uint64_t>(cap_words) - 2);
+  FieldRead f;
+  f.w = *reinterpret_cast<const u2u*>(words + q);
+  f.sh = static_cast<uint32_t>(bit - q * 32) & 63u;
+  return f;
+}
+__device__ __forceinline__ uint32_t field_of(const FieldRead& f, uint32_t width) {
+  const uint64_t v = (static_cast<uint64_t>(f.w.y) << 32 | f.w.x) >> f.sh;
+  return width == 32 ? static_cast<uint32_t>(v) : static_cast<uint32_t>(v) & ((1u << width) - 1u);
+}
+
 struct RowList { uint32_t row[64]; };
 constexpr uint32_t AGG_ENTRIES = 32;     // message entries per block; 8 threads look one entry up in parallel
 constexpr uint32_t AGG_DIR_SHIFT = 10;   // a directory entry per 1024 coordinates
@@ -221,6 +236,61 @@ __global__ __launch_bounds__(BLOCK) void k_aggregate(DevCtx c, const uint8_t* ms
       }
     }
     __syncthreads();                                       // s_val and s_has are reused by the next tile
+  }
+}
+
+// Few entries in all, on a short vector: the whole master line in one launch, whether `out` is added to or written.  A block owns
+// `span` coordinates, with room in LDS for every message's value of each; its waves go through all the messages' entries
+// (wave v: messages v, v + waves, ...) and put those of its range in their places; then each thread adds up a coordinate's values
+// in list order.  Two barriers, three dependent reads: 15 messages of 40 entries on 7,850 coordinates 4.5 us, where clearing and
+// k_aggregate are two launches of 2.0 and 8.4 us.
+constexpr uint32_t SMALL_AGG_THREADS = 512;
+__global__ __launch_bounds__(SMALL_AGG_THREADS) void k_aggregate_small(DevCtx c, const uint8_t* msg, RowList rows, uint32_t R, float scale,
+                                                                       int accumulate, float* out, uint32_t span) {
+  extern __shared__ float s_values[];                    // [R][span], then the messages that hold each coordinate, [span][2]
+  uint32_t* s_who = reinterpret_cast<uint32_t*>(s_values + R * span);
+  const uint32_t lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t base = blockIdx.x * span, n = min(span, static_cast<uint32_t>(c.d) - base);
+  // this wave's messages: their headers and first entries are read before the marks are cleared
+  constexpr uint32_t NW = SMALL_AGG_THREADS / 64, PER = 64 / NW;
+  const bool counts = is_qsgd(c.quantizer) && c.L > 1;
+  const uint32_t hdr = 1 + c.L + (counts ? c.L : 0);
+  uint32_t nnz[PER], idx[PER];
+#pragma unroll
+  for (uint32_t i = 0; i < PER; ++i) {
+    const uint32_t p = wave + i * NW;
+    nnz[i] = 0; idx[i] = 0;
+    if (p >= R) continue;                                // (uniform over the wave)
+    const uint32_t* words = reinterpret_cast<const uint32_t*>(msg + static_cast<uint64_t>(rows.row[p]) * c.cap_words * 4);
+    nnz[i] = min(words[0], c.K);
+    idx[i] = field_of(read_field(words, static_cast<uint64_t>(hdr) * 32 + static_cast<uint64_t>(min(lane, c.K - 1)) * c.w_idx, c.cap_words), c.w_idx);
+  }
+  for (uint32_t i = threadIdx.x; i < 2 * span; i += SMALL_AGG_THREADS) s_who[i] = 0;
+  __syncthreads();
+#pragma unroll
+  for (uint32_t i = 0; i < PER; ++i) {
+    const uint32_t p = wave + i * NW;
+    if (p >= R) break;
+    const uint32_t* words = reinterpret_cast<const uint32_t*>(msg + static_cast<uint64_t>(rows.row[p]) * c.cap_words * 4);
+    const uint64_t code_bit0 = (hdr + (static_cast<uint64_t>(nnz[i]) * c.w_idx + 31) / 32) * 32;
+    for (uint32_t j = lane; j < nnz[i]; j += WAVE) {
+      const uint32_t at = j < WAVE ? idx[i] : field_of(read_field(words, static_cast<uint64_t>(hdr) * 32 + static_cast<uint64_t>(j) * c.w_idx, c.cap_words), c.w_idx);
+      if (at >= c.d && blockIdx.x == 0) atomicOr(c.status, 4u);      // malformed message: the entry is skipped
+      if (at < base || at - base >= n) continue;
+      const uint32_t code = field_of(read_field(words, code_bit0 + static_cast<uint64_t>(j) * c.w_val, c.cap_words), c.w_val);
+      const uint32_t seg = c.L == 1 ? 0u : seg_of_coord(c, at);
+      s_values[p * span + (at - base)] = value_of_code(c, code, __uint_as_float(words[1 + seg]));
+      atomicOr(&s_who[2 * (at - base) + (p >> 5)], 1u << (p & 31u));
+    }
+  }
+  __syncthreads();
+  for (uint32_t i = threadIdx.x; i < n; i += SMALL_AGG_THREADS) {
+    uint64_t who = static_cast<uint64_t>(s_who[2 * i + 1]) << 32 | s_who[2 * i];
+    if (who == 0) { if (!accumulate) out[base + i] = 0.0f; continue; }
+    float sum = s_values[(__ffsll(static_cast<unsigned long long>(who)) - 1) * span + i];
+    for (who &= who - 1; who; who &= who - 1) sum = sum + s_values[(__ffsll(static_cast<unsigned long long>(who)) - 1) * span + i];
+    const float term = scale * sum;
+    out[base + i] = accumulate ? out[base + i] + term : term;
   }
 }
 
@@ -374,21 +444,6 @@ constexpr uint32_t NOBODY = 0xFFFFFFFFu;                 // a NaN that no value 
 
 struct AggPart { uint32_t t; uint16_t i, parts; };       // part i of the 2^parts equal parts of cell t
 struct AggCrowd { const AggPart* part; const uint32_t* bits; uint32_t n; };   // the parts of a level's crowded cells; a bit per cell (null: none is crowded)
-
-typedef uint32_t u2u __attribute__((ext_vector_type(2), aligned(4)));
-// `width` (1 .. 32) bits from bit `bit` of a message on, by one 8-byte read that stays inside its cap_words words
-struct FieldRead { u2u w; uint32_t sh; };
-__device__ __forceinline__ FieldRead read_field(const uint32_t* words, uint64_t bit, uint32_t cap_words) {
-  const uint64_t q = min(bit >> 5, static_cast<uint64_t>(cap_words) - 2);
-  FieldRead f;
-  f.w = *reinterpret_cast<const u2u*>(words + q);
-  f.sh = static_cast<uint32_t>(bit - q * 32) & 63u;
-  return f;
-}
-__device__ __forceinline__ uint32_t field_of(const FieldRead& f, uint32_t width) {
-  const uint64_t v = (static_cast<uint64_t>(f.w.y) << 32 | f.w.x) >> f.sh;
-  return width == 32 ? static_cast<uint32_t>(v) : static_cast<uint32_t>(v) & ((1u << width) - 1u);
-}
 
 // `split`: the cells that are not crowded are given to 2^split waves each (few cells with many entries: a short vector).
 // `pile`: cells that no plan could foresee, in a vector whose large coordinates stand side by side (AGG_PILE entries or more, a

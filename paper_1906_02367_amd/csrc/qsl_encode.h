@@ -135,18 +135,15 @@ __device__ __forceinline__ UnitScale unit_scale(const DevCtx& c, float sc, uint3
   return r;
 }
 
-// One selected coordinate (slot `slot` of the worker-major [R][K] arrays; coordinate idx, value bits): its code
-// (QSGD: Definition 1, example 1; Sign: Definition 2), the arrays the message is packed from, the optional debug outputs;
-// *g_out: the value that its message entry stands for.
-// Returns whether the coordinate is transmitted.  rk1: the random stream of the QSGD rounding.
-__device__ __forceinline__ bool encode_entry_at(const DevCtx& c, uint64_t slot, uint32_t idx, uint32_t bits, UnitScale us,
-                                                const RandKey& rk1, uint32_t* dbg_idx, uint16_t* dbg_level, float* g_out) {
+// One selected coordinate (coordinate idx, value bits): its level (QSGD: Definition 1, example 1; else 1) and sign (Definition 2),
+// *g_out: the value that its message entry stands for.  rk1: the random stream of the QSGD rounding.
+struct LevelSign { uint32_t level; bool neg; };
+__device__ __forceinline__ LevelSign level_of(const DevCtx& c, uint32_t idx, uint32_t bits, UnitScale us, const RandKey& rk1, float* g_out) {
   const float v = __uint_as_float(bits);
-  const bool neg = v < 0.0f;
-  uint32_t level;
-  float g;
+  LevelSign r;
+  r.neg = v < 0.0f; r.level = 1;
   if (is_qsgd(c.quantizer)) {
-    level = 0;
+    r.level = 0;
     if (us.scale > 0.0f) {
       const float a = fabsf(v) / us.scale;
       float t = a * static_cast<float>(c.s);
@@ -154,25 +151,39 @@ __device__ __forceinline__ bool encode_entry_at(const DevCtx& c, uint64_t slot, 
       const float fl = floorf(t);
       const float frac = t - fl;
       const float r01 = static_cast<float>(rand_word(rk1, idx) >> 8) * 0x1p-24f;
-      level = static_cast<uint32_t>(fl) + (r01 < frac ? 1u : 0u);
+      r.level = static_cast<uint32_t>(fl) + (r01 < frac ? 1u : 0u);
     }
-    g = qsgd_value(us.sent, level, c.s, neg);
-  } else if (c.quantizer == QSL_FP32) {
-    level = 1;
-    g = v;
-  } else {
-    level = 1;
-    g = neg ? -us.scale : us.scale;
-  }
-  if (is_qsgd(c.quantizer)) { c.sel_idx[slot] = idx; c.sel_code[slot] = level | (neg ? 0x80000000u : 0u); }   // k_pack_sent reads both
+    *g_out = qsgd_value(us.sent, r.level, c.s, r.neg);
+  } else if (c.quantizer == QSL_FP32) *g_out = v;
+  else *g_out = r.neg ? -us.scale : us.scale;
+  return r;
+}
+
+// ... of slot `slot` of the worker-major [R][K] arrays: the arrays the message is packed from, the optional debug outputs.
+// Returns whether the coordinate is transmitted.
+__device__ __forceinline__ bool encode_entry_at(const DevCtx& c, uint64_t slot, uint32_t idx, uint32_t bits, UnitScale us,
+                                                const RandKey& rk1, uint32_t* dbg_idx, uint16_t* dbg_level, float* g_out) {
+  const LevelSign x = level_of(c, idx, bits, us, rk1, g_out);
+  if (is_qsgd(c.quantizer)) { c.sel_idx[slot] = idx; c.sel_code[slot] = x.level | (x.neg ? 0x80000000u : 0u); }   // k_pack_sent reads both
   else {                                                 // every selected coordinate is sent: nothing to compact
     c.surv_idx[slot] = idx;
-    c.surv_code[slot] = c.quantizer == QSL_FP32 ? bits : (neg ? 1u : 0u);
+    c.surv_code[slot] = c.quantizer == QSL_FP32 ? bits : (x.neg ? 1u : 0u);
   }
   if (dbg_idx) dbg_idx[slot] = idx;
-  if (dbg_level) dbg_level[slot] = static_cast<uint16_t>(level);
-  *g_out = g;
-  return level != 0;
+  if (dbg_level) dbg_level[slot] = static_cast<uint16_t>(x.level);
+  return x.level != 0;
+}
+
+// ... for a message that is packed by the caller: *code, the entry's code field; `mp`, the worker's error memory, is updated.
+__device__ __forceinline__ bool encode_value(const DevCtx& c, uint64_t slot, uint32_t idx, uint32_t bits, UnitScale us, const RandKey& rk1,
+                                             uint32_t* dbg_idx, uint16_t* dbg_level, float* mp, uint32_t* code) {
+  float g;
+  const LevelSign x = level_of(c, idx, bits, us, rk1, &g);
+  if (dbg_idx) dbg_idx[slot] = idx;
+  if (dbg_level) dbg_level[slot] = static_cast<uint16_t>(x.level);
+  *code = c.quantizer == QSL_FP32 ? bits : is_qsgd(c.quantizer) ? (x.level - 1u) | (x.neg ? 1u << c.w_lev : 0u) : (x.neg ? 1u : 0u);
+  if (x.level != 0) mp[idx] = __uint_as_float(bits) - g;
+  return x.level != 0;
 }
 
 // ... and the error update m <- v - g on a transmitted coordinate (Algorithm 1, second worker line)

@@ -869,6 +869,58 @@ def test_index_free_edges(P, d, quantizer, s, factor):
     assert run.q.device_status() == B.OK
 
 
+# short vectors, one launch per call: both sides of the limits (4096, 8192, 16,384 coordinates, 4096 selected ones, guesses from 1024 groups
+# and from groups of four), ties that the guess lets through or not, ties at the threshold in several waves, an update formed from models
+@pytest.mark.parametrize("d,k", [(1, 1), (63, 40), (4_095, 513), (4_097, 1), (4_097, 4_096), (8_192, 512), (8_192, 1_024), (8_193, 1_025), (8_193, 2_049),
+                                 (16_383, 4_096), (16_384, 512), (16_384, 2_048), (16_384, 4_097), (16_385, 300)])
+@pytest.mark.parametrize("sparsifier,quantizer,s", [(W.TOPK, W.QSGD, 15), (W.TOPK, W.FP32, 1), (W.TOPK, W.SIGN_L4, 1), (W.RANDK, W.QSGD_SCALED, 4), (W.RANDK, W.SIGN_L1, 1)])
+def test_short_vectors(P, d, k, sparsifier, quantizer, s):
+    rng = np.random.default_rng(d + k)
+    R = 3
+    wl = custom(d, [0, d], [k], s, sparsifier, quantizer, R=R)
+    v = rng.standard_normal((4, R, d)).astype(f32)
+    v[1] = np.round(v[1] * 2)                                # few magnitudes
+    v[2, :, rng.random(d) < 0.99] = 0                        # fewer values than places
+    v[3, 0] = 1.5
+    run, op, m_host, _ = P.run_parity(wl, 4, deltas=v, worker0=5)
+    x, xhat = rng.standard_normal(d).astype(f32), rng.standard_normal((R, d)).astype(f32)
+    dev = run.q.device
+    m = torch.from_numpy(m_host).to(dev)
+    msg = run.q.new_msg(R).fill_(0xCD)
+    run.q.compress_diff(m, torch.from_numpy(x).to(dev), torch.from_numpy(xhat).to(dev), m, 5, 4, msg)
+    torch.cuda.synchronize()
+    for r in range(R):
+        o = op.compress(m_host[r], x - xhat[r], 5 + r, 4)
+        assert np.array_equal(msg[r].cpu().numpy(), o["msg"]) and np.array_equal(P.bits(m[r].cpu().numpy()), P.bits(o["m_out"]))
+
+
+# the master line in one launch: ranges of 512 coordinates, every number of messages up to 64, segments, entries shared by all messages
+@pytest.mark.parametrize("d,off,k,quantizer,s,R", [(1, [0, 1], [1], W.SIGN_L1, 1, 2), (511, [0, 511], [100], W.FP32, 1, 33), (513, [0, 200, 513], [40, 60], W.QSGD, 3, 64),
+                                                   (100_001, [0, 100_001], [128], W.SIGN_L1, 1, 64), (5_000, [0, 100, 5_000], [100, 400], W.SIGN_L2, 1, 9)])
+def test_aggregate_small(P, d, off, k, quantizer, s, R):
+    from paper_1906_02367_amd import binding as B
+    rng = np.random.default_rng(d + R)
+    wl = custom(d, off, k, s, W.TOPK, quantizer, R=R)
+    q, op = B.from_workload(wl), P.oracle_for(wl)
+    v = (rng.standard_normal((R, d)) * np.exp(2 * rng.standard_normal(d))).astype(f32)
+    v[1 % R] = 0                                             # zeros kept, of both signs (a QSGD message of none)
+    v[1 % R, ::2] = -0.0
+    msg, m = q.new_msg(R), torch.zeros(R, d, device=q.device)
+    q.compress(m, torch.from_numpy(v).to(q.device), m, 0, 0, msg)
+    torch.cuda.synchronize()
+    decoded = [op.decode(x) for x in msg.cpu().numpy()]
+    x0 = rng.standard_normal(d).astype(f32)
+    x0[::3] = -0.0
+    for lst in (list(range(R)), [R - 1, 0] if R > 1 else [0], list(rng.permutation(R))):
+        for accumulate in (False, True):
+            out = torch.from_numpy(x0).to(q.device)
+            q.aggregate(msg, out, -1.0 / R, worker_list=[int(r) for r in lst], accumulate=accumulate)
+            torch.cuda.synchronize()
+            want = _aggregate_by_definition(decoded, lst, -1.0 / R, x0, accumulate, d)
+            assert np.array_equal(out.cpu().numpy().view(np.uint32), want.view(np.uint32)), (lst, accumulate)
+    assert q.device_status() == B.OK
+
+
 # index-free messages of one segment: the norm of values from the smallest subnormal to 1e36, side by side in one wave (several windows
 # of exponents), alone in a chunk, and only subnormal ones; chunks of zeros; a last chunk of one coordinate.  Bit for bit (exact sums).
 @pytest.mark.parametrize("quantizer,s", [(W.SIGN_L1, 1), (W.SIGN_L2, 1), (W.QSGD, 15)])
