@@ -605,7 +605,7 @@ static qsl_status create_ctx(qsl_ctx** out, const qsl_config* cfg, void* hip_str
   const uint64_t o_sels = carve(sizeof(SelInfo) * NSEL), o_cbs = carve(sizeof(CbInfo) * NCB);
   const uint64_t o_samps = carve(sizeof(SelInfo) * samps.size());
   const uint64_t o_fsels = carve(sizeof(SelInfo) * std::max<size_t>(1, fsels.size()));
-  const uint64_t o_ones = carve(4ull * std::max<size_t>(1, ones.size()));
+  const uint64_t o_ones = carve(sizeof(OneInfo) * std::max<size_t>(1, ones.size()));
   const uint64_t o_fulls = carve(sizeof(SelInfo) * std::max<size_t>(1, fulls.size()));
   const uint64_t o_fast = carve(4ull * std::max<size_t>(1, fast.size()));
   const uint64_t o_small = carve(4ull * std::max<size_t>(1, smalls.size()));
@@ -708,7 +708,9 @@ static qsl_status create_ctx(qsl_ctx** out, const qsl_config* cfg, void* hip_str
   upload(o_sels, sels.data(), sizeof(SelInfo) * NSEL);
   upload(o_samps, samps.data(), sizeof(SelInfo) * samps.size());
   upload(o_fsels, fsels.data(), sizeof(SelInfo) * fsels.size());
-  upload(o_ones, ones.data(), 4ull * ones.size());
+  std::vector<OneInfo> one_infos;
+  for (uint32_t l : ones) one_infos.push_back(OneInfo{segs[l], l, 0});
+  upload(o_ones, one_infos.data(), sizeof(OneInfo) * one_infos.size());
   upload(o_fulls, fulls.data(), sizeof(SelInfo) * fulls.size());
   upload(o_cbs, cbs.data(), sizeof(CbInfo) * NCB);
   upload(o_fast, fast.data(), 4 * fast.size());
@@ -746,7 +748,7 @@ static qsl_status create_ctx(qsl_ctx** out, const qsl_config* cfg, void* hip_str
   c.sels = reinterpret_cast<const SelInfo*>(base + o_sels);
   c.samps = reinterpret_cast<const SelInfo*>(base + o_samps);
   c.fsels = reinterpret_cast<const SelInfo*>(base + o_fsels);
-  c.one_segs = reinterpret_cast<const uint32_t*>(base + o_ones); c.none = static_cast<uint32_t>(ones.size());
+  c.ones = reinterpret_cast<const OneInfo*>(base + o_ones); c.none = static_cast<uint32_t>(ones.size());
   c.cbs = reinterpret_cast<const CbInfo*>(base + o_cbs);
   c.fast_segs = reinterpret_cast<const uint32_t*>(base + o_fast);
   c.small_segs = reinterpret_cast<const uint32_t*>(base + o_small);
@@ -895,7 +897,7 @@ static qsl_status launch_compress(qsl_ctx* ctx, const float* m, const float* del
                                   uint16_t* sel_level) {
   DevCtx c = ctx->dc;                              // of this call
   hipStream_t st = ctx->stream;
-  if (static_cast<uint64_t>(std::max(std::max(c.NSEL, c.NCB), std::max(std::max(ctx->nsamp_blocks, c.nblock), c.NSELF + c.nfast + c.none))) * R > 0x7FFFFFFFull)
+  if (static_cast<uint64_t>(std::max(std::max(c.NSEL, c.NCB), std::max(ctx->nsamp_blocks, c.nblock + c.NSELF + c.nfast + c.none))) * R > 0x7FFFFFFFull)
     return QSL_ERR_UNSUPPORTED;                    // the list kernels use one-dimensional grids of (list entries x workers)
   if (xm != nullptr && static_cast<uint64_t>(((c.NWT + 3) / 4 + 7) / 8) * 8 * R > 0x7FFFFFFFull)
     return QSL_ERR_UNSUPPORTED;                    // ... and so does the streaming kernel when it reads x_t
@@ -942,30 +944,22 @@ static qsl_status launch_compress(qsl_ctx* ctx, const float* m, const float* del
   }
   if (timed) { QSL_HIP(hipEventRecord(ctx->ev[ctx->ev_used + 1], st)); ctx->ev_used += 2; }
 
-  // Units that a single block selects and encodes whole need nothing but v: their kernel runs on a stream of the
-  // context's own beside the kernels of the other units (one block works tens of microseconds on a unit of 40,960
-  // coordinates) and is joined before the messages are put together.
-  // With k_lean_one in the call the roles are swapped: the block units start on the caller's stream at once and
-  // k_lean_one follows on the second stream behind the event -- its blocks take a compute unit each (123 registers),
-  // so whichever kernel is dispatched first keeps the other waiting, and the block units are the longer (measured on
-  // the 161-tensor table: k_lean_one first 541-548 us per round, the three kernels 536 us).  Not while failed guesses
-  // are expected: the multi-pass kernels on the caller's stream read what k_lean_one finds out about its units.
-  // ... nor when some guessing units have several blocks: their three kernels would wait on the caller's stream behind
-  // the block units (161 tensors, one worker: 160 us per round that way, against 133 us with the block units on the second stream).
-  const bool swapped = c.nblock != 0 && c.none != 0 && c.NSELF == 0 && !safe;
-  const bool forked = c.nblock != 0 && !swapped && (c.NSELF != 0 || c.none != 0 || ctx->n_other != 0);
+  // Units that a single block selects and encodes whole need nothing but v.  Where every guessing unit has a single block as well,
+  // one launch takes them all, the block units first: they work longest.  (Two launches on two streams, side by side, paid 5 us
+  // at the fork and 9 at the join.)  Otherwise they run on a stream of the context's own beside the kernels of the other units
+  // (one block works tens of microseconds on a unit of 40,960 coordinates) and are joined before the messages are put together:
+  // the guessing units with several blocks would wait behind them (161 tensors, one worker: 160 us per round that way, against 133
+  // us with the block units on the second stream).  Also while failed guesses are expected: the multi-pass kernels on the
+  // caller's stream read what k_lean_one finds out about its units.
+  const bool together = c.nblock != 0 && c.none != 0 && c.NSELF == 0 && !safe;
+  const bool forked = c.nblock != 0 && !together && (c.NSELF != 0 || c.none != 0 || ctx->n_other != 0);
   // Guessing units of both kinds in one call (a single block: k_lean_one; several: the three kernels) and no block units:
   // k_lean_one goes to a stream of its own, beside the three kernels (160 tensors, one worker: 115 -> 106 us per round,
   // two workers 171 -> 162 us).  Beside k_block_units as well, three kernels at once, it loses (161 tensors, one worker:
   // 127 -> 134 us; four workers 293 -> 302 us).
   const bool one_aside = c.none != 0 && c.NSELF != 0 && c.nblock == 0 && !safe;
-  if (swapped) {
-    QSL_HIP(hipEventRecord(ctx->fork_ev, st));
-    QSL_HIP(hipStreamWaitEvent(ctx->side, ctx->fork_ev, 0));
-    k_block_units<SPARS><<<dim3(c.nblock * R), BIG, 0, st>>>(c, R, m_out, worker0, round, sel_idx, sel_level);
-    k_lean_one<SPARS><<<dim3(c.none * R), BIG, 0, ctx->side>>>(c, ctx->segs[0], R, m_out, worker0, round, sel_idx, sel_level, 0);
-    QSL_HIP(hipEventRecord(ctx->join_ev, ctx->side));
-  } else if (c.nblock) {
+  const OneInfo only = {ctx->segs[0], 0, 0};       // (a single segment's plan goes in the arguments)
+  if (c.nblock && !together) {
     hipStream_t bs = st;
     if (forked) {
       QSL_HIP(hipEventRecord(ctx->fork_ev, st));
@@ -978,12 +972,15 @@ static qsl_status launch_compress(qsl_ctx* ctx, const float* m, const float* del
   if (one_aside) {
     if (!forked) QSL_HIP(hipEventRecord(ctx->fork_ev, st));
     QSL_HIP(hipStreamWaitEvent(ctx->side2, ctx->fork_ev, 0));
-    k_lean_one<SPARS><<<dim3(c.none * R), BIG, 0, ctx->side2>>>(c, ctx->segs[0], R, m_out, worker0, round, sel_idx, sel_level, 0);
+    k_lean_one<SPARS, false><<<dim3(c.none * R), BIG, 0, ctx->side2>>>(c, only, R, m_out, worker0, round, sel_idx, sel_level, 0, 0);
     QSL_HIP(hipEventRecord(ctx->join2_ev, ctx->side2));
   }
   if (ctx->nfull_blocks) k_full<<<dim3(ctx->nfull_blocks, R), BLOCK, 0, st>>>(c, m_out);
   // guessing units of a single block: the whole way from the slots to the encoded entries in one launch
-  if (c.none && !swapped && !one_aside) k_lean_one<SPARS><<<dim3(c.none * R), BIG, 0, st>>>(c, ctx->segs[0], R, m_out, worker0, round, sel_idx, sel_level, safe ? 1 : 0);
+  if (together) {
+    const uint32_t n_block = c.nblock * R;
+    k_lean_one<SPARS, true><<<dim3(n_block + c.none * R), BIG, 0, st>>>(c, only, R, m_out, worker0, round, sel_idx, sel_level, 0, n_block);
+  } else if (c.none && !one_aside) k_lean_one<SPARS, false><<<dim3(c.none * R), BIG, 0, st>>>(c, only, R, m_out, worker0, round, sel_idx, sel_level, safe ? 1 : 0, 0);
   if (c.NSELF) {                                   // guessing units: candidates' histogram, threshold bin and dense list
     k_lean_hist<SPARS><<<dim3(c.NSELF * R), BIG, 0, st>>>(c, ctx->segs[0], R, m_out, safe ? 1 : 0);
     k_lean_mark<SPARS><<<dim3(c.NSELF * R), BIG, 0, st>>>(c, ctx->segs[0], R, m_out, safe ? 1 : 0);
@@ -1017,7 +1014,7 @@ static qsl_status launch_compress(qsl_ctx* ctx, const float* m, const float* del
   if (c.NSELF)
     k_lean_emit<SPARS><<<dim3((c.NSELF + c.nfast) * R), BIG, 0, st>>>(c, ctx->segs[0], R, c.NSELF * R, m_out, worker0, round,
                                                                      sel_idx, sel_level, safe ? 1 : 0);
-  if (forked || swapped) QSL_HIP(hipStreamWaitEvent(st, ctx->join_ev, 0));
+  if (forked) QSL_HIP(hipStreamWaitEvent(st, ctx->join_ev, 0));
   if (one_aside) QSL_HIP(hipStreamWaitEvent(st, ctx->join2_ev, 0));
   const uint32_t nzero = safe ? c.nbig : ctx->nbig_general;
   if (is_qsgd(c.quantizer)) {                      // entries may drop out: the message from the selected arrays, a block per 256 slots

@@ -33,7 +33,7 @@ __device__ __forceinline__ double cube_root_fixed(double x) {
   return y;
 }
 
-__device__ float finalize_scale(const uint64_t* acc, uint32_t quantizer, uint32_t k) {
+__device__ __forceinline__ float finalize_scale(const uint64_t* acc, uint32_t quantizer, uint32_t k) {
   const int power = static_cast<int>(norm_power(quantizer));
   const uint32_t lane = lane_id();
   const uint64_t a = lane < acc_slots(quantizer) ? acc[lane] : 0;
@@ -203,7 +203,7 @@ __device__ __forceinline__ bool encode_entry(const DevCtx& c, uint32_t w, uint64
 // added up, the fp32 scale, the codes and the error update of the unit's k selected coordinates (already in the
 // selected arrays), the unit's state.
 template <uint32_t NT, uint32_t ROWS>
-__device__ void block_encode_tail(const DevCtx& c, const SegInfo& sg, uint32_t w, uint64_t u, uint32_t tau, uint32_t need,
+__device__ __forceinline__ void block_encode_tail(const DevCtx& c, const SegInfo& sg, uint32_t w, uint64_t u, uint32_t tau, uint32_t need,
                                   uint32_t worker0, uint64_t round, float* m_out, uint32_t* dbg_idx, uint16_t* dbg_level,
                                   uint64_t* acc, float* s_scale, uint32_t* s_count) {
   constexpr uint32_t NW = NT / 64, PW = (ACC_SLOTS + NW - 1) / NW;      // digit counters per wave

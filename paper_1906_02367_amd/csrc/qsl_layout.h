@@ -75,6 +75,8 @@ constexpr uint32_t NO_CHUNK = 0xFFFFFFFFu;
 struct SelInfo { uint32_t seg, j, pad0, pad1; };                    // one block of a selection kernel
 struct CbInfo { uint32_t seg, b, pad0, pad1; };                     // one compaction block
 
+struct OneInfo { SegInfo sg; uint32_t seg, pad; };                  // a unit of k_lean_one: its plan and its segment in one read
+
 // Every field is written by exactly one kernel of a call and read only by later kernels (the blocks of
 // one launch start at different times: a field that a launch both reads and rewrites would show late
 // blocks the new value).
@@ -113,7 +115,7 @@ struct DevCtx {
   uint2* ovf; uint64_t ovf_stride;      // per worker: overflow pools, for chunks with more candidates than a slot holds
   uint32_t* slot_key; uint32_t* ovf_key; // Rand_k only: the rank key (random word) of every slot element / pool entry
   uint2* d0; uint32_t* d0_key; uint64_t d0_stride;   // per worker: dense, coordinate-ordered candidate lists (+ keys, Rand_k)
-  const uint32_t* one_segs; // the guessing segments whose units have a single block: k_lean_one takes them (heaviest first)
+  const OneInfo* ones;      // the guessing segments whose units have a single block: k_lean_one takes them (heaviest first)
   uint32_t* wave_cnt;   // [R][NWC]: candidates met by each wave of k_lean_hist
   uint32_t* wave_sel;   // [R][NWC]: of these, how many lie in the bins above the threshold's (k_lean_mark)
   uint4* tlist;         // [R][nfast][LISTCAP]: the candidates in the threshold's bin: (place in the dense list, value bits, key, -)
@@ -134,7 +136,7 @@ struct DevCtx {
   uint64_t d, seed;
   uint32_t dense;       // 1: every coordinate is kept and the messages have the index-free format
   uint32_t L, K, NWT, NSEL, NCB, NWC, QB, NSELF, nfast, nblock, Rmax, nbig, s, w_idx, w_lev, w_val, sparsifier, quantizer, cap_words;
-  uint32_t none;        // entries of one_segs
+  uint32_t none;        // entries of ones
   uint32_t win;         // 1: in this call the only segment goes the way of the window (a dense k on a large vector), the multi-pass kernels standing by
 };
 
@@ -172,7 +174,7 @@ __device__ __forceinline__ bool settled(const DevCtx& c, const UnitState& us) {
 // holds fewer than `target` entries, returns bin 0 with *above = total - hist[0].  If `clear`,
 // zeroes the histogram afterwards.  COPIES > 1: the histogram is the sum of COPIES arrays HBINS apart.
 template <uint32_t NT, uint32_t NBINS = HBINS, uint32_t COPIES = 1>
-__device__ uint32_t find_from_top(uint32_t* hist, uint32_t target, uint32_t* above, uint64_t* scratch,
+__device__ __forceinline__ uint32_t find_from_top(uint32_t* hist, uint32_t target, uint32_t* above, uint64_t* scratch,
                                   uint32_t* result, bool clear) {
   constexpr uint32_t PER = NBINS / NT;
   static_assert(PER >= 1 && PER * NT == NBINS, "bins must divide evenly over the threads");
@@ -214,7 +216,7 @@ __device__ uint32_t find_from_top(uint32_t* hist, uint32_t target, uint32_t* abo
 // result[3]: for t1; result[4]: entries in the bin of t0; result[5]: entries in all.  A rank beyond the total gives
 // bin 0 with "above" = total - hist[0], as in find_from_top.
 template <uint32_t NT, uint32_t COPIES = 1>
-__device__ void find2_from_top(uint32_t* hist, uint32_t t0, uint32_t t1, uint64_t* scratch, uint32_t* result, bool clear) {
+__device__ __forceinline__ void find2_from_top(uint32_t* hist, uint32_t t0, uint32_t t1, uint64_t* scratch, uint32_t* result, bool clear) {
   constexpr uint32_t PER = HBINS / NT;
   static_assert(PER >= 1 && PER * NT == HBINS, "bins must divide evenly over the threads");
   const uint32_t t = threadIdx.x;

@@ -10,7 +10,8 @@
 //                 worker line).  Extra blocks, one per guessing unit, take the units whose guess failed or whose
 //                 threshold bin is too crowded for the list: one block selects exactly, by radix digits, from the
 //                 dense list or from v itself.
-//   k_lean_one    the three steps above in one launch, for a unit that has a single block in them
+//   k_lean_one    the three steps above in one launch, for a unit that has a single block in them (beside them, in the same launch, the
+//                 block units of k_block_units)
 // The result never depends on the guess or on the bins: they only decide how much work the exact selection is.
 // Part of the single translation unit qsl.hip (included after qsl_encode.h); not a public header.
 #pragma once
@@ -331,7 +332,7 @@ __global__ __launch_bounds__(BIG) void k_lean_mark(DevCtx c, SegInfo one, uint32
 // without a launch in between.
 // ------------------------------------------------------------------------------------------------
 template <int SPARS>
-__device__ void block_unit(const DevCtx& c, const SegInfo& sg, uint32_t w, uint64_t u, const float* vp, uint32_t worker0,
+__device__ __forceinline__ void block_unit(const DevCtx& c, const SegInfo& sg, uint32_t w, uint64_t u, const float* vp, uint32_t worker0,
                            uint64_t round, float* m_out, uint32_t* dbg_idx, uint16_t* dbg_level, uint32_t* lh,
                            uint64_t* acc, uint64_t* scratch, uint32_t* result, float* s_scale, uint32_t* s_count) {
   const RandKey rk = make_rand_key(c.seed, worker0 + w, round, 0);
@@ -341,13 +342,13 @@ __device__ void block_unit(const DevCtx& c, const SegInfo& sg, uint32_t w, uint6
   // the four coordinates (g * 64 + l) * 4 .. + 3 of group g, so that a load of the wave is 1 KB in a row.  (A thread with
   // 36 consecutive coordinates of its own made every load touch 64 cache lines, and the first pass over a unit of 36,864
   // coordinates, which comes from memory, took 14 of the block's 43 us.)
-  // A pass: the loads of five groups are issued together, then f(e, bits[4], keys[4], nv) sees the lane's four
+  // A pass: the loads of all ten groups are issued together, then f(e, bits[4], keys[4], nv) sees the lane's four
   // coordinates of each group (the first nv of them lie inside the unit), group after group; every lane of the wave
   // makes the same calls.
   const uint32_t gw = (n + (BIG / 64) * 256 - 1) / ((BIG / 64) * 256);
   const uint32_t wbase = wave * gw * 256;
   auto pass = [&](auto&& f) {
-    constexpr uint32_t G = 5;                        // (ten at once: the compiler spills, 600 bytes per lane)
+    constexpr uint32_t G = 10;
     for (uint32_t g0 = 0; g0 < gw; g0 += G) {
       f4u x[G];
 #pragma unroll
@@ -469,7 +470,7 @@ __global__ __launch_bounds__(BIG) void k_block_units(DevCtx c, uint32_t R, float
 // ------------------------------------------------------------------------------------------------
 enum { FROM_LIST, FROM_V, FROM_PARTS };             // FROM_PARTS: `n` places in parts of `cap`, the first part_n[p] of part p filled
 template <int SPARS, int FROM>
-__device__ void block_select_encode(const DevCtx& c, const SegInfo& sg, uint32_t w, uint64_t u, const float* vp,
+__device__ __forceinline__ void block_select_encode(const DevCtx& c, const SegInfo& sg, uint32_t w, uint64_t u, const float* vp,
                                     const uint2* d0, const uint32_t* d0k, uint64_t n, uint32_t cap, const uint32_t* part_n,
                                     uint32_t worker0, uint64_t round,
                                     float* m_out, uint32_t* dbg_idx, uint16_t* dbg_level, uint32_t* lh, uint64_t* acc,
@@ -723,28 +724,173 @@ __global__ __launch_bounds__(BIG) void k_lean_emit(DevCtx c, SegInfo one, uint32
 // ------------------------------------------------------------------------------------------------
 // A guessing unit that the plan gives a single block in the three kernels above needs none of their launch
 // boundaries: what they hand each other through memory (histogram, per-wave counts, norm digits, short list) one
-// block can keep in LDS, with barriers where they had kernel ends.  Same steps, same results; the dense list is still
-// written (the rescue of a crowded threshold bin reads it, and so does the ordered output).
+// block can keep in LDS, with barriers where they had kernel ends.  The slot rows are walked through once: a wave holds up to
+// eight of them in registers from the counting to the writing of the candidates, in coordinate order, to a list in LDS (in
+// memory, as there, if there are more than ONE_CAP); everything after that takes the list a thread per entry, where a walk through
+// the rows, most of whose places are empty, took two visits of a wave per row, twice.
+// What bounds it is the block with the largest unit: 53,000 cycles for 5,500 candidates in 144 rows (its plan and rows 7,700, their
+// histogram 12,100, the list, the threshold's bin and the digits 19,800, the rest 13,000), 65,000 by two walks.  160 tensors, four
+// workers: a round 245 -> 239 us; 161 tensors, eight workers, with the block units in the same launch: 504 -> 488 us.  A block takes
+// a compute unit, by its LDS as by its registers.
+// TOGETHER: the first n_block blocks are those of k_block_units, which work longest; without it the kernel is 1 % of a round faster
+// where there are none.  (Everything that these kernels call is inlined: a function called costs each of them 600 bytes of scratch
+// memory a lane, and twice the time.)
 // ------------------------------------------------------------------------------------------------
-template <int SPARS>
-__global__ __launch_bounds__(BIG) void k_lean_one(DevCtx c, SegInfo one, uint32_t R, float* m_out, uint32_t worker0,
-                                                  uint64_t round, uint32_t* dbg_idx, uint16_t* dbg_level, int safe) {
-  __shared__ uint32_t lh[HBINS];
-  __shared__ uint64_t acc[LEAN_ROWS * (ACC_SLOTS + 1)];
-  __shared__ uint4 s_list[LISTCAP];
-  __shared__ uint8_t s_sel[LISTCAP];
-  __shared__ uint64_t scratch[17];
-  __shared__ uint32_t result[6], s_ctr[CTR_LINES], s_wcnt[BIG / 64], s_wsel[BIG / 64], s_nlist, s_tau, s_need, s_count;
-  __shared__ float s_scale;
+constexpr uint32_t ONE_CAP = 8192;                   // candidates that the list in LDS takes: 64 KB (Rand_k: 96 KB)
+constexpr uint32_t ONE_STEPS = 8;                    // list entries per thread whose places are worked out together
+
+// what the list's phases share
+struct OneShared {
+  uint32_t lh[HBINS];
+  uint64_t acc[LEAN_ROWS * (ACC_SLOTS + 1)];
+  uint64_t scratch[17], digits[ACC_SLOTS], list[LISTCAP];      // list: key << 32 | ~place; a larger one ranks before
+  uint32_t result[6], ctr[CTR_LINES], wcnt[BIG / 64], pos[ONE_STEPS * (BIG / 64)], nlist, tau, tie, need, count;
+  float scale;
+};
+
+// From the list (element p by load(p, &idx, &bits, &key)) to the encoded entries.  The histogram has been scanned: `above`
+// candidates lie above the bin `taubin`, which holds at most LISTCAP.
+template <typename Load>
+__device__ __forceinline__ void lean_one_list(const DevCtx& c, const SegInfo& sg, uint32_t w, uint64_t u, uint32_t cand, uint32_t T, uint32_t sh,
+                                              uint32_t taubin, uint32_t above, Load&& load, OneShared& s, uint32_t worker0, uint64_t round,
+                                              float* m_out, uint32_t* dbg_idx, uint16_t* dbg_level) {
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = lane_id();
+  const uint32_t power = norm_power(c.quantizer), st = acc_stride(c.quantizer), ns = acc_slots(c.quantizer);
+  const bool need_norm = c.quantizer != QSL_FP32;                 // (uniform)
+  uint64_t* mine = s.acc + ((wave & 7u) * 8 + (lane & 7u)) * st;
+  // certainly selected: digits; in the threshold's bin: to the short list
+  for (uint32_t p0 = wave * WAVE; p0 < cand; p0 += BIG) {         // (uniform over the wave)
+    const uint32_t p = p0 + lane;
+    uint32_t idx = 0, bits = 0, key = 0, bin = 0;
+    if (p < cand) { load(p, &idx, &bits, &key); bin = lean_bin(key, T, sh); }
+    if (p < cand && bin > taubin && need_norm) add_digits(mine, bits, power);
+    const bool inside = p < cand && bin == taubin;
+    const uint64_t ib = __ballot(inside);
+    if (ib != 0) {
+      uint32_t base = 0;
+      if (lane == 0) base = atomicAdd(&s.nlist, static_cast<uint32_t>(__popcll(ib)));
+      const uint32_t q = lane_value(base, 0) + popc_below(ib);
+      if (inside && q < LISTCAP) s.list[q] = static_cast<uint64_t>(key) << 32 | (0xFFFFFFFFu - p);
+    }
+  }
+  __syncthreads();
+  const uint32_t n_list = min(s.nlist, LISTCAP), k_rem = sg.k - above;      // k_rem >= 1 of the bin's are selected
+  {                                                               // ranked one against the other, SUB lanes per entry
+    constexpr uint32_t SUB = BIG / LISTCAP;
+    const uint32_t sub = threadIdx.x % SUB, me = threadIdx.x / SUB;
+    if (wave * (WAVE / SUB) < n_list) {                           // (uniform over the wave)
+      const uint64_t x = s.list[min(me, n_list - 1)];
+      uint32_t rank = 0;
+      for (uint32_t j = 0; j < n_list; j += 4 * SUB) {            // four reads in flight
+        uint64_t o[4];
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) o[i] = s.list[min(j + i * SUB + sub, LISTCAP - 1)];
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) rank += j + i * SUB + sub < n_list && o[i] > x ? 1u : 0u;
+      }
+#pragma unroll
+      for (int o = SUB / 2; o > 0; o >>= 1) rank += __shfl_xor(rank, o, WAVE);
+      if (sub == 0 && me < n_list && rank < k_rem) {
+        uint32_t idx, bits, key;
+        load(0xFFFFFFFFu - static_cast<uint32_t>(x), &idx, &bits, &key);
+        if (need_norm) add_digits(mine, bits, power);
+        if (rank == k_rem - 1) { s.tau = key; s.tie = 0xFFFFFFFFu - static_cast<uint32_t>(x); }      // the k-th largest key, the last kept tie
+      }
+    }
+  }
+  __syncthreads();
+  const uint32_t tau = s.tau, tie = s.tie;
+  if (need_norm) {                                                // the rows added up, a row per lane
+    for (uint32_t d = wave; d < ns; d += BIG / 64) {
+      const uint64_t x = wave_sum64(s.acc[lane * st + d]);
+      if (lane == 0) s.digits[d] = x;
+    }
+    __syncthreads();
+    if (wave == 0) {
+      const float sc = finalize_scale(s.digits, c.quantizer, sg.k);
+      if (lane == 0) s.scale = sc;
+    }
+  }
+  const RandKey rk1 = make_rand_key(c.seed, worker0 + w, round, 1);
+  uint32_t run = 0, nsent = 0, nties = 0;
+  UnitScale usc = {0.0f, 0.0f};
+  for (uint32_t g0 = 0; g0 < cand; g0 += ONE_STEPS * BIG) {       // ONE_STEPS entries of every thread: their places, then their codes
+    const uint32_t steps = min(ONE_STEPS, (cand - g0 + BIG - 1) / BIG);
+    uint32_t mask = 0;
+    for (uint32_t i = 0; i < steps; ++i) {
+      const uint32_t p = g0 + i * BIG + threadIdx.x;
+      bool take = false;
+      if (p < cand) {
+        uint32_t idx, bits, key;
+        load(p, &idx, &bits, &key);
+        take = key > tau || (key == tau && p <= tie);
+        nties += take && key == tau ? 1u : 0u;
+      }
+      mask |= (take ? 1u : 0u) << i;
+      const uint64_t tb = __ballot(take);
+      if (lane == 0) s.pos[i * (BIG / 64) + wave] = static_cast<uint32_t>(__popcll(tb));
+    }
+    __syncthreads();
+    if (g0 == 0) usc = unit_scale(c, s.scale, sg.k);
+    for (uint32_t i = 0; i < steps; ++i) {
+      const uint32_t inc = wave_inclusive_scan32(lane < BIG / 64 ? s.pos[i * (BIG / 64) + lane] : 0u);
+      const bool take = (mask >> i) & 1u;
+      const uint64_t tb = __ballot(take);
+      const uint32_t first = run + (wave ? lane_value(inc, wave - 1) : 0u), pos = first + popc_below(tb);
+      run += lane_value(inc, BIG / 64 - 1);
+      bool sent = false;
+      if (take && pos < sg.k) {
+        uint32_t idx, bits, key;
+        load(g0 + i * BIG + threadIdx.x, &idx, &bits, &key);
+        sent = encode_entry(c, w, static_cast<uint64_t>(w) * c.K + sg.koff + pos, idx, bits, usc, rk1, m_out, dbg_idx, dbg_level);
+      }
+      if (is_qsgd(c.quantizer)) {                                 // survivors per block of 256 slots: 64 slots touch at most two
+        const uint64_t sb = __ballot(sent);
+        if (sb != 0) {
+          const uint32_t b_first = (sg.koff + first) >> 8;
+          const uint32_t n0 = static_cast<uint32_t>(__popcll(__ballot(sent && ((sg.koff + pos) >> 8) == b_first)));
+          const uint32_t n1 = static_cast<uint32_t>(__popcll(sb)) - n0;
+          if (lane == 0) {
+            uint32_t* bc = c.blk_cnt + static_cast<uint64_t>(w) * c.QB;
+            if (n0) atomicAdd(&bc[b_first], n0);
+            if (n1) atomicAdd(&bc[b_first + 1], n1);
+            nsent += n0 + n1;
+          }
+        }
+      }
+    }
+    if (g0 + ONE_STEPS * BIG < cand) __syncthreads();             // the counts' room is used again
+  }
+  if (__ballot(nties != 0) != 0) { nties = wave_sum(nties); if (lane == 0) atomicAdd(&s.need, nties); }
+  if (is_qsgd(c.quantizer) && c.L > 1 && lane == 0 && nsent) atomicAdd(&s.count, nsent);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    UnitState* usp = &c.units[u];
+    usp->tau = tau; usp->need = s.need; usp->n_gt = sg.k - s.need; usp->scale_bits = __float_as_uint(usc.sent);
+    if (is_qsgd(c.quantizer) && c.L > 1) usp->nnz = s.count;
+  }
+}
+
+template <int SPARS, bool TOGETHER>
+__global__ __launch_bounds__(BIG) void k_lean_one(DevCtx c, OneInfo one, uint32_t R, float* m_out, uint32_t worker0,
+                                                  uint64_t round, uint32_t* dbg_idx, uint16_t* dbg_level, int safe, uint32_t n_block) {
+  __shared__ OneShared s;
+  __shared__ uint2 s_ent[ONE_CAP];
+  __shared__ uint32_t s_key[SPARS == QSL_RANDK ? ONE_CAP : 1];
   constexpr uint32_t NW = BIG / 64;
-  const uint32_t w = blockIdx.x % R;                 // workers innermost, heaviest units first
-  const uint32_t seg = c.L == 1 ? 0u : c.one_segs[blockIdx.x / R];
-  const SegInfo sg = c.L == 1 ? one : c.segs[seg];
-  const uint64_t u = static_cast<uint64_t>(w) * c.L + seg;
+  if (TOGETHER && blockIdx.x < n_block) {            // (uniform) the block units' blocks come first: they work longest
+    const uint32_t seg = c.small_segs[blockIdx.x / R], bw = blockIdx.x % R;      // workers innermost, largest units first
+    const SegInfo bsg = c.segs[seg];
+    block_unit<SPARS>(c, bsg, bw, static_cast<uint64_t>(bw) * c.L + seg, m_out + static_cast<uint64_t>(bw) * c.d + bsg.start,
+                      worker0, round, m_out, dbg_idx, dbg_level, s.lh, s.acc, s.scratch, s.result, &s.scale, &s.count);
+    return;
+  }
+  const uint32_t bi = TOGETHER ? blockIdx.x - n_block : blockIdx.x, w = bi % R;      // workers innermost, heaviest units first
+  const OneInfo oi = c.L == 1 ? one : c.ones[bi / R];
+  const SegInfo& sg = oi.sg;
+  const uint64_t u = static_cast<uint64_t>(w) * c.L + oi.seg;
   UnitState* usp = &c.units[u];
-  const UnitState us = *usp;
-  const uint32_t T = us.T, sh = us.sh;
-  const uint32_t wave = threadIdx.x >> 6, lane = lane_id();
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = lane_id();
   const uint2* slots = c.slots + static_cast<uint64_t>(w) * c.slot_stride + sg.slot_off;
   const uint2* ovf = c.ovf + static_cast<uint64_t>(w) * c.ovf_stride + sg.ovf_off;
   const uint32_t* slot_key = SPARS == QSL_RANDK ? c.slot_key + static_cast<uint64_t>(w) * c.slot_stride + sg.slot_off : nullptr;
@@ -755,22 +901,28 @@ __global__ __launch_bounds__(BIG) void k_lean_one(DevCtx c, SegInfo one, uint32_
   const uint32_t rpw = (nrows + NW - 1) / NW;        // every wave a contiguous range of slot rows
   const uint64_t r_lo = static_cast<uint64_t>(wave) * rpw;
   const uint64_t r_hi = r_lo + rpw < nrows ? r_lo + rpw : nrows;
-  const uint32_t power = norm_power(c.quantizer);
-  const uint32_t st = acc_stride(c.quantizer);
-  constexpr int RIF = SPARS == QSL_RANDK ? 4 : ROWS_IN_FLIGHT;   // rows in flight (a Rand_k row carries its keys: more registers)
+  constexpr int RIF = SPARS == QSL_RANDK ? 4 : 8;   // rows in registers (a Rand_k row carries its keys)
 
-  // ---- the candidates' histogram and the number each wave holds (what k_lean_hist does)
-  RawRow rr[RIF];
+  // ---- the candidates' histogram and the number each wave holds
+  uint4 rq[RIF]; uint2 rkq[SPARS == QSL_RANDK ? RIF : 1];
+  auto load_row = [&](int b, uint64_t row) {
+    const RawRow r = load_slot_row(slots, slot_key, sg.lpc, sg.nwt, row, r_hi);
+    rq[b] = r.q;
+    if (SPARS == QSL_RANDK) rkq[b] = r.kq;
+  };
 #pragma unroll
-  for (int b = 0; b < RIF; ++b) rr[b] = load_slot_row(slots, slot_key, sg.lpc, sg.nwt, r_lo + b, r_hi);
-  for (uint32_t i = threadIdx.x; i < HBINS; i += BIG) lh[i] = 0;
-  for (uint32_t i = threadIdx.x; i < LEAN_ROWS * st; i += BIG) acc[i] = 0;
-  if (threadIdx.x < CTR_LINES) s_ctr[threadIdx.x] = c.ctr[(u * CTR_LINES + threadIdx.x) * PAD];
-  if (threadIdx.x == 0) { s_nlist = 0; s_need = 0; s_tau = 0; s_count = 0; }
+  for (int b = 0; b < RIF; ++b) load_row(b, r_lo + b);
+  const uint32_t T = usp->T, sh = usp->sh;
+  uint32_t ctr = 0;
+  if (threadIdx.x < CTR_LINES) ctr = c.ctr[(u * CTR_LINES + threadIdx.x) * PAD];
+  for (uint32_t i = threadIdx.x; i < HBINS; i += BIG) s.lh[i] = 0;
+  for (uint32_t i = threadIdx.x; i < LEAN_ROWS * acc_stride(c.quantizer); i += BIG) s.acc[i] = 0;
+  if (threadIdx.x < CTR_LINES) s.ctr[threadIdx.x] = ctr;
+  if (threadIdx.x == 0) { s.nlist = 0; s.need = 0; s.tau = 0; s.tie = 0; s.count = 0; s.scale = 0.0f; }
   __syncthreads();
-  uint32_t cand = 0;
-  for (uint32_t i = 0; i < NSUB; ++i) cand += s_ctr[i];
-  const bool failed = s_ctr[CTR_FAIL] != 0 || cand < sg.k || cand > sg.d0_cap;
+  const uint32_t cand = wave_sum(s.ctr[lane]);       // NSUB = 64 counters
+  static_assert(NSUB == WAVE, "a counter per lane");
+  const bool failed = s.ctr[CTR_FAIL] != 0 || cand < sg.k || cand > sg.d0_cap;
   if (threadIdx.x == 0) {
     usp->cand = cand; usp->fell_back = failed; usp->nnz = 0; usp->crowded = 0;
     if (failed && SPARS == QSL_TOPK) {                // as in k_lean_hist: towards where the candidates are
@@ -783,51 +935,94 @@ __global__ __launch_bounds__(BIG) void k_lean_one(DevCtx c, SegInfo one, uint32_
     if (safe) return;                                 // the multi-pass kernels of this call take the unit
     __syncthreads();
     block_select_encode<SPARS, FROM_V>(c, sg, w, u, m_out + static_cast<uint64_t>(w) * c.d + sg.start, nullptr, nullptr, sg.size, 0, nullptr,
-                                     worker0, round, m_out, dbg_idx, dbg_level, lh, acc, scratch, result, &s_scale, &s_count);
+                                     worker0, round, m_out, dbg_idx, dbg_level, s.lh, s.acc, s.scratch, s.result, &s.scale, &s.count);
     return;
   }
-  uint32_t seen = 0;
-  for (uint64_t row0 = r_lo; row0 < r_hi; row0 += RIF) {
-    if (row0 != r_lo) {
+  const bool in_lds = cand <= ONE_CAP;                // (uniform over the block)
+  // f(row): every row of the wave in turn; the first RIF are in registers the first time
+  auto walk = [&](bool again, auto&& f) {
+    for (uint64_t row0 = r_lo; row0 < r_hi; row0 += RIF) {
+      if (row0 != r_lo || (again && rpw > RIF)) {
 #pragma unroll
-      for (int b = 0; b < RIF; ++b) rr[b] = load_slot_row(slots, slot_key, sg.lpc, sg.nwt, row0 + b, r_hi);
-    }
-#pragma unroll
-    for (int b = 0; b < RIF; ++b) {
-      if (row0 + b >= r_hi) break;
-      const SlotRow r = parse_slot_row(rr[b], sg.lpc);
-      seen += r.n;
-      if (!r.spill) {
-        if (r.has0) atomicAdd(&lh[lean_bin(SPARS == QSL_TOPK ? key_of_value(r.bits0) : r.key0, T, sh)], 1u);
-        if (r.has1) atomicAdd(&lh[lean_bin(SPARS == QSL_TOPK ? key_of_value(r.bits1) : r.key1, T, sh)], 1u);
+        for (int b = 0; b < RIF; ++b) load_row(b, row0 + b);
       }
+#pragma unroll
+      for (int b = 0; b < RIF; ++b) {
+        if (row0 + b >= r_hi) break;                  // (uniform over the wave)
+        f(parse_slot_row(RawRow{rq[b], SPARS == QSL_RANDK ? rkq[SPARS == QSL_RANDK ? b : 0] : make_uint2(0, 0)}, sg.lpc));
+      }
+    }
+  };
+  // g(number, first place in the pool, first place in the list): the chunks whose candidates are in the overflow pool (in a loop of
+  // its own: they are few, and the loop above is unrolled)
+  auto walk_spilled = [&](uint32_t off, auto&& g) {
+    for (uint64_t row = r_lo; row < r_hi; ++row) {
+      const SlotRow r = parse_slot_row(load_slot_row(slots, slot_key, sg.lpc, sg.nwt, row, r_hi), sg.lpc);
+      uint32_t tot;
+      const uint32_t pos = off + wave_exclusive_scan32(r.n, &tot);
+      off += tot;
       for (uint64_t spilled = __ballot(r.spill); spilled; spilled &= spilled - 1) {
         const int holder = __ffsll(static_cast<unsigned long long>(spilled)) - 1;
-        const uint32_t cnt = __shfl(r.count, holder, WAVE), at = __shfl(r.ovf_at, holder, WAVE);
-        for (uint32_t e = lane; e < cnt; e += WAVE) {
-          const uint32_t key = SPARS == QSL_TOPK ? key_of_value(ovf[at + e].y) : ovf_key[at + e];
-          atomicAdd(&lh[lean_bin(key, T, sh)], 1u);
-        }
+        g(lane_value(r.count, holder), lane_value(r.ovf_at, holder), lane_value(pos, holder));
       }
     }
-  }
+  };
+  uint32_t seen = 0;
+  bool spill = false;
+  walk(false, [&](const SlotRow& r) {
+    seen += r.n;
+    spill = spill || r.spill;
+    if (!r.spill) {
+      if (r.has0) atomicAdd(&s.lh[lean_bin(SPARS == QSL_TOPK ? key_of_value(r.bits0) : r.key0, T, sh)], 1u);
+      if (r.has1) atomicAdd(&s.lh[lean_bin(SPARS == QSL_TOPK ? key_of_value(r.bits1) : r.key1, T, sh)], 1u);
+    }
+  });
+  const bool any_spill = __ballot(spill) != 0;
+  if (any_spill)
+    walk_spilled(0, [&](uint32_t cnt, uint32_t at, uint32_t) {
+      for (uint32_t e = lane; e < cnt; e += WAVE)
+        atomicAdd(&s.lh[lean_bin(SPARS == QSL_TOPK ? key_of_value(ovf[at + e].y) : ovf_key[at + e], T, sh)], 1u);
+    });
   seen = wave_sum(seen);
-  if (lane == 0) s_wcnt[wave] = seen;
-  // the first rows again, for the second walk (they come from the cache now)
-#pragma unroll
-  for (int b = 0; b < RIF; ++b) rr[b] = load_slot_row(slots, slot_key, sg.lpc, sg.nwt, r_lo + b, r_hi);
+  if (lane == 0) s.wcnt[wave] = seen;
   __syncthreads();
 
-  // ---- threshold bin, dense list, what is certainly selected, the short list (what k_lean_mark does)
-  find2_from_top<BIG>(lh, sg.k, sg.r_warm, scratch, result, false);
-  const uint32_t taubin = result[0], above = result[1], in_bin = result[4];
+  // ---- the candidates in coordinate order to the list; the threshold's bin; the next call's guess (as in k_lean_mark)
+  {
+    const uint32_t inc = wave_inclusive_scan32(lane < NW ? s.wcnt[lane] : 0u);
+    const uint32_t off0 = wave ? lane_value(inc, wave - 1) : 0u;
+    auto put = [&](uint32_t p, uint32_t idx, uint32_t bits, uint32_t key) {
+      if (in_lds) { if (p < ONE_CAP) { s_ent[p] = make_uint2(idx, bits); if (SPARS == QSL_RANDK) s_key[p] = key; } }
+      else if (p < sg.d0_cap) { d0[p] = make_uint2(idx, bits); if (SPARS == QSL_RANDK) d0k[p] = key; }
+    };
+    uint32_t off = off0;
+    walk(true, [&](const SlotRow& r) {
+      uint32_t tot;
+      const uint32_t pos = off + wave_exclusive_scan32(r.n, &tot);
+      off += tot;
+      if (!r.spill) {
+        if (r.has0) put(pos, r.idx0, r.bits0, r.key0);
+        if (r.has1) put(pos + (r.has0 ? 1u : 0u), r.idx1, r.bits1, r.key1);
+      }
+    });
+    if (any_spill)
+      walk_spilled(off0, [&](uint32_t cnt, uint32_t at, uint32_t first) {
+        for (uint32_t e = lane; e < cnt; e += WAVE) {
+          const uint2 ent = ovf[at + e];
+          put(first + e, ent.x, ent.y, SPARS == QSL_RANDK ? ovf_key[at + e] : 0u);
+        }
+      });
+    if (!in_lds) __threadfence_block();               // read back by other waves
+  }
+  find2_from_top<BIG>(s.lh, sg.k, sg.r_warm, s.scratch, s.result, false);
+  const uint32_t taubin = s.result[0], above = s.result[1], in_bin = s.result[4];
   const bool crowded = in_bin > LISTCAP;
   if (threadIdx.x == 0) {
     usp->taubin = taubin; usp->above = above; usp->crowded = crowded;
-    if (SPARS == QSL_TOPK) {                          // the next call's guess and bin width, as in k_lean_mark
+    if (SPARS == QSL_TOPK) {
       const uint32_t tau_lo = T + (taubin << sh);
       uint32_t T_next;
-      if (result[5] >= sg.r_warm) T_next = T + (result[2] << sh);
+      if (s.result[5] >= sg.r_warm) T_next = T + (s.result[2] << sh);
       else { const uint32_t down = max(tau_lo - T, 1u << sh); T_next = T > down ? T - down : 0u; }
       const uint32_t span = max(tau_lo - T_next, 1u) >> 10;
       uint32_t sh_next = 0;
@@ -836,170 +1031,28 @@ __global__ __launch_bounds__(BIG) void k_lean_one(DevCtx c, SegInfo one, uint32_
       usp->T_next = T_next; usp->sh_next = sh_next;
     }
   }
-  uint32_t off = 0;
-  for (uint32_t g = 0; g < wave; ++g) off += s_wcnt[g];
-  const uint32_t d_off = off, cnt_w = s_wcnt[wave];
-  uint64_t* mine = acc + ((wave & 7u) * 8 + (lane & 7u)) * st;
-  uint32_t n_above = 0;
-  auto visit = [&](bool has, uint32_t p, uint32_t idx, uint32_t bits, uint32_t key) {
-    bool inside = false;
-    if (has) {
-      d0[p] = make_uint2(idx, bits);
-      if (SPARS == QSL_RANDK) d0k[p] = key;
-      const uint32_t b = lean_bin(key, T, sh);
-      if (b > taubin) { ++n_above; add_digits(mine, bits, power); }
-      else inside = b == taubin && !crowded;
-    }
-    const uint64_t ib = __ballot(inside);
-    if (ib != 0) {                                   // wave-uniform
-      const int first = __ffsll(static_cast<unsigned long long>(ib)) - 1;
-      uint32_t base = 0;
-      if (static_cast<int>(lane) == first) base = atomicAdd(&s_nlist, static_cast<uint32_t>(__popcll(ib)));
-      base = lane_value(base, first);
-      const uint32_t q = base + popc_below(ib);
-      if (inside && q < LISTCAP) s_list[q] = make_uint4(p, bits, key, idx);
-    }
-  };
-  for (uint64_t row0 = r_lo; row0 < r_hi; row0 += RIF) {
-    if (row0 != r_lo) {
-#pragma unroll
-      for (int b = 0; b < RIF; ++b) rr[b] = load_slot_row(slots, slot_key, sg.lpc, sg.nwt, row0 + b, r_hi);
-    }
-#pragma unroll
-    for (int b = 0; b < RIF; ++b) {
-      if (row0 + b >= r_hi) break;
-      const SlotRow r = parse_slot_row(rr[b], sg.lpc);
-      uint32_t tot;
-      const uint32_t pos = off + wave_exclusive_scan32(r.n, &tot);
-      off += tot;
-      const bool h0 = !r.spill && r.has0, h1 = !r.spill && r.has1;
-      if (__ballot(h0 || h1) != 0) {
-        visit(h0, pos, r.idx0, r.bits0, SPARS == QSL_TOPK ? key_of_value(r.bits0) : r.key0);
-        visit(h1, pos + (h0 ? 1u : 0u), r.idx1, r.bits1, SPARS == QSL_TOPK ? key_of_value(r.bits1) : r.key1);
-      }
-      for (uint64_t spilled = __ballot(r.spill); spilled; spilled &= spilled - 1) {
-        const int holder = __ffsll(static_cast<unsigned long long>(spilled)) - 1;
-        const uint32_t cnt = __shfl(r.count, holder, WAVE), at = __shfl(r.ovf_at, holder, WAVE);
-        const uint32_t first = __shfl(pos, holder, WAVE);
-        for (uint32_t e0 = 0; e0 < cnt; e0 += WAVE) {
-          const uint32_t e = e0 + lane;
-          uint2 ent = make_uint2(0, 0); uint32_t key = 0;
-          if (e < cnt) { ent = ovf[at + e]; key = SPARS == QSL_TOPK ? key_of_value(ent.y) : ovf_key[at + e]; }
-          visit(e < cnt, first + e, ent.x, ent.y, key);
-        }
-      }
-    }
-  }
-  n_above = wave_sum(n_above);
-  if (lane == 0) s_wsel[wave] = n_above;
-  __threadfence_block();                             // the dense list is read back below, by other waves too
-  __syncthreads();
-  if (crowded) {                                     // more ties in the threshold's bin than the short list holds
-    block_select_encode<SPARS, FROM_LIST>(c, sg, w, u, nullptr, d0, d0k, cand, 0, nullptr, worker0, round, m_out, dbg_idx, dbg_level, lh, acc,
-                                      scratch, result, &s_scale, &s_count);
-    return;
-  }
-
-  // ---- exact threshold from the short list, the scale, ordered output and codes (what k_lean_emit does)
-  // this wave's first candidates, issued before the reductions
-  uint2 ent_first = make_uint2(0, 0);
-  uint32_t key_first = 0;
-  if (lane < cnt_w) { ent_first = d0[d_off + lane]; if (SPARS == QSL_RANDK) key_first = d0k[d_off + lane]; }
-  {                                                  // the accumulator rows added up into row 0 (as block_encode_tail does)
-    constexpr uint32_t PW = (ACC_SLOTS + NW - 1) / NW;
-    const uint32_t ns = acc_slots(c.quantizer);
-    uint64_t x[PW];
-#pragma unroll
-    for (uint32_t i = 0; i < PW; ++i) {
-      const uint32_t sl = wave + i * NW;
-      x[i] = 0;
-      if (sl < ns) x[i] = wave_sum64(acc[lane * st + sl]);       // LEAN_ROWS = 64 rows: one per lane
+  if (crowded) {                                     // more ties in the threshold's bin than the short list holds: selected from the list in memory
+    if (in_lds) {
+      for (uint32_t p = threadIdx.x; p < cand; p += BIG) { d0[p] = s_ent[p]; if (SPARS == QSL_RANDK) d0k[p] = s_key[p]; }
+      __threadfence_block();
     }
     __syncthreads();
-    if (lane == 0) {
-#pragma unroll
-      for (uint32_t i = 0; i < PW; ++i) if (wave + i * NW < ns) acc[wave + i * NW] = x[i];
-    }
+    block_select_encode<SPARS, FROM_LIST>(c, sg, w, u, nullptr, d0, d0k, cand, 0, nullptr, worker0, round, m_out, dbg_idx, dbg_level, s.lh, s.acc,
+                                      s.scratch, s.result, &s.scale, &s.count);
+    return;
   }
-  const uint32_t n_list = min(s_nlist, LISTCAP);
-  const uint32_t k_rem = sg.k - above;
-  uint4 me = make_uint4(0, 0, 0, 0);
-  if (threadIdx.x < n_list) me = s_list[threadIdx.x];
-  __syncthreads();
-  bool sel = false;
-  if (threadIdx.x < n_list) {
-    uint32_t rank = 0;
-    for (uint32_t j = 0; j < n_list; ++j) {
-      const uint4 o = s_list[j];
-      rank += (o.z > me.z || (o.z == me.z && o.x < me.x)) ? 1u : 0u;
-    }
-    sel = rank < k_rem;
-    s_sel[threadIdx.x] = sel;
-    if (rank == k_rem - 1) s_tau = me.z;
-    if (sel) add_digits(acc, me.y, power);
-  }
-  __syncthreads();
-  if (sel && me.z == s_tau) atomicAdd(&s_need, 1u);
-  if (wave == 0) {
-    const float sc = finalize_scale(acc, c.quantizer, sg.k);
-    if (lane == 0) s_scale = sc;
-  }
-  __syncthreads();
-  const UnitScale usc = unit_scale(c, s_scale, sg.k);
-  uint32_t s_off = 0;
-  for (uint32_t g = 0; g < wave; ++g) s_off += s_wsel[g];
-  {
-    uint32_t x = 0;
-    for (uint32_t j = lane; j < n_list; j += WAVE) x += (s_sel[j] && s_list[j].x < d_off) ? 1u : 0u;
-    s_off += wave_sum(x);
-  }
-  const RandKey rk1 = make_rand_key(c.seed, worker0 + w, round, 1);
-  uint32_t nsent = 0;
-  for (uint32_t e0 = 0; e0 < cnt_w; e0 += WAVE) {
-    const uint32_t e = e0 + lane;
-    const uint2 ent = ent_first;                                  // loaded one step ahead
-    const uint32_t key = key_first;
-    if (e + WAVE < cnt_w) { ent_first = d0[d_off + e + WAVE]; if (SPARS == QSL_RANDK) key_first = d0k[d_off + e + WAVE]; }
-    uint32_t bin = 0;
-    if (e < cnt_w) bin = lean_bin(SPARS == QSL_TOPK ? key_of_value(ent.y) : key, T, sh);
-    bool take = e < cnt_w && bin > taubin;
-    const bool maybe = e < cnt_w && bin == taubin;
-    if (__ballot(maybe) != 0) {
-      for (uint32_t j = 0; j < n_list; ++j) {
-        const uint32_t p = s_list[j].x;
-        if (maybe && p == d_off + e && s_sel[j]) take = true;
-      }
-    }
-    const uint64_t tb = __ballot(take);
-    const uint32_t pos = s_off + popc_below(tb);
-    bool sent = false;
-    if (take && pos < sg.k) {
-      const uint64_t slot = static_cast<uint64_t>(w) * c.K + sg.koff + pos;
-      sent = encode_entry(c, w, slot, ent.x, ent.y, usc, rk1, m_out, dbg_idx, dbg_level);
-    }
-    if (is_qsgd(c.quantizer)) {
-      const uint64_t sb = __ballot(sent);
-      if (sb != 0) {
-        const uint32_t b_first = (sg.koff + s_off) >> 8;
-        const bool in_first = ((sg.koff + pos) >> 8) == b_first;
-        const uint32_t n0 = static_cast<uint32_t>(__popcll(__ballot(sent && in_first)));
-        const uint32_t n1 = static_cast<uint32_t>(__popcll(sb)) - n0;
-        if (lane == 0) {
-          uint32_t* bc = c.blk_cnt + static_cast<uint64_t>(w) * c.QB;
-          if (n0) atomicAdd(&bc[b_first], n0);
-          if (n1) atomicAdd(&bc[b_first + 1], n1);
-          nsent += n0 + n1;
-        }
-      }
-    }
-    s_off += static_cast<uint32_t>(__popcll(tb));
-  }
-  if (is_qsgd(c.quantizer) && c.L > 1 && lane == 0 && nsent) atomicAdd(&s_count, nsent);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    usp->tau = s_tau; usp->need = s_need; usp->n_gt = sg.k - s_need; usp->scale_bits = __float_as_uint(usc.sent);
-    if (is_qsgd(c.quantizer) && c.L > 1) usp->nnz = s_count;
-  }
+  if (in_lds)
+    lean_one_list(c, sg, w, u, cand, T, sh, taubin, above,
+                  [&](uint32_t p, uint32_t* idx, uint32_t* bits, uint32_t* key) {
+                    const uint2 e = s_ent[p];
+                    *idx = e.x; *bits = e.y; *key = SPARS == QSL_TOPK ? key_of_value(e.y) : s_key[p];
+                  }, s, worker0, round, m_out, dbg_idx, dbg_level);
+  else
+    lean_one_list(c, sg, w, u, cand, T, sh, taubin, above,
+                  [&](uint32_t p, uint32_t* idx, uint32_t* bits, uint32_t* key) {
+                    const uint2 e = d0[p];
+                    *idx = e.x; *bits = e.y; *key = SPARS == QSL_TOPK ? key_of_value(e.y) : d0k[p];
+                  }, s, worker0, round, m_out, dbg_idx, dbg_level);
 }
 
 }  // namespace

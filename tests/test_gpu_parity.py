@@ -869,6 +869,44 @@ def test_index_free_edges(P, d, quantizer, s, factor):
     assert run.q.device_status() == B.OK
 
 
+# guessing units of a single block with more candidates than the list in LDS takes (13,500 of 8192), with more slot rows than a wave
+# keeps in registers, with chunks that spill to the overflow pool, with ties beyond the short list; beside them units that one block
+# selects from v, in the same launch; against the multi-pass kernels, and one worker against the oracle
+@pytest.mark.parametrize("sparsifier,quantizer,s,dense_unit", [(W.TOPK, W.SIGN_L1, 1, True), (W.TOPK, W.QSGD, 15, False), (W.TOPK, W.FP32, 1, True),
+                                                               (W.RANDK, W.QSGD, 4, True), (W.RANDK, W.SIGN_L2, 1, False)])
+def test_single_block_units_with_long_lists(P, sparsifier, quantizer, s, dense_unit):
+    from paper_1906_02367_amd import binding as B
+    R, sizes, ks = 32, [600_011, 90_001, 20_003, 70_000] * 2, [9_000, 90, 20, 1_000] * 2
+    if dense_unit:
+        sizes.append(36_864); ks.append(3_000)
+    off = np.concatenate([[0], np.cumsum(sizes)]).tolist()
+    d = off[-1]
+    wl = custom(d, off, ks, s, sparsifier, quantizer, R=R)
+    assert set(B.plan_paths(d, wl.seg_offset, wl.seg_k, s, sparsifier, quantizer).tolist()) == ({0, 3} if dense_unit else {0})
+    qa, qb, op = B.from_workload(wl), B.from_workload(wl, flags=B.FLAG_NO_FAST_PATH), P.oracle_for(wl)
+    g = torch.Generator(device=qa.device); g.manual_seed(11)
+    m = torch.zeros(R, d, device=qa.device)
+    for t in range(3):
+        delta = torch.randn(R, d, generator=g, device=qa.device)
+        delta[:, 5_000:5_700] *= 50                              # one chunk and a half of large values
+        if t == 2:
+            delta = torch.round(delta)
+        outs = []
+        for q in (qa, qb):
+            msg, m_out = q.new_msg(R).fill_(0xCD), torch.empty_like(m)
+            q.compress(m, delta, m_out, 0, t, msg)
+            outs.append((msg, m_out))
+        torch.cuda.synchronize()
+        assert qa.device_status() == B.OK and qb.device_status() == B.OK
+        assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1].view(torch.int32), outs[1][1].view(torch.int32)), t
+        units = qa.debug_units()
+        if t == 0:
+            assert not np.any(units[:, 0] == 2) and units[:, 1].max() > 8_192
+            o = op.compress(np.zeros(d, f32), delta[R - 1].cpu().numpy(), R - 1, 0)
+            assert np.array_equal(outs[0][0][R - 1].cpu().numpy(), o["msg"]) and np.array_equal(P.bits(outs[0][1][R - 1].cpu().numpy()), P.bits(o["m_out"]))
+        m = outs[0][1]
+
+
 # short vectors, one launch per call: both sides of the limits (4096, 8192, 16,384 coordinates, 4096 selected ones, guesses from 1024 groups
 # and from groups of four), ties that the guess lets through or not, ties at the threshold in several waves, an update formed from models
 @pytest.mark.parametrize("d,k", [(1, 1), (63, 40), (4_095, 513), (4_097, 1), (4_097, 4_096), (8_192, 512), (8_192, 1_024), (8_193, 1_025), (8_193, 2_049),
