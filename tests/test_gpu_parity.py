@@ -907,6 +907,40 @@ def test_single_block_units_with_long_lists(P, sparsifier, quantizer, s, dense_u
         m = outs[0][1]
 
 
+# the stand-alone error update, in one launch up to 2^23 coordinates of all rows and in two beyond: m + delta - g in single operations,
+# messages that hold nothing, everything or the ends of chunks only, segments, a last chunk of one coordinate; an index >= d is reported
+@pytest.mark.parametrize("d,off,k,quantizer,s,R", [(1, [0, 1], [1], W.FP32, 1, 2), (1_025, [0, 1_025], [1_025], W.SIGN_L1, 1, 2), (5_121, [0, 1_000, 5_121], [1_000, 9], W.QSGD, 3, 3),
+                                                   (70_001, [0, 70_001], [40], W.SIGN_L2, 1, 2), (1_048_577, [0, 1_048_577], [30_000], W.FP32, 1, 8), (1_048_576, [0, 1_048_576], [30_000], W.QSGD, 15, 8)])
+def test_error_update_launches(P, d, off, k, quantizer, s, R):
+    from paper_1906_02367_amd import binding as B
+    rng = np.random.default_rng(d)
+    wl = custom(d, off, k, s, W.TOPK, quantizer, R=R)
+    q, op = B.from_workload(wl), P.oracle_for(wl)
+    m0, delta = rng.standard_normal((R, d)).astype(f32), rng.standard_normal((R, d)).astype(f32)
+    edge = np.arange(d) % 1_024
+    delta[0, (edge == 0) | (edge == 1_023)] *= 100
+    m0[R - 1], delta[R - 1] = 0, 0                               # QSGD sends nothing
+    m, dl = torch.from_numpy(m0).to(q.device), torch.from_numpy(delta).to(q.device)
+    msg, v = q.new_msg(R), torch.empty_like(m)
+    q.compress(m, dl, v, 0, 0, msg)
+    q.error_update(m, dl, msg)
+    torch.cuda.synchronize()
+    assert q.device_status() == B.OK
+    host = msg.cpu().numpy()
+    for r in (0, R - 1):
+        want = m0[r] + delta[r]
+        i, g = op.decode(host[r])
+        want[i] = want[i] - g.astype(f32)
+        assert np.array_equal(P.bits(m[r].cpu().numpy()), P.bits(want)), r
+    if d == 70_001:                                              # the last index beyond the vector
+        bits = np.unpackbits(host[0], bitorder="little")
+        bits[64 + 39 * 17: 64 + 40 * 17] = (d + 1 >> np.arange(17)) & 1
+        bad = torch.from_numpy(np.stack([np.packbits(bits, bitorder="little"), host[1]])).to(q.device)
+        q.error_update(m, dl, bad)
+        torch.cuda.synchronize()
+        assert q.device_status() != B.OK
+
+
 # short vectors, one launch per call: both sides of the limits (4096, 8192, 16,384 coordinates, 4096 selected ones, guesses from 1024 groups
 # and from groups of four), ties that the guess lets through or not, ties at the threshold in several waves, an update formed from models
 @pytest.mark.parametrize("d,k", [(1, 1), (63, 40), (4_095, 513), (4_097, 1), (4_097, 4_096), (8_192, 512), (8_192, 1_024), (8_193, 1_025), (8_193, 2_049),
