@@ -1134,9 +1134,10 @@ static bool aggregate_by_cells(uint32_t nnz_hint, uint32_t ndir, uint32_t R, boo
 }
 
 static void launch_directory(const DevCtx& c, hipStream_t st, const uint8_t* msg, const RowList& rows, uint32_t R, uint32_t* dir,
-                             uint32_t ndir, const AggPile& pile) {
+                             uint32_t ndir, uint32_t nnz_hint, const AggPile& pile) {
   const uint32_t blocks = (c.K + BLOCK - 1) / BLOCK;
-  if (blocks <= 2048) k_msg_directory<1><<<dim3(blocks, R), BLOCK, 0, st>>>(c, msg, rows, dir, ndir, pile);
+  if (pile.list == nullptr && nnz_hint / (ndir - 1) >= DIR_SEARCH) k_msg_directory_search<<<dim3((ndir + BLOCK - 1) / BLOCK, R), BLOCK, 0, st>>>(c, msg, rows, dir, ndir);
+  else if (blocks <= 2048) k_msg_directory<1><<<dim3(blocks, R), BLOCK, 0, st>>>(c, msg, rows, dir, ndir, pile);
   else k_msg_directory<4><<<dim3(2048, R), BLOCK, 0, st>>>(c, msg, rows, dir, ndir, pile);
 }
 
@@ -1176,7 +1177,7 @@ static qsl_status launch_aggregate(const DevCtx& c, hipStream_t st, uint32_t nnz
     // average: above that no cell has more than 32 times its share, and all of them are long.
     AggPile pile = {nullptr, nullptr, nullptr, nullptr, nullptr};
     if (room && nnz_hint / (ndir - 1) < 32) { pile = *room; pile.planned = cr.bits; }
-    launch_directory(c, st, msg, rows, R, dir, ndir, pile);
+    launch_directory(c, st, msg, rows, R, dir, ndir, nnz_hint, pile);
     int in_order = 1;
     for (uint32_t q = 0; q < R; ++q) in_order &= rows.row[q] == q;
     const double per_cell = static_cast<double>(nnz_hint) * R / (ndir - 1);
@@ -1205,7 +1206,7 @@ static qsl_status launch_aggregate(const DevCtx& c, hipStream_t st, uint32_t nnz
   }
   if (R == 1 || nnz_hint < AGG_DIR_MIN) dir = nullptr;   // short messages are searched whole
   if (dir) {                                        // long messages: a thread per entry, searches narrowed by the directories
-    launch_directory(c, st, msg, rows, R, dir, ndir, AggPile{nullptr, nullptr, nullptr, nullptr, nullptr});
+    launch_directory(c, st, msg, rows, R, dir, ndir, nnz_hint, AggPile{nullptr, nullptr, nullptr, nullptr, nullptr});
     const uint32_t eb = std::min((c.K + BLOCK - 1) / BLOCK, std::max(4u, (nnz_hint + BLOCK - 1) / BLOCK));
     k_aggregate_entries<<<dim3(eb, R), BLOCK, 0, st>>>(c, msg, rows, R, scale, accumulate, out, dir, ndir);
   } else {                                          // short messages: 8 threads per entry, a block per expected tile of 32

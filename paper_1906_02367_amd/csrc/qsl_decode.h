@@ -265,6 +265,48 @@ __global__ __launch_bounds__(BLOCK) void k_msg_directory(DevCtx c, const uint8_t
   }
 }
 
+// The same directories where a message is expected to have many entries per 1024 coordinates (DIR_SEARCH or more): a thread per slot
+// finds its entry by bisection, from where it would stand if the entries lay evenly, instead of every entry being read.  Whatever
+// the message holds, slot 0 is 0 and the last one its length, so that every entry, also one with an index >= d, lies between two
+// neighbouring slots and is met by whoever decodes that cell -- but for the last cell, where it may fall to a part behind d that has
+// no coordinates: that cell's entries are looked through here.  Bound by the chain of reads, two and then half the logarithm of the
+// window.  4 messages of 2.6 M entries, d = 25.6 M: 25.7 us
+// by reading every entry, 16.8 this way.
+constexpr uint32_t DIR_SEARCH = 32, DIR_WINDOW = 2048;
+__global__ __launch_bounds__(BLOCK) void k_msg_directory_search(DevCtx c, const uint8_t* msg, RowList rows, uint32_t* dir, uint32_t ndir) {
+  __shared__ uint32_t s_last;
+  const uint32_t q = blockIdx.y, t = blockIdx.x * BLOCK + threadIdx.x;
+  const MsgView v = view_msg(c, msg, rows.row[q]);
+  uint32_t lo = 0, hi = t == 0 ? 0u : v.nnz;
+  if (t >= ndir - 1) lo = hi;
+  const uint64_t target = static_cast<uint64_t>(t) << AGG_DIR_SHIFT;
+  if (lo < hi) {
+    const uint32_t at = static_cast<uint32_t>(static_cast<uint64_t>(v.nnz) * t / (ndir - 1));
+    const uint32_t a = at > DIR_WINDOW ? at - DIR_WINDOW : 0u, z = min(v.nnz - 1, at + DIR_WINDOW);
+    const uint32_t xa = msg_index(c, v, a), xz = msg_index(c, v, z);
+    if (xa >= target) hi = a; else lo = a + 1;           // the first entry at or behind the target lies in [lo, hi]
+    if (lo <= z && z < hi) { if (xz >= target) hi = z; else lo = z + 1; }
+  }
+  while (lo < hi) {
+    uint32_t x[3];
+#pragma unroll
+    for (uint32_t i = 0; i < 3; ++i) x[i] = msg_index(c, v, lo + static_cast<uint32_t>(static_cast<uint64_t>(hi - lo) * (i + 1) >> 2));
+    const uint32_t w = hi - lo, base = lo;
+    auto part = [&](uint32_t i) { return base + static_cast<uint32_t>(static_cast<uint64_t>(w) * i >> 2); };
+    if (x[0] >= target) hi = part(1);
+    else if (x[1] >= target) { lo = part(1) + 1; hi = part(2); }
+    else if (x[2] >= target) { lo = part(2) + 1; hi = part(3); }
+    else lo = part(3) + 1;
+  }
+  if (t < ndir) dir[static_cast<uint64_t>(q) * ndir + t] = lo;
+  if (blockIdx.x != (ndir - 2) / BLOCK) return;          // (uniform) the block with the last cell
+  if (t == ndir - 2) s_last = lo;
+  __syncthreads();
+  bool bad = false;
+  for (uint32_t j = s_last + threadIdx.x; j < v.nnz; j += BLOCK) bad = bad || msg_index(c, v, j) >= c.d;
+  if (bad) atomicOr(c.status, 4u);
+}
+
 // Short messages (no directory).  Entry j of the q-th listed message is served by 8 threads, which look its
 // coordinate up in the other listed messages (binary search on the packed, ascending indices).  The coordinate is
 // written by the earliest listed message that holds it -- one writer per coordinate, no atomics --

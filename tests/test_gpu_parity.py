@@ -907,6 +907,33 @@ def test_single_block_units_with_long_lists(P, sparsifier, quantizer, s, dense_u
         m = outs[0][1]
 
 
+# directories by search (32 entries or more per 1024 coordinates): entries that lie evenly, that all lie far from where an even message would
+# have them, a last cell of one coordinate; messages of QSGD that are shorter than expected, and empty
+@pytest.mark.parametrize("d,k,quantizer,s,where", [(300_033, 30_000, W.SIGN_L1, 1, "even"), (300_033, 30_000, W.FP32, 1, "front"), (409_601, 40_000, W.SIGN_L1, 1, "back"),
+                                                   (409_600, 40_000, W.QSGD, 1_000, "back"), (5_000, 4_500, W.SIGN_L2, 1, "front")])
+def test_aggregate_directory_by_search(P, d, k, quantizer, s, where):
+    from paper_1906_02367_amd import binding as B
+    rng = np.random.default_rng(d)
+    R = 5
+    wl = custom(d, [0, d], [k], s, W.TOPK, quantizer, R=R)
+    q, op = B.from_workload(wl), P.oracle_for(wl)
+    v = rng.standard_normal((R, d)).astype(f32)
+    if where != "even":
+        v[:, slice(0, k + 999) if where == "front" else slice(d - k - 999, d)] *= 1e3
+    v[3] = 0
+    msg, m = q.new_msg(R), torch.zeros(R, d, device=q.device)
+    q.compress(m, torch.from_numpy(v).to(q.device), m, 0, 0, msg)
+    torch.cuda.synchronize()
+    decoded = [op.decode(x) for x in msg.cpu().numpy()]
+    x0 = rng.standard_normal(d).astype(f32)
+    for lst, accumulate in ((list(range(R)), True), ([4, 3, 1, 0], False)):
+        out = torch.from_numpy(x0).to(q.device)
+        q.aggregate(msg, out, -1.0 / R, worker_list=lst, accumulate=accumulate)
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy().view(np.uint32), _aggregate_by_definition(decoded, lst, -1.0 / R, x0, accumulate, d).view(np.uint32)), lst
+    assert q.device_status() == B.OK
+
+
 # the stand-alone error update, in one launch up to 2^23 coordinates of all rows and in two beyond: m + delta - g in single operations,
 # messages that hold nothing, everything or the ends of chunks only, segments, a last chunk of one coordinate; an index >= d is reported
 @pytest.mark.parametrize("d,off,k,quantizer,s,R", [(1, [0, 1], [1], W.FP32, 1, 2), (1_025, [0, 1_025], [1_025], W.SIGN_L1, 1, 2), (5_121, [0, 1_000, 5_121], [1_000, 9], W.QSGD, 3, 3),
