@@ -207,7 +207,7 @@ def main():
     avg_stream_s = stream_ms / 1e3 / max(1, launches)
     algo_bytes = ALGO_BYTES_PER_COORD * R * d + (4 * d if args.from_models else 0)     # + one read of x
     achieved = algo_bytes / avg_stream_s / 1e9 if launches else None
-    kernel = "k_dense_norm" if wl.dense else "k_stream"
+    kernel = "k_dense_norm_one" if wl.dense else "k_stream"
     plain = not (args.from_models or args.workers or args.standalone_update)
     traffic, traffic_source = measured_traffic(kernel, wl.name) if plain else (None, "only the plain entry point is profiled")
     roofline = {"bound": "hbm", "kernel": kernel, "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
