@@ -210,8 +210,10 @@ qsl_status qsl_bits_index_free(const qsl_config *cfg, uint64_t *bits);
 
 /* Synchronise the stream and return QSL_ERR_NONFINITE_INPUT if any compress call since the last
  * query met a NaN or Inf in m + delta (its outputs are then unspecified), QSL_ERR_DEVICE on a HIP
- * error or if a kernel met a malformed message (an index >= d; the entry is skipped), else QSL_OK.
- * Clears the word.  */
+ * error or if a kernel met a malformed message, else QSL_OK.  Clears the word.
+ * An entry with an index >= d is always reported and skipped.  qsl_error_update subtracts all the others; in qsl_aggregate
+ * others of the same message may be lost as well if they stand behind it (the searches take indices to ascend).  Where indices
+ * below d do not ascend, which entries are used is open.  */
 qsl_status qsl_device_status(qsl_ctx *ctx);
 
 /* Per-unit diagnostics of the last compress call (unit = worker-major (worker, segment)); synchronises.

@@ -61,6 +61,21 @@ __device__ __forceinline__ int64_t msg_find(const DevCtx& c, const MsgView& v, u
   return -1;
 }
 
+typedef uint32_t u2u __attribute__((ext_vector_type(2), aligned(4)));
+// `width` (1 .. 32) bits from bit `bit` of a message on, by one 8-byte read that stays inside its cap_words words
+struct FieldRead { u2u w; uint32_t sh; };
+__device__ __forceinline__ FieldRead read_field(const uint32_t* words, uint64_t bit, uint32_t cap_words) {
+  const uint64_t q = min(bit >> 5, static_cast<uint64_t>(cap_words) - 2);
+  FieldRead f;
+  f.w = *reinterpret_cast<const u2u*>(words + q);
+  f.sh = static_cast<uint32_t>(bit - q * 32) & 63u;
+  return f;
+}
+__device__ __forceinline__ uint32_t field_of(const FieldRead& f, uint32_t width) {
+  const uint64_t v = (static_cast<uint64_t>(f.w.y) << 32 | f.w.x) >> f.sh;
+  return width == 32 ? static_cast<uint32_t>(v) : static_cast<uint32_t>(v) & ((1u << width) - 1u);
+}
+
 // m <- m + delta over the flat [R * d] arrays: the streaming recipe of k_stream (a wave per 1024 elements,
 // non-temporal dwordx4 accesses, 3 waves per SIMD)
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_add_rows(float* m, const float* delta,
@@ -121,16 +136,19 @@ __global__ __launch_bounds__(BLOCK) void k_update_rows(DevCtx c, float* m, const
       for (uint32_t j = 0; j < 4; ++j) if (e + j < valid) { a[t][j] = mp[e + j]; b[t][j] = dp[e + j]; }
     }
   }
-  // lanes 0 .. 31: the first entry at or behind `first`; 32 .. 63: at or behind the chunk's end (the last chunk takes what is left, so
-  // that a malformed index is met)
+  // lanes 0 .. 31: the first entry at or behind `first`; 32 .. 63: at or behind the chunk's end (the last chunk takes what is left, and
+  // neighbouring chunks find the same end between them, so that every entry of the message is looked at)
   const bool tail = lane >= 32;
-  const uint64_t target = tail ? first + CHUNK : first;
+  const uint32_t d = static_cast<uint32_t>(c.d), target = static_cast<uint32_t>(first) + (tail ? CHUNK : 0u);      // (< d where there is a search)
   uint32_t lo = tail && first + CHUNK >= c.d ? v.nnz : 0u, hi = first == 0 && !tail ? 0u : v.nnz;
+  bool bad = false;                                      // a step met an index >= d (a malformed message), which says nothing about where to go on
   while (__ballot(lo < hi) != 0) {                       // (each half of the wave agrees on its lo and hi)
     const uint32_t width = hi - lo, part = lane & 31u;
     const uint32_t at = lo + static_cast<uint32_t>(static_cast<uint64_t>(width) * (part + 1) / 33);
-    const bool less = lo < hi && msg_index(c, v, min(at, v.nnz - 1)) < target;
-    const uint64_t bal = __ballot(less);
+    const uint32_t x = field_of(read_field(v.words, v.idx_bit0 + static_cast<uint64_t>(min(at, v.nnz - 1)) * c.w_idx, c.cap_words), c.w_idx);
+    const bool open = lo < hi;
+    bad |= open & (x >= d);
+    const uint64_t bal = __ballot(open & (x < target));
     const uint32_t n = static_cast<uint32_t>(__popcll(tail ? bal >> 32 : bal & 0xFFFFFFFFull));
     if (lo < hi) {
       const uint32_t base = lo;
@@ -138,7 +156,9 @@ __global__ __launch_bounds__(BLOCK) void k_update_rows(DevCtx c, float* m, const
       if (n < 32) hi = base + static_cast<uint32_t>(static_cast<uint64_t>(width) * (n + 1) / 33);
     }
   }
-  const uint32_t j_lo = lane_value(lo, 0), j_hi = lane_value(lo, 32);
+  // (then the wave goes through the whole message; where no step met such an index, what the steps found holds for all the others)
+  const bool lost = __ballot(bad) != 0;
+  const uint32_t j_lo = lost ? 0u : lane_value(lo, 0), j_hi = lost ? v.nnz : lane_value(lo, 32);
 #pragma unroll
   for (uint32_t t = 0; t < 4; ++t) a[t] = a[t] + b[t];
   if (j_lo < j_hi) {                                     // (uniform)
@@ -150,7 +170,7 @@ __global__ __launch_bounds__(BLOCK) void k_update_rows(DevCtx c, float* m, const
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     for (uint32_t j = j_lo + lane; j < j_hi; j += WAVE) {
       const uint32_t idx = msg_index(c, v, j);
-      if (idx < first || idx - first >= valid) { atomicOr(c.status, 4u); continue; }      // malformed message
+      if (idx < first || idx - first >= valid) { if (!lost || idx >= c.d) atomicOr(c.status, 4u); continue; }      // malformed message
       image[idx - first] = image[idx - first] - msg_value(c, v, j, idx);
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -177,21 +197,6 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3, 3))) v
     if (i + 4 <= n) __builtin_nontemporal_store(z, reinterpret_cast<f4u*>(out + i));
     else for (uint64_t j = i; j < n; ++j) out[j] = 0.f;
   }
-}
-
-typedef uint32_t u2u __attribute__((ext_vector_type(2), aligned(4)));
-// `width` (1 .. 32) bits from bit `bit` of a message on, by one 8-byte read that stays inside its cap_words words
-struct FieldRead { u2u w; uint32_t sh; };
-__device__ __forceinline__ FieldRead read_field(const uint32_t* words, uint64_t bit, uint32_t cap_words) {
-  const uint64_t q = min(bit >> 5, static_cast<uint64_t>(cap_words) - 2);
-  FieldRead f;
-  f.w = *reinterpret_cast<const u2u*>(words + q);
-  f.sh = static_cast<uint32_t>(bit - q * 32) & 63u;
-  return f;
-}
-__device__ __forceinline__ uint32_t field_of(const FieldRead& f, uint32_t width) {
-  const uint64_t v = (static_cast<uint64_t>(f.w.y) << 32 | f.w.x) >> f.sh;
-  return width == 32 ? static_cast<uint32_t>(v) : static_cast<uint32_t>(v) & ((1u << width) - 1u);
 }
 
 struct RowList { uint32_t row[64]; };

@@ -968,6 +968,45 @@ def test_error_update_launches(P, d, off, k, quantizer, s, R):
         assert q.device_status() != B.OK
 
 
+# messages with indices >= d in the stand-alone error update: each such entry is reported and skipped, wherever it stands and however many
+# there are; every other entry is subtracted
+@pytest.mark.parametrize("d,off,k,quantizer,s", [(70_001, [0, 70_001], [3_000], W.SIGN_L1, 1), (70_001, [0, 30_000, 70_001], [1_000, 2_000], W.QSGD, 15),
+                                                 (5_000, [0, 5_000], [5_000], W.FP32, 1), (1_500_001, [0, 1_500_001], [20_000], W.SIGN_L2, 1)])
+def test_error_update_malformed_indices(P, d, off, k, quantizer, s):
+    from paper_1906_02367_amd import binding as B
+    rng = np.random.default_rng(d + s)
+    wl = custom(d, off, k, s, W.TOPK, quantizer, R=2)
+    q, op = B.from_workload(wl), P.oracle_for(wl)
+    m0, delta = rng.standard_normal((2, d)).astype(f32), rng.standard_normal((2, d)).astype(f32)
+    dl = torch.from_numpy(delta).to(q.device)
+    msg, v = q.new_msg(2), torch.empty(2, d, device=q.device)
+    q.compress(torch.from_numpy(m0).to(q.device), dl, v, 0, 0, msg)
+    torch.cuda.synchronize()
+    good = msg.cpu().numpy()
+    i0, g0 = op.decode(good[0])
+    i1, g1 = op.decode(good[1])
+    n, w_idx, L = i0.size, (d - 1).bit_length(), len(k)
+    bit0 = 32 * (1 + L + (L if quantizer == W.QSGD and L > 1 else 0))
+    other = m0[1] + delta[1]
+    other[i1] = other[i1] - g1.astype(f32)
+    for where in ([0], [n // 2], [n - 1], [16 * n // 33], [32 * n // 33], range(n // 3, n // 2), range(0, n, 2), range(1, n), range(n)):
+        where = np.array(where)
+        bad = good.copy()
+        bits = np.unpackbits(bad[0], bitorder="little")
+        for j in where:
+            bits[bit0 + j * w_idx: bit0 + (j + 1) * w_idx] = ((d if j % 3 else (1 << w_idx) - 1) >> np.arange(w_idx)) & 1
+        bad[0] = np.packbits(bits, bitorder="little")
+        m = torch.from_numpy(m0).to(q.device)
+        q.error_update(m, dl, torch.from_numpy(bad).to(q.device))
+        assert q.device_status() == B.ERR_DEVICE and q.device_status() == B.OK, where[:3]
+        keep = np.ones(n, bool)
+        keep[where] = False
+        want = m0[0] + delta[0]
+        want[i0[keep]] = want[i0[keep]] - g0[keep].astype(f32)
+        got = m.cpu().numpy()
+        assert np.array_equal(P.bits(got[0]), P.bits(want)) and np.array_equal(P.bits(got[1]), P.bits(other)), where[:3]
+
+
 # short vectors, one launch per call: both sides of the limits (4096, 8192, 16,384 coordinates, 4096 selected ones, guesses from 1024 groups
 # and from groups of four), ties that the guess lets through or not, ties at the threshold in several waves, an update formed from models
 @pytest.mark.parametrize("d,k", [(1, 1), (63, 40), (4_095, 513), (4_097, 1), (4_097, 4_096), (8_192, 512), (8_192, 1_024), (8_193, 1_025), (8_193, 2_049),
