@@ -1088,8 +1088,9 @@ extern "C" qsl_status qsl_compress_diff(qsl_ctx* ctx, const float* m, const floa
   return compress_checked(ctx, m, xhat_half, x, m_out, worker0, R, round, msg, msg_bits, sel_idx, sel_level);
 }
 
-// Coordinates of all rows up to which the stand-alone error update is one launch (us a call, two launches / one: 4 x 20,000 12.4 / 9.6,
-// 4 x 10^6 12.7 / 10.6, 4 x 3 M 30.0 / 29.7, 8 x 3 M 47.3 / 49.8, 25.6 M 50.1 / 58.3).
+// Coordinates of all rows up to which the stand-alone error update is one launch (us a call, two launches / one: 4 x 20,000 and 1 % of
+// entries 11.4 / 9.2, 4 x 10^6 12.0 / 9.3, 4 x 2.09 M 20.9 / 17.2, with 0.03 % 18.4 / 17.6, with 20 % 32.5 / 18.2; eight waves per SIMD take 8.4 M
+// coordinates at once, beyond that the search's reads are no longer hidden).
 constexpr uint64_t UPDATE_ROWS_MAX = 1ull << 23;
 
 extern "C" qsl_status qsl_error_update(qsl_ctx* ctx, float* m, const float* delta, const uint8_t* msg, uint32_t R) {

@@ -111,16 +111,30 @@ __global__ __launch_bounds__(BLOCK) void k_subtract_msg(DevCtx c, float* m, cons
 
 // Both in one launch, for vectors so short that a launch counts: a wave per 1024 coordinates of a row finds the message's entries among
 // them itself -- half of its lanes the first, half the last, 32 parts of the message a step -- while its reads of m and delta
-// are under way.  Where there are entries, the sums take the way through LDS to meet them.  What bounds it is the chain of reads: three
-// or four search steps of about a microsecond.  4 x 10^6 coordinates, 10,000 entries each: 12.7 us by k_add_rows and
-// k_subtract_msg, 10.6 this way; on long vectors the search's reads cost more than a launch.
-__global__ __launch_bounds__(BLOCK) void k_update_rows(DevCtx c, float* m, const float* delta, const uint8_t* msg) {
+// are under way.  Where there are entries, the sums take the way through LDS to meet them, UPDATE_STEPS times 64 entries' reads in flight.
+// What bounds it is the chain of reads, so registers are kept to what eight waves per SIMD allow, and an entry's segment comes from bits
+// in two lane moves.  With four waves per SIMD (126 registers), 64 entries a step and a search in memory for every entry's segment it lost to the
+// two launches above where small tensors fill a chunk (176 tensors, 7 x 119,847, k = 1000: 11.5 by two launches, 18.3 that way, 11.4 us
+// now) and beyond 4.2 M coordinates (4 x 2.09 M, 0.1 %: 18.9, 20.6, 17.2).
+constexpr uint32_t UPDATE_STEPS = 2;      // (4: 80 registers, and slower from 6 M coordinates on)
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_update_rows(DevCtx c, float* m, const float* delta, const uint8_t* msg) {
   __shared__ f4u s_image[BLOCK / 64][CHUNK / 4];
+  __shared__ uint32_t s_starts[BLOCK / 64][CHUNK / 32];
   const uint32_t w = blockIdx.y, lane = lane_id(), wave = threadIdx.x >> 6;
   const uint64_t first = (static_cast<uint64_t>(blockIdx.x) * (BLOCK / 64) + wave) * CHUNK;
   if (first >= c.d) return;                              // (no barrier follows)
   const uint32_t valid = static_cast<uint32_t>(min(static_cast<uint64_t>(CHUNK), c.d - first));
+  // the segments of the chunk, a bit per coordinate where one begins: lane l < 32 holds those of 32 coordinates and how many lie before
+  // them.  Their reads come first: a wave's loads return in order.
+  uint32_t seg_lo = 0, n_seg = 1, my_start = 0, starts = 0, starts_before = 0;
+  if (c.L > 1) {
+    seg_lo = __builtin_amdgcn_readfirstlane(c.seg_dir[first >> 10]);
+    n_seg = __builtin_amdgcn_readfirstlane(c.seg_dir[(first >> 10) + 1]) + 1 - seg_lo;
+    my_start = c.seg_start[seg_lo + min(lane, n_seg - 1)];
+  }
   const MsgView v = view_msg(c, msg, w);
+  const bool few = n_seg <= WAVE;                        // then lane l holds the message's scale of the l-th
+  const float my_scale = __uint_as_float(v.words[1 + seg_lo + min(lane, n_seg - 1)]);
   float* mp = m + static_cast<uint64_t>(w) * c.d + first;
   const float* dp = delta + static_cast<uint64_t>(w) * c.d + first;
   f4u a[4], b[4];
@@ -135,6 +149,22 @@ __global__ __launch_bounds__(BLOCK) void k_update_rows(DevCtx c, float* m, const
 #pragma unroll
       for (uint32_t j = 0; j < 4; ++j) if (e + j < valid) { a[t][j] = mp[e + j]; b[t][j] = dp[e + j]; }
     }
+  }
+  if (n_seg > 1) {
+    if (lane < CHUNK / 32) s_starts[wave][lane] = 0;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    for (uint32_t l = lane; l < n_seg; l += WAVE) {
+      const uint32_t at = (l < WAVE ? my_start : c.seg_start[seg_lo + l]) - static_cast<uint32_t>(first);
+      if (l != 0 && at < CHUNK) atomicOr(&s_starts[wave][at >> 5], 1u << (at & 31u));      // (the last one may begin with the next chunk)
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    if (lane < CHUNK / 32) starts = s_starts[wave][lane];
+    uint32_t all;
+    starts_before = wave_exclusive_scan32(static_cast<uint32_t>(__popc(starts)), &all);
   }
   // lanes 0 .. 31: the first entry at or behind `first`; 32 .. 63: at or behind the chunk's end (the last chunk takes what is left, and
   // neighbouring chunks find the same end between them, so that every entry of the message is looked at)
@@ -168,10 +198,27 @@ __global__ __launch_bounds__(BLOCK) void k_update_rows(DevCtx c, float* m, const
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");      // the image is private to the wave
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    for (uint32_t j = j_lo + lane; j < j_hi; j += WAVE) {
-      const uint32_t idx = msg_index(c, v, j);
-      if (idx < first || idx - first >= valid) { if (!lost || idx >= c.d) atomicOr(c.status, 4u); continue; }      // malformed message
-      image[idx - first] = image[idx - first] - msg_value(c, v, j, idx);
+    for (uint32_t j0 = j_lo; j0 < j_hi; j0 += UPDATE_STEPS * WAVE) {
+      FieldRead fi[UPDATE_STEPS], fc[UPDATE_STEPS];
+#pragma unroll
+      for (uint32_t u = 0; u < UPDATE_STEPS; ++u) {
+        const uint32_t j = min(j0 + u * WAVE + lane, v.nnz - 1);
+        fi[u] = read_field(v.words, v.idx_bit0 + static_cast<uint64_t>(j) * c.w_idx, c.cap_words);
+        fc[u] = read_field(v.words, v.code_bit0 + static_cast<uint64_t>(j) * c.w_val, c.cap_words);
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < UPDATE_STEPS; ++u) {
+        const uint32_t idx = field_of(fi[u], c.w_idx);
+        const bool in = j0 + u * WAVE + lane < j_hi, ok = in && idx >= first && idx - first < valid;
+        if (in && !ok && (!lost || idx >= d)) atomicOr(c.status, 4u);      // malformed message
+        uint32_t seg = 0;                                // the entry's segment, of the chunk's
+        if (n_seg > 1) {
+          const uint32_t r = idx - static_cast<uint32_t>(first), word = __shfl(starts, r >> 5 & 31u, WAVE), before = __shfl(starts_before, r >> 5 & 31u, WAVE);
+          seg = before + static_cast<uint32_t>(__popc(word & ((2u << (r & 31u)) - 1u)));
+        }
+        const float scale = few ? __shfl(my_scale, seg, WAVE) : __uint_as_float(v.words[1 + seg_lo + seg]);
+        if (ok) image[idx - first] = image[idx - first] - value_of_code(c, field_of(fc[u], c.w_val), scale);
+      }
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();

@@ -935,9 +935,11 @@ def test_aggregate_directory_by_search(P, d, k, quantizer, s, where):
 
 
 # the stand-alone error update, in one launch up to 2^23 coordinates of all rows and in two beyond: m + delta - g in single operations,
-# messages that hold nothing, everything or the ends of chunks only, segments, a last chunk of one coordinate; an index >= d is reported
+# messages that hold nothing, everything or the ends of chunks only, segments (more than 64 to a chunk, ends on the ends of chunks), a last
+# chunk of one coordinate; an index >= d is reported
 @pytest.mark.parametrize("d,off,k,quantizer,s,R", [(1, [0, 1], [1], W.FP32, 1, 2), (1_025, [0, 1_025], [1_025], W.SIGN_L1, 1, 2), (5_121, [0, 1_000, 5_121], [1_000, 9], W.QSGD, 3, 3),
-                                                   (70_001, [0, 70_001], [40], W.SIGN_L2, 1, 2), (1_048_577, [0, 1_048_577], [30_000], W.FP32, 1, 8), (1_048_576, [0, 1_048_576], [30_000], W.QSGD, 15, 8)])
+                                                   (70_001, [0, 70_001], [40], W.SIGN_L2, 1, 2), (3_000, list(range(0, 3_001, 5)), [2, 5] * 300, W.SIGN_L1, 1, 2),
+                                                   (5_121, [0, 1, 1_024, 2_048, 2_049, 3_071, 5_121], [1, 1_000, 1_024, 1, 1_022, 3], W.SIGN_L2, 1, 2), (1_048_577, [0, 1_048_577], [30_000], W.FP32, 1, 8), (1_048_576, [0, 1_048_576], [30_000], W.QSGD, 15, 8)])
 def test_error_update_launches(P, d, off, k, quantizer, s, R):
     from paper_1906_02367_amd import binding as B
     rng = np.random.default_rng(d)
