@@ -1137,7 +1137,7 @@ static bool aggregate_by_cells(uint32_t nnz_hint, uint32_t ndir, uint32_t R, boo
 static void launch_directory(const DevCtx& c, hipStream_t st, const uint8_t* msg, const RowList& rows, uint32_t R, uint32_t* dir,
                              uint32_t ndir, uint32_t nnz_hint, const AggPile& pile) {
   const uint32_t blocks = (c.K + BLOCK - 1) / BLOCK;
-  if (pile.list == nullptr && nnz_hint / (ndir - 1) >= DIR_SEARCH) k_msg_directory_search<<<dim3((ndir + BLOCK - 1) / BLOCK, R), BLOCK, 0, st>>>(c, msg, rows, dir, ndir);
+  if (pile.list == nullptr && directory_by_search(nnz_hint, ndir - 1, R)) k_msg_directory_search<<<dim3((ndir + BLOCK - 1) / BLOCK, R), BLOCK, 0, st>>>(c, msg, rows, dir, ndir);
   else if (blocks <= 2048) k_msg_directory<1><<<dim3(blocks, R), BLOCK, 0, st>>>(c, msg, rows, dir, ndir, pile);
   else k_msg_directory<4><<<dim3(2048, R), BLOCK, 0, st>>>(c, msg, rows, dir, ndir, pile);
 }

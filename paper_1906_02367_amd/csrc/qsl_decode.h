@@ -317,14 +317,14 @@ __global__ __launch_bounds__(BLOCK) void k_msg_directory(DevCtx c, const uint8_t
   }
 }
 
-// The same directories where a message is expected to have many entries per 1024 coordinates (DIR_SEARCH or more): a thread per slot
+// The same directories where there are many entries to a cell (directory_by_search): a thread per slot
 // finds its entry by bisection, from where it would stand if the entries lay evenly, instead of every entry being read.  Whatever
 // the message holds, slot 0 is 0 and the last one its length, so that every entry, also one with an index >= d, lies between two
 // neighbouring slots and is met by whoever decodes that cell -- but for the last cell, where it may fall to a part behind d that has
 // no coordinates: that cell's entries are looked through here.  Bound by the chain of reads, two and then half the logarithm of the
 // window.  4 messages of 2.6 M entries, d = 25.6 M: 25.7 us
 // by reading every entry, 16.8 this way.
-constexpr uint32_t DIR_SEARCH = 32, DIR_WINDOW = 2048;
+constexpr uint32_t DIR_WINDOW = 2048;
 __global__ __launch_bounds__(BLOCK) void k_msg_directory_search(DevCtx c, const uint8_t* msg, RowList rows, uint32_t* dir, uint32_t ndir) {
   __shared__ uint32_t s_last;
   const uint32_t q = blockIdx.y, t = blockIdx.x * BLOCK + threadIdx.x;

@@ -1,5 +1,6 @@
-// qsl_policy.h -- What the host makes of the failures that the kernels report through pinned words.  Plain C++, no HIP.  A
-// report may be seen a few calls late; only speed depends on it, never the result.
+// qsl_policy.h -- What the host makes of the failures that the kernels report through pinned words (a report may be seen a few calls
+// late), and which of the master line's kernels it takes for given sizes.  Only speed depends on any of it, never the result.  Plain C++,
+// no HIP.
 #pragma once
 
 #include <algorithm>
@@ -69,5 +70,16 @@ struct PilePolicy {
     return true;
   }
 };
+
+// Whether the directories of `R` messages of about `entries` entries each, `cells` of 1024 coordinates, are made by search
+// (k_msg_directory_search) or by reading every entry (k_msg_directory).  A search waits for some eight dependent reads whatever there is
+// to find, so there have to be about 3 M entries in all; its reads are scattered, twenty to a cell and message, so there
+// have to be many entries to each of them, and fewer cells in all than keep the caches busy.  Entries that lie evenly, us for the master
+// line by reading / by search: 100,001 coordinates, 4 messages, 48 to a cell 11.9 / 14.5; 10^6, 8, 100: 17.3 / 19.1; 10^6, 64, 48: 42.5 / 37.4; 4 M,
+// 4, 200: 29.4 / 27.8; 25.6 M, 4, 100: 75.2 / 68.5; 25.6 M, 16, 48: 125 / 179; 60 M, 2, 64: 103 / 106; 25.6 M, 10, 200: 251 / 211.
+inline bool directory_by_search(uint32_t entries, uint32_t cells, uint32_t R) {
+  const uint64_t all = static_cast<uint64_t>(cells) * R, per_cell = entries / cells;
+  return per_cell >= 48 && static_cast<uint64_t>(entries) * R >= 2900000 && all <= (per_cell >= 200 ? 256u << 10 : 112u << 10);
+}
 
 }  // namespace

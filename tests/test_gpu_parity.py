@@ -907,14 +907,17 @@ def test_single_block_units_with_long_lists(P, sparsifier, quantizer, s, dense_u
         m = outs[0][1]
 
 
-# directories by search (32 entries or more per 1024 coordinates): entries that lie evenly, that all lie far from where an even message would
-# have them, a last cell of one coordinate; messages of QSGD that are shorter than expected, and empty
-@pytest.mark.parametrize("d,k,quantizer,s,where", [(300_033, 30_000, W.SIGN_L1, 1, "even"), (300_033, 30_000, W.FP32, 1, "front"), (409_601, 40_000, W.SIGN_L1, 1, "back"),
-                                                   (409_600, 40_000, W.QSGD, 1_000, "back"), (5_000, 4_500, W.SIGN_L2, 1, "front")])
-def test_aggregate_directory_by_search(P, d, k, quantizer, s, where):
+# directories of messages with many entries per 1024 coordinates, by search (the large lists, see directory_by_search) or by reading every entry:
+# entries that lie evenly, that all lie far from where an even message would have them, a last cell of one coordinate; messages of QSGD
+# that are shorter than expected, and empty
+@pytest.mark.parametrize("d,k,quantizer,s,where,R", [
+    (300_033, 30_000, W.SIGN_L1, 1, "even", 5), (300_033, 30_000, W.FP32, 1, "front", 5), (409_601, 40_000, W.SIGN_L1, 1, "back", 5),
+    (409_600, 40_000, W.QSGD, 1_000, "back", 5), (5_000, 4_500, W.SIGN_L2, 1, "front", 5),
+    (300_033, 60_000, W.SIGN_L1, 1, "even", 50), (300_033, 60_000, W.FP32, 1, "front", 50), (409_601, 82_000, W.SIGN_L1, 1, "back", 40),
+    (409_600, 90_000, W.QSGD, 1_000, "back", 64), (51_000, 50_000, W.SIGN_L2, 1, "front", 60)])
+def test_aggregate_directory_by_search(P, d, k, quantizer, s, where, R):
     from paper_1906_02367_amd import binding as B
     rng = np.random.default_rng(d)
-    R = 5
     wl = custom(d, [0, d], [k], s, W.TOPK, quantizer, R=R)
     q, op = B.from_workload(wl), P.oracle_for(wl)
     v = rng.standard_normal((R, d)).astype(f32)

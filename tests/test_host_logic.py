@@ -305,6 +305,10 @@ int main(int, char** a) {
     printf("%d %d\n", tried, last);
     return 0;
   }
+  if (kind == "directory") {                       // argv: kind, entries of a message, coordinates, messages
+    printf("%d\n", directory_by_search(atoi(a[2]), (atoi(a[3]) + 1023) / 1024, atoi(a[4])));
+    return 0;
+  }
   if (kind == "pile") {                            // entries pile up in the calls 10 .. 119: calls that list the cells, of those and of all
     PilePolicy w;
     int listed = 0, in_time = 0;
@@ -373,3 +377,14 @@ def test_a_failing_window_is_left_out(policy):
 
 def test_piled_up_cells_are_listed_while_there_are_any(policy):
     assert policy("pile", 400, 1) == [109, 109 + 64]              # from the second call with them on, and 64 calls beyond the last
+
+
+# which kernel makes the directories, at sizes where both were measured: (coordinates, messages, entries per 1024 coordinates) of which the search
+# was the slower, the faster (entries that lie evenly)
+@pytest.mark.parametrize("d,R,per_cell,search", [
+    (100_001, 2, 48, 0), (100_001, 4, 200, 0), (100_001, 16, 200, 0), (1_000_003, 2, 33, 0), (1_000_003, 16, 64, 0), (1_000_003, 4, 200, 0), (2_000_000, 8, 64, 0),
+    (16_000_000, 24, 64, 0), (25_557_032, 8, 33, 0), (25_557_032, 16, 48, 0), (40_000_000, 8, 64, 0), (60_000_000, 2, 64, 0),
+    (100_000_000, 4, 100, 0), (300_033, 64, 200, 1), (70_001, 64, 900, 1), (1_000_003, 64, 48, 1), (1_000_003, 4, 800, 1), (2_000_001, 2, 800, 1), (4_000_001, 4, 200, 1),
+    (16_000_000, 4, 64, 1), (25_557_032, 4, 48, 1), (25_557_032, 4, 100, 1), (25_557_032, 10, 200, 1), (100_000_000, 2, 200, 1)])
+def test_directories_are_searched_where_that_is_faster(policy, d, R, per_cell, search):
+    assert policy("directory", per_cell * ((d + 1023) // 1024), d, R) == [search]
