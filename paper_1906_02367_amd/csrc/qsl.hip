@@ -58,6 +58,7 @@
 #include <algorithm>
 #include <mutex>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "qsl.h"
@@ -1142,12 +1143,13 @@ static void launch_directory(const DevCtx& c, hipStream_t st, const uint8_t* msg
   else k_msg_directory<4><<<dim3(2048, R), BLOCK, 0, st>>>(c, msg, rows, dir, ndir, pile);
 }
 
-// Whether k_aggregate_small takes the listed messages.  Every block reads all of their entries, so they have to be few; where `out`
-// is added to it saves no launch and pays only against the look-ups of many messages (GPU and call, us, by clearing and look-ups /
-// this way: 8 x 1,000 entries, d = 50,000: 12.2 / 10.8; 8 x 4,000, d = 4,200: 11.4 / 19.2; 35 x 100, d = 130,000, added: 16.1 / 8.9;
-// 8 x 1,000, d = 260,000, added: 8.7 / 8.9).
+// Whether k_aggregate_small takes the listed messages.  Every block looks at all of them, so they have to be few and short; where
+// `out` is added to it saves no launch and pays only against the look-ups of many messages.  us by clearing and look-ups / this way, GPU alone: 8 x
+// 1,000 entries, d = 50,000: 7.8 / 3.4; 4 x 500, d = 260,000: 7.4 / 3.6; 1 x 300, d = 260,000: 4.4 / 3.3; 35 x 231, d = 260,000: 18.9 / 8.8; 24 x
+// 166, d = 50,000, added: 11.0 / 5.8; calls one behind the other: 1 x 8,192, d = 260,000: 11.2 / 8.4; 2 x 4,000, 50 tensors: 10.4 / 8.5 (30 and 17 when a
+// wave went through the whole of each of its messages).
 static bool aggregate_small(uint64_t d, uint32_t nnz_hint, uint32_t R, bool accumulate) {
-  return d <= 1u << 18 && static_cast<uint64_t>(nnz_hint) * R <= 1u << 13 && (!accumulate || R >= 24);
+  return d <= 1u << 18 && R <= SMALL_AGG_R && static_cast<uint64_t>(nnz_hint) * R <= 1u << 13 && (!accumulate || R >= 24);
 }
 
 // The launches of the master line.  `dir` is room for R directories of `ndir` words, or null (then every message is
@@ -1195,9 +1197,10 @@ static qsl_status launch_aggregate(const DevCtx& c, hipStream_t st, uint32_t nnz
     return QSL_OK;
   }
   if (aggregate_small(c.d, nnz_hint, R, accumulate != 0)) {
-    uint32_t span = SMALL_AGG_THREADS;                     // the fewest coordinates that give every thread of a block one
-    const uint32_t lds = 4 * (R + 2) * span;
-    k_aggregate_small<<<dim3(static_cast<uint32_t>((c.d + span - 1) / span)), SMALL_AGG_THREADS, lds, st>>>(c, msg, rows, R, scale, accumulate, out, span);
+    // 64 entries of a message are looked at first; messages of up to 128 are read whole (35 x 85, d = 260,000: every second one first 8.4 us, all 7.2)
+    const uint32_t stride = nnz_hint <= 128 ? 1u : (nnz_hint + 63) / 64;
+    k_aggregate_small<<<dim3(static_cast<uint32_t>((c.d + SMALL_AGG_SPAN - 1) / SMALL_AGG_SPAN)), SMALL_AGG_THREADS, small_agg_lds(R), st>>>(
+        c, msg, rows, R, scale, accumulate, out, stride);
     QSL_HIP(hipGetLastError());
     return QSL_OK;
   }

@@ -410,55 +410,97 @@ __global__ __launch_bounds__(BLOCK) void k_aggregate(DevCtx c, const uint8_t* ms
 }
 
 // Few entries in all, on a short vector: the whole master line in one launch, whether `out` is added to or written.  A block owns
-// `span` coordinates, with room in LDS for every message's value of each; its waves go through all the messages' entries
-// (wave v: messages v, v + waves, ...) and put those of its range in their places; then each thread adds up a coordinate's values
-// in list order.  Two barriers, three dependent reads: 15 messages of 40 entries on 7,850 coordinates 4.5 us, where clearing and
-// k_aggregate are two launches of 2.0 and 8.4 us.
-constexpr uint32_t SMALL_AGG_THREADS = 512;
+// SMALL_AGG_SPAN coordinates, with room in LDS for every message's value of each; its waves (wave v: messages v, v + waves, ...) put the
+// entries of its range in their places; then each thread adds up a coordinate's values in list order.  A wave looks at every
+// `stride`-th entry first, all in one step, and then reads only what lies between the two that enclose the block's range.  What bounds it
+// is the chain of reads, four or five whatever the messages' lengths: 15 messages of 40 entries on 7,850 coordinates 4.5 us, where
+// clearing and k_aggregate are two launches of 2.0 and 8.4 us.
+// Whatever a message holds, the parts that neighbouring blocks read meet, so that every entry is looked at; where one of the entries
+// looked at first has an index >= d, all blocks go through the whole message, and no other entry is lost.
+constexpr uint32_t SMALL_AGG_THREADS = 512, SMALL_AGG_SPAN = 512;      // (the fewest coordinates that give every thread one)
+constexpr uint32_t SMALL_AGG_R = AGG_CELLS_MIN_R - 1;                  // messages: more of them go to k_aggregate_cells
+constexpr uint32_t SMALL_AGG_STEPS = 4;                                // entries of a lane whose reads are in flight together
+constexpr uint32_t small_agg_lds(uint32_t R) { return 4 * (R + 2) * SMALL_AGG_SPAN; }
+static_assert(SMALL_AGG_R <= 64 && small_agg_lds(SMALL_AGG_R) <= 160 * 1024, "a mark per message in 64 bits, the LDS of a compute unit");
 __global__ __launch_bounds__(SMALL_AGG_THREADS) void k_aggregate_small(DevCtx c, const uint8_t* msg, RowList rows, uint32_t R, float scale,
-                                                                       int accumulate, float* out, uint32_t span) {
-  extern __shared__ float s_values[];                    // [R][span], then the messages that hold each coordinate, [span][2]
-  uint32_t* s_who = reinterpret_cast<uint32_t*>(s_values + R * span);
-  const uint32_t lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t base = blockIdx.x * span, n = min(span, static_cast<uint32_t>(c.d) - base);
-  // this wave's messages: their headers and first entries are read before the marks are cleared
-  constexpr uint32_t NW = SMALL_AGG_THREADS / 64, PER = 64 / NW;
+                                                                       int accumulate, float* out, uint32_t stride) {
+  extern __shared__ float s_values[];                    // [R][SPAN], then the messages that hold each coordinate, [SPAN][2]
+  uint32_t* s_who = reinterpret_cast<uint32_t*>(s_values + R * SMALL_AGG_SPAN);
+  const uint32_t lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), d = static_cast<uint32_t>(c.d);
+  const uint32_t base = blockIdx.x * SMALL_AGG_SPAN, n = min(SMALL_AGG_SPAN, d - base);
+  // this wave's messages: their headers and the entries looked at first are read before the marks are cleared
+  constexpr uint32_t NW = SMALL_AGG_THREADS / 64, PER = (SMALL_AGG_R + NW - 1) / NW;
   const bool counts = is_qsgd(c.quantizer) && c.L > 1;
   const uint32_t hdr = 1 + c.L + (counts ? c.L : 0);
-  uint32_t nnz[PER], idx[PER];
+  uint32_t nnz[PER], probe[PER], next[PER];               // next: with stride 1, the 64 entries behind
+  const bool two = stride == 1 && c.K > WAVE;
 #pragma unroll
   for (uint32_t i = 0; i < PER; ++i) {
     const uint32_t p = wave + i * NW;
-    nnz[i] = 0; idx[i] = 0;
+    nnz[i] = 0; probe[i] = 0; next[i] = 0;
     if (p >= R) continue;                                // (uniform over the wave)
     const uint32_t* words = reinterpret_cast<const uint32_t*>(msg + static_cast<uint64_t>(rows.row[p]) * c.cap_words * 4);
-    nnz[i] = min(words[0], c.K);
-    idx[i] = field_of(read_field(words, static_cast<uint64_t>(hdr) * 32 + static_cast<uint64_t>(min(lane, c.K - 1)) * c.w_idx, c.cap_words), c.w_idx);
+    nnz[i] = __builtin_amdgcn_readfirstlane(min(words[0], c.K));
+    probe[i] = field_of(read_field(words, static_cast<uint64_t>(hdr) * 32 + static_cast<uint64_t>(lane * stride) * c.w_idx, c.cap_words), c.w_idx);
+    if (two) next[i] = field_of(read_field(words, static_cast<uint64_t>(hdr) * 32 + static_cast<uint64_t>(lane + WAVE) * c.w_idx, c.cap_words), c.w_idx);
   }
-  for (uint32_t i = threadIdx.x; i < 2 * span; i += SMALL_AGG_THREADS) s_who[i] = 0;
+  for (uint32_t i = threadIdx.x; i < 2 * SMALL_AGG_SPAN; i += SMALL_AGG_THREADS) s_who[i] = 0;
   __syncthreads();
 #pragma unroll
   for (uint32_t i = 0; i < PER; ++i) {
     const uint32_t p = wave + i * NW;
     if (p >= R) break;
     const uint32_t* words = reinterpret_cast<const uint32_t*>(msg + static_cast<uint64_t>(rows.row[p]) * c.cap_words * 4);
-    const uint64_t code_bit0 = (hdr + (static_cast<uint64_t>(nnz[i]) * c.w_idx + 31) / 32) * 32;
-    for (uint32_t j = lane; j < nnz[i]; j += WAVE) {
-      const uint32_t at = j < WAVE ? idx[i] : field_of(read_field(words, static_cast<uint64_t>(hdr) * 32 + static_cast<uint64_t>(j) * c.w_idx, c.cap_words), c.w_idx);
-      if (at >= c.d && blockIdx.x == 0) atomicOr(c.status, 4u);      // malformed message: the entry is skipped
-      if (at < base || at - base >= n) continue;
-      const uint32_t code = field_of(read_field(words, code_bit0 + static_cast<uint64_t>(j) * c.w_val, c.cap_words), c.w_val);
+    const uint64_t idx_bit0 = static_cast<uint64_t>(hdr) * 32, code_bit0 = (hdr + (static_cast<uint64_t>(nnz[i]) * c.w_idx + 31) / 32) * 32;
+    auto code_at = [&](uint32_t j) { return read_field(words, code_bit0 + static_cast<uint64_t>(j) * c.w_val, c.cap_words); };
+    auto put = [&](uint32_t at, const FieldRead& code) {
       const uint32_t seg = c.L == 1 ? 0u : seg_of_coord(c, at);
-      s_values[p * span + (at - base)] = value_of_code(c, code, __uint_as_float(words[1 + seg]));
+      s_values[p * SMALL_AGG_SPAN + (at - base)] = value_of_code(c, field_of(code, c.w_val), __uint_as_float(words[1 + seg]));
       atomicOr(&s_who[2 * (at - base) + (p >> 5)], 1u << (p & 31u));
+    };
+    const bool there = lane * stride < nnz[i];
+    if (there && probe[i] >= d) atomicOr(c.status, 4u);  // malformed message: the entry is skipped
+    if (stride == 1) {                                   // the first 64 entries are here, and the 64 behind them
+      if (there && probe[i] >= base && probe[i] - base < n) put(probe[i], code_at(lane));
+      const bool behind = lane + WAVE < nnz[i];
+      if (behind && next[i] >= d) atomicOr(c.status, 4u);
+      if (behind && next[i] >= base && next[i] - base < n) put(next[i], code_at(lane + WAVE));
+      if (nnz[i] <= 2 * WAVE) continue;
+    }
+    const uint32_t n_there = static_cast<uint32_t>(__popcll(__ballot(there)));
+    const uint32_t n_lo = static_cast<uint32_t>(__popcll(__ballot(there && probe[i] < base))), n_hi = static_cast<uint32_t>(__popcll(__ballot(there && probe[i] < base + n)));
+    uint32_t j0 = n_lo ? (n_lo - 1) * stride + 1 : 0u, end = n_hi < n_there ? n_hi * stride : nnz[i];
+    if (__ballot(there && probe[i] >= d) != 0) { j0 = 0; end = nnz[i]; }
+    if (stride == 1) j0 = max(j0, 2 * WAVE);
+    auto read = [&](auto steps) {                        // 64 entries from j0 on, or 256
+      constexpr uint32_t STEPS = decltype(steps)::value;
+      FieldRead fi[STEPS], fc[STEPS];
+#pragma unroll
+      for (uint32_t u = 0; u < STEPS; ++u) {
+        const uint32_t j = min(j0 + u * WAVE + lane, nnz[i] - 1);
+        fi[u] = read_field(words, idx_bit0 + static_cast<uint64_t>(j) * c.w_idx, c.cap_words);
+        fc[u] = code_at(j);
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < STEPS; ++u) {
+        const uint32_t at = field_of(fi[u], c.w_idx);
+        if (j0 + u * WAVE + lane >= end) continue;
+        if (at >= d) atomicOr(c.status, 4u);             // malformed message: the entry is skipped
+        if (at >= base && at - base < n) put(at, fc[u]);
+      }
+      j0 += STEPS * WAVE;
+    };
+    while (j0 < end) {                                   // (uniform over the wave)
+      if (end - j0 <= WAVE) read(std::integral_constant<uint32_t, 1>());
+      else read(std::integral_constant<uint32_t, SMALL_AGG_STEPS>());
     }
   }
   __syncthreads();
   for (uint32_t i = threadIdx.x; i < n; i += SMALL_AGG_THREADS) {
     uint64_t who = static_cast<uint64_t>(s_who[2 * i + 1]) << 32 | s_who[2 * i];
     if (who == 0) { if (!accumulate) out[base + i] = 0.0f; continue; }
-    float sum = s_values[(__ffsll(static_cast<unsigned long long>(who)) - 1) * span + i];
-    for (who &= who - 1; who; who &= who - 1) sum = sum + s_values[(__ffsll(static_cast<unsigned long long>(who)) - 1) * span + i];
+    float sum = s_values[(__ffsll(static_cast<unsigned long long>(who)) - 1) * SMALL_AGG_SPAN + i];
+    for (who &= who - 1; who; who &= who - 1) sum = sum + s_values[(__ffsll(static_cast<unsigned long long>(who)) - 1) * SMALL_AGG_SPAN + i];
     const float term = scale * sum;
     out[base + i] = accumulate ? out[base + i] + term : term;
   }

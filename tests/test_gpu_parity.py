@@ -1037,9 +1037,13 @@ def test_short_vectors(P, d, k, sparsifier, quantizer, s):
         assert np.array_equal(msg[r].cpu().numpy(), o["msg"]) and np.array_equal(P.bits(m[r].cpu().numpy()), P.bits(o["m_out"]))
 
 
-# the master line in one launch: ranges of 512 coordinates, every number of messages up to 64, segments, entries shared by all messages
+# the master line in one launch (up to 35 messages; lists of 64 go by cells): ranges of 512 coordinates, segments, entries shared by all
+# messages; few messages with many entries (64 of them are looked at first, one in 2 .. 128), all of them in one range or everywhere
 @pytest.mark.parametrize("d,off,k,quantizer,s,R", [(1, [0, 1], [1], W.SIGN_L1, 1, 2), (511, [0, 511], [100], W.FP32, 1, 33), (513, [0, 200, 513], [40, 60], W.QSGD, 3, 64),
-                                                   (100_001, [0, 100_001], [128], W.SIGN_L1, 1, 64), (5_000, [0, 100, 5_000], [100, 400], W.SIGN_L2, 1, 9)])
+                                                   (100_001, [0, 100_001], [128], W.SIGN_L1, 1, 64), (5_000, [0, 100, 5_000], [100, 400], W.SIGN_L2, 1, 9),
+                                                   (70_001, [0, 70_001], [234], W.FP32, 1, 35), (1_025, [0, 1_025], [64], W.FP32, 1, 24), (1_025, [0, 1_025], [65], W.SIGN_L1, 1, 24),
+                                                   (262_144, [0, 262_144], [8_192], W.SIGN_L1, 1, 1), (20_001, [0, 3_000, 20_001], [2_990, 1_000], W.FP32, 1, 2),
+                                                   (9_001, [0, 9_001], [4_095], W.QSGD, 32, 2), (60_000, [0, 59_000, 60_000], [10, 999], W.SIGN_L2, 1, 3)])
 def test_aggregate_small(P, d, off, k, quantizer, s, R):
     from paper_1906_02367_amd import binding as B
     rng = np.random.default_rng(d + R)
@@ -1062,6 +1066,70 @@ def test_aggregate_small(P, d, off, k, quantizer, s, R):
             want = _aggregate_by_definition(decoded, lst, -1.0 / R, x0, accumulate, d)
             assert np.array_equal(out.cpu().numpy().view(np.uint32), want.view(np.uint32)), (lst, accumulate)
     assert q.device_status() == B.OK
+
+
+# ... and with malformed messages: every index >= d is reported and skipped, wherever it stands (the last block is a ragged one), and no
+# other entry is lost; a length above K is K
+@pytest.mark.parametrize("d,off,k,quantizer,s,R,accumulate", [(50_001, [0, 50_001], [200], W.SIGN_L1, 1, 32, True), (50_001, [0, 50_001], [1_500], W.FP32, 1, 4, False),
+                                                              (3_001, [0, 700, 3_001], [30, 25], W.QSGD, 15, 4, False), (200_001, [0, 200_001], [8_000], W.SIGN_L2, 1, 1, False),
+                                                              (9_000, [0, 4_000, 9_000], [1_000, 3_000], W.SIGN_L1, 1, 2, False), (20_001, [0, 20_001], [100], W.FP32, 1, 8, False)])
+def test_aggregate_small_malformed(P, d, off, k, quantizer, s, R, accumulate):
+    from paper_1906_02367_amd import binding as B
+    rng = np.random.default_rng(d + R)
+    wl = custom(d, off, k, s, W.TOPK, quantizer, R=R)
+    q, op = B.from_workload(wl), P.oracle_for(wl)
+    msg, m = q.new_msg(R), torch.zeros(R, d, device=q.device)
+    q.compress(m, torch.from_numpy(rng.standard_normal((R, d)).astype(f32)).to(q.device), m, 0, 0, msg)
+    torch.cuda.synchronize()
+    good = msg.cpu().numpy()
+    decoded = [op.decode(x) for x in good]
+    n, w_idx, L, r = decoded[R - 1][0].size, (d - 1).bit_length(), len(k), R - 1
+    bit0 = 32 * (1 + L + (L if quantizer == W.QSGD and L > 1 else 0))
+    x0 = rng.standard_normal(d).astype(f32)
+
+    def check(bad, entries, status):
+        out = torch.from_numpy(x0).to(q.device)
+        q.aggregate(torch.from_numpy(bad).to(q.device), out, -0.5, accumulate=accumulate)
+        assert q.device_status() == status and q.device_status() == B.OK
+        want = _aggregate_by_definition(decoded[:r] + [entries], list(range(R)), -0.5, x0, accumulate, d)
+        assert np.array_equal(out.cpu().numpy().view(np.uint32), want.view(np.uint32))
+
+    for where in ([0], [1], [n // 2], [n - 1], [n * 40 // 64], range(n // 3, n // 2), range(0, n, 2), range(1, n), range(n)):
+        where = np.array(where)
+        bad, keep = good.copy(), np.ones(n, bool)
+        bits = np.unpackbits(bad[r], bitorder="little")
+        for j in where:
+            bits[bit0 + j * w_idx: bit0 + (j + 1) * w_idx] = ((d if j % 3 else (1 << w_idx) - 1) >> np.arange(w_idx)) & 1
+        bad[r] = np.packbits(bits, bitorder="little")
+        keep[where] = False
+        check(bad, tuple(x[keep] for x in decoded[r]), B.ERR_DEVICE)
+    if quantizer != W.QSGD:
+        bad = good.copy()
+        bad[r, :4].view(np.uint32)[0] = sum(k) + 7
+        check(bad, decoded[r], B.OK)
+
+
+# ... whose time goes with the entries, not with how many of the messages there are: one message of 8192 takes what eight of 1024 take
+# (30.5 against 8.4 us when a wave went through the whole of each of its messages)
+def test_aggregate_small_time_of_few_messages(P):
+    def us(R):
+        wl = custom(130_003, [0, 130_003], [8_192 // R], 1, W.TOPK, W.SIGN_L1, R=R)
+        from paper_1906_02367_amd import binding as B
+        q = B.from_workload(wl)
+        msg, m, out = q.new_msg(R), torch.zeros(R, wl.d, device=q.device), torch.zeros(wl.d, device=q.device)
+        q.compress(m, torch.randn(R, wl.d, device=q.device), m, 0, 0, msg)
+        best = 1e9
+        for _ in range(10):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            for _ in range(50):
+                q.aggregate(msg, out, 0.5)
+            e1.record()
+            e1.synchronize()
+            best = min(best, e0.elapsed_time(e1) * 20)
+        return best
+    one, eight = us(1), us(8)
+    assert one < 2 * eight, (one, eight)
 
 
 # index-free messages of one segment: the norm of values from the smallest subnormal to 1e36, side by side in one wave (several windows
