@@ -114,6 +114,9 @@ enum {
  * reports, before any failed guess: 0 = single-pass with a guessed threshold, 1 = multi-pass (on a large vector mostly by
  * a window of rank keys, see qsl_debug_units), 3 = one block, 4 = no selection (k = size).  The decision depends on (size, k, sparsifier, flags) only; qsl_create makes it
  * with the same code.  Needs no context and no GPU.
+ * A short vector by itself -- one segment of at most 16,384 coordinates, k <= 4096, without QSL_FLAG_NO_FAST_PATH,
+ * QSL_FLAG_NO_SMALL_PATH and QSL_FLAG_DENSE_FORMAT, path 0 or 3 -- has all of qsl_compress in one launch of a block per
+ * worker; its path says how a segment of that size and k is selected beside others.
  *   cfg host; path_out host, uint32 [num_segments] */
 qsl_status qsl_plan_paths(const qsl_config *cfg, uint32_t *path_out);
 
@@ -222,7 +225,9 @@ qsl_status qsl_device_status(qsl_ctx *ctx);
  * configuration (a dense k on a large vector: with candidates > 0 the window of rank keys that holds the threshold was
  * enough, with 0 the multi-pass kernels went over all of it), 2 = multi-pass path after a failed guess or a window that did
  * not hold, 3 = one-block selection of a small segment, 4 = no selection (k equals the size of the segment: every
- * coordinate is kept).  */
+ * coordinate is kept).  Where the whole call is one launch (a short vector by itself, see qsl_plan_paths), path 0 and 3 are the
+ * planned ones, 2 in place of 0: the lower bound that the launch forms for the threshold left more than 4096 coordinates
+ * and was dropped; candidates: the coordinates that it left, or all of them if none was formed.  */
 qsl_status qsl_debug_units(qsl_ctx *ctx, uint32_t *out_host, uint32_t max_units, uint32_t *n_units);
 
 /* Kernel timing for the benchmark: when enabled, compress calls bracket the streaming kernel with

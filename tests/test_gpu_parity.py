@@ -135,7 +135,7 @@ def _adversarial(d, rng):
     yield "wide_range", (rng.standard_normal(d) * np.exp(8 * rng.standard_normal(d))).astype(f32)
 
 
-@pytest.mark.parametrize("flags,path", [(0, 3), (2, 1)])      # one-block selection / multi-pass kernels
+@pytest.mark.parametrize("flags,path", [(0, 3), (2, 1)])      # one launch for the whole call / multi-pass kernels
 @pytest.mark.parametrize("quantizer,s", [(W.QSGD, 16), (W.SIGN_L1, 1)])
 @pytest.mark.parametrize("k", [1, 37, 4_001])
 def test_degenerate_inputs(P, quantizer, s, k, flags, path):
@@ -148,10 +148,21 @@ def test_degenerate_inputs(P, quantizer, s, k, flags, path):
         P.run_parity(wl, 1, deltas=[v[None, :].copy()], flags=flags, expect_path=path)
 
 
-@pytest.mark.parametrize("d,k", [(40_009, 1), (40_009, 37), (40_009, 200), (12_011, 1), (12_011, 37), (12_011, 60)])
+# the one-block selection of a segment of a larger operator (4,001: inside the streaming kernel) and of one of more than 16,384 coordinates
+@pytest.mark.parametrize("quantizer,s", [(W.QSGD, 16), (W.SIGN_L1, 1)])
+@pytest.mark.parametrize("off,k", [([0, 4_001, 4_100], [1, 9]), ([0, 4_001, 4_100], [37, 9]), ([0, 20_011], [2_500]), ([0, 16_385], [9_000])])
+def test_degenerate_inputs_one_block(P, quantizer, s, off, k):
+    rng = np.random.default_rng(17)
+    wl = custom(off[-1], off, k, s, W.TOPK, quantizer, R=1)
+    for name, v in _adversarial(off[-1], rng):
+        P.run_parity(wl, 1, deltas=[v[None, :].copy()], expect_path=3)
+
+
+@pytest.mark.parametrize("d,k", [(40_009, 1), (40_009, 37), (40_009, 200), (16_411, 1), (20_011, 37), (18_003, 60), (12_011, 1), (12_011, 37), (12_011, 60)])
 def test_degenerate_inputs_whole_unit_guess(P, k, d):
-    # 5 .. 255 chunks: the guess comes from a histogram of the whole unit; inputs with few distinct
-    # magnitudes put everything into one bin, overflow the candidate list and must fall back
+    # 17 .. 255 chunks: the guess comes from a histogram of the whole unit; inputs with few distinct
+    # magnitudes put everything into one bin, overflow the candidate list and must fall back.  12,011: the whole call is one
+    # launch (path 2: its lower bound leaves more than 4096 coordinates)
     rng = np.random.default_rng(23)
     wl = custom(d, [0, d], [k], 16, W.TOPK, W.QSGD, R=1)
     seen = set()
@@ -161,7 +172,8 @@ def test_degenerate_inputs_whole_unit_guess(P, k, d):
     assert seen == {0, 2}, seen
 
 
-# sizes around the limit of the one-block selection (4096 coordinates) and of its 16-per-thread layout
+# sizes around the limit of the one-block selection (4096 coordinates) and of its 16-per-thread layout: by itself (up to 16,384 coordinates one
+# launch for the whole call), and as a segment beside another
 @pytest.mark.parametrize("sparsifier", [W.TOPK, W.RANDK])
 @pytest.mark.parametrize("d,k", [(4_096, 100), (4_096, 4_096), (4_097, 4_097), (4_097, 3), (4_095, 4_095), (2_063, 1_000),
                                  (16_385, 16_385), (8_209, 4_000), (32_769, 1), (65_537, 655), (17, 16), (15, 15),
@@ -174,6 +186,11 @@ def test_small_units_one_block_boundaries(P, sparsifier, d, k):
     P.run_parity(wl, 1, flags=3, expect_path=1)                   # the same through the multi-pass kernels
     ties = np.round(np.random.default_rng(d).standard_normal((1, 2, d)) * 2).astype(f32)     # many equal magnitudes
     P.run_parity(wl, 1, deltas=ties, expect_path=3 if small else None)
+    if small:
+        wl = custom(d + 70, [0, d, d + 70], [k, 9], 7, sparsifier, W.QSGD, R=2)
+        P.run_parity(wl, 2, expect_path=3)
+        ties = np.round(np.random.default_rng(d).standard_normal((1, 2, d + 70)) * 2).astype(f32)
+        P.run_parity(wl, 1, deltas=ties, expect_path=3)
 
 
 def test_small_and_large_units_mixed(P):
