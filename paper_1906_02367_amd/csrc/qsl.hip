@@ -771,7 +771,7 @@ static qsl_status create_ctx(qsl_ctx** out, const qsl_config* cfg, void* hip_str
   c.cb_cnt = reinterpret_cast<uint2*>(base + o_cbc);
   c.tlist = reinterpret_cast<uint4*>(base + o_tlist);
   c.win = window ? 1u : 0u;
-  // (longer vectors would spill registers; a longer list of selected entries would not fit LDS beside the histogram)
+  // (longer vectors would spill registers; a longer list of selected entries would fit LDS and has not been tried)
   ctx->whole = L == 1 && d <= WHOLE_MAX && K <= WHOLE_K && !(cfg->flags & (QSL_FLAG_NO_FAST_PATH | QSL_FLAG_NO_SMALL_PATH | QSL_FLAG_DENSE_FORMAT)) &&
                segs[0].mode != PATH_FULL;
   WinCtx& wc = ctx->wc;

@@ -223,7 +223,7 @@ __device__ __forceinline__ void add_wave_digits(uint64_t* row, const f4u (&v)[4]
 #pragma unroll
   for (uint32_t i = 0; i < 16; ++i) { ab[i] = __float_as_uint(v[i >> 2][i & 3]) & 0x7FFFFFFFu; top = max(top, ab[i]); }
   top = wave_max(top);
-  while (top != 0) {                                         // (uniform) a window; at most 9 of them
+  while (top != 0) {                                         // (uniform) a window; at most 10 of them (squares: 9)
     const bool last = top < 2u << 23;                        // exponents 0 and 1: the bits are the mantissa, the unit is the same
     const uint32_t e0 = last ? 1u : max(2u, (top >> 23) - min(top >> 23, POWER == 1 ? 29u : 31u)), low = last ? 1u : e0 << 23;
     uint64_t lo = 0, hi = 0;                                 // the lane's sum is hi * 2^64 + lo
