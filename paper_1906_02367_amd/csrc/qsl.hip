@@ -946,13 +946,18 @@ static qsl_status launch_compress(qsl_ctx* ctx, const float* m, const float* del
   if (timed) { QSL_HIP(hipEventRecord(ctx->ev[ctx->ev_used + 1], st)); ctx->ev_used += 2; }
 
   // Units that a single block selects and encodes whole need nothing but v.  Where every guessing unit has a single block as well,
-  // one launch takes them all, the block units first: they work longest.  (Two launches on two streams, side by side, paid 5 us
-  // at the fork and 9 at the join.)  Otherwise they run on a stream of the context's own beside the kernels of the other units
-  // (one block works tens of microseconds on a unit of 40,960 coordinates) and are joined before the messages are put together:
-  // the guessing units with several blocks would wait behind them (161 tensors, one worker: 160 us per round that way, against 133
-  // us with the block units on the second stream).  Also while failed guesses are expected: the multi-pass kernels on the
-  // caller's stream read what k_lean_one finds out about its units.
-  const bool together = c.nblock != 0 && c.none != 0 && c.NSELF == 0 && !safe;
+  // one launch takes them all, the block units first: they work longest.  Two launches on two streams, side by side, pay 5 us at the fork
+  // and 9 at the join (us a call, two launches / one: 161 tensors, eight workers, k = 1000: 457 / 448; 100 tensors, 10^6 coordinates, one
+  // worker, k = 100: 83 / 70; 300 tensors, 4 M, four workers, k = 100: 158 / 149).  Otherwise they run on a stream of the context's own
+  // beside the kernels of the other units (one block works tens of microseconds on a unit of 40,960 coordinates) and are joined before the
+  // messages are put together: the guessing units with several blocks would wait behind them (161 tensors, one worker: 160 us per round
+  // that way, against 133 us with the block units on the second stream), and so would multi-pass kernels, unless the guessing units' blocks
+  // alone keep the chip busy, more than 300 of them and no fewer than the block units' (k = 1000, two / one: 12 tensors, two of them
+  // multi-pass units, 0.5 M, one worker 93 / 107, 60 178 / 184, 90 235 / 240, 128 302 / 298; 300 tensors, 4 M, one 102 / 124, 32 832 / 870; 40, 2 M, 32
+  // 251 / 255, 48 344 / 340; 161, 25 M, five 352 / 349, eight 529 / 519).
+  // Also while failed guesses are expected: the multi-pass kernels on the caller's stream read what k_lean_one finds out about its units.
+  const bool beside = ctx->nsel_general != 0 && (c.none < c.nblock || static_cast<uint64_t>(c.none) * R <= 300);
+  const bool together = c.nblock != 0 && c.none != 0 && c.NSELF == 0 && !beside && !safe;
   const bool forked = c.nblock != 0 && !together && (c.NSELF != 0 || c.none != 0 || ctx->n_other != 0);
   // Guessing units of both kinds in one call (a single block: k_lean_one; several: the three kernels) and no block units:
   // k_lean_one goes to a stream of its own, beside the three kernels (160 tensors, one worker: 115 -> 106 us per round,

@@ -203,6 +203,19 @@ def test_small_and_large_units_mixed(P):
         assert sorted(set(paths[0].tolist())) == [0, 1, 3], paths[0]
 
 
+# multi-pass units, one-block units and guessing units of a single block in one call: the one-block units beside the multi-pass kernels (few
+# workers), or in one launch with the guessing units (more than 300 blocks of those)
+@pytest.mark.parametrize("sparsifier,quantizer,s", [(W.TOPK, W.QSGD, 15), (W.TOPK, W.SIGN_L1, 1), (W.RANDK, W.SIGN_L2, 1)])
+@pytest.mark.parametrize("R", [2, 40])
+def test_one_block_units_with_multi_pass_units(P, sparsifier, quantizer, s, R):
+    sizes = [20_011] + [5_003] * 8 + [46_815, 300]
+    k = [2_500] + [10] * 8 + [4_000, 40]
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    wl = custom(int(off[-1]), off, k, s, sparsifier, quantizer, R=R)
+    run, op, m_host, paths = P.run_parity(wl, 2)
+    assert paths[0][:11].tolist() == [3] + [0] * 8 + [1, 3], paths[0][:11]
+
+
 def test_degenerate_inputs_on_fast_sizes(P):
     d, k = 600_000, 500
     rng = np.random.default_rng(19)
