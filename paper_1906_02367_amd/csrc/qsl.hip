@@ -1202,10 +1202,11 @@ static qsl_status launch_aggregate(const DevCtx& c, hipStream_t st, uint32_t nnz
     return QSL_OK;
   }
   if (aggregate_small(c.d, nnz_hint, R, accumulate != 0)) {
-    // 64 entries of a message are looked at first; messages of up to 128 are read whole (35 x 85, d = 260,000: every second one first 8.4 us, all 7.2)
-    const uint32_t stride = nnz_hint <= 128 ? 1u : (nnz_hint + 63) / 64;
-    k_aggregate_small<<<dim3(static_cast<uint32_t>((c.d + SMALL_AGG_SPAN - 1) / SMALL_AGG_SPAN)), SMALL_AGG_THREADS, small_agg_lds(R), st>>>(
-        c, msg, rows, R, scale, accumulate, out, stride);
+    // 64 entries of a message are looked at first; messages of up to 128 are read whole (35 x 85, d = 260,000: every second one first 8.4 us, all 7.3)
+    const dim3 grid(static_cast<uint32_t>((c.d + SMALL_AGG_SPAN - 1) / SMALL_AGG_SPAN));
+    const uint32_t lds = small_agg_lds(R);
+    if (nnz_hint <= 128) k_aggregate_small<true><<<grid, SMALL_AGG_THREADS, lds, st>>>(c, msg, rows, R, scale, accumulate, out, 1);
+    else k_aggregate_small<false><<<grid, SMALL_AGG_THREADS, lds, st>>>(c, msg, rows, R, scale, accumulate, out, (nnz_hint + 63) / 64);
     QSL_HIP(hipGetLastError());
     return QSL_OK;
   }

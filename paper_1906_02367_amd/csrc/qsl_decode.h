@@ -422,6 +422,7 @@ constexpr uint32_t SMALL_AGG_R = AGG_CELLS_MIN_R - 1;                  // messag
 constexpr uint32_t SMALL_AGG_STEPS = 4;                                // entries of a lane whose reads are in flight together
 constexpr uint32_t small_agg_lds(uint32_t R) { return 4 * (R + 2) * SMALL_AGG_SPAN; }
 static_assert(SMALL_AGG_R <= 64 && small_agg_lds(SMALL_AGG_R) <= 160 * 1024, "a mark per message in 64 bits, the LDS of a compute unit");
+template <bool SHORT>      // messages expected to hold 128 entries at most: all of them are read at once (stride is 1)
 __global__ __launch_bounds__(SMALL_AGG_THREADS) void k_aggregate_small(DevCtx c, const uint8_t* msg, RowList rows, uint32_t R, float scale,
                                                                        int accumulate, float* out, uint32_t stride) {
   extern __shared__ float s_values[];                    // [R][SPAN], then the messages that hold each coordinate, [SPAN][2]
@@ -432,17 +433,17 @@ __global__ __launch_bounds__(SMALL_AGG_THREADS) void k_aggregate_small(DevCtx c,
   constexpr uint32_t NW = SMALL_AGG_THREADS / 64, PER = (SMALL_AGG_R + NW - 1) / NW;
   const bool counts = is_qsgd(c.quantizer) && c.L > 1;
   const uint32_t hdr = 1 + c.L + (counts ? c.L : 0);
-  uint32_t nnz[PER], probe[PER], next[PER];               // next: with stride 1, the 64 entries behind
-  const bool two = stride == 1 && c.K > WAVE;
+  uint32_t nnz[PER], probe[PER], next[SHORT ? PER : 1];   // next: the 64 entries behind the first
 #pragma unroll
   for (uint32_t i = 0; i < PER; ++i) {
     const uint32_t p = wave + i * NW;
-    nnz[i] = 0; probe[i] = 0; next[i] = 0;
+    nnz[i] = 0; probe[i] = 0;
+    if (SHORT) next[i] = 0;
     if (p >= R) continue;                                // (uniform over the wave)
     const uint32_t* words = reinterpret_cast<const uint32_t*>(msg + static_cast<uint64_t>(rows.row[p]) * c.cap_words * 4);
     nnz[i] = __builtin_amdgcn_readfirstlane(min(words[0], c.K));
     probe[i] = field_of(read_field(words, static_cast<uint64_t>(hdr) * 32 + static_cast<uint64_t>(lane * stride) * c.w_idx, c.cap_words), c.w_idx);
-    if (two) next[i] = field_of(read_field(words, static_cast<uint64_t>(hdr) * 32 + static_cast<uint64_t>(lane + WAVE) * c.w_idx, c.cap_words), c.w_idx);
+    if (SHORT && c.K > WAVE) next[i] = field_of(read_field(words, static_cast<uint64_t>(hdr) * 32 + static_cast<uint64_t>(lane + WAVE) * c.w_idx, c.cap_words), c.w_idx);
   }
   for (uint32_t i = threadIdx.x; i < 2 * SMALL_AGG_SPAN; i += SMALL_AGG_THREADS) s_who[i] = 0;
   __syncthreads();
@@ -460,18 +461,19 @@ __global__ __launch_bounds__(SMALL_AGG_THREADS) void k_aggregate_small(DevCtx c,
     };
     const bool there = lane * stride < nnz[i];
     if (there && probe[i] >= d) atomicOr(c.status, 4u);  // malformed message: the entry is skipped
-    if (stride == 1) {                                   // the first 64 entries are here, and the 64 behind them
+    if (SHORT) {
       if (there && probe[i] >= base && probe[i] - base < n) put(probe[i], code_at(lane));
-      const bool behind = lane + WAVE < nnz[i];
-      if (behind && next[i] >= d) atomicOr(c.status, 4u);
-      if (behind && next[i] >= base && next[i] - base < n) put(next[i], code_at(lane + WAVE));
-      if (nnz[i] <= 2 * WAVE) continue;
+      for (uint32_t j = lane + WAVE; j < nnz[i]; j += WAVE) {
+        const uint32_t at = j < 2 * WAVE ? next[i] : field_of(read_field(words, idx_bit0 + static_cast<uint64_t>(j) * c.w_idx, c.cap_words), c.w_idx);
+        if (at >= d) atomicOr(c.status, 4u);
+        if (at >= base && at - base < n) put(at, code_at(j));
+      }
+      continue;
     }
     const uint32_t n_there = static_cast<uint32_t>(__popcll(__ballot(there)));
     const uint32_t n_lo = static_cast<uint32_t>(__popcll(__ballot(there && probe[i] < base))), n_hi = static_cast<uint32_t>(__popcll(__ballot(there && probe[i] < base + n)));
     uint32_t j0 = n_lo ? (n_lo - 1) * stride + 1 : 0u, end = n_hi < n_there ? n_hi * stride : nnz[i];
     if (__ballot(there && probe[i] >= d) != 0) { j0 = 0; end = nnz[i]; }
-    if (stride == 1) j0 = max(j0, 2 * WAVE);
     auto read = [&](auto steps) {                        // 64 entries from j0 on, or 256
       constexpr uint32_t STEPS = decltype(steps)::value;
       FieldRead fi[STEPS], fc[STEPS];

@@ -1139,6 +1139,43 @@ def test_aggregate_small_malformed(P, d, off, k, quantizer, s, R, accumulate):
         check(bad, decoded[r], B.OK)
 
 
+# ... and with a message that holds more entries than one of its operator is expected to (QSGD; written by hand: all of level 1)
+@pytest.mark.parametrize("n", [128, 129, 300, 5_000])
+def test_aggregate_small_longer_than_expected(P, n):
+    from paper_1906_02367_amd import binding as B
+    d, rng = 200_001, np.random.default_rng(n)
+    wl = custom(d, [0, d], [10_000], 1, W.TOPK, W.QSGD, R=2)                    # expected: 125 entries at most
+    q, op = B.from_workload(wl), P.oracle_for(wl)
+    w_idx, x0 = (d - 1).bit_length(), rng.standard_normal(d).astype(f32)
+    for at in (None, 3, 70, n - 1):                                            # an entry with an index >= d
+        msgs = np.zeros((2, q.capacity), np.uint8)
+        decoded = []
+        for r in range(2):
+            idx = np.sort(rng.choice(d, n, replace=False))
+            neg = rng.integers(0, 2, n)
+            if at is not None and r == 1:
+                idx[at] = d
+            fields = ((idx[:, None] >> np.arange(w_idx)) & 1).astype(np.uint8).ravel()
+            words = 2 + (n * w_idx + 31) // 32
+            bits = np.zeros(msgs.shape[1] * 8, np.uint8)
+            bits[64: 64 + fields.size] = fields
+            bits[32 * words: 32 * words + n] = neg                            # s = 1: a code is the sign
+            msgs[r] = np.packbits(bits, bitorder="little")
+            msgs[r, :8].view(np.uint32)[:] = [n, np.float32(1.5 + r).view(np.uint32)]
+            i, v = (idx, np.where(neg, -1.0, 1.0) * (1.5 + r))
+            keep = idx < d
+            decoded.append((i[keep], v[keep].astype(f32)))
+        out = torch.from_numpy(x0).to(q.device)
+        q.aggregate(torch.from_numpy(msgs).to(q.device), out, -0.5)
+        assert q.device_status() == (B.OK if at is None else B.ERR_DEVICE)
+        if at is None:
+            for r in range(2):
+                i, v = op.decode(msgs[r])
+                assert np.array_equal(i, decoded[r][0]) and np.array_equal(v.astype(f32), decoded[r][1])
+        want = _aggregate_by_definition(decoded, [0, 1], -0.5, x0, False, d)
+        assert np.array_equal(out.cpu().numpy().view(np.uint32), want.view(np.uint32)), at
+
+
 # ... whose time goes with the entries, not with how many of the messages there are: one message of 8192 takes what eight of 1024 take
 # (30.5 against 8.4 us when a wave went through the whole of each of its messages)
 def test_aggregate_small_time_of_few_messages(P):
